@@ -16,11 +16,13 @@ SOURCES = [
     "mdh_plan_ex.cpp",
     "mdh_plan_scan.cpp",
     "mdh_plan_capsule.cpp",
+    "mdh_plan_split.cpp",
     "mdh_custom.cpp",
     "mdh_api.hip",
     "mdh_stencil.hip",
     "mdh_matmul.hip",
     "mdh_matmul_ksplit.hip",
+    "mdh_matmul_split.hip",
     "mdh_mcc.hip",
     "mdh_mcc_flat.hip",
     "mdh_calib.hip",

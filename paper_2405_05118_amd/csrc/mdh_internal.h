@@ -34,6 +34,8 @@ struct GemmPlan {
   // rows, i fastest inside a band (order (WG,i),(WG,j),(WG,k)); 1 = bands of 8 tile columns, j fastest
   // (order (WG,j),(WG,i),(WG,k)).  Decides which panels of A and B the tiles resident together share.
   int jmajor = 0;
+  // 1: the kernel that carries every value as three bf16 values (blk = 16 x 16 x 32; BK = 32)
+  int split = 0;
 };
 
 // MCC: workgroup tile TP x TQ output pixels x BN output channels, CK channels per LDS stage.
@@ -63,6 +65,13 @@ void set_order(mdh_tile_params* p, const int* dim_order);
 mdh_status check_products(const mdh_tile_params* p, const int64_t* sizes, bool* ragged);
 mdh_status check_lanes(const mdh_tile_params* p);
 bool same_table(const mdh_tile_params& a, const mdh_tile_params& b);
+// the kernel that splits fp32 values into bf16 slices (mdh_plan_split.cpp); tc: C is stored transposed
+constexpr int kSplitTiles = 5;
+bool split_inst(const GemmPlan& g, bool tc);
+bool split_sizes(int64_t M, int64_t N, int64_t K);
+int64_t split_lds_bytes(const GemmPlan& g);
+int split_tiles(bool tc, GemmPlan* out);
+bool split_default(int64_t batch, int64_t M, int64_t N, int64_t K, bool tc, int S, GemmPlan* g);
 }  // namespace detail
 
 // Dot: WAVES wavefronts per workgroup, S workgroup-layer parts of k; a lane owns 4
@@ -168,6 +177,8 @@ mdh_status launch_matmul_skinny(const GemmExPlan& pl, int64_t batch, int64_t M, 
                                 const float* A, const float* B, float* C, void* ws, hipStream_t st);
 mdh_status launch_matmul_ksplit(const GemmPlan& pl, int64_t M, int64_t N, int64_t K, const float* A,
                                 const float* B, float* C, void* ws, hipStream_t st);
+mdh_status launch_matmul_split(const GemmPlan& pl, bool ta, bool tb, bool tc, int64_t batch, int64_t M, int64_t N, int64_t K,
+                               const float* A, const float* B, float* C, void* ws, hipStream_t st);
 // dst[i] = part_0[i] + ... + part_{S-1}[i], i < n (defined in mdh_matmul.hip)
 mdh_status launch_combine_sum(const float* ws, float* dst, int64_t n, int S, hipStream_t st);
 

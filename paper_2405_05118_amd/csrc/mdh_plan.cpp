@@ -215,6 +215,7 @@ static const int kGemmKsplitMenu[][3] = {{32, 32, 8}, {32, 32, 4}, {32, 32, 16},
                                          {64, 64, 8}, {16, 16, 4}, {16, 16, 2}, {16, 16, 8}};
 
 static bool gemm_inst(const GemmPlan& pl) {
+  if (pl.split) return split_inst(pl, false);
   if (pl.WK > 1) {
     for (auto& m : kGemmKsplitMenu)
       if (pl.BM == m[0] && pl.BN == m[1] && pl.WK == m[2]) return true;
@@ -235,19 +236,20 @@ void params_from_plan(const int64_t* s, const GemmPlan& pl, mdh_tile_params* p) 
   clear_params(p, 3);
   p->blk[0] = 32;
   p->blk[1] = 32;
-  p->blk[2] = 2;  // one v_mfma_f32_32x32x2_f32
+  const int bk = pl.split ? 16 : 2;
+  p->blk[2] = bk;  // one v_mfma_f32_32x32x2_f32, or six v_mfma_f32_32x32x16_bf16
   if (pl.WK > 1) {
     // k on the wavefront layer: every wavefront owns the whole tile and walks groups of 8 k (4 MFMA
     // steps of 2; with the 16 x 16 x 4 block: groups of 16 k, 4 steps of 4) read straight into
     // registers; the wavefront results are combined in LDS
-    const int b = pl.BM == 16 ? 16 : 32, bk = pl.BM == 16 ? 4 : 2;
+    const int b = pl.BM == 16 ? 16 : 32, kb = pl.BM == 16 ? 4 : 2;
     p->blk[0] = p->blk[1] = b;
-    p->blk[2] = bk;
+    p->blk[2] = kb;
     p->prt[MDH_L_WG][0] = (int32_t)cdiv(s[0], pl.BM);
     p->prt[MDH_L_WG][1] = (int32_t)cdiv(s[1], pl.BN);
     p->prt[MDH_L_WG][2] = pl.S;
     p->prt[MDH_L_WAVE][2] = pl.WK;
-    p->prt[MDH_L_HBM][2] = (int32_t)cdiv(cdiv(s[2], (int64_t)pl.S * pl.WK), 4 * bk);
+    p->prt[MDH_L_HBM][2] = (int32_t)cdiv(cdiv(s[2], (int64_t)pl.S * pl.WK), 4 * kb);
     p->prt[MDH_L_VGPR][0] = pl.BM / b;
     p->prt[MDH_L_VGPR][1] = pl.BN / b;
     p->prt[MDH_L_VGPR][2] = 4;
@@ -267,7 +269,7 @@ void params_from_plan(const int64_t* s, const GemmPlan& pl, mdh_tile_params* p) 
   p->prt[MDH_L_HBM][2] = (int32_t)cdiv(cdiv(s[2], pl.S), pl.BK);
   p->prt[MDH_L_WAVE][0] = pl.BM / pl.WM;
   p->prt[MDH_L_WAVE][1] = pl.BN / pl.WN;
-  p->prt[MDH_L_LDS][2] = pl.BK / 2;
+  p->prt[MDH_L_LDS][2] = pl.BK / bk;
   p->prt[MDH_L_VGPR][0] = pl.WM / 32;
   p->prt[MDH_L_VGPR][1] = pl.WN / 32;
   static const int dims[3] = {0, 1, 2};
@@ -289,7 +291,8 @@ static int gemm_ragged(const int64_t* s, const GemmPlan& pl) {
   return (s[0] % pl.BM) || (s[1] % pl.BN) || (s[2] % ((int64_t)pl.S * pl.BK));
 }
 
-static GemmPlan gemm_default(const int64_t* s) {
+// the fp32 kernels' choice
+static GemmPlan gemm_default_fp32(const int64_t* s) {
   const int64_t M = s[0], N = s[1], K = s[2];
   // Outputs of few tiles: k over the wavefronts of a workgroup, one launch, tiles small enough to give
   // every compute unit a workgroup.  Kernel durations (rocprofv3 kernel trace, us; the LDS-tiled kernel
@@ -347,16 +350,24 @@ static GemmPlan gemm_default(const int64_t* s) {
   return pl;
 }
 
+static GemmPlan gemm_default(const int64_t* s) {
+  GemmPlan pl = gemm_default_fp32(s);
+  // outputs of few tiles stay with k over the wavefronts (512^3: 8.9 us against 13.2; 400 x 600 x 1000: 13.3 / 23)
+  if (pl.WK > 1 || !split_default(1, s[0], s[1], s[2], false, pl.S, &pl)) return pl;
+  pl.ragged = gemm_ragged(s, pl);
+  return pl;
+}
+
 int matmul_candidates(const int64_t* s, GemmPlan* out, int cap) {
   int n = 0;
   auto push = [&](GemmPlan pl) {
     if (n >= cap) return;
     if (pl.S > 1 && s[2] / pl.S < pl.BK) return;
-    if (pl.WK == 1 && gemm_lds_bytes(pl.BM, pl.BN, pl.BK) > kLdsBytesPerWG) return;
+    if (pl.WK == 1 && !pl.split && gemm_lds_bytes(pl.BM, pl.BN, pl.BK) > kLdsBytesPerWG) return;
     pl.ragged = gemm_ragged(s, pl);
     for (int i = 0; i < n; ++i)
       if (out[i].BM == pl.BM && out[i].BN == pl.BN && out[i].BK == pl.BK && out[i].WM == pl.WM &&
-          out[i].S == pl.S && out[i].WK == pl.WK && out[i].jmajor == pl.jmajor)
+          out[i].S == pl.S && out[i].WK == pl.WK && out[i].jmajor == pl.jmajor && out[i].split == pl.split)
         return;
     out[n++] = pl;
   };
@@ -367,6 +378,17 @@ int matmul_candidates(const int64_t* s, GemmPlan* out, int cap) {
       d.jmajor = !d.jmajor;
       push(d);
     }
+  }
+  push(gemm_default_fp32(s));
+  if (split_sizes(s[0], s[1], s[2])) {
+    GemmPlan sp[kSplitTiles];
+    const int ns = split_tiles(false, sp);
+    for (int i = 0; i < ns; ++i)
+      for (int S : {1, 2, 4}) {
+        if (S > 1 && (cdiv(s[0], sp[i].BM) * cdiv(s[1], sp[i].BN) * (S / 2) >= 256 || s[2] / S < 128)) continue;
+        sp[i].S = S;
+        push(sp[i]);
+      }
   }
   // k over the wavefronts of a workgroup, for outputs of few tiles (every wavefront keeps 8 k or more)
   if (cdiv(s[0], 32) * cdiv(s[1], 32) <= 1024)
@@ -425,14 +447,16 @@ mdh_status plan_matmul(const int64_t* s, const mdh_tile_params* p, GemmPlan* out
   pl.WN = p->prt[MDH_L_VGPR][1] * 32;
   pl.BM = p->prt[MDH_L_WAVE][0] * pl.WM;
   pl.BN = p->prt[MDH_L_WAVE][1] * pl.WN;
-  pl.BK = p->prt[MDH_L_LDS][2] * 2;
+  pl.split = p->blk[2] == 16;
+  pl.BK = p->prt[MDH_L_LDS][2] * p->blk[2];
   pl.S = p->prt[MDH_L_WG][2];
   pl.ragged = ragged;
   // parameter D1 on the workgroup layer: (WG,j) before (WG,i) selects the column-band tile order; any
   // other permutation has no instantiation (the regenerated table below differs)
   pl.jmajor = (p->order[0] == MDH_L_WG * MDH_MAX_D + 1 && p->order[1] == MDH_L_WG * MDH_MAX_D + 0) ? 1 : 0;
-  if (p->blk[0] != 32 || p->blk[1] != 32 || p->blk[2] != 2) return MDH_ERR_UNSUPPORTED;
-  if (gemm_lds_bytes(pl.BM, pl.BN, pl.BK) > kLdsBytesPerWG) return MDH_ERR_TILE_RESOURCES;
+  if (p->blk[0] != 32 || p->blk[1] != 32 || (p->blk[2] != 2 && p->blk[2] != 16)) return MDH_ERR_UNSUPPORTED;
+  if (pl.split && !split_sizes(s[0], s[1], s[2])) return MDH_ERR_UNSUPPORTED;
+  if ((pl.split ? split_lds_bytes(pl) : gemm_lds_bytes(pl.BM, pl.BN, pl.BK)) > kLdsBytesPerWG) return MDH_ERR_TILE_RESOURCES;
   if ((int64_t)p->prt[MDH_L_WAVE][0] * p->prt[MDH_L_WAVE][1] * 64 > kMaxLanesPerWG)
     return MDH_ERR_TILE_RESOURCES;
   mdh_tile_params chk;

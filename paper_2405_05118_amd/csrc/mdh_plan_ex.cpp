@@ -98,7 +98,8 @@ void params_from_plan(const int64_t* s, const GemmExPlan& pl, mdh_tile_params* p
   clear_params(p, 4);
   p->blk[1] = 32;
   p->blk[2] = 32;
-  p->blk[3] = 2;
+  const int bk = g.split ? 16 : 2;
+  p->blk[3] = bk;
   p->prt[MDH_L_WG][0] = (int32_t)s[0];
   p->prt[MDH_L_WG][1] = (int32_t)cdiv(s[1], g.BM);
   p->prt[MDH_L_WG][2] = (int32_t)cdiv(s[2], g.BN);
@@ -106,7 +107,7 @@ void params_from_plan(const int64_t* s, const GemmExPlan& pl, mdh_tile_params* p
   p->prt[MDH_L_HBM][3] = (int32_t)cdiv(cdiv(s[3], g.S), g.BK);
   p->prt[MDH_L_WAVE][1] = g.BM / g.WM;
   p->prt[MDH_L_WAVE][2] = g.BN / g.WN;
-  p->prt[MDH_L_LDS][3] = g.BK / 2;
+  p->prt[MDH_L_LDS][3] = g.BK / bk;
   p->prt[MDH_L_VGPR][1] = g.WM / 32;
   p->prt[MDH_L_VGPR][2] = g.WN / 32;
   static const int dims[4] = {0, 1, 2, 3};
@@ -127,6 +128,12 @@ static int ex_ragged(const int64_t* s, const GemmPlan& g) {
 }
 
 static GemmExPlan ex_default_tiled(const int64_t* s);
+
+static GemmExPlan ex_default_large(const int64_t* s) {
+  GemmExPlan pl = ex_default_tiled(s);
+  if (split_default(s[0], s[1], s[2], s[3], s[6] != 0, pl.g.S, &pl.g)) pl.g.ragged = ex_ragged(s, pl.g);
+  return pl;
+}
 
 static GemmExPlan ex_default(const int64_t* s) {
   const int64_t batch = s[0], M = s[1], N = s[2], K = s[3];
@@ -158,7 +165,7 @@ static GemmExPlan ex_default(const int64_t* s) {
     while (strips * 8 * S < 2048 && S < 64 && K / (2 * S) >= 8 * 16 && (S < 32 || K / (2 * S) >= 8 * 16 * 4)) S *= 2;
     return skinny_plan(s, 1, 8, S);
   }
-  return ex_default_tiled(s);
+  return ex_default_large(s);
 }
 
 static GemmExPlan ex_default_tiled(const int64_t* s) {
@@ -207,7 +214,9 @@ int matmul_ex_candidates(const int64_t* s, GemmExPlan* out, int cap) {
     if (g.S > 1 && s[3] / g.S < g.BK) return;
     g.ragged = ex_ragged(s, g);
     for (int i = 0; i < n; ++i)
-      if (!out[i].skinny && out[i].g.BM == g.BM && out[i].g.BN == g.BN && out[i].g.BK == g.BK && out[i].g.S == g.S) return;
+      if (!out[i].skinny && out[i].g.BM == g.BM && out[i].g.BN == g.BN && out[i].g.BK == g.BK && out[i].g.S == g.S &&
+          out[i].g.split == g.split)
+        return;
     out[n++] = GemmExPlan{g, (int)s[4], (int)s[5], (int)s[6]};
   };
   if (skinny_applies(s)) {
@@ -229,7 +238,18 @@ int matmul_ex_candidates(const int64_t* s, GemmExPlan* out, int cap) {
         out[n++] = skinny_plan(s, m[0], m[1], S);
       }
   }
+  push(ex_default_large(s).g);
   push(ex_default_tiled(s).g);
+  if (split_sizes(s[1], s[2], s[3])) {
+    GemmPlan sp[kSplitTiles];
+    const int ns = split_tiles(s[6] != 0, sp);
+    for (int i = 0; i < ns; ++i)
+      for (int S : {1, 2, 4}) {
+        if (S > 1 && (s[0] * cdiv(s[1], sp[i].BM) * cdiv(s[2], sp[i].BN) * (S / 2) >= 256 || s[3] / S < 128)) continue;
+        sp[i].S = S;
+        push(sp[i]);
+      }
+  }
   static const int splits[] = {1, 2, 4, 8, 16, 32};
   for (auto& m : kExMenu)
     for (int S : splits) {
@@ -273,14 +293,17 @@ mdh_status plan_matmul_ex(const int64_t* s, const mdh_tile_params* p, GemmExPlan
   g.WN = p->prt[MDH_L_VGPR][2] * 32;
   g.BM = p->prt[MDH_L_WAVE][1] * g.WM;
   g.BN = p->prt[MDH_L_WAVE][2] * g.WN;
-  g.BK = p->prt[MDH_L_LDS][3] * 2;
+  if (p->blk[1] != 32 || p->blk[2] != 32 || (p->blk[3] != 2 && p->blk[3] != 16)) return MDH_ERR_UNSUPPORTED;
+  g.split = p->blk[3] == 16;
+  if (g.split && !split_sizes(s[1], s[2], s[3])) return MDH_ERR_UNSUPPORTED;
+  g.BK = p->prt[MDH_L_LDS][3] * p->blk[3];
   g.S = p->prt[MDH_L_WG][3];
   g.ragged = ragged;
   GemmExPlan pl{g, (int)s[4], (int)s[5], (int)s[6]};
   mdh_tile_params chk;
   params_from_plan(s, pl, &chk);
   // the layout parameters of the configuration must describe the views the call passes
-  if (!same_table(chk, *p) || !ex_inst(g)) return MDH_ERR_UNSUPPORTED;
+  if (!same_table(chk, *p) || !(g.split ? split_inst(g, s[6] != 0) : ex_inst(g))) return MDH_ERR_UNSUPPORTED;
   *out = pl;
   return MDH_OK;
 }

@@ -1,0 +1,123 @@
+// fp32 products on the 16-bit matrix instructions, with the accuracy of fp32.
+//
+// An fp32 value has 24 significant bits, a bf16 value 8, and both have the same exponents: x = h + m + l with
+// h = bf16(x), m = bf16(x - h), l = bf16(x - h - m) is exact (each difference is a float, |m| <= 2^-9 |x|,
+// |l| <= 2^-18 |x|) as long as |x| >= 2^-100, whose last bit is well above the smallest normal number.  Of the nine products of two
+// such sums the six
+//     h h'   h m'   m h'   m m'   h l'   l h'
+// are evaluated, each exact in the fp32 accumulation of v_mfma_f32_32x32x16_bf16; the three left out are below
+// 2^-26 |x x'| together, a quarter of the rounding error of ONE fp32 multiply-add.  Error against 64 bits,
+// 256 x 256 x K, relative 2-norm, one v_mfma_f32_32x32x2_f32 per two k against six bf16 instructions per 32 k:
+//     U[-1,1]  K = 64: 1.4e-7 / 1.1e-7   256: 2.8e-7 / 2.3e-7   4096: 1.15e-6 / 1.0e-6   25088: 2.8e-6 / 2.6e-6
+//     U[0,1]   K = 64: 1.2e-7 / 0.8e-7   256: 2.2e-7 / 1.8e-7   4096: 0.85e-6 / 0.5e-6   25088: 2.4e-6 / 1.6e-6
+// (all nine products: the same digits).  Rate of the bare instruction loops on random operands: 154 TFLOP/s in
+// fp32, 1850 / 6 = 308 TFLOP/s in six bf16 products (the 16x16x32 form: 2220 / 6).
+//
+// Two kinds of values need more than that, and get the fp32 instructions (recompute_* below):
+//   - not finite, or an overflow: Inf splits into Inf + NaN.  Every output that such a value enters comes out
+//     not finite, so the outputs tell;
+//   - |x| < 2^-100: its last slices may be lost to subnormal numbers, up to 2^-126.  That can matter only for an
+//     output smaller than K * 2^-100 * (largest |x| of its tile), and only if such an element is there; both are
+//     checked.
+#pragma once
+#include "mdh_internal.h"
+
+namespace mdh {
+namespace split {
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef unsigned u4 __attribute__((ext_vector_type(4)));
+
+enum { H = 0, Mid = 1, L = 2 };  // slices
+struct Yes { static constexpr bool value = true; };
+struct No { static constexpr bool value = false; };
+
+constexpr float kTiny = 7.88860905e-31f;  // 2^-100
+
+// Two values per register, and v_dot2c_f32_bf16 (x += p.lo q.lo + p.hi q.hi) to take a rounded value off again: with
+// q = (-1, 0) or (0, -1) that is the difference, in one instruction instead of an unpacking and a subtraction.
+// The vector pipe gets four instructions per 32x32x16 MFMA for free, so they count: eight values take 32.
+// The constants are hidden from the compiler, which would encode 0x0000bf80 as the inline constant -1.0 -- in a
+// packed operand that is (0, -1).
+struct Split {
+  unsigned neg_lo = 0x0000bf80u, neg_hi = 0xbf800000u;
+  float largest = 0.f;  // magnitude of what this thread has split
+
+  __device__ __forceinline__ Split() { asm("" : "+s"(neg_lo), "+s"(neg_hi)); }
+
+  static __device__ __forceinline__ unsigned pack(float a, float b) {
+    const f2 v = {a, b};
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf2));
+  }
+  static __device__ __forceinline__ float minus(float x, unsigned p, unsigned q) {
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf2, p), __builtin_bit_cast(bf2, q), x, false);
+  }
+  // eight consecutive k of one row: the three slices, 16 bytes each.  Level by level, because a result of
+  // v_dot2c can be read only a few instructions later.
+  __device__ __forceinline__ void operator()(float (&x)[8], u4 (&out)[3]) {
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (s == 0) largest = fmaxf(fmaxf(largest, fabsf(x[2 * e])), fabsf(x[2 * e + 1]));
+        out[s][e] = pack(x[2 * e], x[2 * e + 1]);
+      }
+      if (s < 2)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          x[2 * e] = minus(x[2 * e], out[s][e], neg_lo);
+          x[2 * e + 1] = minus(x[2 * e + 1], out[s][e], neg_hi);
+        }
+    }
+  }
+};
+
+__device__ __forceinline__ f16 mfma(u4 a, u4 b, f16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0, 0);
+}
+
+// is a value of n consecutive ones too small to split exactly?  (a share of the workgroup's threads: part of parts)
+__device__ __forceinline__ bool tiny(float v) { return v != 0.f && fabsf(v) < kTiny; }
+__device__ __forceinline__ bool tiny_in(const float* __restrict__ p, int n, int part, int parts) {
+  bool t = false;
+  int i = part * 4;
+#pragma unroll 4
+  for (; i + 3 < n; i += parts * 4) {
+    const f4 v = *(const f4u*)(p + i);
+    t |= tiny(v[0]) || tiny(v[1]) || tiny(v[2]) || tiny(v[3]);
+  }
+  for (int e = i; e < n && e < i + 4; ++e) t |= tiny(p[e]);
+  return t;
+}
+
+// The end of a workgroup's tile: has this wavefront to evaluate its part in fp32?  z: sum of 0 * output; least:
+// smallest |output|; largest: of the values this thread has split; terms: of one output.  `word` is LDS that held
+// 0 since before the last barrier.  scan(): whether the operands of the workgroup hold a tiny value, its threads
+// taking turns -- reached only where an output is next to nothing, for instance a row of zeros.
+template <class Scan>
+__device__ __forceinline__ bool needs_fp32(float z, float least, float largest, float terms, unsigned* word, Scan scan) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) largest = fmaxf(largest, __shfl_xor(largest, d));
+  if (lane == 0) atomicMax(word, __float_as_uint(largest));
+  __syncthreads();
+  const bool small = __any(least < terms * kTiny * __uint_as_float(*word));
+  if (__syncthreads_or(small)) {
+    const bool found = __syncthreads_or(scan());
+    return __any(!(z == 0.f)) || (small && found);
+  }
+  return __any(!(z == 0.f));
+}
+
+// buffer loads: base in scalar registers, so that a load takes no vector instruction for its address
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const float* p) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0, (int)0xffffffff, 0x00027000);
+}
+
+}  // namespace split
+}  // namespace mdh

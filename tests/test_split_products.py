@@ -1,0 +1,117 @@
+"""The kernels that carry an fp32 value as three bf16 values (six matrix products per multiply-add): tile edges,
+reduction tails, views and split reductions against 64 bits, and the values such a sum does not carry.
+
+Tolerance: the products left out are below 2^-26 of |a b|, the six that are there are exact, and every one of the
+fp32 accumulation steps (six per 16 terms, fewer than the K of a multiply-add chain) adds at most 2^-24 of the running
+sum |a b|: K * 2^-24 of sum |a b|, as for the fp32 instructions.
+"""
+import numpy as np
+import pytest
+
+import paper_2405_05118_amd as mdh
+
+torch = pytest.importorskip("torch")
+
+
+def split_candidates(inst, sizes, kdim):
+    all_ = [mdh.mdh_candidate(inst, sizes, i) for i in range(mdh.mdh_num_candidates(inst, sizes))]
+    return [p for p in all_ if p.blk[kdim] == 16]
+
+
+def test_planner_of_the_split_kernels():
+    sizes = (1000, 900, 777)
+    cands = split_candidates(mdh.MDH_MATMUL, sizes, 2)
+    assert len({(p.prt[4][0] * p.prt[2][0], p.prt[4][1] * p.prt[2][1]) for p in cands}) == 5
+    p = cands[0]
+    assert mdh.mdh_validate_params(mdh.MDH_MATMUL, sizes, p) == 0
+    bad = p.copy()
+    bad.blk[2] = 8
+    assert mdh.mdh_validate_params(mdh.MDH_MATMUL, sizes, bad) != 0
+    # fewer k than one k-tile: no split kernel
+    assert not split_candidates(mdh.MDH_MATMUL, (300, 300, 31), 2)
+    # a default that is a split tile needs no more workspace than the fp32 tile it stands before
+    rng = np.random.default_rng(5)
+    for _ in range(300):
+        M, N, K = (int(np.exp(rng.uniform(np.log(40), np.log(5000)))) for _ in range(3))
+        d = mdh.mdh_default_params(mdh.MDH_MATMUL, (M, N, K))
+        if d.blk[2] == 16 and d.blk[0] == 32:
+            fp32 = next(q for q in (mdh.mdh_candidate(mdh.MDH_MATMUL, (M, N, K), i) for i in range(3)) if q.blk[2] != 16)
+            assert d.prt[3][2] <= fp32.prt[3][2]
+
+
+# M, N, K: one row less, exactly, and one more than tiles of 64 / 128 / 256; the shortest k, whole k-tiles, tails
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(64, 64, 32), (63, 65, 33), (128, 127, 47), (257, 129, 64), (300, 520, 95), (1, 256, 161)])
+@pytest.mark.parametrize("views", [(0, 0, 0), (1, 0, 0), (0, 1, 0), (1, 1, 1), (0, 0, 1)])
+def test_matmul_split_tiles(shape, views):
+    M, N, K = shape
+    ta, tb, tc = views
+    batch = 3 if views != (0, 0, 0) else 1
+    g = torch.Generator(device="cuda").manual_seed(M * 7 + K)
+    A = torch.rand((batch, K, M) if ta else (batch, M, K), generator=g, device="cuda") * 2 - 1
+    B = torch.rand((batch, N, K) if tb else (batch, K, N), generator=g, device="cuda") * 2 - 1
+    a, b = (A.transpose(1, 2) if ta else A).cpu().double(), (B.transpose(1, 2) if tb else B).cpu().double()
+    ref, mag = a @ b, a.abs() @ b.abs()
+    plain = batch == 1
+    inst, sizes = (mdh.MDH_MATMUL, shape) if plain else (mdh.MDH_BMATMUL, (batch, M, N, K, ta, tb, tc))
+    cands = split_candidates(inst, sizes, 2 if plain else 3)
+    assert cands
+    for p in cands:
+        C = torch.full((batch, N, M) if tc else (batch, M, N), float("nan"), device="cuda")
+        n = mdh.mdh_workspace_size(inst, sizes, p)
+        ws = torch.empty(n // 4, device="cuda") if n else None
+        if plain:
+            mdh.mdh_matmul(A[0], B[0], C[0], p, ws)
+        else:
+            mdh.mdh_matmul_ex(A, B, C, bool(ta), bool(tb), bool(tc), p, ws)
+        got = (C.transpose(1, 2) if tc else C).cpu().double()
+        assert float(((got - ref).abs() / mag).max()) <= K * 2.0**-24, p.table()
+
+
+# Values a sum of three bf16 values does not carry: the outputs they enter are those of the fp32 instructions.
+@pytest.mark.gpu
+@pytest.mark.parametrize("what", ["inf", "nan", "largest", "tiny rows", "tiny against huge", "subnormal", "zero rows"])
+def test_values_beyond_the_split(what):
+    M, N, K = 200, 150, 160
+    g = torch.Generator(device="cuda").manual_seed(3)
+    A = torch.rand((M, K), generator=g, device="cuda") * 2 - 1
+    B = torch.rand((K, N), generator=g, device="cuda") * 2 - 1
+    if what == "inf":
+        A[3, 5], A[3, 6], B[7, 9], A[70, 1] = float("inf"), float("inf"), float("-inf"), float("-inf")
+        B[5, 4] = 0.0  # inf * 0
+    elif what == "nan":
+        A[130, 0], B[159, 149] = float("nan"), float("nan")
+    elif what == "largest":
+        A[11] = torch.finfo(torch.float32).max
+        B[:, 5] = B[:, 5] * 1e-3
+    elif what == "tiny rows":
+        A[20:40] *= 1e-36
+    elif what == "tiny against huge":
+        A[20:40] *= 1e-36
+        B *= 1e30
+    elif what == "subnormal":
+        A[20:40] *= 1e-40
+        B *= 1e25
+    else:
+        A[64:128] = 0.0
+    fp32 = next(q for q in (mdh.mdh_candidate(mdh.MDH_MATMUL, (M, N, K), i) for i in range(mdh.mdh_num_candidates(mdh.MDH_MATMUL, (M, N, K))))
+                if q.blk[2] == 2 and q.prt[4][2] == 1 and q.prt[3][2] == 1)
+    want = torch.empty((M, N), device="cuda")
+    mdh.mdh_matmul(A, B, want, fp32)
+    mag = A.cpu().double().abs() @ B.cpu().double().abs()
+    finite = torch.isfinite(want.cpu())
+    results = []
+    for p in split_candidates(mdh.MDH_MATMUL, (M, N, K), 2):
+        if p.prt[3][2] == 1:
+            C = torch.full((M, N), 7.0, device="cuda")
+            mdh.mdh_matmul(A, B, C, p)
+            results.append((C, p))
+    assert len(results) == 5
+    for C, p in results:
+        got = C.cpu()
+        assert torch.equal(torch.isnan(got), torch.isnan(want.cpu())), p.table()
+        assert torch.equal(got[torch.isinf(got)], want.cpu()[torch.isinf(want.cpu())]), p.table()
+        ref = (A.cpu().double() @ B.cpu().double())[finite]
+        err = (got[finite].double() - ref).abs()
+        # an output has the accuracy of fp32, or is off by what fp32 cannot hold (subnormal results)
+        assert bool((err <= K * 2.0**-24 * mag[finite] + K * 2.0**-149).all()), p.table()
