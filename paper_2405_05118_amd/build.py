@@ -24,6 +24,7 @@ SOURCES = [
     "mdh_matmul_ksplit.hip",
     "mdh_matmul_split.hip",
     "mdh_mcc.hip",
+    "mdh_mcc_split.hip",
     "mdh_mcc_flat.hip",
     "mdh_calib.hip",
     "mdh_scan.hip",

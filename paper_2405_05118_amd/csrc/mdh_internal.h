@@ -48,6 +48,8 @@ struct MccPlan {
   // few-channel kernel: 1 = the workgroup-layer parts of (n, p, q) are dealt out to resident workgroups in
   // arrival order (QT = 1), 0 = a workgroup owns QT consecutive column tiles
   int dealt = 0;
+  // 1: the channel-chunked kernel that carries every value as three bf16 values (16 channels per MFMA: prt[VGPR][c] = 8)
+  int split = 0;
 };
 
 // Custom reduce: RA records of A per lane, WB wavefronts of a workgroup split B,
@@ -228,6 +230,8 @@ mdh_status launch_matmul(const GemmPlan& pl, int64_t M, int64_t N, int64_t K, co
 mdh_status launch_mcc(const MccPlan& pl, int64_t N, int64_t H, int64_t W, int64_t C, int64_t K,
                       int64_t R, int64_t S, int64_t sh, int64_t sw, const float* in,
                       const float* filt, float* out, void* ws, hipStream_t st);
+mdh_status launch_mcc_split(const MccPlan& pl, int64_t N, int64_t H, int64_t W, int64_t C, int64_t K, int64_t R, int64_t S,
+                            int64_t sh, int64_t sw, const float* in, const float* filt, float* out, void* ws, hipStream_t st);
 mdh_status launch_mcc_flat(const MccPlan& pl, int64_t N, int64_t H, int64_t W, int64_t C, int64_t K,
                            int64_t R, int64_t S, int64_t sh, int64_t sw, const float* in,
                            const float* filt, float* out, hipStream_t st);

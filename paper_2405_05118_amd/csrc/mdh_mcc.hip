@@ -265,6 +265,7 @@ mdh_status launch_t(int SC, int64_t N, int64_t H, int64_t W, int64_t C, int64_t 
 mdh_status launch_mcc(const MccPlan& pl, int64_t N, int64_t H, int64_t W, int64_t C, int64_t K,
                       int64_t R, int64_t S, int64_t sh, int64_t sw, const float* in,
                       const float* filt, float* out, void* ws, hipStream_t st) {
+  if (pl.split) return launch_mcc_split(pl, N, H, W, C, K, R, S, sh, sw, in, filt, out, ws, st);
 #define MDH_MCC(tp, tq, bn, ck, wm, wn)                                                          \
   if (pl.TP == tp && pl.TQ == tq && pl.BN == bn && pl.CK == ck && pl.WM == wm && pl.WN == wn)    \
     return launch_t<tp, tq, bn, ck, wm, wn>(pl.S, N, H, W, C, K, R, S, sh, sw, in, filt, out, ws, st);

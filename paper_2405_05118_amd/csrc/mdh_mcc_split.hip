@@ -1,0 +1,360 @@
+// Multi-channel convolution instance of md_hom(*, (++,++,++,++,+,+,+)) for gfx950 on the bf16 matrix instructions,
+// every fp32 value carried as a sum of three bf16 values (mdh_split.h: six products per multiply-add, accuracy of
+// fp32).  out[n,p,q,k] = sum_{c,r,s} in[n, p*sh + r, q*sw + s, c] * filt[k,r,s,c]    (NHWC, KRSC, NPQK)
+//
+// De-composition as in mdh_mcc.hip, dims (n,p,q,k,c,r,s): a workgroup owns TP x TQ pixels of one image and BN
+// output channels; per chunk of CK channels the input patch is split and staged ONCE for all R*S taps -- so a value
+// of the input is split about once per workgroup, not once per product -- and the filter slice of a tap is split and
+// staged while the tap before it is multiplied.  Block: 32 pixels x 32 output channels x 16 input channels, six
+// v_mfma_f32_32x32x16_bf16.
+// LDS: patch [slice][c / 8][pixel] and filter [slice][c / 8][k], 16 bytes (eight channels) per entry, so that an
+// MFMA operand of a lane is one ds_read_b128.
+#include "mdh_split.h"
+
+namespace mdh {
+namespace {
+
+using namespace split;
+
+template <int TP, int TQ, int BN, int CK, int WM, int WN>
+struct Cfg {
+  static_assert(TQ == 32 || TQ == 16 || TQ == 8, "an MFMA block spans 32 pixels: 32/TQ rows of TQ columns");
+  static constexpr int RB = 32 / TQ;  // output rows per block
+  static constexpr int MI = WM / 32, NI = WN / 32;
+  static_assert(TP % (MI * RB) == 0, "rows of the tile = wavefronts x blocks x rows per block");
+  static constexpr int WAVES_M = TP / (MI * RB), WAVES_N = BN / WN;
+  static constexpr int NT = WAVES_M * WAVES_N * 64;
+  static constexpr int KP = CK / 8, KH = CK / 16;
+  static constexpr int F_PLANE = BN * 16, F_SLICE = KP * F_PLANE, F_STAGE = 3 * F_SLICE;
+  static constexpr int F_CHUNKS = BN * KP;
+  static constexpr int F_CH = (F_CHUNKS + NT - 1) / NT;
+  // patch planes are padded so that the planes of one pixel start 64 (CK = 16) or 32 bytes apart in the banks
+  static constexpr int PAD = CK == 16 ? 4 : 2;
+  static __host__ __device__ __forceinline__ int plane(int npix) { return ((npix + 7) / 8 * 8 + PAD) * 16; }
+};
+
+struct Conv {
+  const float *in, *filt;
+  float* out;
+  int H, W, C, K, R, S, sh, sw, P, Q;
+};
+
+// fp32 evaluation of a wavefront's blocks, for values the split does not carry
+template <int TP, int TQ, int BN, int CK, int WM, int WN>
+__device__ __forceinline__ void recompute_fp32(const Conv& g, float* __restrict__ dst, int n, int p0, int q0, int k0, int cbeg, int cend) {
+  using C = Cfg<TP, TQ, BN, CK, WM, WN>;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, lh = lane >> 5;
+  const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
+  for (int mi = 0; mi < C::MI; ++mi)
+    for (int ni = 0; ni < C::NI; ++ni) {
+      const int pb = p0 + (wm * C::MI + mi) * C::RB, kb = k0 + wn * WN + ni * 32;
+      if (pb >= g.P || kb >= g.K) continue;
+      const int p = min(pb + l32 / TQ, g.P - 1), q = min(q0 + l32 % TQ, g.Q - 1), k = min(kb + l32, g.K - 1);
+      f16 acc;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+      for (int r = 0; r < g.R; ++r)
+        for (int s = 0; s < g.S; ++s) {
+          const float* a = g.in + (((int64_t)n * g.H + p * g.sh + r) * g.W + q * g.sw + s) * g.C;
+          const float* b = g.filt + (((int64_t)k * g.R + r) * g.S + s) * g.C;
+#pragma unroll 4
+          for (int c0 = cbeg; c0 < cend; c0 += 8)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+              const int c = c0 + lh * 4 + t;
+              acc = __builtin_amdgcn_mfma_f32_32x32x2f32(c < cend ? b[c] : 0.f, c < cend ? a[c] : 0.f, acc, 0, 0, 0);
+            }
+        }
+      if (pb + l32 / TQ >= g.P || q0 + l32 % TQ >= g.Q) continue;
+      float* o = dst + (((int64_t)n * g.P + p) * g.Q + q) * g.K;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int ko = kb + 8 * (r / 4) + 4 * lh + r % 4;
+        if (ko < g.K) o[ko] = acc[r];
+      }
+    }
+}
+
+// does the workgroup's part of the input or of the filter hold an element too small to split exactly?  (this thread's share)
+template <int NT>
+__device__ __forceinline__ bool holds_tiny(const Conv& g, int n, int h0, int nh, int w0, int nw, int k0, int nk, int cbeg, int cend) {
+  bool t = false;
+  constexpr int W = 4;  // threads per contiguous run of channels
+  const int part = threadIdx.x % W, nc = cend - cbeg;
+  nh = min(nh, g.H - h0), nw = min(nw, g.W - w0), nk = min(nk, g.K - k0);
+  for (int i = threadIdx.x / W; i < nh * nw; i += NT / W)
+    t |= tiny_in(g.in + (((int64_t)n * g.H + h0 + i / nw) * g.W + w0 + i % nw) * g.C + cbeg, nc, part, W);
+  for (int i = threadIdx.x / W; i < nk * g.R * g.S; i += NT / W)
+    t |= tiny_in(g.filt + ((int64_t)k0 * g.R * g.S + i) * g.C + cbeg, nc, part, W);
+  return t;
+}
+
+// One tap is six phases, one per product, as a k-tile of the split MatMul: LDS holds the filter slices of two taps,
+// the filter of tap t+1 is split while tap t is multiplied, that of tap t+2 is on its way from memory, and the one
+// barrier of a tap stands where all its operands are in registers.
+template <int TP, int TQ, int BN, int CK, int WM, int WN>
+__global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT)) void mcc_split_kernel(Conv g, float* __restrict__ ws, int tp_n, int tq_n,
+                                                                                    int tk_n, int n_img, int SC, int cchunk) {
+  using F = Cfg<TP, TQ, BN, CK, WM, WN>;
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  // XCD-aware order: each of the 8 XCDs gets a contiguous run of tiles; inside a run the channel tiles of one
+  // pixel patch come first (they share the patch), then q, p, n.
+  int b = blockIdx.x;
+  const int nb = gridDim.x;
+  if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);
+  const int tk = b % tk_n, tq = (b / tk_n) % tq_n, tp = (b / (tk_n * tq_n)) % tp_n;
+  const int n = (b / (tk_n * tq_n * tp_n)) % n_img;
+  const int sc = b / (tk_n * tq_n * tp_n * n_img);  // part of the reduction dimension c
+  const int p0 = tp * TP, q0 = tq * TQ, k0 = tk * BN;
+  const int cbeg = sc * cchunk, cend = min(g.C, cbeg + cchunk);
+  float* const dst = SC > 1 ? ws + (int64_t)sc * n_img * g.P * g.Q * g.K : g.out;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wm = wave / F::WAVES_N, wn = wave % F::WAVES_N;
+  const int l32 = lane & 31, lh = lane >> 5;
+  const int PH = (TP - 1) * g.sh + g.R, PW = (TQ - 1) * g.sw + g.S, npix = PH * PW;
+  const int pplane = F::plane(npix), pslice = F::KP * pplane;
+  char* const patch = lds + 2 * F::F_STAGE;
+  unsigned* const largest = (unsigned*)(patch + 3 * pslice);
+  if (tid == 0) *largest = 0;
+
+  f16 acc[F::MI][F::NI];
+#pragma unroll
+  for (int mi = 0; mi < F::MI; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < F::NI; ++ni)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
+
+  Split split;
+  const int taps = g.R * g.S;
+  // filter chunks of this thread: eight channels of one output channel; channels beyond K repeat the last one
+  float fx[F::F_CH][8];
+  unsigned foff[F::F_CH];
+#pragma unroll
+  for (int c = 0; c < F::F_CH; ++c) {
+    const int f = (tid + c * F::NT) % F::F_CHUNKS;
+    foff[c] = (unsigned)(min(f / F::KP, g.K - 1 - k0) * (taps * g.C) + f % F::KP * 8) * 4u;
+  }
+  const float* const fbase = g.filt + (int64_t)k0 * taps * g.C;
+  auto load_filter = [&](int tap, int c0, int c) {
+    const auto r = rsrc(fbase + tap * g.C + c0);
+    const f4 a = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, foff[c], 0, 0));
+    const f4 d = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, foff[c] + 16, 0, 0));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) fx[c][e] = a[e], fx[c][e + 4] = d[e];
+  };
+  // (a workgroup with more threads than chunks writes some of them twice, the same bytes)
+  auto store_filter = [&](char* st, int c) {
+    const int f = (tid + c * F::NT) % F::F_CHUNKS;
+    const int k = f / F::KP, kc = f % F::KP;
+    u4 v[3];
+    split(fx[c], v);
+    char* p = st + kc * F::F_PLANE + (k ^ (64 / CK * kc)) * 16;
+#pragma unroll
+    for (int s = 0; s < 3; ++s) *(u4*)(p + s * F::F_SLICE) = v[s];
+  };
+  // input patch of the channels from c0 on; the first `skip` of them belong to the chunk before and read as 0
+  auto stage_patch = [&](int c0, int skip) {
+    for (int f = tid; f < npix * F::KP; f += F::NT) {
+      const int pix = f / F::KP, kc = f % F::KP;
+      const int ph = pix / PW, pw = pix - ph * PW;
+      const int hy = min(p0 * g.sh + ph, g.H - 1), wx = min(q0 * g.sw + pw, g.W - 1);
+      const float* p = g.in + (((int64_t)n * g.H + hy) * g.W + wx) * g.C + c0 + kc * 8;
+      const f4 a = *(const f4u*)p, d = *(const f4u*)(p + 4);
+      float x[8];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] = a[e], x[e + 4] = d[e];
+      if (skip) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = kc * 8 + e < skip ? 0.f : x[e];
+      }
+      u4 v[3];
+      split(x, v);
+#pragma unroll
+      for (int s = 0; s < 3; ++s) *(u4*)(patch + s * pslice + kc * pplane + pix * 16) = v[s];
+    }
+  };
+
+  u4 y[3][F::MI][F::KH], x[3][F::NI][F::KH];
+  const int pix0 = (wm * F::MI * F::RB + l32 / TQ) * g.sh * PW + l32 % TQ * g.sw;
+  const int block_rows = F::RB * g.sh * PW * 16;  // LDS distance between consecutive blocks of a wavefront
+  auto read_y = [&](int at, int s) {  // at: the tap's pixel offset
+#pragma unroll
+    for (int h = 0; h < F::KH; ++h)
+#pragma unroll
+      for (int mi = 0; mi < F::MI; ++mi)
+        y[s][mi][h] = *(const u4*)(patch + s * pslice + (2 * h + lh) * pplane + (pix0 + at) * 16 + mi * block_rows);
+  };
+  auto read_x = [&](const char* st, int s) {
+#pragma unroll
+    for (int h = 0; h < F::KH; ++h) {
+      const int kc = 2 * h + lh;
+      const char* p = st + s * F::F_SLICE + kc * F::F_PLANE + (wn * WN + (l32 ^ (64 / CK * kc))) * 16;
+#pragma unroll
+      for (int ni = 0; ni < F::NI; ++ni) x[s][ni][h] = *(const u4*)(p + ni * 512);
+    }
+  };
+  auto mma = [&](int sy, int sx) {
+#pragma unroll
+    for (int h = 0; h < F::KH; ++h)
+#pragma unroll
+      for (int mi = 0; mi < F::MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < F::NI; ++ni) acc[mi][ni] = mfma(x[sx][ni][h], y[sy][mi][h], acc[mi][ni]);
+  };
+  // phases 0 to 3 are one scheduling region: an MFMA, an LDS read for a later phase, a share of the next tap's split
+  auto body = [&](int tap, int at, int at_next, int c0, auto more_) {
+    constexpr bool more = decltype(more_)::value;
+    const char* cur = lds + (tap & 1) * F::F_STAGE;
+    read_x(cur, H);
+    mma(H, L);
+    read_y(at, L);
+    mma(H, H);
+    read_x(cur, Mid);
+    mma(L, H);
+    read_y(at, Mid);
+    mma(H, Mid);
+    if (more) {
+#pragma unroll
+      for (int c = 0; c < F::F_CH; ++c) {
+        store_filter(lds + ((tap + 1) & 1) * F::F_STAGE, c);
+        load_filter(min(tap + 2, taps - 1), c0, c);
+      }
+    }
+    constexpr int NM = 4 * F::KH * F::MI * F::NI, V = (36 * F::F_CH + NM - 1) / NM;
+#pragma unroll
+    for (int i = 0; i < NM; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      if (more) __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (more) {
+      __syncthreads();
+      read_y(at_next, H);
+      read_x(lds + ((tap + 1) & 1) * F::F_STAGE, L);
+    }
+    mma(Mid, H);
+    mma(Mid, Mid);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  for (int cc = cbeg; cc < cend; cc += CK) {
+    // the last chunk ends with the last channel: where the part is no whole number of chunks it starts inside the
+    // chunk before it
+    const int c0 = min(cc, cend - CK);
+#pragma unroll
+    for (int c = 0; c < F::F_CH; ++c) load_filter(0, c0, c);
+    if (cc > cbeg) __syncthreads();  // every wavefront is done with the previous patch and filter stages
+    stage_patch(c0, cc - c0);
+#pragma unroll
+    for (int c = 0; c < F::F_CH; ++c) {
+      store_filter(lds, c);
+      load_filter(min(1, taps - 1), c0, c);
+    }
+    __syncthreads();
+    read_y(0, H);
+    read_x(lds, L);
+    int r = 0, s = 0;
+    for (int tap = 0; tap + 1 < taps; ++tap) {
+      const int at = r * PW + s;
+      if (++s == g.S) s = 0, ++r;
+      body(tap, at, r * PW + s, c0, Yes{});
+    }
+    body(taps - 1, r * PW + s, 0, c0, No{});
+  }
+
+  // values the split does not carry (mdh_split.h)
+  float z = 0.f, least = __builtin_huge_valf();
+#pragma unroll
+  for (int mi = 0; mi < F::MI; ++mi)
+#pragma unroll
+    for (int ni = 0; ni < F::NI; ++ni)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        z = __builtin_fmaf(acc[mi][ni][r], 0.f, z);
+        least = fminf(least, fabsf(acc[mi][ni][r]));
+      }
+  if (needs_fp32(z, least, split.largest, (float)(taps * (cend - cbeg)), largest, [&] {
+        return holds_tiny<F::NT>(g, n, p0 * g.sh, PH, q0 * g.sw, PW, k0, BN, cbeg, cend);
+      })) {
+    recompute_fp32<TP, TQ, BN, CK, WM, WN>(g, dst, n, p0, q0, k0, cbeg, cend);
+    return;
+  }
+
+  // output view (n,p,q,k,0,0,0) -> out[n,p,q,k]: a lane holds four consecutive k of one pixel
+  const bool whole = p0 + TP <= g.P && q0 + TQ <= g.Q && k0 + BN <= g.K;
+#pragma unroll
+  for (int mi = 0; mi < F::MI; ++mi) {
+    const int p = p0 + (wm * F::MI + mi) * F::RB + l32 / TQ, q = q0 + l32 % TQ, kb = k0 + wn * WN + 4 * lh;
+    float* const o = dst + (((int64_t)n * g.P + p) * g.Q + q) * g.K + kb;
+#pragma unroll
+    for (int ni = 0; ni < F::NI; ++ni)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const int j = ni * 32 + 8 * q4;
+        const f4 v = {acc[mi][ni][4 * q4], acc[mi][ni][4 * q4 + 1], acc[mi][ni][4 * q4 + 2], acc[mi][ni][4 * q4 + 3]};
+        if (whole) {
+          *(f4u*)(o + j) = v;
+        } else if (p < g.P && q < g.Q) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (kb + j + e < g.K) o[j + e] = v[e];
+        }
+      }
+  }
+}
+
+template <int TP, int TQ, int BN, int CK, int WM, int WN>
+mdh_status launch_t(int SC, int64_t N, const Conv& g, void* ws, hipStream_t st) {
+  using F = Cfg<TP, TQ, BN, CK, WM, WN>;
+  const int npix = ((TP - 1) * g.sh + g.R) * ((TQ - 1) * g.sw + g.S);
+  const int64_t lds_bytes = 2ll * F::F_STAGE + 3ll * F::KP * F::plane(npix) + 16;
+  if (lds_bytes > 160 * 1024) return MDH_ERR_TILE_RESOURCES;
+  auto kern = mcc_split_kernel<TP, TQ, BN, CK, WM, WN>;
+  static int64_t lds_allowed[kMaxDevices] = {};
+  if (allow_dynamic_lds((const void*)kern, lds_bytes, lds_allowed) != MDH_OK) return MDH_ERR_LAUNCH;
+  const int64_t tp_n = cdiv(g.P, TP), tq_n = cdiv(g.Q, TQ), tk_n = cdiv(g.K, BN);
+  if (SC < 1) return MDH_ERR_UNSUPPORTED;
+  const int64_t cchunk = cdiv(cdiv(g.C, SC), CK) * CK;
+  if ((SC - 1) * cchunk >= g.C) return MDH_ERR_TILE_NOT_DIVIDING;  // a part without channels
+  const int64_t nblocks = N * tp_n * tq_n * tk_n * SC;
+  if (nblocks > 0x7fffffff) return MDH_ERR_SIZE;
+  clear_stale_error();
+  hipLaunchKernelGGL(kern, dim3((unsigned)nblocks), dim3(F::NT), (size_t)lds_bytes, st, g, (float*)ws, (int)tp_n, (int)tq_n,
+                     (int)tk_n, (int)N, SC, (int)cchunk);
+  mdh_status r = launch_status();
+  if (r != MDH_OK || SC <= 1) return r;
+  return launch_combine_sum((const float*)ws, g.out, N * g.P * g.Q * g.K, SC, st);
+}
+
+}  // namespace
+
+mdh_status launch_mcc_split(const MccPlan& pl, int64_t N, int64_t H, int64_t W, int64_t C, int64_t K, int64_t R, int64_t S,
+                            int64_t sh, int64_t sw, const float* in, const float* filt, float* out, void* ws, hipStream_t st) {
+  const Conv g{in,     filt,   out,    (int)H,  (int)W, (int)C, (int)K, (int)R, (int)S, (int)sh, (int)sw,
+               (int)((H - R) / sh + 1), (int)((W - S) / sw + 1)};
+#define MDH_CS(tp, tq, bn, ck, wm, wn)                                                        \
+  if (pl.TP == tp && pl.TQ == tq && pl.BN == bn && pl.CK == ck && pl.WM == wm && pl.WN == wn) \
+    return launch_t<tp, tq, bn, ck, wm, wn>(pl.S, N, g, ws, st);
+  MDH_CS(8, 32, 128, 16, 64, 64)
+  MDH_CS(4, 32, 128, 16, 64, 64)
+  MDH_CS(4, 32, 64, 16, 64, 32)
+  MDH_CS(8, 16, 128, 16, 64, 64)
+  MDH_CS(8, 16, 64, 16, 64, 32)
+  MDH_CS(8, 8, 128, 16, 32, 64)
+  MDH_CS(8, 8, 64, 16, 32, 32)
+  MDH_CS(8, 32, 128, 32, 64, 64)
+  MDH_CS(4, 32, 128, 32, 64, 64)
+  MDH_CS(4, 32, 64, 32, 64, 32)
+  MDH_CS(8, 16, 128, 32, 64, 64)
+  MDH_CS(8, 16, 64, 32, 64, 32)
+  MDH_CS(16, 8, 64, 32, 64, 32)
+  MDH_CS(8, 8, 128, 32, 32, 64)
+  MDH_CS(8, 8, 64, 32, 32, 32)
+#undef MDH_CS
+  return MDH_ERR_UNSUPPORTED;
+}
+
+}  // namespace mdh

@@ -546,9 +546,16 @@ static const MccInst kMccFlatMenu[] = {
     {8, 16, 64, 0, 32, 32},  {4, 32, 64, 0, 32, 32},   {16, 16, 32, 0, 32, 32},  {8, 32, 32, 0, 32, 32},  // eight wavefronts
 };
 
+// channel-chunked kernel that splits fp32 values into bf16 slices
+static const MccInst kMccSplitMenu[] = {
+    {8, 32, 128, 16, 64, 64}, {4, 32, 128, 16, 64, 64}, {4, 32, 64, 16, 64, 32}, {8, 16, 128, 16, 64, 64}, {8, 16, 64, 16, 64, 32},
+    {8, 8, 128, 16, 32, 64},  {8, 8, 64, 16, 32, 32},   {8, 32, 128, 32, 64, 64}, {4, 32, 128, 32, 64, 64}, {4, 32, 64, 32, 64, 32},
+    {8, 16, 128, 32, 64, 64}, {8, 16, 64, 32, 64, 32},  {16, 8, 64, 32, 64, 32}, {8, 8, 128, 32, 32, 64}, {8, 8, 64, 32, 32, 32},
+};
+
 static bool mcc_inst(const MccPlan& pl) {
-  const MccInst* menu = pl.flat ? kMccFlatMenu : kMccMenu;
-  const int n = pl.flat ? (int)(sizeof(kMccFlatMenu) / sizeof(MccInst)) : (int)(sizeof(kMccMenu) / sizeof(MccInst));
+  const MccInst* menu = pl.flat ? kMccFlatMenu : pl.split ? kMccSplitMenu : kMccMenu;
+  const int n = (int)(pl.flat ? sizeof(kMccFlatMenu) : pl.split ? sizeof(kMccSplitMenu) : sizeof(kMccMenu)) / (int)sizeof(MccInst);
   for (int i = 0; i < n; ++i) {
     const MccInst& m = menu[i];
     if (m.TP == pl.TP && m.TQ == pl.TQ && m.BN == pl.BN && m.CK == pl.CK && m.WM == pl.WM && m.WN == pl.WN)
@@ -561,6 +568,7 @@ static bool mcc_inst(const MccPlan& pl) {
 int64_t mcc_lds_bytes(const MccPlan& pl, const int64_t* s) {
   if (pl.flat) return mcc_flat_lds_bytes(pl.TQ, pl.TP, pl.BN, s[4], s[5], s[6], s[7], s[8]);
   const int64_t ph = (pl.TP - 1) * s[7] + s[5], pw = (pl.TQ - 1) * s[8] + s[6];
+  if (pl.split) return 6ll * pl.CK * (cdiv(ph * pw, 8) * 8 + (pl.CK == 16 ? 4 : 2)) + 12ll * pl.BN * pl.CK + 16;
   return (ph * pw * (pl.CK + 4) + 2ll * pl.BN * (pl.CK + 4)) * 4;
 }
 
@@ -592,9 +600,10 @@ void params_from_plan(const int64_t* s, const MccPlan& pl, mdh_tile_params* p) {
     p->blk[1] = rb;
     p->blk[2] = pl.TQ;
     p->blk[4] = 2;
+    if (pl.split) p->prt[MDH_L_VGPR][4] = 8;  // 16 channels per v_mfma_f32_32x32x16_bf16
     p->prt[MDH_L_WG][4] = pl.S;  // parts of the reduction dimension c over workgroups
     p->prt[MDH_L_HBM][4] = (int32_t)cdiv(cdiv(s[4], pl.S), pl.CK);
-    p->prt[MDH_L_LDS][4] = pl.CK / 2;
+    p->prt[MDH_L_LDS][4] = pl.split ? pl.CK / 16 : pl.CK / 2;
     // wavefront grid: TP/(mi*rb) along p, BN/WN along k; mi blocks along p per wavefront
     p->prt[MDH_L_WAVE][1] = pl.TP / (mi * rb);
     p->prt[MDH_L_VGPR][1] = mi;
@@ -609,6 +618,13 @@ void params_from_plan(const int64_t* s, const MccPlan& pl, mdh_tile_params* p) {
   p->in_region[1] = MDH_MR_LDS;
   p->out_region = MDH_MR_VGPR;
   p->ragged = (uint8_t)pl.ragged;
+}
+
+// the split kernel reads whole channel chunks, the last one ending with the last channel; a filter row's address is
+// a 32-bit offset from the tile's first
+static bool mcc_split_sizes(const int64_t* s, const MccPlan& pl) {
+  const int64_t part = cdiv(cdiv(s[4], pl.S), pl.CK) * pl.CK;
+  return s[4] >= pl.CK && (pl.S - 1) * part < s[4] && s[5] * s[6] * s[4] <= (1 << 22);
 }
 
 static int mcc_ragged(const int64_t* s, const MccPlan& pl) {
@@ -676,7 +692,8 @@ static bool flat_input_ok(const int64_t* s) {
   return (s[0] > 0 ? s[0] : 1) * ((s[1] > 0 ? s[1] - 1 : 0) * s[7] + s[5]) * ((s[2] > 0 ? s[2] - 1 : 0) * s[8] + s[6]) * s[4] >= 4;
 }
 
-static MccPlan mcc_default(const int64_t* s) {
+// the fp32 kernels' choice
+static MccPlan mcc_default_fp32(const int64_t* s) {
   if (s[4] <= 8 && flat_input_ok(s)) {  // fewer channels than half a channel chunk: fuse s and c
     MccPlan f = mcc_flat_plan(s);
     if (mcc_lds_bytes(f, s) <= kLdsBytesPerWG) return f;
@@ -730,6 +747,63 @@ static MccPlan mcc_default(const int64_t* s) {
   return pl;
 }
 
+// Microseconds one filter tap of 32 channels takes the workgroups a compute unit holds (index: how many, less one),
+// per tile of kMccSplitMenu's shapes.  Measured on 3 x 3 and 7 x 7 layers of 16 to 512 channels.
+struct TapTime {
+  int px, BN, held;
+  double us[4];
+};
+static const TapTime kTap[] = {{64, 64, 4, {0.58, 0.80, 1.10, 1.40}}, {64, 128, 2, {0.80, 1.40}}, {128, 64, 3, {0.76, 1.32, 1.90}},
+                               {128, 128, 2, {1.22, 2.25}},          {256, 128, 1, {2.17}}};
+
+static double mcc_split_estimate(const int64_t* s, const MccPlan& pl) {
+  const int64_t P = s[1] > 0 ? s[1] : 1, Q = s[2] > 0 ? s[2] : 1;
+  const TapTime* t = kTap;
+  while (t->px != pl.TP * pl.TQ || t->BN != pl.BN) ++t;
+  const int64_t lds = kLdsBytesPerWG / mcc_lds_bytes(pl, s);
+  const int held = (int)(lds < t->held ? lds : t->held);
+  const int64_t work = (s[0] > 0 ? s[0] : 1) * cdiv(P, pl.TP) * cdiv(Q, pl.TQ) * cdiv(s[3] > 0 ? s[3] : 1, pl.BN) * pl.S;
+  const int64_t npix = ((pl.TP - 1) * s[7] + s[5]) * ((pl.TQ - 1) * s[8] + s[6]);
+  // per chunk of channels: the patch, then the taps; a chunk of 16 channels takes a little more than half of 32
+  const double half = pl.CK == 16 ? 0.55 : 1.0;
+  const int64_t chunks = cdiv(cdiv(s[4], pl.S), pl.CK);
+  auto round = [&](int r) {
+    return chunks * (s[5] * s[6] * t->us[r - 1] * half + (0.5 + 0.002 * npix * half) * (1 + 0.3 * (r - 1)));
+  };
+  double us = (double)(work / (256 * held)) * round(held);
+  const int64_t rest = work % (256 * held);
+  if (rest) us += round((int)cdiv(rest, 256));
+  if (pl.S > 1) us += 4.0 + (double)(pl.S + 1) * s[0] * P * Q * s[3] * 1e-6;  // second pass: 4 bytes at 4 TB/s
+  return us;
+}
+
+// Which tile of the split kernel the default is.  The pixel block is the fp32 rule's (TQ).  `S` is the number of parts the fp32 rule splits c into: not more
+// parts here, so that no call needs more workspace than it does there.  It is ahead of the fp32 kernels on every
+// layer measured from 16 channels on (us, against theirs): 16 x 224 x 224 x 64 -> 128, 7 x 7: 2766 / 4829; 16 x 56 x
+// 56 x 64 -> 64, 3 x 3: 28.8 / 51.1; 1 x 1, 256 -> 64: 21.5 / 29.6; 16 x 7 x 7 x 512 -> 512, 3 x 3 at N = 32: 67.5 / 109;
+// 1 x 18 x 19 x 40 -> 33: 10.5 / 14.8.  Below 16 channels a chunk is mostly padding, and a reduction of less than 128 terms
+// is all first and last tap (1 x 1, 64 -> 256: 29.0 / 27.8).
+static bool mcc_split_default(const int64_t* s, int TQ, int S, MccPlan* out) {
+  double best = -1;
+  if (s[4] * s[5] * s[6] < 128) return false;
+  for (auto& m : kMccSplitMenu)
+    for (int parts = 1; parts <= S; parts *= 2) {
+      MccPlan pl{m.TP, m.TQ, m.BN, m.CK, m.WM, m.WN, 0, 0};
+      pl.S = parts;
+      pl.split = 1;
+      if (pl.TQ != TQ || !mcc_split_sizes(s, pl) || mcc_lds_bytes(pl, s) > kLdsBytesPerWG) continue;
+      const double us = mcc_split_estimate(s, pl);
+      if (best < 0 || us < best) best = us, *out = pl;
+    }
+  return best >= 0;
+}
+
+static MccPlan mcc_default(const int64_t* s) {
+  MccPlan pl = mcc_default_fp32(s);
+  if (!pl.flat && mcc_split_default(s, pl.TQ, pl.S, &pl)) pl.ragged = mcc_ragged(s, pl);
+  return pl;
+}
+
 int mcc_candidates(const int64_t* s, MccPlan* out, int cap) {
   int n = 0;
   auto push = [&](MccPlan pl) {
@@ -738,12 +812,23 @@ int mcc_candidates(const int64_t* s, MccPlan* out, int cap) {
     pl.ragged = mcc_ragged(s, pl);
     for (int i = 0; i < n; ++i)
       if (out[i].flat == pl.flat && out[i].TP == pl.TP && out[i].TQ == pl.TQ && out[i].BN == pl.BN && out[i].CK == pl.CK &&
-          out[i].WM == pl.WM && out[i].WN == pl.WN && out[i].QT == pl.QT && out[i].S == pl.S && out[i].dealt == pl.dealt)
+          out[i].WM == pl.WM && out[i].WN == pl.WN && out[i].QT == pl.QT && out[i].S == pl.S && out[i].dealt == pl.dealt && out[i].split == pl.split)
         return;
     out[n++] = pl;
   };
   push(mcc_default(s));
+  push(mcc_default_fp32(s));
   for (auto& m : kMccMenu) push(MccPlan{m.TP, m.TQ, m.BN, m.CK, m.WM, m.WN, 0, 0});
+  for (int S : {1, 2, 4, 8})
+    for (auto& m : kMccSplitMenu) {
+      MccPlan pl{m.TP, m.TQ, m.BN, m.CK, m.WM, m.WN, 0, 0};
+      pl.S = S;
+      pl.split = 1;
+      const int64_t wg = (s[0] > 0 ? s[0] : 1) * cdiv(s[1] > 0 ? s[1] : 1, m.TP) * cdiv(s[2] > 0 ? s[2] : 1, m.TQ) *
+                         cdiv(s[3] > 0 ? s[3] : 1, m.BN);
+      if ((S > 1 && wg * (S / 2) >= 512) || !mcc_split_sizes(s, pl)) continue;
+      push(pl);
+    }
   // the reduction dimension c over workgroups, where the concatenation dimensions leave the chip empty
   for (int S : {2, 4, 8})
     for (auto& m : kMccMenu) {
@@ -802,11 +887,13 @@ mdh_status plan_mcc(const int64_t* s, const mdh_tile_params* p, MccPlan* out) {
     if (pl.TQ != 8 && pl.TQ != 16 && pl.TQ != 32) return MDH_ERR_UNSUPPORTED;
     pl.WM = p->prt[MDH_L_VGPR][1] * 32;
     pl.TP = p->prt[MDH_L_WAVE][1] * p->prt[MDH_L_VGPR][1] * (32 / pl.TQ);
-    pl.CK = p->prt[MDH_L_LDS][4] * 2;
+    pl.split = p->prt[MDH_L_VGPR][4] == 8;
+    pl.CK = p->prt[MDH_L_LDS][4] * 2 * p->prt[MDH_L_VGPR][4];
     pl.S = p->prt[MDH_L_WG][4];
     // a workgroup part of c that owns no channel would leave its partial output unset
     if (pl.S > 1 && pl.CK > 0 && (int64_t)(pl.S - 1) * cdiv(cdiv(s[4], pl.S), pl.CK) * pl.CK >= s[4])
       return MDH_ERR_TILE_NOT_DIVIDING;
+    if (pl.split && (pl.CK < 16 || !mcc_split_sizes(s, pl))) return MDH_ERR_UNSUPPORTED;
   }
   pl.ragged = ragged;
   if (mcc_lds_bytes(pl, s) > kLdsBytesPerWG) return MDH_ERR_TILE_RESOURCES;

@@ -15,6 +15,8 @@ torch = pytest.importorskip("torch")
 
 def split_candidates(inst, sizes, kdim):
     all_ = [mdh.mdh_candidate(inst, sizes, i) for i in range(mdh.mdh_num_candidates(inst, sizes))]
+    if inst == mdh.MDH_MCC:  # 16 input channels per matrix instruction, as eight register parts of two
+        return [p for p in all_ if p.prt[2][kdim] == 8]
     return [p for p in all_ if p.blk[kdim] == 16]
 
 
@@ -27,8 +29,10 @@ def test_planner_of_the_split_kernels():
     bad = p.copy()
     bad.blk[2] = 8
     assert mdh.mdh_validate_params(mdh.MDH_MATMUL, sizes, bad) != 0
-    # fewer k than one k-tile: no split kernel
+    # fewer k than one k-tile, few channels: no split kernel
     assert not split_candidates(mdh.MDH_MATMUL, (300, 300, 31), 2)
+    assert not split_candidates(mdh.MDH_MCC, (2, 20, 20, 64, 15, 3, 3, 1, 1), 4)
+    assert split_candidates(mdh.MDH_MCC, (2, 20, 20, 64, 16, 3, 3, 1, 1), 4)
     # a default that is a split tile needs no more workspace than the fp32 tile it stands before
     rng = np.random.default_rng(5)
     for _ in range(300):
@@ -68,6 +72,30 @@ def test_matmul_split_tiles(shape, views):
         assert float(((got - ref).abs() / mag).max()) <= K * 2.0**-24, p.table()
 
 
+# N, H, W, C, K, R, S, stride: channel tails of both chunk sizes, edges of p, q and k, one tap, strides
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", [(1, 10, 34, 16, 64, 3, 3, 1), (2, 11, 19, 33, 70, 3, 2, 1), (1, 9, 9, 47, 129, 1, 1, 1),
+                                  (2, 17, 40, 70, 31, 5, 5, 2), (1, 14, 38, 64, 128, 7, 7, 1)])
+def test_mcc_split_tiles(case):
+    N, H, W, C, K, R, S, st = case
+    P, Q = (H - R) // st + 1, (W - S) // st + 1
+    g = torch.Generator(device="cuda").manual_seed(C * 11 + K)
+    x = torch.randn((N, H, W, C), generator=g, device="cuda")
+    f = torch.randn((K, R, S, C), generator=g, device="cuda")
+    win = x.cpu().double().unfold(1, R, st).unfold(2, S, st).permute(0, 1, 2, 4, 5, 3).reshape(N * P * Q, R * S * C)
+    flat = f.cpu().double().reshape(K, R * S * C).t()
+    ref, mag = (win @ flat).view(N, P, Q, K), (win.abs() @ flat.abs()).view(N, P, Q, K)
+    sizes = (N, P, Q, K, C, R, S, st, st)
+    cands = split_candidates(mdh.MDH_MCC, sizes, 4)
+    assert cands
+    for p in cands:
+        out = torch.full((N, P, Q, K), float("nan"), device="cuda")
+        n = mdh.mdh_workspace_size(mdh.MDH_MCC, sizes, p)
+        mdh.mdh_mcc(x, f, out, (st, st), p, torch.empty(n // 4, device="cuda") if n else None)
+        err = float(((out.cpu().double() - ref).abs() / mag).max())
+        assert err <= R * S * C * 2.0**-24, (p.table(), err)
+
+
 # Values a sum of three bf16 values does not carry: the outputs they enter are those of the fp32 instructions.
 @pytest.mark.gpu
 @pytest.mark.parametrize("what", ["inf", "nan", "largest", "tiny rows", "tiny against huge", "subnormal", "zero rows"])
@@ -100,13 +128,19 @@ def test_values_beyond_the_split(what):
     mdh.mdh_matmul(A, B, want, fp32)
     mag = A.cpu().double().abs() @ B.cpu().double().abs()
     finite = torch.isfinite(want.cpu())
+    x, f = A.view(1, 1, M, K), B.t().contiguous().view(N, 1, 1, K)
     results = []
     for p in split_candidates(mdh.MDH_MATMUL, (M, N, K), 2):
         if p.prt[3][2] == 1:
             C = torch.full((M, N), 7.0, device="cuda")
             mdh.mdh_matmul(A, B, C, p)
             results.append((C, p))
-    assert len(results) == 5
+    for p in split_candidates(mdh.MDH_MCC, (1, 1, M, N, K, 1, 1, 1, 1), 4):  # the same product as a 1 x 1 layer
+        if p.prt[3][4] == 1:
+            C = torch.full((1, 1, M, N), 7.0, device="cuda")
+            mdh.mdh_mcc(x, f, C, (1, 1), p)
+            results.append((C.view(M, N), p))
+    assert len(results) > 5
     for C, p in results:
         got = C.cpu()
         assert torch.equal(torch.isnan(got), torch.isnan(want.cpu())), p.table()
