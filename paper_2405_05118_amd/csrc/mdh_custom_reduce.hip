@@ -145,33 +145,33 @@ __global__ __launch_bounds__(WA* WB * 64) void prl_kernel(
   }
 }
 
-// ---- the same instance for nF = 8 in the instruction kinds the vector ALU issues at twice the rate ----
+// ---- the same instance in the instruction kinds the vector ALU issues at twice the rate ----
 //
 // On this chip a wavefront instruction of the kinds {fp32 add / subtract / multiply / fused multiply-add,
 // 32-bit integer add / subtract, bitwise logic, move} takes ~2.3 cycles of a SIMD (also with one scalar
 // operand), every other kind (compare, select, min / max, three-operand integer forms) ~4.1; a result can
 // feed an instruction issued four or more instructions later at no cost (all measured: the calibration
-// kernels of this library).  The loop above spends 24 instructions of the slow kinds per pair.  Here
-// wght is evaluated with three fast ones per field:
+// kernels of this library).  The loop above spends three instructions of the slow kinds per field.  Here
+// wght is evaluated with three fast ones:
 //     d = a_f - b_f            exact in fp32: both sides are stored as the float 2^23 + value
 //     t = clamp(d * d)         1 if the fields differ (|d| >= 1), 0 if they agree
 //     acc = fma(t, w_disagree_f - w_agree_f, acc)      acc starts at sum_f w_agree_f
-// over eight independent (record of A, record of B) chains per lane, and max_idx is applied to blocks of
+// over eight (four from 11 fields on, whose records of B would not fit the scalar registers eight at a time)
+// independent (record of A, record of B) chains per lane, and max_idx is applied to blocks of
 // four consecutive records of B: two three-operand maxima, one compare and one select per block instead
 // of compare + maximum + select per record; which record of the winning block scored the maximum is
 // found once at the end by scoring that block again.  Everything stays exact under these conditions,
 // which the kernel checks itself: field values in [0, 2^23) (the records of A up front, those of B as
-// they stream by -- a part that saw a value outside is evaluated again by the integer loop), and
+// they stream by, after every 512: from the run of 512 that holds a value outside, the integer loop goes on), and
 // sum_f max(|w_agree_f|, |w_disagree_f|) < 2^24 (all partial sums are then integers fp32 holds exactly).
 // The result is the unique (score, index) of the definition, bit for bit, on either path.
-template <int RA, int WB, int WA>
+template <int NF, int RA, int WB, int WA>
 __global__ __launch_bounds__(WA* WB * 64) void prl_fast_kernel(
     const int* __restrict__ A, const int* __restrict__ B, const int* __restrict__ wp,
     const int* __restrict__ wm, int* __restrict__ out_s, int* __restrict__ out_i,
     int* __restrict__ ws, int nA, int nB, int S, int bchunk) {
-  constexpr int NF = 8;
-  constexpr int BI = 8 / RA;  // records of B interleaved per step: RA * BI = 8 independent chains
-  static_assert(RA == 2 || RA == 4, "eight chains per lane");
+  constexpr int BI = (NF > 10 ? 4 : 8) / RA;  // records of B interleaved per step: RA * BI independent chains
+  static_assert(RA == 2 || RA == 4, "eight or four chains per lane");
   __shared__ int red_s[WB > 1 ? (WB - 1) * WA * RA * 64 : 1];
   __shared__ int red_i[WB > 1 ? (WB - 1) * WA * RA * 64 : 1];
   const int lane = threadIdx.x & 63;
@@ -184,18 +184,15 @@ __global__ __launch_bounds__(WA* WB * 64) void prl_fast_kernel(
   const int b0 = min((int64_t)part * bchunk, (int64_t)nB);
   const int b1 = min((int64_t)b0 + bchunk, (int64_t)nB);
 
-  // weights (wavefront-uniform): integer form for the fallback loop, float form for the fast one
-  unsigned dw[NF];
-  unsigned base = 0;
+  // weights (wavefront-uniform; from nine fields on in vector registers, the scalar ones hold the records of B)
   float ndw[NF];
   float agree_sum = 0.f;
   int64_t wabs = 0;
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
     const int p = wp[f], m = wm[f];
-    dw[f] = (unsigned)p - (unsigned)m;
-    base += (unsigned)m;
     ndw[f] = (float)((int64_t)m - (int64_t)p);
+    if (NF > 8) asm("" : "+v"(ndw[f]));
     agree_sum += (float)p;
     wabs += max(abs((int64_t)p), abs((int64_t)m));
   }
@@ -221,63 +218,77 @@ __global__ __launch_bounds__(WA* WB * 64) void prl_fast_kernel(
 #pragma unroll
   for (int ra = 0; ra < RA; ++ra) best[ra] = Best{INT_MIN, b0 < b1 ? b0 : INT_MAX};
 
-  unsigned b_or = 0;  // OR of every field value of B this wavefront has met (scalar)
+  int done = b0;  // records of B before this one are in `best`
   if (fast && b0 < b1) {
+    unsigned b_or = 0;  // OR of every field value of B this wavefront has met (scalar)
     float fbest[RA];
     int blk[RA];
 #pragma unroll
     for (int ra = 0; ra < RA; ++ra) fbest[ra] = -3.0e38f, blk[ra] = b0;
     const float vbase = agree_sum + __uint_as_float(__float_as_uint(0.f) | (lane & 0));  // a vector register
 
-    for (int bb = b0; bb < b1; bb += 4) {
-      float sc[4][RA];
+    constexpr int kRun = 512;
+    while (done < b1) {
+      const int end = min(done + kRun, b1);
+      float fbefore[RA];
+      int before[RA];
 #pragma unroll
-      for (int h = 0; h < 4; h += BI) {
-        float fb[BI][NF];  // wavefront-uniform: scalar loads, coded on the scalar unit
+      for (int ra = 0; ra < RA; ++ra) fbefore[ra] = fbest[ra], before[ra] = blk[ra];
+      for (int bb = done; bb < end; bb += 4) {
+        float sc[4][RA];
 #pragma unroll
-        for (int u = 0; u < BI; ++u) {
-          const int* rb = B + (int64_t)min(bb + h + u, b1 - 1) * NF;  // the tail repeats the last record
+        for (int h = 0; h < 4; h += BI) {
+          float fb[BI][NF];  // wavefront-uniform: scalar loads, coded on the scalar unit
+#pragma unroll
+          for (int u = 0; u < BI; ++u) {
+            const int* rb = B + (int64_t)min(bb + h + u, b1 - 1) * NF;  // the tail repeats the last record
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+              const unsigned v = (unsigned)rb[f];
+              b_or |= v;
+              fb[u][f] = __uint_as_float(kCode + v);
+            }
+          }
+          float acc[BI][RA];
 #pragma unroll
           for (int f = 0; f < NF; ++f) {
-            const unsigned v = (unsigned)rb[f];
-            b_or |= v;
-            fb[u][f] = __uint_as_float(kCode + v);
+            float t[BI][RA];
+#pragma unroll
+            for (int u = 0; u < BI; ++u)
+#pragma unroll
+              for (int ra = 0; ra < RA; ++ra) t[u][ra] = fa[ra][f] - fb[u][f];
+#pragma unroll
+            for (int u = 0; u < BI; ++u)
+#pragma unroll
+              for (int ra = 0; ra < RA; ++ra) asm("v_mul_f32_e64 %0, %1, %1 clamp" : "=v"(t[u][ra]) : "v"(t[u][ra]));
+#pragma unroll
+            for (int u = 0; u < BI; ++u)
+#pragma unroll
+              for (int ra = 0; ra < RA; ++ra)
+                acc[u][ra] = __builtin_fmaf(t[u][ra], ndw[f], f == 0 ? vbase : acc[u][ra]);
           }
+#pragma unroll
+          for (int u = 0; u < BI; ++u)
+#pragma unroll
+            for (int ra = 0; ra < RA; ++ra) sc[h + u][ra] = acc[u][ra];
         }
-        float acc[BI][RA];
+        // max_idx over the block: a strictly larger maximum takes the block (b ascends: first block wins ties)
 #pragma unroll
-        for (int f = 0; f < NF; ++f) {
-          float t[BI][RA];
-#pragma unroll
-          for (int u = 0; u < BI; ++u)
-#pragma unroll
-            for (int ra = 0; ra < RA; ++ra) t[u][ra] = fa[ra][f] - fb[u][f];
-#pragma unroll
-          for (int u = 0; u < BI; ++u)
-#pragma unroll
-            for (int ra = 0; ra < RA; ++ra) asm("v_mul_f32_e64 %0, %1, %1 clamp" : "=v"(t[u][ra]) : "v"(t[u][ra]));
-#pragma unroll
-          for (int u = 0; u < BI; ++u)
-#pragma unroll
-            for (int ra = 0; ra < RA; ++ra)
-              acc[u][ra] = __builtin_fmaf(t[u][ra], ndw[f], f == 0 ? vbase : acc[u][ra]);
+        for (int ra = 0; ra < RA; ++ra) {
+          const float m = __builtin_fmaxf(__builtin_fmaxf(sc[0][ra], sc[1][ra]), sc[2][ra]);
+          const float nb = __builtin_fmaxf(__builtin_fmaxf(fbest[ra], m), sc[3][ra]);
+          blk[ra] = nb > fbest[ra] ? bb : blk[ra];
+          fbest[ra] = nb;
         }
-#pragma unroll
-        for (int u = 0; u < BI; ++u)
-#pragma unroll
-          for (int ra = 0; ra < RA; ++ra) sc[h + u][ra] = acc[u][ra];
       }
-      // max_idx over the block: a strictly larger maximum takes the block (b ascends: first block wins ties)
+      if (b_or >> 23) {
 #pragma unroll
-      for (int ra = 0; ra < RA; ++ra) {
-        const float m = __builtin_fmaxf(__builtin_fmaxf(sc[0][ra], sc[1][ra]), sc[2][ra]);
-        const float nb = __builtin_fmaxf(__builtin_fmaxf(fbest[ra], m), sc[3][ra]);
-        blk[ra] = nb > fbest[ra] ? bb : blk[ra];
-        fbest[ra] = nb;
+        for (int ra = 0; ra < RA; ++ra) fbest[ra] = fbefore[ra], blk[ra] = before[ra];
+        break;
       }
+      done = end;
     }
-    fast = (b_or >> 23) == 0;  // every value of B met on the way was in range: the scores are exact
-    if (fast) {
+    if (done > b0) {
       // which record of the winning block: score its (up to) four records again, the first that
       // reaches the maximum is the answer
 #pragma unroll
@@ -286,7 +297,7 @@ __global__ __launch_bounds__(WA* WB * 64) void prl_fast_kernel(
         bool found = false;
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-          const int b = min(blk[ra] + u, b1 - 1);
+          const int b = min(blk[ra] + u, b1 - 1);  // (a whole block: the walk ends between blocks)
           const int* rb = B + (int64_t)b * NF;
           float acc = vbase;
 #pragma unroll
@@ -303,8 +314,15 @@ __global__ __launch_bounds__(WA* WB * 64) void prl_fast_kernel(
       }
     }
   }
-  if (!fast && b0 < b1) {
+  if (done < b1) {
     // the integer loop of prl_kernel: any int32 field values and weights
+    unsigned dw[NF];
+    unsigned base = 0;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      dw[f] = (unsigned)wp[f] - (unsigned)wm[f];
+      base += (unsigned)wm[f];
+    }
     int ar[RA][NF];
 #pragma unroll
     for (int ra = 0; ra < RA; ++ra) {
@@ -312,7 +330,7 @@ __global__ __launch_bounds__(WA* WB * 64) void prl_fast_kernel(
 #pragma unroll
       for (int f = 0; f < NF; ++f) ar[ra][f] = A[(int64_t)a * NF + f];
     }
-    for (int b = b0; b < b1; ++b) {
+    for (int b = done; b < b1; ++b) {
       int br[NF];
       const int* rb = B + (int64_t)b * NF;
 #pragma unroll
@@ -396,7 +414,7 @@ mdh_status launch_t(const PrlPlan& pl, int64_t nA, int64_t nB, int nF, const int
   return launch_status();
 }
 
-template <int RA, int WB, int WA>
+template <int NF, int RA, int WB, int WA>
 mdh_status launch_fast(const PrlPlan& pl, int64_t nA, int64_t nB, const int32_t* A, const int32_t* B,
                        const int32_t* wp, const int32_t* wm, int32_t* score, int32_t* index, void* ws,
                        hipStream_t st) {
@@ -405,7 +423,7 @@ mdh_status launch_fast(const PrlPlan& pl, int64_t nA, int64_t nB, const int32_t*
   if (nblocks > 0x7fffffff) return MDH_ERR_SIZE;
   const int64_t bchunk = cdiv(nB, (int64_t)pl.S * WB);
   clear_stale_error();
-  hipLaunchKernelGGL((prl_fast_kernel<RA, WB, WA>), dim3((unsigned)nblocks), dim3(WA * WB * 64), 0, st, A, B,
+  hipLaunchKernelGGL((prl_fast_kernel<NF, RA, WB, WA>), dim3((unsigned)nblocks), dim3(WA * WB * 64), 0, st, A, B,
                      wp, wm, score, index, (int*)ws, (int)nA, (int)nB, pl.S, (int)bchunk);
   mdh_status r = launch_status();
   if (r != MDH_OK || pl.S <= 1) return r;
@@ -419,9 +437,20 @@ template <int RA, int WB, int WA>
 mdh_status launch_nf(const PrlPlan& pl, int64_t nA, int64_t nB, int nF, const int32_t* A,
                      const int32_t* B, const int32_t* wp, const int32_t* wm, int32_t* score,
                      int32_t* index, void* ws, hipStream_t st) {
-  // eight fields, two or four records of A per lane: the loop built from the fast instruction kinds
+  // two or four records of A per lane: the loop built from the fast instruction kinds -- for every number of fields
+  // with the default's workgroup, for eight fields with the others too.  2^15 x 2^16 records, against the loop of
+  // selects above, us: 4 fields 545 / 759; 6: 741 / 1323; 10: 1219 / 2704; 12: 1561 / 2706; 16: 2169 / 2735.
   if constexpr (RA == 2 || RA == 4)
-    if (nF == 8) return launch_fast<RA, WB, WA>(pl, nA, nB, A, B, wp, wm, score, index, ws, st);
+    if (nF == 8) return launch_fast<8, RA, WB, WA>(pl, nA, nB, A, B, wp, wm, score, index, ws, st);
+  if constexpr (RA == 2 && WB == 4 && WA == 1) {
+    if (nB <= 0x7ffffff0) switch (nF) {  // (the walk looks up to seven records past the end before it clamps)
+#define MDH_NF(n) \
+  case n: return launch_fast<n, RA, WB, WA>(pl, nA, nB, A, B, wp, wm, score, index, ws, st);
+      MDH_NF(1) MDH_NF(2) MDH_NF(3) MDH_NF(4) MDH_NF(5) MDH_NF(6) MDH_NF(7)
+      MDH_NF(9) MDH_NF(10) MDH_NF(11) MDH_NF(12) MDH_NF(13) MDH_NF(14) MDH_NF(15) MDH_NF(16)
+#undef MDH_NF
+    }
+  }
   if (nF == 8) return launch_t<8, true, RA, WB, WA>(pl, nA, nB, nF, A, B, wp, wm, score, index, ws, st);
   if (nF <= 4) return launch_t<4, false, RA, WB, WA>(pl, nA, nB, nF, A, B, wp, wm, score, index, ws, st);
   if (nF < 8) return launch_t<8, false, RA, WB, WA>(pl, nA, nB, nF, A, B, wp, wm, score, index, ws, st);
