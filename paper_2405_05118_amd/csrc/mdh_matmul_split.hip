@@ -15,10 +15,11 @@
 // What bounds it.  Large products: power.  4096^3 runs at 1.9 GHz, and leaving single parts of the work out takes off
 // (256 x 128 tiles, of 738 us) loads 187, LDS reads 159, the split 110, LDS writes 55, and MFMAs alone are 417 us:
 // the parts add up instead of overlapping.  So what counts is bytes and instructions per product, and the largest
-// tile wins: 256 x 256 583 us, 256 x 128 628, 128 x 128 759, 64 x 64 887 (fp32 instructions: 1003).  The 256 x 256
+// tile wins: 256 x 256 564 us, 256 x 128 612, 128 x 128 688, 64 x 64 858 (fp32 instructions: 1003).  The 256 x 256
 // tile has k-tiles of 16, because two of 32 (192 KB) exceed LDS.  32x32x16 against 16x16x32 MFMAs: 4096^3 equal
 // (726 / 717), 1024^3 in 128 x 128 tiles 48.8 / 55.2 -- the smaller one leaves room for one vector instruction
-// beside it, the larger for four.  Two or three k-tiles on their way instead of one, and another first k-tile per
+// beside it, the larger for four.  128 x 128 tiles take eight wavefronts of 32 x 64 rather than four of 64 x 64
+// (2048^3 99.6 / 107 us, 4096^3 776 / 819): with one wavefront per SIMD nothing covers its waits.  Two or three k-tiles on their way instead of one, and another first k-tile per
 // workgroup for tall operands: no difference.
 #include "mdh_split.h"
 
@@ -410,7 +411,7 @@ mdh_status launch_matmul_split(const GemmPlan& pl, bool ta, bool tb, bool tc, in
   if (g.BM == bm && g.BN == bn && g.BK == bk && g.WM == wm && g.WN == wn) return launch_views<bm, bn, bk, wm, wn>(c, yk, xk);
   MDH_MS(256, 256, 16, 64, 128)
   MDH_MS(256, 128, 32, 64, 64)
-  MDH_MS(128, 128, 32, 64, 64)
+  MDH_MS(128, 128, 32, 32, 64)
   MDH_MS(128, 64, 32, 64, 32)
   MDH_MS(64, 64, 32, 32, 32)
 #undef MDH_MS

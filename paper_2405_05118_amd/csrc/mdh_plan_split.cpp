@@ -7,7 +7,7 @@ namespace mdh {
 namespace detail {
 
 static const int kSplitMenu[][5] = {  // BM, BN, BK, WM, WN
-    {256, 256, 16, 64, 128}, {256, 128, 32, 64, 64}, {128, 128, 32, 64, 64}, {128, 64, 32, 64, 32}, {64, 64, 32, 32, 32}};
+    {256, 256, 16, 64, 128}, {256, 128, 32, 64, 64}, {128, 128, 32, 32, 64}, {128, 64, 32, 64, 32}, {64, 64, 32, 32, 32}};
 
 // C stored transposed runs as the product of the transposed operands in the other order: the tile swaps too
 bool split_inst(const GemmPlan& g, bool tc) {
@@ -41,10 +41,10 @@ int split_tiles(bool tc, GemmPlan* out) {
 // K = 300 ... 4096; with all compute units at work on a large tile the clock gives way, which the second figure adds.
 struct StepTime {
   double us[3], full;
-  int held;
+  int held, first;  // first: what the first, not overlapped k-tile and the output take, in steps
 };
 static const StepTime kStep[kSplitTiles] = {
-    {{3.5}, 0.9, 1}, {{1.95}, 0.45, 1}, {{1.4}, 0.06, 1}, {{0.98, 1.56}, 0, 2}, {{0.57, 0.95, 1.30}, 0, 3}};
+    {{3.5}, 0.9, 1, 3}, {{1.95}, 0.45, 1, 3}, {{1.1}, 0.2, 1, 3}, {{0.98, 1.56}, 0, 2, 2}, {{0.57, 0.95, 1.30}, 0, 3, 1}};
 
 static double estimate(int i, int64_t tiles, int64_t M, int64_t N, int64_t batch, int64_t K, int S) {
   const StepTime& t = kStep[i];
@@ -52,13 +52,13 @@ static double estimate(int i, int64_t tiles, int64_t M, int64_t N, int64_t batch
   const double fill = t.full * (work < 256 ? (double)work / 256 : 1.0);
   double round = (double)(work / slots) * (t.us[t.held - 1] + fill);
   if (rest) round += t.us[cdiv(rest, 256) - 1] + t.full * (double)(rest < 256 ? rest : 256) / 256;
-  const double steps = (double)cdiv(K, 32 * S) + 1;  // the first k-tile is not overlapped
+  const double steps = (double)cdiv(K, 32 * S) + t.first;
   return round * steps + (S > 1 ? 2.0 + (double)(S + 1) * batch * M * N * 4e-6 / 4.0 : 0.0);
 }
 
 // Is the default one of these tiles, and which?  `S` is the number of parts the fp32 rule splits k into: not more
 // parts here, so that no call needs more workspace than it does there.
-// Against the fp32 kernels, us: 4096^3 583 / 1003; 3000^3 352 / 504; 2048^3 100 / 150; 1021 x 1531 x 777 28.5 / 40.4;
+// Against the fp32 kernels, us: 4096^3 566 / 1003; 3000^3 364 / 504; 2048^3 93 / 150; 1021 x 1531 x 777 28.5 / 40.4;
 // 65536 x 64 x 4096 258 / 312; 16 x 1024^3 157 / 253; 8 x 200 x 333 x 650 16.7 / 24.4; 1024^3 23.8 / 24.4.  The line:
 // below 128 k the first and last tile are most of the walk (4096 x 4096 x 64: 27.9 / 27.0; 16 x 512 x 512 x 64: 10.7
 // / 10.5), below 2^26 products a call is its launch (16 x 128^3: 8.1 / 7.8), and less than 48 rows or columns
