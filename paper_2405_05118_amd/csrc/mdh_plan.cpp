@@ -303,8 +303,10 @@ static GemmPlan gemm_default_fp32(const int64_t* s) {
   //   768^3 and 1024^3: the LDS-tiled kernel stays ahead (18.9 against 20.0; 26.3 against 28.1)
   if (K >= 32 && K <= 8192 && M > 0 && N > 0) {
     const int64_t t16 = cdiv(M, 16) * cdiv(N, 16), t32 = cdiv(M, 32) * cdiv(N, 32);
-    if (t16 <= 320 || t32 <= 320) {
-      const int b = t16 <= 320 ? 16 : 32;
+    // (up to 384 where k is short: 300^3 5.4 with 16 x 16 tiles, 6.8 with 32 x 32; 700 x 450 x 150: 7.1 / 8.5 LDS-tiled)
+    const int64_t few = K <= 512 ? 384 : 320;
+    if (t16 <= few || t32 <= few) {
+      const int b = t16 <= few ? 16 : 32;
       GemmPlan pl{b, b, b == 16 ? 16 : 8, b, b, 1, 0};
       pl.WK = (b == 16 && K <= 128) ? 2 : 4;
       pl.ragged = gemm_ragged(s, pl);
@@ -350,12 +352,52 @@ static GemmPlan gemm_default_fp32(const int64_t* s) {
   return pl;
 }
 
-static GemmPlan gemm_default(const int64_t* s) {
+// The default without more workspace than the fp32 rule asks for.
+static GemmPlan gemm_default_lean(const int64_t* s) {
   GemmPlan pl = gemm_default_fp32(s);
   // outputs of few tiles stay with k over the wavefronts (512^3: 8.9 us against 13.2; 400 x 600 x 1000: 13.3 / 23)
   if (pl.WK > 1 || !split_default(1, s[0], s[1], s[2], false, pl.S, &pl)) return pl;
   pl.ragged = gemm_ragged(s, pl);
   return pl;
+}
+
+static GemmPlan gemm_default(const int64_t* s) {
+  GemmPlan pl = gemm_default_lean(s);
+  if (pl.WK <= 1) return pl;
+  // Few tiles and many k: parts of k over workgroups too, as many as leave a compute unit one workgroup and a part
+  // its worth of k, against the second pass (us, replayed from a graph; WK wavefronts, S parts)
+  const int64_t K = s[2];
+  auto parts = [&](int64_t tiles, int64_t least) {
+    int S = 1;
+    while (S < 8 && tiles * 2 * S <= 320 && K / (2 * S) >= least) S *= 2;
+    return S;
+  };
+  if (pl.BM == 16) {
+    // 20 x 1000 x 3000: 13.8 with S = 2, 19.4 without; 90 x 90 x 8000: 14.9 with 4 and eight wavefronts, 46 without;
+    // 128 x 300 x 2000: 8.9 with eight wavefronts, 11.2 with four.  A second launch costs the host about 6 us: not
+    // below 14 us, which whole blocks reach at a deeper k (64 x 64 x 4096: 10.9 in one launch, 6.6 + the launch)
+    const bool whole = s[0] % 16 == 0 && s[1] % 16 == 0 && K % 16 == 0;
+    if (K >= (whole ? 6000 : 2400)) pl.S = parts(cdiv(s[0], 16) * cdiv(s[1], 16), 1024);
+    if (K / (8 * pl.S) >= 250) pl.WK = 8;
+  } else if (K >= 1500 && (s[0] % 32 || s[1] % 32) && s[0] >= 40 && s[1] >= 40 && split_sizes(s[0], s[1], K)) {
+    // ragged tiles go through the checked loads, which take twice as long: the split kernel's do not (320 x 900 x
+    // 2500: 26 against 53; 40 x 2000 x 2000: 17 against 26; 512 x 512 x 4096: 28.8 against 28.7)
+    const GemmPlan sp{64, 64, 32, 32, 32, 1, 0};
+    const int S = parts(cdiv(s[0], 64) * cdiv(s[1], 64), 256);
+    if (S >= 4) {
+      pl = sp;
+      pl.split = 1;
+      pl.S = S;
+    }
+  }
+  while (pl.S > 1 && (pl.S - 1) * (cdiv(cdiv(K, pl.S), 32) * 32) >= K) pl.S /= 2;
+  pl.ragged = gemm_ragged(s, pl);
+  return pl;
+}
+
+mdh_status plan_matmul_lean(const int64_t* s, GemmPlan* out) {
+  *out = gemm_default_lean(s);
+  return MDH_OK;
 }
 
 int matmul_candidates(const int64_t* s, GemmPlan* out, int cap) {

@@ -5,7 +5,6 @@ Tolerance: the products left out are below 2^-26 of |a b|, the six that are ther
 fp32 accumulation steps (six per 16 terms, fewer than the K of a multiply-add chain) adds at most 2^-24 of the running
 sum |a b|: K * 2^-24 of sum |a b|, as for the fp32 instructions.
 """
-import numpy as np
 import pytest
 
 import paper_2405_05118_amd as mdh
@@ -33,14 +32,23 @@ def test_planner_of_the_split_kernels():
     assert not split_candidates(mdh.MDH_MATMUL, (300, 300, 31), 2)
     assert not split_candidates(mdh.MDH_MCC, (2, 20, 20, 64, 15, 3, 3, 1, 1), 4)
     assert split_candidates(mdh.MDH_MCC, (2, 20, 20, 64, 16, 3, 3, 1, 1), 4)
-    # a default that is a split tile needs no more workspace than the fp32 tile it stands before
-    rng = np.random.default_rng(5)
-    for _ in range(300):
-        M, N, K = (int(np.exp(rng.uniform(np.log(40), np.log(5000)))) for _ in range(3))
-        d = mdh.mdh_default_params(mdh.MDH_MATMUL, (M, N, K))
-        if d.blk[2] == 16 and d.blk[0] == 32:
-            fp32 = next(q for q in (mdh.mdh_candidate(mdh.MDH_MATMUL, (M, N, K), i) for i in range(3)) if q.blk[2] != 16)
-            assert d.prt[3][2] <= fp32.prt[3][2]
+
+
+# the default splits a deep k further when the workspace it asks for is there, and does without when it is not
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(90, 90, 8000), (40, 2000, 2000), (64, 64, 4096), (320, 900, 2500), (128, 300, 2001)])
+def test_matmul_default_with_and_without_workspace(shape):
+    M, N, K = shape
+    g = torch.Generator(device="cuda").manual_seed(K)
+    A = torch.rand((M, K), generator=g, device="cuda") * 2 - 1
+    B = torch.rand((K, N), generator=g, device="cuda") * 2 - 1
+    ref = A.cpu().double() @ B.cpu().double()
+    mag = A.cpu().double().abs() @ B.cpu().double().abs()
+    n = mdh.mdh_workspace_size(mdh.MDH_MATMUL, shape)
+    for ws in (None, torch.empty(max(n // 4 - 1, 1), device="cuda"), torch.empty(max(n // 4, 1), device="cuda")):
+        C = torch.full((M, N), float("nan"), device="cuda")
+        mdh.mdh_matmul(A, B, C, None, ws)
+        assert float(((C.cpu().double() - ref).abs() / mag).max()) <= K * 2.0**-24
 
 
 # M, N, K: one row less, exactly, and one more than tiles of 64 / 128 / 256; the shortest k, whole k-tiles, tails
