@@ -390,7 +390,7 @@ static GemmPlan gemm_default(const int64_t* s) {
       pl.S = S;
     }
   }
-  while (pl.S > 1 && (pl.S - 1) * (cdiv(cdiv(K, pl.S), 32) * 32) >= K) pl.S /= 2;
+  while (pl.split && (pl.S - 1) * split_part(K, pl) >= K) pl.S /= 2;
   pl.ragged = gemm_ragged(s, pl);
   return pl;
 }
@@ -427,7 +427,7 @@ int matmul_candidates(const int64_t* s, GemmPlan* out, int cap) {
     const int ns = split_tiles(false, sp);
     for (int i = 0; i < ns; ++i)
       for (int S : {1, 2, 4}) {
-        if (S > 1 && (cdiv(s[0], sp[i].BM) * cdiv(s[1], sp[i].BN) * (S / 2) >= 256 || s[2] / S < 128)) continue;
+        if (S > 1 && (cdiv(s[0], sp[i].BM) * cdiv(s[1], sp[i].BN) * (S / 2) >= 2048 || s[2] / S < 128)) continue;
         sp[i].S = S;
         push(sp[i]);
       }
@@ -498,6 +498,7 @@ mdh_status plan_matmul(const int64_t* s, const mdh_tile_params* p, GemmPlan* out
   pl.jmajor = (p->order[0] == MDH_L_WG * MDH_MAX_D + 1 && p->order[1] == MDH_L_WG * MDH_MAX_D + 0) ? 1 : 0;
   if (p->blk[0] != 32 || p->blk[1] != 32 || (p->blk[2] != 2 && p->blk[2] != 16)) return MDH_ERR_UNSUPPORTED;
   if (pl.split && !split_sizes(s[0], s[1], s[2])) return MDH_ERR_UNSUPPORTED;
+  if (pl.split && (pl.S - 1) * split_part(s[2], pl) >= s[2]) return MDH_ERR_TILE_NOT_DIVIDING;  // a part without k
   if ((pl.split ? split_lds_bytes(pl) : gemm_lds_bytes(pl.BM, pl.BN, pl.BK)) > kLdsBytesPerWG) return MDH_ERR_TILE_RESOURCES;
   if ((int64_t)p->prt[MDH_L_WAVE][0] * p->prt[MDH_L_WAVE][1] * 64 > kMaxLanesPerWG)
     return MDH_ERR_TILE_RESOURCES;
@@ -795,8 +796,8 @@ struct TapTime {
   int px, BN, held;
   double us[4];
 };
-static const TapTime kTap[] = {{64, 64, 4, {0.58, 0.80, 1.10, 1.40}}, {64, 128, 2, {0.80, 1.40}}, {128, 64, 3, {0.76, 1.32, 1.90}},
-                               {128, 128, 2, {1.22, 2.25}},          {256, 128, 1, {2.17}}};
+static const TapTime kTap[] = {{64, 64, 4, {0.58, 0.80, 1.10, 1.40}}, {64, 128, 2, {0.80, 1.40}}, {128, 64, 3, {0.70, 1.30, 1.90}},
+                               {128, 128, 2, {1.40, 2.40}},          {256, 128, 1, {2.17}}};
 
 static double mcc_split_estimate(const int64_t* s, const MccPlan& pl) {
   const int64_t P = s[1] > 0 ? s[1] : 1, Q = s[2] > 0 ? s[2] : 1;
@@ -815,7 +816,7 @@ static double mcc_split_estimate(const int64_t* s, const MccPlan& pl) {
   double us = (double)(work / (256 * held)) * round(held);
   const int64_t rest = work % (256 * held);
   if (rest) us += round((int)cdiv(rest, 256));
-  if (pl.S > 1) us += 4.0 + (double)(pl.S + 1) * s[0] * P * Q * s[3] * 1e-6;  // second pass: 4 bytes at 4 TB/s
+  if (pl.S > 1) us += 3.0 + 0.5 * pl.S + (double)(pl.S + 1) * s[0] * P * Q * s[3] * 1e-6;  // second pass: 4 bytes at 4 TB/s
   return us;
 }
 
@@ -824,10 +825,11 @@ static double mcc_split_estimate(const int64_t* s, const MccPlan& pl) {
 // layer measured from 16 channels on (us, against theirs): 16 x 224 x 224 x 64 -> 128, 7 x 7: 2766 / 4829; 16 x 56 x
 // 56 x 64 -> 64, 3 x 3: 28.8 / 51.1; 1 x 1, 256 -> 64: 21.5 / 29.6; 16 x 7 x 7 x 512 -> 512, 3 x 3 at N = 32: 67.5 / 109;
 // 1 x 18 x 19 x 40 -> 33: 10.5 / 14.8.  Below 16 channels a chunk is mostly padding, and a reduction of less than 128 terms
-// is all first and last tap (1 x 1, 64 -> 256: 29.0 / 27.8).
+// is all first and last tap (1 x 1, 64 -> 256: 29.0 / 27.8), as is a small layer of one tap (9 x 5 x 5 x 136 -> 92: 12.8 / 12.2).
 static bool mcc_split_default(const int64_t* s, int TQ, int S, MccPlan* out) {
   double best = -1;
   if (s[4] * s[5] * s[6] < 128) return false;
+  if (s[5] * s[6] == 1 && (double)s[0] * s[1] * s[2] * s[3] * s[4] < (double)(1 << 24)) return false;
   for (auto& m : kMccSplitMenu)
     for (int parts = 1; parts <= S; parts *= 2) {
       MccPlan pl{m.TP, m.TQ, m.BN, m.CK, m.WM, m.WN, 0, 0};

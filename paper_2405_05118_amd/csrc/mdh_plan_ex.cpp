@@ -245,7 +245,7 @@ int matmul_ex_candidates(const int64_t* s, GemmExPlan* out, int cap) {
     const int ns = split_tiles(s[6] != 0, sp);
     for (int i = 0; i < ns; ++i)
       for (int S : {1, 2, 4}) {
-        if (S > 1 && (s[0] * cdiv(s[1], sp[i].BM) * cdiv(s[2], sp[i].BN) * (S / 2) >= 256 || s[3] / S < 128)) continue;
+        if (S > 1 && (s[0] * cdiv(s[1], sp[i].BM) * cdiv(s[2], sp[i].BN) * (S / 2) >= 2048 || s[3] / S < 128)) continue;
         sp[i].S = S;
         push(sp[i]);
       }
@@ -299,6 +299,7 @@ mdh_status plan_matmul_ex(const int64_t* s, const mdh_tile_params* p, GemmExPlan
   g.BK = p->prt[MDH_L_LDS][3] * p->blk[3];
   g.S = p->prt[MDH_L_WG][3];
   g.ragged = ragged;
+  if (g.split && g.BK > 0 && (g.S - 1) * split_part(s[3], g) >= s[3]) return MDH_ERR_TILE_NOT_DIVIDING;  // a part without k
   GemmExPlan pl{g, (int)s[4], (int)s[5], (int)s[6]};
   mdh_tile_params chk;
   params_from_plan(s, pl, &chk);

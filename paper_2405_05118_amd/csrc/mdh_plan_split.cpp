@@ -71,12 +71,12 @@ bool split_default(int64_t batch, int64_t M, int64_t N, int64_t K, bool tc, int 
   double best = -1;
   for (int i = 0; i < n; ++i)
     for (int s = 1; s <= S; s *= 2) {
-      if ((s - 1) * (cdiv(cdiv(K, s), sp[i].BK) * sp[i].BK) >= K) break;  // a part without k
+      sp[i].S = s;
+      if ((s - 1) * split_part(K, sp[i]) >= K) break;  // a part without k
       const double t = estimate(i, batch * cdiv(M, sp[i].BM) * cdiv(N, sp[i].BN), M, N, batch, K, s);
       if (best < 0 || t < best) {
         best = t;
         *g = sp[i];
-        g->S = s;
       }
     }
   return true;
