@@ -26,6 +26,9 @@ METRIC = "per-instance GFLOP/s or GB/s and % of roofline on 1 MI355X"
 # MI355X published peaks
 PEAK_HBM_GBS = 8000.0
 PEAK_FP32_MFMA_TFLOPS = 157.3
+# the contractions that carry an fp32 value as three bf16 values spend six bf16 matrix products on a multiply-add:
+# 256 CU x 4096 FLOP/clk x 2.4 GHz / 6
+PEAK_SPLIT_MFMA_TFLOPS = 2516.6 / 6
 # Vector ALU: 256 CUs x 4 SIMDs x 32 lanes x 2.4 GHz = 78.6 T lane-op/s.  This is the width behind the
 # published FP32 vector peak (157.3 TFLOP/s = 78.6 T fused multiply-adds a second), and no instruction
 # kind issues faster: moves, 32-bit add / subtract, bitwise logic and fp32 add / multiply / FMA on
@@ -191,6 +194,12 @@ def _split_variant(mdh, sizes, S):
     return None
 
 
+def _mfma_roofline(tf, sliced, traffic):
+    """Roofline object of a contraction; sliced: six bf16 matrix products per multiply-add instead of fp32 ones."""
+    peak = PEAK_SPLIT_MFMA_TFLOPS if sliced else PEAK_FP32_MFMA_TFLOPS
+    return {"bound": "mfma", "achieved": tf, "peak": peak, "unit": "TFLOP/s", "frac": tf / peak, "traffic": traffic}
+
+
 def bench_matmul(torch, mdh, W, name, steps, warmup, cpu, split=None):
     cfg = W.CONFIGS[name]
     sizes = (cfg.M, cfg.N, cfg.K)
@@ -198,6 +207,7 @@ def bench_matmul(torch, mdh, W, name, steps, warmup, cpu, split=None):
     b = W.device_uniform(cfg.seed, 2, (cfg.K, cfg.N), -1.0, 1.0)
     c = torch.empty((cfg.M, cfg.N), dtype=torch.float32, device="cuda")
     p = mdh.mdh_default_params(mdh.MDH_MATMUL, sizes) if split is None else _split_variant(mdh, sizes, split)
+    sliced = p.blk[2] == 16  # values carried as three bf16 values
     nws = mdh.mdh_workspace_size(mdh.MDH_MATMUL, sizes, p)
     ws = torch.empty(max(nws, 4) // 4, dtype=torch.int32, device="cuda") if nws else None
     ms, wall = _events_ms(torch, lambda: mdh.mdh_matmul(a, b, c, p, ws), steps, warmup)
@@ -205,13 +215,11 @@ def bench_matmul(torch, mdh, W, name, steps, warmup, cpu, split=None):
     tf = flop / ms / 1e9
     res = {
         "value": flop / wall / 1e6, "unit": "GFLOP/s", "ms_per_step": wall, "kernel_ms": ms, "dtype": "f32",
-        "kernel": ("matmul_ksplit16_kernel" if p.blk[0] == 16 else "matmul_ksplit_kernel" if p.prt[4][2] > 1 else "matmul_kernel")
+        "kernel": ("matmul_split_kernel" if sliced else "matmul_ksplit16_kernel" if p.blk[0] == 16 else "matmul_ksplit_kernel" if p.prt[4][2] > 1 else "matmul_kernel")
         + (" + combine_sum_kernel" if p.prt[3][2] > 1 else ""),
         "wavefront_parts_of_k": int(p.prt[4][2]),
         "split_k": int(p.prt[3][2]),
-        "roofline": {"bound": "mfma", "achieved": tf, "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
-                     "frac": tf / PEAK_FP32_MFMA_TFLOPS,
-                     "traffic": TRAFFIC_BYTES.get(name if split is None else "%s_split_k%d" % (name, split))},
+        "roofline": _mfma_roofline(tf, sliced, TRAFFIC_BYTES.get(name if split is None else "%s_split_k%d" % (name, split))),
         "algorithmic_flop": flop,
         "algorithmic_bytes": 4 * (cfg.M * cfg.K + cfg.K * cfg.N + cfg.M * cfg.N),
         "cache_resident": 4 * (cfg.M * cfg.K + cfg.K * cfg.N + cfg.M * cfg.N) < LLC_BYTES,
@@ -250,15 +258,16 @@ def bench_mcc(torch, mdh, W, name, steps, warmup, cpu):
     x = W.device_normal(cfg.seed, 1, (cfg.N, cfg.H, cfg.W, cfg.C))
     f = W.device_normal(cfg.seed, 2, (cfg.K, cfg.R, cfg.S, cfg.C))
     o = torch.empty((cfg.N, P, Q, cfg.K), dtype=torch.float32, device="cuda")
-    ws = _ws(torch, mdh, mdh.MDH_MCC, (cfg.N, P, Q, cfg.K, cfg.C, cfg.R, cfg.S, cfg.stride[0], cfg.stride[1]))
+    sizes = (cfg.N, P, Q, cfg.K, cfg.C, cfg.R, cfg.S, cfg.stride[0], cfg.stride[1])
+    ws = _ws(torch, mdh, mdh.MDH_MCC, sizes)
+    sliced = mdh.mdh_default_params(mdh.MDH_MCC, sizes).prt[2][4] == 8  # values carried as three bf16 values
     ms, wall = _events_ms(torch, lambda: mdh.mdh_mcc(x, f, o, cfg.stride, None, ws), steps, warmup)
     flop = 2.0 * cfg.N * P * Q * cfg.K * cfg.C * cfg.R * cfg.S
     tf = flop / ms / 1e9
     res = {
         "value": flop / wall / 1e6, "unit": "GFLOP/s", "ms_per_step": wall, "kernel_ms": ms, "dtype": "f32",
-        "kernel": "mcc_flat_kernel" if cfg.C <= 8 else "mcc_kernel",
-        "roofline": {"bound": "mfma", "achieved": tf, "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
-                     "frac": tf / PEAK_FP32_MFMA_TFLOPS, "traffic": TRAFFIC_BYTES.get(name)},
+        "kernel": "mcc_flat_kernel" if cfg.C <= 8 else "mcc_split_kernel" if sliced else "mcc_kernel",
+        "roofline": _mfma_roofline(tf, sliced, TRAFFIC_BYTES.get(name)),
         "algorithmic_flop": flop,
         "algorithmic_bytes": 4 * (x.numel() + f.numel() + o.numel()),
         "cache_resident": 4 * (x.numel() + f.numel() + o.numel()) < LLC_BYTES,
@@ -434,9 +443,8 @@ def bench_bmatmul(torch, mdh, W, name, steps, warmup, cpu):
     tf = flop / ms / 1e9
     res = {
         "value": flop / wall / 1e6, "unit": "GFLOP/s", "ms_per_step": wall, "kernel_ms": ms, "dtype": "f32",
-        "kernel": "matmul_ex_kernel", "split_k": int(p.prt[3][3]),
-        "roofline": {"bound": "mfma", "achieved": tf, "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
-                     "frac": tf / PEAK_FP32_MFMA_TFLOPS, "traffic": TRAFFIC_BYTES.get(name)},
+        "kernel": "matmul_split_kernel" if p.blk[3] == 16 else "matmul_ex_kernel", "split_k": int(p.prt[3][3]),
+        "roofline": _mfma_roofline(tf, p.blk[3] == 16, TRAFFIC_BYTES.get(name)),
         "algorithmic_flop": flop,
         "algorithmic_bytes": 4 * cfg.batch * (cfg.M * cfg.K + cfg.K * cfg.N + cfg.M * cfg.N),
     }

@@ -227,10 +227,14 @@ size_t mdh_workspace_size(mdh_instance inst, const int64_t* sizes, const mdh_til
  * (paper: Section "Examples", Subfigure 1).
  *   A: M x K, B: K x N, C: M x N, fp32, row-major, device.  K >= 1.
  *   M == 0 or N == 0 is a valid empty call.
- *   FP32 MFMA arithmetic, fp32 accumulation; if prt[MDH_L_WG][k] = S > 1 the
+ *   Accuracy of fp32 arithmetic, fp32 accumulation; if prt[MDH_L_WG][k] = S > 1 the
  *   S partial results go to `workspace` (S*M*N floats) and a second kernel adds
  *   them in ascending part order.  The library default may split k, so pass the
- *   workspace mdh_workspace_size asks for.  Two kernels, told apart in the table by
+ *   workspace mdh_workspace_size asks for (for some sizes it is asked for but not needed:
+ *   a call that brings less then runs with fewer parts).  blk = (32,32,16) selects the
+ *   kernel that carries a value as three bf16 values and multiplies with six bf16 matrix
+ *   products (K >= 32; the default for large products; Inf, NaN, overflow and values below
+ *   2^-100 take the fp32 instructions).  Two kernels with fp32 instructions, told apart by
  *   prt[MDH_L_WAVE][k]: 1 = the wavefronts of a workgroup tile its output tile,
  *   operands staged in LDS (in_region = MDH_MR_LDS); WK > 1 = every wavefront owns
  *   the whole (small) output tile and 1/WK of the k-range, operands go straight to
@@ -265,8 +269,10 @@ mdh_status mdh_stencil(int64_t nx, int64_t ny, int64_t nz, const float* in, floa
  *   P = (H-R)/stride_h + 1, Q = (W-S)/stride_w + 1 (no implicit padding),
  *   fp32, device.  C, R, S >= 1; H >= R; W >= S; strides >= 1.
  * Tile parameters: blk[p] x blk[q] is the pixel shape of the 32-pixel MFMA block
- * (1 x 32, 2 x 16 or 4 x 8), blk[k] = 32; blk[c] = 2 selects the channel-chunked
- * kernel, blk[c] = 1 the few-channel kernel that walks s and c as one dimension.
+ * (1 x 32, 2 x 16 or 4 x 8), blk[k] = 32; blk[c] = 2 selects a channel-chunked
+ * kernel -- with prt[MDH_L_VGPR][c] = 8 the one that carries a value as three bf16 values
+ * (see mdh_matmul; C >= 16), else the one with fp32 instructions --, blk[c] = 1 the
+ * few-channel kernel that walks s and c as one dimension.
  * prt[MDH_L_WG][c] = S > 1 splits the reduction dimension c over workgroups: the S
  * partial outputs go to `workspace` (S * N*P*Q*K floats, see mdh_workspace_size) and
  * a second kernel adds them in ascending part order.  The library default does
