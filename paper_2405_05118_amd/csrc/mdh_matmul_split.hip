@@ -19,8 +19,8 @@
 // tile has k-tiles of 16, because two of 32 (192 KB) exceed LDS.  32x32x16 against 16x16x32 MFMAs: 4096^3 equal
 // (726 / 717), 1024^3 in 128 x 128 tiles 48.8 / 55.2 -- the smaller one leaves room for one vector instruction
 // beside it, the larger for four.  128 x 128 tiles take eight wavefronts of 32 x 64 rather than four of 64 x 64
-// (2048^3 99.6 / 107 us, 4096^3 776 / 819): with one wavefront per SIMD nothing covers its waits.  Two or three k-tiles on their way instead of one, and another first k-tile per
-// workgroup for tall operands: no difference.
+// (2048^3 99.6 / 107 us, 4096^3 776 / 819): with one wavefront per SIMD nothing covers its waits.  Two or three
+// k-tiles on their way instead of one, and another first k-tile per workgroup for tall operands: no difference.
 #include "mdh_split.h"
 
 namespace mdh {
@@ -88,40 +88,63 @@ struct Operand {
   }
 };
 
-// element (row, k) of an operand for the checks and the fp32 evaluation of a wavefront's tile
+// four consecutive k of a row, elements at or beyond kend as 0
 template <bool KC>
-__device__ __forceinline__ float element(const float* __restrict__ P, int64_t ld, int row, int k) {
-  return KC ? P[row * ld + k] : P[k * ld + row];
+__device__ __forceinline__ f4 four_k(const float* __restrict__ P, int64_t ld, int row, int k, int kend) {
+  if (KC && k + 3 < kend) return *(const f4u*)(P + row * ld + k);
+  f4 v;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) v[t] = k + t < kend ? (KC ? P[row * ld + k + t] : P[(k + t) * ld + row]) : 0.f;
+  return v;
 }
 
+// fp32 evaluation of a wavefront's tile, 64 x 64 at a time, for values the split does not carry
 template <int WM, int WN, bool YK, bool XK>
-__device__ __noinline__ void recompute_fp32(const float* __restrict__ Y, const float* __restrict__ X, float* __restrict__ Cout,
+__device__ __forceinline__ void recompute_fp32(const float* __restrict__ Y, const float* __restrict__ X, float* __restrict__ Cout,
                                             int M, int N, int64_t ldy, int64_t ldx, int m0, int n0, int kbeg, int kend) {
+  constexpr int MB = WM < 64 ? 1 : 2, NB = WN < 64 ? 1 : 2;
   const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
-  for (int mi = 0; mi < WM; mi += 32)
-    for (int ni = 0; ni < WN; ni += 32) {
+  for (int mi = 0; mi < WM; mi += MB * 32)
+    for (int ni = 0; ni < WN; ni += NB * 32) {
       if (m0 + mi >= M || n0 + ni >= N) continue;
-      const int row = min(m0 + mi + l32, M - 1), col = min(n0 + ni + l32, N - 1);
-      f16 acc;
+      f16 acc[MB][NB];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-#pragma unroll 4
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      f4 y[MB], x[NB];
+      auto load = [&](int k0) {
+#pragma unroll
+        for (int i = 0; i < MB; ++i) y[i] = four_k<YK>(Y, ldy, min(m0 + mi + i * 32 + l32, M - 1), k0 + lh * 4, kend);
+#pragma unroll
+        for (int j = 0; j < NB; ++j) x[j] = four_k<XK>(X, ldx, min(n0 + ni + j * 32 + l32, N - 1), k0 + lh * 4, kend);
+      };
+      load(kbeg);
       for (int k0 = kbeg; k0 < kend; k0 += 8) {
-        float y[4], x[4];
+        f4 yc[MB], xc[NB];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int k = k0 + lh * 4 + t;
-          y[t] = k < kend ? element<YK>(Y, ldy, row, k) : 0.f;
-          x[t] = k < kend ? element<XK>(X, ldx, col, k) : 0.f;
-        }
+        for (int i = 0; i < MB; ++i) yc[i] = y[i];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(y[t], x[t], acc, 0, 0, 0);
+        for (int j = 0; j < NB; ++j) xc[j] = x[j];
+        if (k0 + 8 < kend) load(k0 + 8);  // on its way while these are multiplied
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int i = 0; i < MB; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(yc[i][t], xc[j][t], acc[i][j], 0, 0, 0);
       }
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int ro = m0 + mi + 8 * (r / 4) + 4 * lh + (r % 4), co = n0 + ni + l32;
-        if (ro < M && co < N) Cout[(int64_t)ro * N + co] = acc[r];
-      }
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int ro = m0 + mi + i * 32 + 8 * (r / 4) + 4 * lh + (r % 4), co = n0 + ni + j * 32 + l32;
+            if (ro < M && co < N) Cout[(int64_t)ro * N + co] = acc[i][j][r];
+          }
     }
 }
 
