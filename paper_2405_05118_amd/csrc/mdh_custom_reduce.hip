@@ -20,6 +20,7 @@
 #include <mutex>
 
 #include "mdh_internal.h"
+#include "mdh_walk.h"
 
 // Scratch memory of mdh_custom_reduce_static, the entry point for callers that cannot allocate: the
 // partial (score, index) results of a reduction split over workgroups, 2 * S * nA int32.  One copy per
@@ -227,9 +228,8 @@ __global__ __launch_bounds__(WA* WB * 64) void prl_fast_kernel(
     for (int ra = 0; ra < RA; ++ra) fbest[ra] = -3.0e38f, blk[ra] = b0;
     const float vbase = agree_sum + __uint_as_float(__float_as_uint(0.f) | (lane & 0));  // a vector register
 
-    constexpr int kRun = 512;
     while (done < b1) {
-      const int end = min(done + kRun, b1);
+      const int end = run_end(done, b1);
       float fbefore[RA];
       int before[RA];
 #pragma unroll
@@ -443,7 +443,7 @@ mdh_status launch_nf(const PrlPlan& pl, int64_t nA, int64_t nB, int nF, const in
   if constexpr (RA == 2 || RA == 4)
     if (nF == 8) return launch_fast<8, RA, WB, WA>(pl, nA, nB, A, B, wp, wm, score, index, ws, st);
   if constexpr (RA == 2 && WB == 4 && WA == 1) {
-    if (nB <= 0x7ffffff0) switch (nF) {  // (the walk looks up to seven records past the end before it clamps)
+    if (nB <= kMaxWalked) switch (nF) {
 #define MDH_NF(n) \
   case n: return launch_fast<n, RA, WB, WA>(pl, nA, nB, A, B, wp, wm, score, index, ws, st);
       MDH_NF(1) MDH_NF(2) MDH_NF(3) MDH_NF(4) MDH_NF(5) MDH_NF(6) MDH_NF(7)
