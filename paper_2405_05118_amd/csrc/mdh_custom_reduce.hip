@@ -163,8 +163,9 @@ __global__ __launch_bounds__(WA* WB * 64) void prl_kernel(
 // of compare + maximum + select per record; which record of the winning block scored the maximum is
 // found once at the end by scoring that block again.  Everything stays exact under these conditions,
 // which the kernel checks itself: field values in [0, 2^23) (the records of A up front, those of B as
-// they stream by, after every 512: from the run of 512 that holds a value outside, the integer loop goes on), and
-// sum_f max(|w_agree_f|, |w_disagree_f|) < 2^24 (all partial sums are then integers fp32 holds exactly).
+// they stream by, after every 512: from the run of 512 that holds a value outside, the integer loop goes on),
+// sum_f max(|w_agree_f|, |w_disagree_f|) < 2^24 and every |w_disagree_f - w_agree_f| <= 2^24 (all partial sums, and
+// what a field that differs adds, are then integers fp32 holds exactly).
 // The result is the unique (score, index) of the definition, bit for bit, on either path.
 template <int NF, int RA, int WB, int WA>
 __global__ __launch_bounds__(WA* WB * 64) void prl_fast_kernel(
@@ -189,6 +190,7 @@ __global__ __launch_bounds__(WA* WB * 64) void prl_fast_kernel(
   float ndw[NF];
   float agree_sum = 0.f;
   int64_t wabs = 0;
+  bool fast = true;
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
     const int p = wp[f], m = wm[f];
@@ -196,8 +198,9 @@ __global__ __launch_bounds__(WA* WB * 64) void prl_fast_kernel(
     if (NF > 8) asm("" : "+v"(ndw[f]));
     agree_sum += (float)p;
     wabs += max(abs((int64_t)p), abs((int64_t)m));
+    fast = fast && abs((int64_t)m - (int64_t)p) <= (1 << 24);
   }
-  bool fast = wabs < (1 << 24);
+  fast = fast && wabs < (1 << 24);
 
   // the lane's records of A, float-coded (the integer loop, should it be needed, reads them again)
   constexpr unsigned kCode = 0x4B000000u;  // bits of 2^23: kCode + v is the float 2^23 + v for 0 <= v < 2^23
