@@ -497,7 +497,7 @@ mdh_status plan_matmul(const int64_t* s, const mdh_tile_params* p, GemmPlan* out
   // other permutation has no instantiation (the regenerated table below differs)
   pl.jmajor = (p->order[0] == MDH_L_WG * MDH_MAX_D + 1 && p->order[1] == MDH_L_WG * MDH_MAX_D + 0) ? 1 : 0;
   if (p->blk[0] != 32 || p->blk[1] != 32 || (p->blk[2] != 2 && p->blk[2] != 16)) return MDH_ERR_UNSUPPORTED;
-  if (pl.split && !split_sizes(s[0], s[1], s[2])) return MDH_ERR_UNSUPPORTED;
+  if (pl.split && (!split_inst(pl, false) || !split_sizes(s[0], s[1], s[2]))) return MDH_ERR_UNSUPPORTED;
   if (pl.split && (pl.S - 1) * split_part(s[2], pl) >= s[2]) return MDH_ERR_TILE_NOT_DIVIDING;  // a part without k
   if ((pl.split ? split_lds_bytes(pl) : gemm_lds_bytes(pl.BM, pl.BN, pl.BK)) > kLdsBytesPerWG) return MDH_ERR_TILE_RESOURCES;
   if ((int64_t)p->prt[MDH_L_WAVE][0] * p->prt[MDH_L_WAVE][1] * 64 > kMaxLanesPerWG)
@@ -937,7 +937,7 @@ mdh_status plan_mcc(const int64_t* s, const mdh_tile_params* p, MccPlan* out) {
     // a workgroup part of c that owns no channel would leave its partial output unset
     if (pl.S > 1 && pl.CK > 0 && (int64_t)(pl.S - 1) * cdiv(cdiv(s[4], pl.S), pl.CK) * pl.CK >= s[4])
       return MDH_ERR_TILE_NOT_DIVIDING;
-    if (pl.split && (pl.CK < 16 || !mcc_split_sizes(s, pl))) return MDH_ERR_UNSUPPORTED;
+    if (pl.split && (!mcc_inst(pl) || !mcc_split_sizes(s, pl))) return MDH_ERR_UNSUPPORTED;
   }
   pl.ragged = ragged;
   if (mcc_lds_bytes(pl, s) > kLdsBytesPerWG) return MDH_ERR_TILE_RESOURCES;

@@ -295,16 +295,16 @@ mdh_status plan_matmul_ex(const int64_t* s, const mdh_tile_params* p, GemmExPlan
   g.BN = p->prt[MDH_L_WAVE][2] * g.WN;
   if (p->blk[1] != 32 || p->blk[2] != 32 || (p->blk[3] != 2 && p->blk[3] != 16)) return MDH_ERR_UNSUPPORTED;
   g.split = p->blk[3] == 16;
-  if (g.split && !split_sizes(s[1], s[2], s[3])) return MDH_ERR_UNSUPPORTED;
   g.BK = p->prt[MDH_L_LDS][3] * p->blk[3];
+  if (g.split && (!split_inst(g, s[6] != 0) || !split_sizes(s[1], s[2], s[3]))) return MDH_ERR_UNSUPPORTED;
   g.S = p->prt[MDH_L_WG][3];
   g.ragged = ragged;
-  if (g.split && g.BK > 0 && (g.S - 1) * split_part(s[3], g) >= s[3]) return MDH_ERR_TILE_NOT_DIVIDING;  // a part without k
+  if (g.split && (g.S - 1) * split_part(s[3], g) >= s[3]) return MDH_ERR_TILE_NOT_DIVIDING;  // a part without k
   GemmExPlan pl{g, (int)s[4], (int)s[5], (int)s[6]};
   mdh_tile_params chk;
   params_from_plan(s, pl, &chk);
   // the layout parameters of the configuration must describe the views the call passes
-  if (!same_table(chk, *p) || !(g.split ? split_inst(g, s[6] != 0) : ex_inst(g))) return MDH_ERR_UNSUPPORTED;
+  if (!same_table(chk, *p) || !(g.split || ex_inst(g))) return MDH_ERR_UNSUPPORTED;
   *out = pl;
   return MDH_OK;
 }

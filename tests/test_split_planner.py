@@ -1,0 +1,30 @@
+"""Tables of the kernels that carry a value as three bf16 values: what the planner refuses and what it offers."""
+import os
+import subprocess
+import sys
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+# every entry of the table that the k-tile or the part of k is computed from, at values whose products wrap to nothing,
+# to a valid tile or to a negative one; one table a line, so that a crash names its table
+HUGE = """
+import paper_2405_05118_amd as mdh
+for inst, sizes, k in ((mdh.MDH_MATMUL, (256, 256, 256), 2), (mdh.MDH_BMATMUL, (2, 256, 256, 256, 0, 1, 0), 3),
+                       (mdh.MDH_BMATMUL, (2, 256, 256, 256, 0, 1, 1), 3), (mdh.MDH_MCC, (1, 16, 32, 64, 64, 3, 3, 1, 1), 4)):
+    cands = [mdh.mdh_candidate(inst, sizes, i) for i in range(mdh.mdh_num_candidates(inst, sizes))]
+    p = next(p for p in cands if (p.prt[2][4] == 8 if inst == mdh.MDH_MCC else p.blk[k] == 16))
+    for layer in range(6):
+        for d in range(p.D):
+            for v in (1 << 25, 1 << 26, (1 << 26) + 1, 1 << 27, (1 << 27) + 1, 1 << 28, (1 << 28) + 1, (1 << 28) + 2, 1 << 30, (1 << 31) - 1):
+                q = p.copy()
+                q.ragged = 1
+                q.prt[layer][d] = v
+                print(inst, sizes, layer, d, v, flush=True)
+                assert mdh.mdh_validate_params(inst, sizes, q) != 0
+print("all refused")
+"""
+
+
+def test_tables_whose_products_wrap_are_refused():
+    r = subprocess.run([sys.executable, "-c", HUGE], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.endswith("all refused\n"), (r.returncode, r.stdout[-200:], r.stderr[-500:])
