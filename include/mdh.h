@@ -231,7 +231,8 @@ size_t mdh_workspace_size(mdh_instance inst, const int64_t* sizes, const mdh_til
  *   S partial results go to `workspace` (S*M*N floats) and a second kernel adds
  *   them in ascending part order.  The library default may split k, so pass the
  *   workspace mdh_workspace_size asks for (for some sizes it is asked for but not needed:
- *   a call that brings less then runs with fewer parts).  blk = (32,32,16) selects the
+ *   a call with the default, as NULL or as its table, that brings less then runs with
+ *   fewer parts).  blk = (32,32,16) selects the
  *   kernel that carries a value as three bf16 values and multiplies with six bf16 matrix
  *   products (K >= 32; the default for large products; Inf, NaN, overflow and values below
  *   2^-100 take the fp32 instructions).  Two kernels with fp32 instructions, told apart by

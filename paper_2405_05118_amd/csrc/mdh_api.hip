@@ -51,7 +51,7 @@ mdh_status mdh_matmul(int64_t M, int64_t N, int64_t K, const float* A, const flo
   if (!A || !B || !C) return MDH_ERR_NULL;
   auto fits = [&] { return pl.S <= 1 || (workspace && workspace_bytes >= (size_t)pl.S * (size_t)M * (size_t)N * sizeof(float)); };
   // the default splits k further where there is room for it
-  if (!params && !fits() && (st = plan_matmul_lean(sizes, &pl)) != MDH_OK) return st;
+  if (!fits()) plan_matmul_lean(sizes, &pl);
   if (pl.S > 1 && too_big((int64_t)pl.S * M * N)) return MDH_ERR_SIZE;
   if (!fits()) return MDH_ERR_WORKSPACE;
   return launch_matmul(pl, M, N, K, A, B, C, workspace, (hipStream_t)stream);

@@ -208,8 +208,8 @@ mdh_status launch_matvec(const MatVecPlan& pl, int64_t M, int64_t K, const float
 
 mdh_status plan_stencil(const int64_t* sizes, const mdh_tile_params* p, StencilPlan* out);
 mdh_status plan_matmul(const int64_t* sizes, const mdh_tile_params* p, GemmPlan* out);
-// the default for a caller without the workspace the default asks for
-mdh_status plan_matmul_lean(const int64_t* sizes, GemmPlan* out);
+// for a caller without the workspace the plan asks for: the default, given as none or as its table, does with less
+void plan_matmul_lean(const int64_t* sizes, GemmPlan* pl);
 mdh_status plan_mcc(const int64_t* sizes, const mdh_tile_params* p, MccPlan* out);
 mdh_status plan_prl(const int64_t* sizes, const mdh_tile_params* p, PrlPlan* out);
 

@@ -395,9 +395,12 @@ static GemmPlan gemm_default(const int64_t* s) {
   return pl;
 }
 
-mdh_status plan_matmul_lean(const int64_t* s, GemmPlan* out) {
-  *out = gemm_default_lean(s);
-  return MDH_OK;
+void plan_matmul_lean(const int64_t* s, GemmPlan* pl) {
+  const GemmPlan d = gemm_default(s);
+  mdh_tile_params a, b;
+  params_from_plan(s, d, &a);
+  params_from_plan(s, *pl, &b);
+  if (same_table(a, b)) *pl = gemm_default_lean(s);
 }
 
 int matmul_candidates(const int64_t* s, GemmPlan* out, int cap) {

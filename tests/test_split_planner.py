@@ -3,6 +3,10 @@ import os
 import subprocess
 import sys
 
+import pytest
+
+import paper_2405_05118_amd as mdh
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 # every entry of the table that the k-tile or the part of k is computed from, at values whose products wrap to nothing,
@@ -28,3 +32,24 @@ print("all refused")
 def test_tables_whose_products_wrap_are_refused():
     r = subprocess.run([sys.executable, "-c", HUGE], cwd=ROOT, capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and r.stdout.endswith("all refused\n"), (r.returncode, r.stdout[-200:], r.stderr[-500:])
+
+
+# the default of these sizes asks for a workspace it can do without, also where the caller passes its table
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(90, 90, 8000), (40, 2000, 2000), (128, 300, 5001)])
+def test_table_of_the_default_without_workspace(shape):
+    import torch
+
+    M, N, K = shape
+    p = mdh.mdh_default_params(mdh.MDH_MATMUL, shape)
+    assert mdh.mdh_workspace_size(mdh.MDH_MATMUL, shape, p) > 0
+    A, B = torch.ones((M, K), device="cuda"), torch.ones((K, N), device="cuda")
+    for q in (None, p):
+        C = torch.full((M, N), float("nan"), device="cuda")
+        mdh.mdh_matmul(A, B, C, q, None)
+        assert bool((C == K).all())
+    # another table that splits k is taken as it stands
+    cands = [mdh.mdh_candidate(mdh.MDH_MATMUL, shape, i) for i in range(1, mdh.mdh_num_candidates(mdh.MDH_MATMUL, shape))]
+    with pytest.raises(mdh.MdhError) as e:
+        mdh.mdh_matmul(A, B, C, next(q for q in cands if q.prt[3][2] == 2), None)
+    assert e.value.status == 5
