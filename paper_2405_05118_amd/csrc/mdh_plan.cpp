@@ -416,15 +416,15 @@ int matmul_candidates(const int64_t* s, GemmPlan* out, int cap) {
         return;
     out[n++] = pl;
   };
-  push(gemm_default(s));
-  {  // the default's tile with the other loop order of the workgroup layer (column bands)
-    GemmPlan d = gemm_default(s);
-    if (d.WK == 1 && cdiv(s[0], d.BM) > 1 && cdiv(s[1], d.BN) > 1) {
-      d.jmajor = !d.jmajor;
-      push(d);
-    }
+  // (for few rows candidate 0 is shown as the small-M kernel: what it hides is the fp32 kernels' choice, as ever)
+  if (small_m_matmul(s, nullptr)) push(gemm_default_fp32(s));
+  for (const GemmPlan& d : {gemm_default(s), gemm_default_fp32(s)}) {
+    push(d);
+    // its tile with the other loop order of the workgroup layer (column bands)
+    GemmPlan t = d;
+    t.jmajor = !t.jmajor;
+    if (t.WK == 1 && cdiv(s[0], t.BM) > 1 && cdiv(s[1], t.BN) > 1) push(t);
   }
-  push(gemm_default_fp32(s));
   if (split_sizes(s[0], s[1], s[2])) {
     GemmPlan sp[kSplitTiles];
     const int ns = split_tiles(false, sp);

@@ -7,6 +7,7 @@ import pytest
 
 import paper_2405_05118_amd as mdh
 
+MAX_D = 10
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 # every entry of the table that the k-tile or the part of k is computed from, at values whose products wrap to nothing,
@@ -32,6 +33,18 @@ print("all refused")
 def test_tables_whose_products_wrap_are_refused():
     r = subprocess.run([sys.executable, "-c", HUGE], cwd=ROOT, capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and r.stdout.endswith("all refused\n"), (r.returncode, r.stdout[-200:], r.stderr[-500:])
+
+
+# the default's tile in column bands, and what the small-M kernel stands in front of, where the split kernels or parts
+# of k have become the default: WG, WAVE and VGPR parts of (i, j, k), and the loop order's first entry
+@pytest.mark.parametrize("sizes, wg, wave, vgpr, first", [
+    ((496, 139, 20778), (8, 3, 16), (2, 2, 1), (1, 1, 1), 3 * MAX_D + 1),
+    ((87, 5853, 17022), (2, 92, 2), (2, 2, 1), (1, 1, 1), 3 * MAX_D + 1),
+    ((1, 1861, 5605), (1, 117, 2), (1, 1, 8), (1, 1, 4), 3 * MAX_D),
+])
+def test_candidates_beside_the_default(sizes, wg, wave, vgpr, first):
+    assert any((tuple(p.prt[3][:3]), tuple(p.prt[4][:3]), tuple(p.prt[2][:3])) == (wg, wave, vgpr) and p.order[0] == first and p.blk[2] != 16
+               for p in (mdh.mdh_candidate(mdh.MDH_MATMUL, sizes, i) for i in range(mdh.mdh_num_candidates(mdh.MDH_MATMUL, sizes))))
 
 
 # the default of these sizes asks for a workspace it can do without, also where the caller passes its table
