@@ -40,6 +40,7 @@ struct Operand {
   static constexpr int BYTES = 3 * SLICE;
 
   float x[CH][8];
+  float top[CH];     // largest magnitude of the chunk's row among what this thread has split
   unsigned off[CH];  // byte offset of the thread's chunk from the tile's first element
 
   // rows beyond the operand's edge repeat its last row: they only reach outputs that are not stored
@@ -47,6 +48,7 @@ struct Operand {
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
       const int f = threadIdx.x + c * NT;
+      top[c] = 0.f;
       if (KC)
         off[c] = (unsigned)(min(f / KP, rmax - 1 - r0) * ld + f % KP * 8) * 4u;
       else
@@ -77,14 +79,28 @@ struct Operand {
 #pragma unroll
     for (int e = 0; e < 8; ++e) x[c][e] = k + e < skip ? 0.f : x[c][e];
   }
-  __device__ __forceinline__ void store(char* st, Split& split, int c) {
+  __device__ __forceinline__ void store(char* st, const Split& split, int c) {
     const int f = threadIdx.x + c * NT;
     const int row = KC ? f / KP : f % ROWS, kc = KC ? f % KP : f / ROWS;
     u4 v[3];
-    split(x[c], v);
+    split(x[c], v, top[c]);
     char* p = st + kc * PLANE + (row ^ (SWZ * kc)) * 16;
 #pragma unroll
     for (int s = 0; s < 3; ++s) *(u4*)(p + s * SLICE) = v[s];
+  }
+  __device__ __forceinline__ float largest() const {
+    float t = 0.f;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) t = fmaxf(t, top[c]);
+    return t;
+  }
+  // rows: LDS, the largest magnitude of every row (bits of a float), 0 before
+  __device__ __forceinline__ void merge(unsigned* rows) const {
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const int f = threadIdx.x + c * NT;
+      atomicMax(rows + (KC ? f / KP : f % ROWS), __float_as_uint(top[c]));
+    }
   }
 };
 
@@ -327,9 +343,32 @@ __device__ __forceinline__ void split_tile(const float* __restrict__ Y, const fl
         z = __builtin_fmaf(acc[mi][ni][r], 0.f, z);
         least = fminf(least, fabsf(acc[mi][ni][r]));
       }
-  if (needs_fp32(z, least, split.largest, (float)(kend - kbeg), largest, [&] {
-        return holds_tiny<BM, NT, YK>(Y, ldy, m0, M, kbeg, kend) || holds_tiny<BN, NT, XK>(X, ldx, n0, N, kbeg, kend);
-      })) {
+  const float bound = (float)(kend - kbeg) * kTiny * workgroup_largest(fmaxf(oy.largest(), ox.largest()), largest);
+  bool fp32 = __any(!(z == 0.f));
+  if (__syncthreads_or(least < bound)) {
+    unsigned* const rows = (unsigned*)lds;  // the operands' stages are done with
+    for (int i = threadIdx.x; i < BM + BN; i += NT) rows[i] = 0;
+    __syncthreads();
+    oy.merge(rows);
+    ox.merge(rows + BM);
+    __syncthreads();
+    bool small = false;
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni) {
+      const unsigned cols = nonzero_bits(rows + BM + wn + ni * 32 + 4 * lh);
+#pragma unroll
+      for (int mi = 0; mi < MI; ++mi)
+        if (rows[wm + mi * 32 + l32])
+#pragma unroll
+          for (int r = 0; r < 16; ++r) small |= fabsf(acc[mi][ni][r]) < bound && (cols >> r & 1);
+    }
+    small = __any(small);
+    if (__syncthreads_or(small)) {
+      const bool found = holds_tiny<BM, NT, YK>(Y, ldy, m0, M, kbeg, kend) || holds_tiny<BN, NT, XK>(X, ldx, n0, N, kbeg, kend);
+      if (__syncthreads_or(found)) fp32 |= small;
+    }
+  }
+  if (fp32) {
     recompute_fp32<WM, WN, YK, XK>(Y, X, Cout, M, N, ldy, ldx, m0 + wm, n0 + wn, kbeg, kend);
     return;
   }

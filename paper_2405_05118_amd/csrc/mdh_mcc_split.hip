@@ -24,12 +24,17 @@ struct Cfg {
   static_assert(TP % (MI * RB) == 0, "rows of the tile = wavefronts x blocks x rows per block");
   static constexpr int WAVES_M = TP / (MI * RB), WAVES_N = BN / WN;
   static constexpr int NT = WAVES_M * WAVES_N * 64;
+  // Wavefronts a SIMD must be able to hold: what LDS has room for.  Without a demand the compiler keeps accumulators in
+  // accumulation registers and moves them about, or not, as the rest of the kernel comes out (2 x 17 x 22 x 292 -> 728,
+  // 3 x 9, 8 x 16 x 64 tiles 170 / 189 us; 8 x 16 x 128 in chunks of 16 channels 315 / 356).
+  static constexpr int HELD = CK == 32 && MI * NI == 4 ? 2 : 3;
   static constexpr int KP = CK / 8, KH = CK / 16;
   static constexpr int F_PLANE = BN * 16, F_SLICE = KP * F_PLANE, F_STAGE = 3 * F_SLICE;
   static constexpr int F_CHUNKS = BN * KP;
   static constexpr int F_CH = (F_CHUNKS + NT - 1) / NT;
   // patch planes are padded so that the planes of one pixel start 64 (CK = 16) or 32 bytes apart in the banks
   static constexpr int PAD = CK == 16 ? 4 : 2;
+  static_assert((160 * 1024 - 2 * F_STAGE) / (3 * KP * 16) * KP <= 31 * NT, "a bit per pixel of a thread");
   static __host__ __device__ __forceinline__ int plane(int npix) { return ((npix + 7) / 8 * 8 + PAD) * 16; }
 };
 
@@ -92,11 +97,10 @@ __device__ __forceinline__ bool holds_tiny(const Conv& g, int n, int h0, int nh,
 // One tap is six phases, one per product, as a k-tile of the split MatMul: LDS holds the filter slices of two taps,
 // the filter of tap t+1 is split while tap t is multiplied, that of tap t+2 is on its way from memory, and the one
 // barrier of a tap stands where all its operands are in registers.  The smaller products come first, for the reason
-// given there; of the four such orders this one, which reads the input's slices before the filter's, keeps the
-// schedule (16 x 30 x 30 x 128, 3 x 3, 16 x 8 x 64 tiles: 32.9 us, filter first 35.6).
+// given there.
 template <int TP, int TQ, int BN, int CK, int WM, int WN>
-__global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT)) void mcc_split_kernel(Conv g, float* __restrict__ ws, int tp_n, int tq_n,
-                                                                                    int tk_n, int n_img, int SC, int cchunk) {
+__global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT), (Cfg<TP, TQ, BN, CK, WM, WN>::HELD)) void mcc_split_kernel(
+    Conv g, float* __restrict__ ws, int tp_n, int tq_n, int tk_n, int n_img, int SC, int cchunk) {
   using F = Cfg<TP, TQ, BN, CK, WM, WN>;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   // XCD-aware order: each of the 8 XCDs gets a contiguous run of tiles; inside a run the channel tiles of one
@@ -128,14 +132,17 @@ __global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT)) void mcc_split_k
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
 
-  Split split;
+  const Split split;
   const int taps = g.R * g.S;
   // filter chunks of this thread: eight channels of one output channel; channels beyond K repeat the last one
   float fx[F::F_CH][8];
+  float ftop[F::F_CH], ptop = 0.f;  // largest magnitude split: of the chunk's output channel, of the patch
+  unsigned pnz = 0;                 // bit i: this thread's i-th pixel is not all zeros (a patch that fits has less than 32)
   unsigned foff[F::F_CH];
 #pragma unroll
   for (int c = 0; c < F::F_CH; ++c) {
     const int f = (tid + c * F::NT) % F::F_CHUNKS;
+    ftop[c] = 0.f;
     foff[c] = (unsigned)(min(f / F::KP, g.K - 1 - k0) * (taps * g.C) + f % F::KP * 8) * 4u;
   }
   const float* const fbase = g.filt + (int64_t)k0 * taps * g.C;
@@ -151,14 +158,15 @@ __global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT)) void mcc_split_k
     const int f = (tid + c * F::NT) % F::F_CHUNKS;
     const int k = f / F::KP, kc = f % F::KP;
     u4 v[3];
-    split(fx[c], v);
+    split(fx[c], v, ftop[c]);
     char* p = st + kc * F::F_PLANE + (k ^ (64 / CK * kc)) * 16;
 #pragma unroll
     for (int s = 0; s < 3; ++s) *(u4*)(p + s * F::F_SLICE) = v[s];
   };
   // input patch of the channels from c0 on; the first `skip` of them belong to the chunk before and read as 0
   auto stage_patch = [&](int c0, int skip) {
-    for (int f = tid; f < npix * F::KP; f += F::NT) {
+    unsigned bit = 1;
+    for (int f = tid; f < npix * F::KP; f += F::NT, bit <<= 1) {
       const int pix = f / F::KP, kc = f % F::KP;
       const int ph = pix / PW, pw = pix - ph * PW;
       const int hy = min(p0 * g.sh + ph, g.H - 1), wx = min(q0 * g.sw + pw, g.W - 1);
@@ -172,7 +180,10 @@ __global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT)) void mcc_split_k
         for (int e = 0; e < 8; ++e) x[e] = kc * 8 + e < skip ? 0.f : x[e];
       }
       u4 v[3];
-      split(x, v);
+      float top = 0.f;
+      split(x, v, top);
+      ptop = fmaxf(ptop, top);
+      pnz |= top != 0.f ? bit : 0;
 #pragma unroll
       for (int s = 0; s < 3; ++s) *(u4*)(patch + s * pslice + kc * pplane + pix * 16) = v[s];
     }
@@ -209,14 +220,14 @@ __global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT)) void mcc_split_k
   auto body = [&](int tap, int at, int at_next, int c0, auto more_) {
     constexpr bool more = decltype(more_)::value;
     const char* cur = lds + (tap & 1) * F::F_STAGE;
-    read_y(at, H);
-    mma(Mid, Mid);
     read_x(cur, H);
-    mma(H, Mid);
-    read_y(at, L);
+    mma(Mid, Mid);
+    read_y(at, H);
     mma(Mid, H);
     read_x(cur, L);
-    mma(L, H);
+    mma(H, Mid);
+    read_y(at, L);
+    mma(H, L);
     if (more) {
 #pragma unroll
       for (int c = 0; c < F::F_CH; ++c) {
@@ -237,7 +248,7 @@ __global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT)) void mcc_split_k
       read_y(at_next, Mid);
       read_x(lds + ((tap + 1) & 1) * F::F_STAGE, Mid);
     }
-    mma(H, L);
+    mma(L, H);
     mma(H, H);
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -278,9 +289,56 @@ __global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT)) void mcc_split_k
         z = __builtin_fmaf(acc[mi][ni][r], 0.f, z);
         least = fminf(least, fabsf(acc[mi][ni][r]));
       }
-  if (needs_fp32(z, least, split.largest, (float)(taps * (cend - cbeg)), largest, [&] {
-        return holds_tiny<F::NT>(g, n, p0 * g.sh, PH, q0 * g.sw, PW, k0, BN, cbeg, cend);
-      })) {
+  float top = ptop;
+#pragma unroll
+  for (int c = 0; c < F::F_CH; ++c) top = fmaxf(top, ftop[c]);
+  const float bound = (float)(taps * (cend - cbeg)) * kTiny * workgroup_largest(top, largest);
+  bool fp32 = __any(!(z == 0.f));
+  if (__syncthreads_or(least < bound)) {
+    // the operands' stages are done with: the largest magnitude of every output channel (bits of a float), and whether a
+    // pixel of the patch is not all zeros
+    unsigned* const filters = (unsigned*)lds;
+    unsigned* const pixels = filters + BN;
+    for (int i = tid; i < BN + npix; i += F::NT) filters[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < F::F_CH; ++c) atomicMax(filters + (tid + c * F::NT) % F::F_CHUNKS / F::KP, __float_as_uint(ftop[c]));
+    __syncthreads();
+    unsigned small[F::MI];  // of the block's pixel of this lane
+#pragma unroll
+    for (int mi = 0; mi < F::MI; ++mi) small[mi] = 0;
+#pragma unroll
+    for (int ni = 0; ni < F::NI; ++ni) {
+      const unsigned live = nonzero_bits(filters + wn * WN + ni * 32 + 4 * lh);
+#pragma unroll
+      for (int mi = 0; mi < F::MI; ++mi)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) small[mi] |= fabsf(acc[mi][ni][r]) < bound ? live >> r & 1 : 0;
+    }
+    bool open = false;
+#pragma unroll
+    for (int mi = 0; mi < F::MI; ++mi) {
+      if (p0 + (wm * F::MI + mi) * F::RB + l32 / TQ >= g.P || q0 + l32 % TQ >= g.Q) small[mi] = 0;
+      open |= small[mi] != 0;
+    }
+    if (__syncthreads_or(open)) {
+      for (int i = 0; tid + i * F::NT < npix * F::KP; ++i)
+        if (pnz >> i & 1) pixels[(tid + i * F::NT) / F::KP] = 1;
+      __syncthreads();
+      open = false;
+#pragma unroll
+      for (int mi = 0; mi < F::MI; ++mi)
+        if (small[mi])
+          for (int r = 0; r < g.R; ++r)
+            for (int s = 0; s < g.S; ++s) open |= pixels[pix0 + (mi * F::RB * g.sh + r) * PW + s] != 0;
+      open = __any(open);
+      if (__syncthreads_or(open)) {
+        const bool found = holds_tiny<F::NT>(g, n, p0 * g.sh, PH, q0 * g.sw, PW, k0, BN, cbeg, cend);
+        if (__syncthreads_or(found)) fp32 |= open;
+      }
+    }
+  }
+  if (fp32) {
     recompute_fp32<TP, TQ, BN, CK, WM, WN>(g, dst, n, p0, q0, k0, cbeg, cend);
     return;
   }

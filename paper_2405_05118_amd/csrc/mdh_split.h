@@ -1,8 +1,8 @@
 // fp32 products on the 16-bit matrix instructions, with the accuracy of fp32.
 //
 // An fp32 value has 24 significant bits, a bf16 value 8, and both have the same exponents: x = h + m + l with
-// h = bf16(x), m = bf16(x - h), l = bf16(x - h - m) is exact (each difference is a float, |m| <= 2^-9 |x|,
-// |l| <= 2^-18 |x|) as long as |x| >= 2^-100, whose last bit is well above the smallest normal number.  Of the nine products of two
+// h = bf16(x), m = bf16(x - h), l = bf16(x - h - m) is exact (each difference is a float, |m| <= 2^-8 |x|,
+// |l| <= 2^-17 |x|) as long as |x| >= 2^-100, whose last bit is well above the smallest normal number.  Of the nine products of two
 // such sums the six
 //     h h'   h m'   m h'   m m'   h l'   l h'
 // are evaluated, each exact in the fp32 accumulation of v_mfma_f32_32x32x16_bf16; the three left out are below
@@ -13,12 +13,13 @@
 // (all nine products: the same digits).  Rate of the bare instruction loops on random operands: 154 TFLOP/s in
 // fp32, 1850 / 6 = 308 TFLOP/s in six bf16 products (the 16x16x32 form: 2220 / 6).
 //
-// Two kinds of values need more than that, and get the fp32 instructions (recompute_* below):
+// Two kinds of values need more than that, and get the fp32 instructions (recompute_* in the kernels):
 //   - not finite, or an overflow: Inf splits into Inf + NaN.  Every output that such a value enters comes out
 //     not finite, so the outputs tell;
 //   - |x| < 2^-100: its last slices may be lost to subnormal numbers, up to 2^-126.  That can matter only for an
 //     output smaller than K * 2^-100 * (largest |x| of its tile), and only if such an element is there; both are
-//     checked.
+//     checked.  An output whose row or column is all zeros -- padding, a dead filter -- is small and exact: the largest
+//     magnitude of every row, kept as the values are split, tells without reading the operands again.
 #pragma once
 #include "mdh_internal.h"
 
@@ -46,7 +47,6 @@ constexpr float kTiny = 7.88860905e-31f;  // 2^-100
 // packed operand that is (0, -1).
 struct Split {
   unsigned neg_lo = 0x0000bf80u, neg_hi = 0xbf800000u;
-  float largest = 0.f;  // magnitude of what this thread has split
 
   __device__ __forceinline__ Split() { asm("" : "+s"(neg_lo), "+s"(neg_hi)); }
 
@@ -57,9 +57,9 @@ struct Split {
   static __device__ __forceinline__ float minus(float x, unsigned p, unsigned q) {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf2, p), __builtin_bit_cast(bf2, q), x, false);
   }
-  // eight consecutive k of one row: the three slices, 16 bytes each.  Level by level, because a result of
-  // v_dot2c can be read only a few instructions later.
-  __device__ __forceinline__ void operator()(float (&x)[8], u4 (&out)[3]) {
+  // eight consecutive k of one row: the three slices, 16 bytes each, and the largest magnitude met so far.  Level by
+  // level, because a result of v_dot2c can be read only a few instructions later.
+  __device__ __forceinline__ void operator()(float (&x)[8], u4 (&out)[3], float& largest) const {
 #pragma unroll
     for (int s = 0; s < 3; ++s) {
 #pragma unroll
@@ -95,23 +95,22 @@ __device__ __forceinline__ bool tiny_in(const float* __restrict__ p, int n, int 
   return t;
 }
 
-// The end of a workgroup's tile: has this wavefront to evaluate its part in fp32?  z: sum of 0 * output; least:
-// smallest |output|; largest: of the values this thread has split; terms: of one output.  `word` is LDS that held
-// 0 since before the last barrier.  scan(): whether the operands of the workgroup hold a tiny value, its threads
-// taking turns -- reached only where an output is next to nothing, for instance a row of zeros.
-template <class Scan>
-__device__ __forceinline__ bool needs_fp32(float z, float least, float largest, float terms, unsigned* word, Scan scan) {
-  const int lane = threadIdx.x & 63;
+// The end of a workgroup's tile.  largest: magnitude of the values this thread has split; returns that of the
+// workgroup's.  `word` is LDS that held 0 since before the last barrier.
+__device__ __forceinline__ float workgroup_largest(float largest, unsigned* word) {
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) largest = fmaxf(largest, __shfl_xor(largest, d));
-  if (lane == 0) atomicMax(word, __float_as_uint(largest));
+  if ((threadIdx.x & 63) == 0) atomicMax(word, __float_as_uint(largest));
   __syncthreads();
-  const bool small = __any(least < terms * kTiny * __uint_as_float(*word));
-  if (__syncthreads_or(small)) {
-    const bool found = __syncthreads_or(scan());
-    return __any(!(z == 0.f)) || (small && found);
-  }
-  return __any(!(z == 0.f));
+  return __uint_as_float(*word);
+}
+
+// bit r: is the word of an accumulator's output r of this lane not zero?  (rows of a 32 x 32 block, from the lane's on)
+__device__ __forceinline__ unsigned nonzero_bits(const unsigned* words) {
+  unsigned bits = 0;
+#pragma unroll 4
+  for (int r = 0; r < 16; ++r) bits |= (unsigned)(words[8 * (r / 4) + r % 4] != 0) << r;
+  return bits;
 }
 
 // buffer loads: base in scalar registers, so that a load takes no vector instruction for its address
