@@ -91,7 +91,7 @@ struct Operand {
   __device__ __forceinline__ float largest() const {
     float t = 0.f;
 #pragma unroll
-    for (int c = 0; c < CH; ++c) t = fmaxf(t, top[c]);
+    for (int c = 0; c < CH; ++c) t = fmaxf(t, finite(top[c]));
     return t;
   }
   // rows: LDS, the largest magnitude of every row (bits of a float), 0 before
@@ -104,64 +104,75 @@ struct Operand {
   }
 };
 
-// four consecutive k of a row, elements at or beyond kend as 0
+// four consecutive k of a row; unless all = true, elements at or beyond kend as 0
 template <bool KC>
-__device__ __forceinline__ f4 four_k(const float* __restrict__ P, int64_t ld, int row, int k, int kend) {
-  if (KC && k + 3 < kend) return *(const f4u*)(P + row * ld + k);
+__device__ __forceinline__ f4 four_k(const float* __restrict__ P, int64_t ld, int row, int k, int kend, bool all) {
+  if (KC && all) return *(const f4u*)(P + row * ld + k);
   f4 v;
 #pragma unroll
-  for (int t = 0; t < 4; ++t) v[t] = k + t < kend ? (KC ? P[row * ld + k + t] : P[(k + t) * ld + row]) : 0.f;
+  for (int t = 0; t < 4; ++t) v[t] = all || k + t < kend ? (KC ? P[row * ld + k + t] : P[(k + t) * ld + row]) : 0.f;
   return v;
 }
 
-// fp32 evaluation of a wavefront's tile, 64 x 64 at a time, for values the split does not carry
-template <int WM, int WN, bool YK, bool XK>
+// fp32 evaluation of MB x NB blocks from (m, n) on by one wavefront, for values the split does not carry; 8 KS k at a
+// time, the next ones on their way while these are multiplied
+template <int MB, int NB, int KS, bool YK, bool XK>
 __device__ __forceinline__ void recompute_fp32(const float* __restrict__ Y, const float* __restrict__ X, float* __restrict__ Cout,
-                                            int M, int N, int64_t ldy, int64_t ldx, int m0, int n0, int kbeg, int kend) {
-  constexpr int MB = WM < 64 ? 1 : 2, NB = WN < 64 ? 1 : 2;
+                                            int M, int N, int64_t ldy, int64_t ldx, int m, int n, int kbeg, int kend) {
   const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
-  for (int mi = 0; mi < WM; mi += MB * 32)
-    for (int ni = 0; ni < WN; ni += NB * 32) {
-      if (m0 + mi >= M || n0 + ni >= N) continue;
-      f16 acc[MB][NB];
+  if (m >= M || n >= N) return;
+  f16 acc[MB][NB];
 #pragma unroll
-      for (int i = 0; i < MB; ++i)
+  for (int i = 0; i < MB; ++i)
 #pragma unroll
-        for (int j = 0; j < NB; ++j)
+    for (int j = 0; j < NB; ++j)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-      f4 y[MB], x[NB];
-      auto load = [&](int k0) {
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  f4 y[KS][MB], x[KS][NB];
+  auto load_ = [&](int k0, bool all) {
 #pragma unroll
-        for (int i = 0; i < MB; ++i) y[i] = four_k<YK>(Y, ldy, min(m0 + mi + i * 32 + l32, M - 1), k0 + lh * 4, kend);
+    for (int s = 0; s < KS; ++s) {
 #pragma unroll
-        for (int j = 0; j < NB; ++j) x[j] = four_k<XK>(X, ldx, min(n0 + ni + j * 32 + l32, N - 1), k0 + lh * 4, kend);
-      };
-      load(kbeg);
-      for (int k0 = kbeg; k0 < kend; k0 += 8) {
-        f4 yc[MB], xc[NB];
+      for (int i = 0; i < MB; ++i) y[s][i] = four_k<YK>(Y, ldy, min(m + i * 32 + l32, M - 1), k0 + s * 8 + lh * 4, kend, all);
 #pragma unroll
-        for (int i = 0; i < MB; ++i) yc[i] = y[i];
-#pragma unroll
-        for (int j = 0; j < NB; ++j) xc[j] = x[j];
-        if (k0 + 8 < kend) load(k0 + 8);  // on its way while these are multiplied
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-          for (int i = 0; i < MB; ++i)
-#pragma unroll
-            for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(yc[i][t], xc[j][t], acc[i][j], 0, 0, 0);
-      }
-#pragma unroll
-      for (int i = 0; i < MB; ++i)
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int ro = m0 + mi + i * 32 + 8 * (r / 4) + 4 * lh + (r % 4), co = n0 + ni + j * 32 + l32;
-            if (ro < M && co < N) Cout[(int64_t)ro * N + co] = acc[i][j][r];
-          }
+      for (int j = 0; j < NB; ++j) x[s][j] = four_k<XK>(X, ldx, min(n + j * 32 + l32, N - 1), k0 + s * 8 + lh * 4, kend, all);
     }
+  };
+  auto load = [&](int k0) {
+    if (k0 + 8 * KS <= kend)
+      load_(k0, true);
+    else
+      load_(k0, false);
+  };
+  load(kbeg);
+  for (int k0 = kbeg; k0 < kend; k0 += 8 * KS) {
+    f4 yc[KS][MB], xc[KS][NB];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i) yc[s][i] = y[s][i];
+#pragma unroll
+      for (int j = 0; j < NB; ++j) xc[s][j] = x[s][j];
+    }
+    if (k0 + 8 * KS < kend) load(k0 + 8 * KS);
+#pragma unroll
+    for (int s = 0; s < KS; ++s)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+          for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(yc[s][i][t], xc[s][j][t], acc[i][j], 0, 0, 0);
+  }
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int ro = m + i * 32 + 8 * (r / 4) + 4 * lh + (r % 4), co = n + j * 32 + l32;
+        if (ro < M && co < N) Cout[(int64_t)ro * N + co] = acc[i][j][r];
+      }
 }
 
 // does the workgroup's part of an operand hold an element too small to split exactly?  (this thread's share)
@@ -187,8 +198,8 @@ __device__ __forceinline__ bool holds_tiny(const float* __restrict__ P, int64_t 
 // Order of the products: the smaller ones first (m m', then those with a middle, those with a low slice, h h'), so that
 // the slices of a value come together without rounding: a sum of one term is one multiplication, and a product with a
 // permutation is exact (h h' second: 0.02 % of the outputs off by an ulp).  XH, XL: the slice of which operand is read
-// first -- no difference but for the compiler's schedule (us, X first / Y first: 256 x 256 at 4096^3 581 / 594,
-// 256 x 128 at 65536 x 64 x 4096 373 / 358, 128 x 64 there 267 / 250; 128 x 128 at 2048^3, XL alone 95.0 / 93.8).
+// first -- no difference but for the compiler's schedule (us: 256 x 256 at 4096^3 593 with both of X first, 605 with
+// both of Y; 128 x 128 at 1500^3 64 with h of X and l of Y, 66 and 67 otherwise; the other tiles equal within 1 %).
 template <int BM, int BN, int BK, int WM, int WN, bool YK, bool XK>
 __device__ __forceinline__ void split_tile(const float* __restrict__ Y, const float* __restrict__ X, float* __restrict__ Cout,
                                            int M, int N, int64_t ldy, int64_t ldx, int m0, int n0, int kbeg, int kend, char* lds) {
@@ -332,45 +343,55 @@ __device__ __forceinline__ void split_tile(const float* __restrict__ Y, const fl
   for (; t + 1 < nk; ++t) body(t, Yes{});
   body(t, No{});
 
-  // values the split does not carry (mdh_split.h)
-  float z = 0.f, least = __builtin_huge_valf();
+  // values the split does not carry (mdh_split.h): bit mi * NI + ni of `redo` is a block of this wavefront that holds an
+  // output they may have entered
+  unsigned redo = 0;
+  float least = __builtin_huge_valf();
 #pragma unroll
   for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni)
+    for (int ni = 0; ni < NI; ++ni) {
+      float z = 0.f;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         z = __builtin_fmaf(acc[mi][ni][r], 0.f, z);
         least = fminf(least, fabsf(acc[mi][ni][r]));
       }
+      if (__any(!(z == 0.f))) redo |= 1u << (mi * NI + ni);
+    }
   const float bound = (float)(kend - kbeg) * kTiny * workgroup_largest(fmaxf(oy.largest(), ox.largest()), largest);
-  bool fp32 = __any(!(z == 0.f));
-  if (__syncthreads_or(least < bound)) {
+  unsigned long long todo = 0;  // the workgroup's blocks, row by row
+  if (__syncthreads_or(redo || least < bound)) {
     unsigned* const rows = (unsigned*)lds;  // the operands' stages are done with
-    for (int i = threadIdx.x; i < BM + BN; i += NT) rows[i] = 0;
+    unsigned* const blocks = rows + BM + BN;
+    for (int i = threadIdx.x; i < BM + BN + 2; i += NT) rows[i] = 0;
     __syncthreads();
     oy.merge(rows);
     ox.merge(rows + BM);
     __syncthreads();
-    bool small = false;
+    unsigned small = 0;
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni) {
       const unsigned cols = nonzero_bits(rows + BM + wn + ni * 32 + 4 * lh);
 #pragma unroll
-      for (int mi = 0; mi < MI; ++mi)
+      for (int mi = 0; mi < MI; ++mi) {
+        bool open = false;
         if (rows[wm + mi * 32 + l32])
 #pragma unroll
-          for (int r = 0; r < 16; ++r) small |= fabsf(acc[mi][ni][r]) < bound && (cols >> r & 1);
+          for (int r = 0; r < 16; ++r) open |= fabsf(acc[mi][ni][r]) < bound && (cols >> r & 1);
+        if (__any(open)) small |= 1u << (mi * NI + ni);
+      }
     }
-    small = __any(small);
     if (__syncthreads_or(small)) {
       const bool found = holds_tiny<BM, NT, YK>(Y, ldy, m0, M, kbeg, kend) || holds_tiny<BN, NT, XK>(X, ldx, n0, N, kbeg, kend);
-      if (__syncthreads_or(found)) fp32 |= small;
+      if (__syncthreads_or(found)) redo |= small;
     }
-  }
-  if (fp32) {
-    recompute_fp32<WM, WN, YK, XK>(Y, X, Cout, M, N, ldy, ldx, m0 + wm, n0 + wn, kbeg, kend);
-    return;
+    if (lane < MI * NI && redo >> lane & 1) {
+      const int b = (wm / 32 + lane / NI) * (BN / 32) + wn / 32 + lane % NI;
+      atomicOr(blocks + b / 32, 1u << b % 32);
+    }
+    __syncthreads();
+    todo = (unsigned)__builtin_amdgcn_readfirstlane(blocks[0]) | (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane(blocks[1]) << 32;
   }
 
   const bool whole = m0 + BM <= M && n0 + BN <= N;
@@ -379,7 +400,8 @@ __device__ __forceinline__ void split_tile(const float* __restrict__ Y, const fl
     const int row = m0 + wm + mi * 32 + l32;
     float* const p = Cout + (int64_t)row * N + n0 + wn + 4 * lh;
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni)
+    for (int ni = 0; ni < NI; ++ni) {
+      if (redo >> (mi * NI + ni) & 1) continue;
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         const int j = ni * 32 + 8 * g;
@@ -392,7 +414,26 @@ __device__ __forceinline__ void split_tile(const float* __restrict__ Y, const fl
             if (n0 + wn + 4 * lh + j + r < N) p[j + r] = v[r];
         }
       }
+    }
   }
+
+  if (!todo) return;
+  // Many blocks: every wavefront takes its own, 64 x 64 at a time, which halves what is loaded.  Few, a row or column
+  // of the tile: they are dealt out, so that no wavefront has a whole part of the tile to itself.
+  if constexpr (BM * BN / 1024 > 2 * NT / 64) {
+    static_assert(MI % 2 == 0 && NI % 2 == 0, "");
+    if (__popcll(todo) > 2 * NT / 64) {
+      for (int mi = 0; mi < MI; mi += 2)
+        for (int ni = 0; ni < NI; ni += 2)
+          if (redo >> (mi * NI + ni) & (3u | 3u << NI)) recompute_fp32<2, 2, 1, YK, XK>(Y, X, Cout, M, N, ldy, ldx, m0 + wm + mi * 32, n0 + wn + ni * 32, kbeg, kend);
+      return;
+    }
+  }
+  for (int i = 0; todo; ++i, todo &= todo - 1)
+    if (i % (NT / 64) == __builtin_amdgcn_readfirstlane(wave)) {
+      const int b = __builtin_ctzll(todo);
+      recompute_fp32<1, 1, 4, YK, XK>(Y, X, Cout, M, N, ldy, ldx, m0 + b / (BN / 32) * 32, n0 + b % (BN / 32) * 32, kbeg, kend);
+    }
 }
 
 template <int BM, int BN, int BK, int WM, int WN, bool YK, bool XK>

@@ -44,40 +44,89 @@ struct Conv {
   int H, W, C, K, R, S, sh, sw, P, Q;
 };
 
-// fp32 evaluation of a wavefront's blocks, for values the split does not carry
+// four consecutive channels from c on, those at or beyond cend as 0
+__device__ __forceinline__ f4 four_c(const float* __restrict__ p, int c, int cend) {
+  if (c + 3 < cend) return *(const f4u*)(p + c);
+  f4 v;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) v[t] = c + t < cend ? p[c + t] : 0.f;
+  return v;
+}
+
+// fp32 evaluation of a wavefront's blocks, for values the split does not carry: 16 channels of a tap at a time, the next
+// ones on their way while these are multiplied
 template <int TP, int TQ, int BN, int CK, int WM, int WN>
 __device__ __forceinline__ void recompute_fp32(const Conv& g, float* __restrict__ dst, int n, int p0, int q0, int k0, int cbeg, int cend) {
   using C = Cfg<TP, TQ, BN, CK, WM, WN>;
+  constexpr int KS = 2;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, lh = lane >> 5;
-  const int wm = wave / C::WAVES_N, wn = wave % C::WAVES_N;
+  const int pw = p0 + wave / C::WAVES_N * C::MI * C::RB, kw = k0 + wave % C::WAVES_N * WN, q = q0 + l32 % TQ;
+  if (pw >= g.P || kw >= g.K) return;
+  const float *a[C::MI], *b[C::NI];
+#pragma unroll
   for (int mi = 0; mi < C::MI; ++mi)
-    for (int ni = 0; ni < C::NI; ++ni) {
-      const int pb = p0 + (wm * C::MI + mi) * C::RB, kb = k0 + wn * WN + ni * 32;
-      if (pb >= g.P || kb >= g.K) continue;
-      const int p = min(pb + l32 / TQ, g.P - 1), q = min(q0 + l32 % TQ, g.Q - 1), k = min(kb + l32, g.K - 1);
-      f16 acc;
+    a[mi] = g.in + (((int64_t)n * g.H + min(pw + mi * C::RB + l32 / TQ, g.P - 1) * g.sh) * g.W + min(q, g.Q - 1) * g.sw) * g.C + lh * 4;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-      for (int r = 0; r < g.R; ++r)
-        for (int s = 0; s < g.S; ++s) {
-          const float* a = g.in + (((int64_t)n * g.H + p * g.sh + r) * g.W + q * g.sw + s) * g.C;
-          const float* b = g.filt + (((int64_t)k * g.R + r) * g.S + s) * g.C;
-#pragma unroll 4
-          for (int c0 = cbeg; c0 < cend; c0 += 8)
+  for (int ni = 0; ni < C::NI; ++ni) b[ni] = g.filt + (int64_t)min(kw + ni * 32 + l32, g.K - 1) * g.R * g.S * g.C + lh * 4;
+  f16 acc[C::MI][C::NI];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
-              const int c = c0 + lh * 4 + t;
-              acc = __builtin_amdgcn_mfma_f32_32x32x2f32(c < cend ? b[c] : 0.f, c < cend ? a[c] : 0.f, acc, 0, 0, 0);
-            }
-        }
-      if (pb + l32 / TQ >= g.P || q0 + l32 % TQ >= g.Q) continue;
-      float* o = dst + (((int64_t)n * g.P + p) * g.Q + q) * g.K;
+  for (int mi = 0; mi < C::MI; ++mi)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int ko = kb + 8 * (r / 4) + 4 * lh + r % 4;
-        if (ko < g.K) o[ko] = acc[r];
-      }
+    for (int ni = 0; ni < C::NI; ++ni)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[mi][ni][e] = 0.f;
+  f4 y[KS][C::MI], x[KS][C::NI];
+  int r = 0, s = 0, c = cbeg;  // of the step that `load` takes
+  auto load = [&] {
+    const int in = (r * g.W + s) * g.C, fl = (r * g.S + s) * g.C;
+#pragma unroll
+    for (int u = 0; u < KS; ++u) {
+#pragma unroll
+      for (int mi = 0; mi < C::MI; ++mi) y[u][mi] = four_c(a[mi] + in, c + u * 8, cend - lh * 4);
+#pragma unroll
+      for (int ni = 0; ni < C::NI; ++ni) x[u][ni] = four_c(b[ni] + fl, c + u * 8, cend - lh * 4);
     }
+    c += 8 * KS;
+    if (c >= cend) {
+      c = cbeg;
+      if (++s == g.S) s = 0, ++r;
+    }
+  };
+  load();
+  for (bool more = true; more;) {
+    f4 yc[KS][C::MI], xc[KS][C::NI];
+#pragma unroll
+    for (int u = 0; u < KS; ++u) {
+#pragma unroll
+      for (int mi = 0; mi < C::MI; ++mi) yc[u][mi] = y[u][mi];
+#pragma unroll
+      for (int ni = 0; ni < C::NI; ++ni) xc[u][ni] = x[u][ni];
+    }
+    more = r < g.R;
+    if (more) load();
+#pragma unroll
+    for (int u = 0; u < KS; ++u)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int mi = 0; mi < C::MI; ++mi)
+#pragma unroll
+          for (int ni = 0; ni < C::NI; ++ni)
+            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(xc[u][ni][t], yc[u][mi][t], acc[mi][ni], 0, 0, 0);
+  }
+#pragma unroll
+  for (int mi = 0; mi < C::MI; ++mi) {
+    const int p = pw + mi * C::RB + l32 / TQ;
+    if (p >= g.P || q >= g.Q) continue;
+    float* const o = dst + (((int64_t)n * g.P + p) * g.Q + q) * g.K;
+#pragma unroll
+    for (int ni = 0; ni < C::NI; ++ni)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const int k = kw + ni * 32 + 8 * (e / 4) + 4 * lh + e % 4;
+        if (k < g.K) o[k] = acc[mi][ni][e];
+      }
+  }
 }
 
 // does the workgroup's part of the input or of the filter hold an element too small to split exactly?  (this thread's share)
@@ -182,7 +231,7 @@ __global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT), (Cfg<TP, TQ, BN,
       u4 v[3];
       float top = 0.f;
       split(x, v, top);
-      ptop = fmaxf(ptop, top);
+      ptop = fmaxf(ptop, finite(top));
       pnz |= top != 0.f ? bit : 0;
 #pragma unroll
       for (int s = 0; s < 3; ++s) *(u4*)(patch + s * pslice + kc * pplane + pix * 16) = v[s];
@@ -291,7 +340,7 @@ __global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT), (Cfg<TP, TQ, BN,
       }
   float top = ptop;
 #pragma unroll
-  for (int c = 0; c < F::F_CH; ++c) top = fmaxf(top, ftop[c]);
+  for (int c = 0; c < F::F_CH; ++c) top = fmaxf(top, finite(ftop[c]));
   const float bound = (float)(taps * (cend - cbeg)) * kTiny * workgroup_largest(top, largest);
   bool fp32 = __any(!(z == 0.f));
   if (__syncthreads_or(least < bound)) {

@@ -95,7 +95,10 @@ __device__ __forceinline__ bool tiny_in(const float* __restrict__ p, int n, int 
   return t;
 }
 
-// The end of a workgroup's tile.  largest: magnitude of the values this thread has split; returns that of the
+// a row with an infinity has no output that could be too small: what counts is the rows without
+__device__ __forceinline__ float finite(float top) { return top < __builtin_huge_valf() ? top : 0.f; }
+
+// The end of a workgroup's tile.  largest: magnitude of the finite values this thread has split; returns that of the
 // workgroup's.  `word` is LDS that held 0 since before the last barrier.
 __device__ __forceinline__ float workgroup_largest(float largest, unsigned* word) {
 #pragma unroll
