@@ -163,7 +163,7 @@ __global__ __launch_bounds__(WA* WB * 64) void prl_kernel(
 // of compare + maximum + select per record; which record of the winning block scored the maximum is
 // found once at the end by scoring that block again.  Everything stays exact under these conditions,
 // which the kernel checks itself: field values in [0, 2^23) (the records of A up front, those of B as
-// they stream by, after every 512: from the run of 512 that holds a value outside, the integer loop goes on),
+// they stream by, after every 64: from the run of 64 that holds a value outside, the integer loop goes on),
 // sum_f max(|w_agree_f|, |w_disagree_f|) < 2^24 and every |w_disagree_f - w_agree_f| <= 2^24 (all partial sums, and
 // what a field that differs adds, are then integers fp32 holds exactly).
 // The result is the unique (score, index) of the definition, bit for bit, on either path.
@@ -232,7 +232,7 @@ __global__ __launch_bounds__(WA* WB * 64) void prl_fast_kernel(
     const float vbase = agree_sum + __uint_as_float(__float_as_uint(0.f) | (lane & 0));  // a vector register
 
     while (done < b1) {
-      const int end = run_end(done, b1);
+      const int end = run_end(done, b0, b1);
       float fbefore[RA];
       int before[RA];
 #pragma unroll
@@ -333,11 +333,21 @@ __global__ __launch_bounds__(WA* WB * 64) void prl_fast_kernel(
 #pragma unroll
       for (int f = 0; f < NF; ++f) ar[ra][f] = A[(int64_t)a * NF + f];
     }
+    // From nine fields on the next record is on its way meanwhile: the registers leave fewer wavefronts to cover the load
+    // (2^14 x 2^17 records of 16 fields: 3030 / 2940 us; of one field, 2^13 x 2^15: 56 / 66).
+    constexpr bool kAhead = NF > 8;
+    int next[NF];
+    if (kAhead)
+#pragma unroll
+      for (int f = 0; f < NF; ++f) next[f] = B[(int64_t)done * NF + f];
     for (int b = done; b < b1; ++b) {
       int br[NF];
-      const int* rb = B + (int64_t)b * NF;
+      const int* rb = B + (int64_t)(kAhead && b + 1 < b1 ? b + 1 : b) * NF;
 #pragma unroll
-      for (int f = 0; f < NF; ++f) br[f] = rb[f];
+      for (int f = 0; f < NF; ++f) {
+        br[f] = kAhead ? next[f] : rb[f];
+        if (kAhead) next[f] = rb[f];
+      }
 #pragma unroll
       for (int ra = 0; ra < RA; ++ra) {
         unsigned sc = base;

@@ -16,7 +16,7 @@ WALK = r"""
 extern "C" long long walk(int b0, int b1) {
   long long taken = 0;
   for (int done = b0; done < b1;) {
-    const int end = mdh::run_end(done, b1);
+    const int end = mdh::run_end(done, b0, b1);
     if (end <= done || end > b1) return -1;
     for (long long bb = done; bb < end; bb += 4) {
       if (bb + 4 > 0x7fffffffll) return -1;
@@ -43,7 +43,7 @@ def test_bounds_of_the_walk(tmp_path):
         for part in (0, 1, 1022, 1023):
             b0, b1 = min(part * chunk, nB), min((part + 1) * chunk, nB)
             assert L.walk(b0, b1) == b1 - b0, (nB, part)
-    for n in (1, 3, 4, 511, 512, 513, 1023, 1024, 1025):
+    for n in (1, 3, 4, 31, 32, 33, 95, 96, 97, 511, 512, 513, 1025):
         assert L.walk(most - n, most) == n
         assert L.walk(7, 7 + n) == n
 
