@@ -96,3 +96,11 @@ def test_convolutions_of_one_term():
         out.fill_(float("nan"))
         mdh.mdh_mcc(pixel, f, out, (1, 1), p, ws)
         assert torch.equal(out, want), p and p.table()
+        # one tap of one channel per output channel: a multiplication each
+        for r, s in ((0, 0), (1, 2), (2, 1)):
+            one = torch.zeros_like(f)
+            one[torch.arange(C), r, s, perm] = f[torch.arange(C), r, s, perm]
+            ref = x[:, r : r + P, s : s + Q][..., perm].double() * f[torch.arange(C), r, s, perm].double()
+            out.fill_(float("nan"))
+            mdh.mdh_mcc(x, one, out, (1, 1), p, ws)
+            assert float(((out.double() - ref).abs() / ref.abs().clamp(min=2.0**-100)).max()) <= ONE_TERM, p and p.table()
