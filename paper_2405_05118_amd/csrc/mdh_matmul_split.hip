@@ -175,10 +175,22 @@ __device__ __forceinline__ void recompute_fp32(const float* __restrict__ Y, cons
       }
 }
 
-// does the workgroup's part of an operand hold an element too small to split exactly?  (this thread's share)
+// does the workgroup's part of an operand, or of its listed rows where they are few, hold an element too small to split
+// exactly?  (this thread's share)
 template <int ROWS, int NT, bool KC>
-__device__ __forceinline__ bool holds_tiny(const float* __restrict__ P, int64_t ld, int r0, int rmax, int kbeg, int kend) {
+__device__ __forceinline__ bool holds_tiny(const float* __restrict__ P, int64_t ld, int r0, int rmax, int kbeg, int kend, const Marks& m) {
   bool t = false;
+  const unsigned n = *m.count;
+  if (n <= Marks::kFew) {
+    for (unsigned i = 0; i < n; ++i) {
+      const int r = min(r0 + m.list[i], rmax - 1);
+      if (KC)
+        t |= tiny_in(P + r * ld + kbeg, kend - kbeg, threadIdx.x, NT);
+      else
+        for (int k = kbeg + threadIdx.x; k < kend; k += NT) t |= tiny(P[k * ld + r]);
+    }
+    return t;
+  }
   const int rows = min(ROWS, rmax - r0);
   constexpr int W = 16;  // threads per contiguous run
   if (KC) {
@@ -364,7 +376,9 @@ __device__ __forceinline__ void split_tile(const float* __restrict__ Y, const fl
   if (__syncthreads_or(redo || least < bound)) {
     unsigned* const rows = (unsigned*)lds;  // the operands' stages are done with
     unsigned* const blocks = rows + BM + BN;
-    for (int i = threadIdx.x; i < BM + BN + 2; i += NT) rows[i] = 0;
+    const Marks ym(blocks + 2, BM), xm(blocks + 2 + Marks::words(BM), BN);
+    static_assert((BM + BN + 2 + Marks::words(BM) + Marks::words(BN)) * 4 <= 2 * STAGE, "");
+    for (int i = threadIdx.x; i < BM + BN + 2 + Marks::words(BM) + Marks::words(BN); i += NT) rows[i] = 0;
     __syncthreads();
     oy.merge(rows);
     ox.merge(rows + BM);
@@ -375,15 +389,22 @@ __device__ __forceinline__ void split_tile(const float* __restrict__ Y, const fl
       const unsigned cols = nonzero_bits(rows + BM + wn + ni * 32 + 4 * lh);
 #pragma unroll
       for (int mi = 0; mi < MI; ++mi) {
-        bool open = false;
+        unsigned open = 0;  // the block's outputs of this lane
         if (rows[wm + mi * 32 + l32])
 #pragma unroll
-          for (int r = 0; r < 16; ++r) open |= fabsf(acc[mi][ni][r]) < bound && (cols >> r & 1);
-        if (__any(open)) small |= 1u << (mi * NI + ni);
+          for (int r = 0; r < 16; ++r) open |= (unsigned)(fabsf(acc[mi][ni][r]) < bound) << r;
+        open &= cols;
+        if (!__any(open)) continue;
+        small |= 1u << (mi * NI + ni);
+        if (open) ym.add(wm + mi * 32 + l32);
+        for (; open; open &= open - 1) {
+          const int r = __builtin_ctz(open);
+          xm.add(wn + ni * 32 + 8 * (r / 4) + 4 * lh + r % 4);
+        }
       }
     }
     if (__syncthreads_or(small)) {
-      const bool found = holds_tiny<BM, NT, YK>(Y, ldy, m0, M, kbeg, kend) || holds_tiny<BN, NT, XK>(X, ldx, n0, N, kbeg, kend);
+      const bool found = holds_tiny<BM, NT, YK>(Y, ldy, m0, M, kbeg, kend, ym) || holds_tiny<BN, NT, XK>(X, ldx, n0, N, kbeg, kend, xm);
       if (__syncthreads_or(found)) redo |= small;
     }
     if (lane < MI * NI && redo >> lane & 1) {
@@ -436,8 +457,10 @@ __device__ __forceinline__ void split_tile(const float* __restrict__ Y, const fl
     }
 }
 
+// (second launch bound: the wavefronts of a SIMD that LDS has room for, so that the fp32 evaluation, whose registers
+// would allow fewer, does not come into it)
 template <int BM, int BN, int BK, int WM, int WN, bool YK, bool XK>
-__global__ __launch_bounds__(((BM / WM) * (BN / WN) * 64)) void matmul_split_kernel(
+__global__ __launch_bounds__(((BM / WM) * (BN / WN) * 64), (BM + BN > 128 ? 2 : 3)) void matmul_split_kernel(
     const float* __restrict__ Y, const float* __restrict__ X, float* __restrict__ C, float* __restrict__ ws, int M, int N,
     int K, int tiles_m, int tiles_n, int S, int kchunk, int nbatch, int jmajor) {
   extern __shared__ __attribute__((aligned(16))) char lds[];

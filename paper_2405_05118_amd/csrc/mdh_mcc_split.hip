@@ -129,17 +129,38 @@ __device__ __forceinline__ void recompute_fp32(const Conv& g, float* __restrict_
   }
 }
 
-// does the workgroup's part of the input or of the filter hold an element too small to split exactly?  (this thread's share)
-template <int NT>
-__device__ __forceinline__ bool holds_tiny(const Conv& g, int n, int h0, int nh, int w0, int nw, int k0, int nk, int cbeg, int cend) {
+// does one of `runs` runs of nc channels, run i at p + at(i), hold an element too small to split exactly?  (this thread's
+// share)
+template <int NT, class At>
+__device__ __forceinline__ bool tiny_runs(const float* __restrict__ p, int runs, int nc, At at) {
   bool t = false;
-  constexpr int W = 4;  // threads per contiguous run of channels
-  const int part = threadIdx.x % W, nc = cend - cbeg;
-  nh = min(nh, g.H - h0), nw = min(nw, g.W - w0), nk = min(nk, g.K - k0);
-  for (int i = threadIdx.x / W; i < nh * nw; i += NT / W)
-    t |= tiny_in(g.in + (((int64_t)n * g.H + h0 + i / nw) * g.W + w0 + i % nw) * g.C + cbeg, nc, part, W);
-  for (int i = threadIdx.x / W; i < nk * g.R * g.S; i += NT / W)
-    t |= tiny_in(g.filt + ((int64_t)k0 * g.R * g.S + i) * g.C + cbeg, nc, part, W);
+  constexpr int W = 16;  // threads per run
+  for (int i = threadIdx.x / W; i < runs; i += NT / W) t |= tiny_in(p + at(i), nc, threadIdx.x % W, W);
+  return t;
+}
+
+// does the workgroup's part of the input and of the filter -- of the windows and output channels that are listed, where
+// they are few -- hold an element too small to split exactly?  (this thread's share)
+template <int NT, int TQ>
+__device__ __forceinline__ bool holds_tiny(const Conv& g, int n, int p0, int q0, int PH, int PW, int k0, int BN, int cbeg, int cend,
+                                           const Marks& pm, const Marks& fm) {
+  bool t = false;
+  const int nc = cend - cbeg, h0 = p0 * g.sh, w0 = q0 * g.sw, taps = g.R * g.S;
+  const int nh = min(PH, g.H - h0), nw = min(PW, g.W - w0);
+  const float* const in = g.in + (((int64_t)n * g.H + h0) * g.W + w0) * g.C + cbeg;
+  if (*pm.count <= Marks::kFew)
+    for (unsigned i = 0; i < *pm.count; ++i) {
+      const int first = pm.list[i] / TQ * g.sh * g.W + pm.list[i] % TQ * g.sw;
+      t |= tiny_runs<NT>(in, taps, nc, [&](int r) { return (int64_t)(first + r / g.S * g.W + r % g.S) * g.C; });
+    }
+  else
+    t |= tiny_runs<NT>(in, nh * nw, nc, [&](int i) { return (int64_t)(i / nw * g.W + i % nw) * g.C; });
+  const float* const f = g.filt + (int64_t)k0 * taps * g.C + cbeg;
+  if (*fm.count <= Marks::kFew)
+    for (unsigned i = 0; i < *fm.count; ++i)
+      t |= tiny_runs<NT>(f + (int64_t)fm.list[i] * taps * g.C, taps, nc, [&](int r) { return (int64_t)r * g.C; });
+  else
+    t |= tiny_runs<NT>(f, min(BN, g.K - k0) * taps, nc, [&](int i) { return (int64_t)i * g.C; });
   return t;
 }
 
@@ -348,27 +369,27 @@ __global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT), (Cfg<TP, TQ, BN,
     // pixel of the patch is not all zeros
     unsigned* const filters = (unsigned*)lds;
     unsigned* const pixels = filters + BN;
-    for (int i = tid; i < BN + npix; i += F::NT) filters[i] = 0;
+    const Marks pm(pixels + npix, TP * TQ), fm(pixels + npix + Marks::words(TP * TQ), BN);
+    static_assert((BN + Marks::words(TP * TQ) + Marks::words(BN)) * 4 <= 2 * F::F_STAGE, "");  // and 4 bytes a pixel in the patch
+    for (int i = tid; i < BN + npix + Marks::words(TP * TQ) + Marks::words(BN); i += F::NT) filters[i] = 0;
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < F::F_CH; ++c) atomicMax(filters + (tid + c * F::NT) % F::F_CHUNKS / F::KP, __float_as_uint(ftop[c]));
     __syncthreads();
-    unsigned small[F::MI];  // of the block's pixel of this lane
-#pragma unroll
-    for (int mi = 0; mi < F::MI; ++mi) small[mi] = 0;
+    unsigned small[F::MI][F::NI];  // the block's outputs of this lane
+    bool open = false;
 #pragma unroll
     for (int ni = 0; ni < F::NI; ++ni) {
       const unsigned live = nonzero_bits(filters + wn * WN + ni * 32 + 4 * lh);
 #pragma unroll
-      for (int mi = 0; mi < F::MI; ++mi)
+      for (int mi = 0; mi < F::MI; ++mi) {
+        unsigned bits = 0;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) small[mi] |= fabsf(acc[mi][ni][r]) < bound ? live >> r & 1 : 0;
-    }
-    bool open = false;
-#pragma unroll
-    for (int mi = 0; mi < F::MI; ++mi) {
-      if (p0 + (wm * F::MI + mi) * F::RB + l32 / TQ >= g.P || q0 + l32 % TQ >= g.Q) small[mi] = 0;
-      open |= small[mi] != 0;
+        for (int r = 0; r < 16; ++r) bits |= (unsigned)(fabsf(acc[mi][ni][r]) < bound) << r;
+        const bool stored = p0 + (wm * F::MI + mi) * F::RB + l32 / TQ < g.P && q0 + l32 % TQ < g.Q;
+        small[mi][ni] = stored ? bits & live : 0;
+        open |= small[mi][ni] != 0;
+      }
     }
     if (__syncthreads_or(open)) {
       for (int i = 0; tid + i * F::NT < npix * F::KP; ++i)
@@ -376,13 +397,26 @@ __global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT), (Cfg<TP, TQ, BN,
       __syncthreads();
       open = false;
 #pragma unroll
-      for (int mi = 0; mi < F::MI; ++mi)
-        if (small[mi])
+      for (int mi = 0; mi < F::MI; ++mi) {
+        unsigned any = 0, window = 0;
+#pragma unroll
+        for (int ni = 0; ni < F::NI; ++ni) any |= small[mi][ni];
+        if (any)
           for (int r = 0; r < g.R; ++r)
-            for (int s = 0; s < g.S; ++s) open |= pixels[pix0 + (mi * F::RB * g.sh + r) * PW + s] != 0;
+            for (int s = 0; s < g.S; ++s) window |= pixels[pix0 + (mi * F::RB * g.sh + r) * PW + s];
+        if (!window) continue;
+        open = true;
+        pm.add(((wm * F::MI + mi) * F::RB + l32 / TQ) * TQ + l32 % TQ);
+#pragma unroll
+        for (int ni = 0; ni < F::NI; ++ni)
+          for (unsigned bits = small[mi][ni]; bits; bits &= bits - 1) {
+            const int r = __builtin_ctz(bits), k = wn * WN + ni * 32 + 8 * (r / 4) + 4 * lh + r % 4;
+            if (k0 + k < g.K) fm.add(k);
+          }
+      }
       open = __any(open);
       if (__syncthreads_or(open)) {
-        const bool found = holds_tiny<F::NT>(g, n, p0 * g.sh, PH, q0 * g.sw, PW, k0, BN, cbeg, cend);
+        const bool found = holds_tiny<F::NT, TQ>(g, n, p0, q0, PH, PW, k0, BN, cbeg, cend, pm, fm);
         if (__syncthreads_or(found)) fp32 |= open;
       }
     }

@@ -18,7 +18,7 @@
 //     not finite, so the outputs tell;
 //   - |x| < 2^-100: its last slices may be lost to subnormal numbers, up to 2^-126.  That can matter only for an
 //     output smaller than K * 2^-100 * (largest |x| of its tile), and only if such an element is there; both are
-//     checked.  An output whose row or column is all zeros -- padding, a dead filter -- is small and exact: the largest
+//     checked, in the output's own row and column.  An output whose row or column is all zeros -- padding, a dead filter -- is small and exact: the largest
 //     magnitude of every row, kept as the values are split, tells without reading the operands again.
 #pragma once
 #include "mdh_internal.h"
@@ -115,6 +115,22 @@ __device__ __forceinline__ unsigned nonzero_bits(const unsigned* words) {
   for (int r = 0; r < 16; ++r) bits |= (unsigned)(words[8 * (r / 4) + r % 4] != 0) << r;
   return bits;
 }
+
+// Rows (columns, pixels, output channels) that hold an output the split may not carry, in LDS that was 0: marked by any
+// thread, each listed once.  An output depends on its own row and column only, so where few are listed -- a sum that
+// came out zero by chance: 16 x 1024^3 random products hold about one -- those are read again, not the operands.
+struct Marks {
+  static constexpr unsigned kFew = 16;
+  unsigned *count, *mark;
+  unsigned short* list;
+  static __host__ __device__ constexpr int words(int n) { return 1 + n + kFew / 2; }
+  __device__ __forceinline__ Marks(unsigned* p, int n) : count(p), mark(p + 1), list((unsigned short*)(p + 1 + n)) {}
+  __device__ __forceinline__ void add(int i) const {
+    if (mark[i] || atomicExch(mark + i, 1u)) return;
+    const unsigned at = atomicAdd(count, 1u);
+    if (at < kFew) list[at] = (unsigned short)i;
+  }
+};
 
 // buffer loads: base in scalar registers, so that a load takes no vector instruction for its address
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const float* p) {
