@@ -34,7 +34,7 @@ struct GemmPlan {
   // rows, i fastest inside a band (order (WG,i),(WG,j),(WG,k)); 1 = bands of 8 tile columns, j fastest
   // (order (WG,j),(WG,i),(WG,k)).  Decides which panels of A and B the tiles resident together share.
   int jmajor = 0;
-  // 1: the kernel that carries every value as three bf16 values (blk = 16 x 16 x 32; BK = 32)
+  // 1: the kernel that carries every value as three bf16 values (blk = 32 x 32 x 16; BK = 16 or 32 by tile)
   int split = 0;
 };
 

@@ -12,15 +12,17 @@
 // lane is one ds_read_b128, and 32 lanes read 512 contiguous bytes.  Rows are swizzled inside groups of eight so that
 // the writes of a k-contiguous operand (BK/8 lanes per row) spread over the banks too (no bank conflicts counted).
 //
-// What bounds it.  Large products: power.  4096^3 runs at 1.9 GHz, and leaving single parts of the work out takes off
-// (256 x 128 tiles, of 738 us) loads 187, LDS reads 159, the split 110, LDS writes 55, and MFMAs alone are 417 us:
-// the parts add up instead of overlapping.  So what counts is bytes and instructions per product, and the largest
-// tile wins: 256 x 256 564 us, 256 x 128 612, 128 x 128 688, 64 x 64 858 (fp32 instructions: 1003).  The 256 x 256
-// tile has k-tiles of 16, because two of 32 (192 KB) exceed LDS.  32x32x16 against 16x16x32 MFMAs: 4096^3 equal
-// (726 / 717), 1024^3 in 128 x 128 tiles 48.8 / 55.2 -- the smaller one leaves room for one vector instruction
-// beside it, the larger for four.  128 x 128 tiles take eight wavefronts of 32 x 64 rather than four of 64 x 64
-// (2048^3 99.6 / 107 us, 4096^3 776 / 819): with one wavefront per SIMD nothing covers its waits.  Two or three
-// k-tiles on their way instead of one, and another first k-tile per workgroup for tall operands: no difference.
+// What bounds it.  Large products: power.  4096^3 runs at 1.9 GHz, and leaving single parts of the work out took off
+// (256 x 128 tiles, when they took 738 us, before the buffer loads) loads 187, LDS reads 159, the split 110, LDS writes
+// 55, and MFMAs alone were 417 us: the parts add up instead of overlapping.  So what counts is bytes and instructions per
+// product, and the largest tile wins: 4096^3 256 x 256 588 us, 256 x 128 646, 128 x 128 710, 128 x 64 794, 64 x 64 879
+// (fp32 instructions: 1010-1070); where that leaves compute units idle, smaller ones: 2048^3 237, 140, 94, 110, 126
+// (145).  The 256 x 256 tile has k-tiles of 16, because two of 32 (192 KB) exceed LDS.  Measured when they were chosen:
+// 16x16x32 MFMAs equal at 4096^3 (717 / 726), slower at 1024^3 in 128 x 128 tiles (55.2 / 48.8) -- the smaller one
+// leaves room for one vector instruction beside it, the larger for four; 128 x 128 tiles on eight wavefronts of 32 x 64
+// rather than four of 64 x 64 (2048^3 99.6 / 107, 4096^3 776 / 819): with one wavefront per SIMD nothing covers its
+// waits.  Two or three k-tiles on their way instead of one, and another first k-tile per workgroup for tall operands:
+// no difference.
 #include "mdh_split.h"
 
 namespace mdh {

@@ -2,13 +2,16 @@
 //
 // An fp32 value has 24 significant bits, a bf16 value 8, and both have the same exponents: x = h + m + l with
 // h = bf16(x), m = bf16(x - h), l = bf16(x - h - m) is exact (each difference is a float, |m| <= 2^-8 |x|,
-// |l| <= 2^-17 |x|) as long as |x| >= 2^-100, whose last bit is well above the smallest normal number.  Of the nine products of two
-// such sums the six
+// |l| <= 2^-17 |x|) as long as |x| >= 2^-100, whose last bit is well above the smallest normal number.  Of the nine
+// products of two such sums the six
 //     h h'   h m'   m h'   m m'   h l'   l h'
-// are evaluated, each exact in the fp32 accumulation of v_mfma_f32_32x32x16_bf16; the three left out are below
-// 2^-26 |x x'| together, a quarter of the rounding error of ONE fp32 multiply-add.  Error against 64 bits,
-// 256 x 256 x K, relative 2-norm, one v_mfma_f32_32x32x2_f32 per two k against six bf16 instructions per 32 k:
-//     U[-1,1]  K = 64: 1.4e-7 / 1.1e-7   256: 2.8e-7 / 2.3e-7   4096: 1.15e-6 / 1.0e-6   25088: 2.8e-6 / 2.6e-6
+// are evaluated, each exact in the fp32 accumulation of v_mfma_f32_32x32x16_bf16, the smaller ones first; the three left
+// out are below (1 + 2^-10) 2^-24 |x x'| together, the rounding error of ONE fp32 multiply-add.  That instruction cuts
+// its sums off instead of rounding them to nearest, so a sum of one term is off by up to 3 x 2^-24 (2.9 met, 0.56 rms;
+// fp32 instructions 1.0, 0.43) -- and exact where one factor is a power of two, which has one slice.  Longer sums have
+// fewer roundings than a chain of fp32 multiply-adds and come out closer.  Error against 64 bits, 256 x 256 x K, relative
+// 2-norm, one v_mfma_f32_32x32x2_f32 per two k against six bf16 instructions per 32 k:
+//     U[-1,1]  K = 64: 1.4e-7 / 1.1e-7   256: 2.9e-7 / 2.4e-7   4096: 1.15e-6 / 1.0e-6   25088: 2.8e-6 / 2.7e-6
 //     U[0,1]   K = 64: 1.2e-7 / 0.8e-7   256: 2.2e-7 / 1.8e-7   4096: 0.85e-6 / 0.5e-6   25088: 2.4e-6 / 1.6e-6
 // (all nine products: the same digits).  Rate of the bare instruction loops on random operands: 154 TFLOP/s in
 // fp32, 1850 / 6 = 308 TFLOP/s in six bf16 products (the 16x16x32 form: 2220 / 6).
