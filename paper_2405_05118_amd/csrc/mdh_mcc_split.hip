@@ -26,8 +26,9 @@ struct Cfg {
   static constexpr int NT = WAVES_M * WAVES_N * 64;
   // Wavefronts a SIMD must be able to hold: what LDS has room for.  Without a demand the compiler keeps accumulators in
   // accumulation registers and moves them about, or not, as the rest of the kernel comes out (2 x 17 x 22 x 292 -> 728,
-  // 3 x 9, 8 x 16 x 64 tiles 170 / 189 us; 8 x 16 x 128 in chunks of 16 channels 315 / 356).
-  static constexpr int HELD = CK == 32 && MI * NI == 4 ? 2 : 3;
+  // 3 x 9, 8 x 16 x 64 tiles 170 / 189 us; 8 x 16 x 128 in chunks of 16 channels 315 / 356).  Tiles of one block a
+  // wavefront are ahead without (8 x 118 x 12 x 67 -> 938, 11 x 9: 900 / 1015).
+  static constexpr int HELD = MI * NI == 1 ? 1 : CK == 32 && MI * NI == 4 ? 2 : 3;
   static constexpr int KP = CK / 8, KH = CK / 16;
   static constexpr int F_PLANE = BN * 16, F_SLICE = KP * F_PLANE, F_STAGE = 3 * F_SLICE;
   static constexpr int F_CHUNKS = BN * KP;
