@@ -21,8 +21,9 @@
 //     not finite, so the outputs tell;
 //   - |x| < 2^-100: its last slices may be lost to subnormal numbers, up to 2^-126.  That can matter only for an
 //     output smaller than K * 2^-100 * (largest |x| of its tile), and only if such an element is there; both are
-//     checked, in the output's own row and column.  An output whose row or column is all zeros -- padding, a dead filter -- is small and exact: the largest
-//     magnitude of every row, kept as the values are split, tells without reading the operands again.
+//     checked, in the output's own row and column.  An output whose row or column is all zeros -- padding, a dead
+//     filter -- is small and exact: the largest magnitude of every row, kept as the values are split, tells without
+//     reading the operands again.
 #pragma once
 #include "mdh_internal.h"
 
