@@ -414,7 +414,8 @@ __device__ __forceinline__ void split_tile(const float* __restrict__ Y, const fl
       atomicOr(blocks + b / 32, 1u << b % 32);
     }
     __syncthreads();
-    todo = (unsigned)__builtin_amdgcn_readfirstlane(blocks[0]) | (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane(blocks[1]) << 32;
+    const unsigned lo = __builtin_amdgcn_readfirstlane(blocks[0]), hi = __builtin_amdgcn_readfirstlane(blocks[1]);
+    todo = lo | (unsigned long long)hi << 32;
   }
 
   const bool whole = m0 + BM <= M && n0 + BN <= N;
@@ -448,7 +449,8 @@ __device__ __forceinline__ void split_tile(const float* __restrict__ Y, const fl
     if (__popcll(todo) > 2 * NT / 64) {
       for (int mi = 0; mi < MI; mi += 2)
         for (int ni = 0; ni < NI; ni += 2)
-          if (redo >> (mi * NI + ni) & (3u | 3u << NI)) recompute_fp32<2, 2, 1, YK, XK>(Y, X, Cout, M, N, ldy, ldx, m0 + wm + mi * 32, n0 + wn + ni * 32, kbeg, kend);
+          if (redo >> (mi * NI + ni) & (3u | 3u << NI))
+            recompute_fp32<2, 2, 1, YK, XK>(Y, X, Cout, M, N, ldy, ldx, m0 + wm + mi * 32, n0 + wn + ni * 32, kbeg, kend);
       return;
     }
   }

@@ -114,7 +114,7 @@ def main(argv):
         sys.stderr.write("usage: python3 -m paper_2405_05118_amd.profile_summary <directory of the raw profiler output> | --workloads\n")
         return 2
     root = argv[1]
-    shown = os.path.relpath(os.path.abspath(root), ROOT)  # as the summaries print it in their commands
+    shown = "$D"  # as the summaries print it in their commands
     workloads = sorted(os.path.basename(d) for d in glob.glob(os.path.join(root, "trace", "*")))
     if not workloads:
         sys.stderr.write("no passes under %s\n" % root)
@@ -133,7 +133,7 @@ def main(argv):
         step_ns[wl] = total
     with open(os.path.join(ROOT, "profiles", "all_workloads_kernel_trace.md"), "w") as fh:
         fh.write("# rocprofv3 kernel trace: every kernel of every bench.py workload (MI355X, gfx950)\n\n"
-                 "One pass per workload W (from the repository root on the GPU box):\n\n"
+                 "One pass per workload W (from the repository root):\n\n"
                  "    rocprofv3 --kernel-trace --stats --output-format csv -d " + shown + "/trace/W -o p -- " + cmd + " --steps 50 --warmup 5\n\n"
                  "Per-dispatch durations (ns) from the kernel trace, warm-up launches dropped; a workload with a split\n"
                  "reduction shows its second-pass kernel on a line of its own.  `bench.py` itself times the same launches\n"

@@ -4,8 +4,8 @@ reduction tails, views and split reductions against 64 bits, and the values such
 Tolerance: the products left out are below (1 + 2^-10) 2^-24 of |a b| (test_split_exact), the six that are there are
 exact, and every one of the fp32 accumulation steps (six per 16 terms, fewer than the K of a multiply-add chain, each
 cutting less than an ulp off) adds at most 2^-23 of the running sum |a b|: (0.75 K + 1) 2^-24 of sum |a b|, below
-K * 2^-24 from five terms on, as for the fp32 instructions.  That is an elementwise bound for edges, tails and parts; test_split_accuracy has the
-limits that tell a missing product.
+K * 2^-24 from five terms on, as for the fp32 instructions.  That is an elementwise bound for edges, tails and parts;
+test_split_accuracy has the limits that tell a missing product.
 """
 import pytest
 
