@@ -163,7 +163,7 @@ __global__ __launch_bounds__(WA* WB * 64) void prl_kernel(
 // of compare + maximum + select per record; which record of the winning block scored the maximum is
 // found once at the end by scoring that block again.  Everything stays exact under these conditions,
 // which the kernel checks itself: field values in [0, 2^23) (the records of A up front, those of B as
-// they stream by, after every 64: from the run of 64 that holds a value outside, the integer loop goes on),
+// they stream by, after every 128: from the run of 128 that holds a value outside, the integer loop goes on),
 // sum_f max(|w_agree_f|, |w_disagree_f|) < 2^24 and every |w_disagree_f - w_agree_f| <= 2^24 (all partial sums, and
 // what a field that differs adds, are then integers fp32 holds exactly).
 // The result is the unique (score, index) of the definition, bit for bit, on either path.
