@@ -31,6 +31,7 @@ SOURCES = [
     "mdh_capsule.hip",
     "mdh_matmul_skinny.hip",
     "mdh_custom_reduce.hip",
+    "mdh_custom_reduce_bits.hip",
     "mdh_reduce.hip",
     "mdh_matmul_ex.hip",
 ]

@@ -20,6 +20,7 @@
 #include <mutex>
 
 #include "mdh_internal.h"
+#include "mdh_prl_bits.h"
 #include "mdh_walk.h"
 
 // Scratch memory of mdh_custom_reduce_static, the entry point for callers that cannot allocate: the
@@ -171,7 +172,8 @@ template <int NF, int RA, int WB, int WA>
 __global__ __launch_bounds__(WA* WB * 64) void prl_fast_kernel(
     const int* __restrict__ A, const int* __restrict__ B, const int* __restrict__ wp,
     const int* __restrict__ wm, int* __restrict__ out_s, int* __restrict__ out_i,
-    int* __restrict__ ws, int nA, int nB, int S, int bchunk) {
+    int* __restrict__ ws, int nA, int nB, int S, int bchunk, const int* __restrict__ gate) {
+  if (gate && !*gate) return;  // the bit maps did it
   constexpr int BI = (NF > 10 ? 4 : 8) / RA;  // records of B interleaved per step: RA * BI independent chains
   static_assert(RA == 2 || RA == 4, "eight or four chains per lane");
   __shared__ int red_s[WB > 1 ? (WB - 1) * WA * RA * 64 : 1];
@@ -431,13 +433,25 @@ template <int NF, int RA, int WB, int WA>
 mdh_status launch_fast(const PrlPlan& pl, int64_t nA, int64_t nB, const int32_t* A, const int32_t* B,
                        const int32_t* wp, const int32_t* wm, int32_t* score, int32_t* index, void* ws,
                        hipStream_t st) {
+  if constexpr (RA == 2 && WB == 4 && WA == 1) {
+    if (prl_bits_applies(pl.S, nA, nB, NF)) {
+      mdh_status r = launch_prl_bits(pl.S, nA, nB, NF, A, B, wp, wm, ws, st);
+      if (r != MDH_OK) return r;
+      const int S = pl.S - 1;
+      hipLaunchKernelGGL((prl_fast_kernel<NF, RA, WB, WA>), dim3((unsigned)(cdiv(nA, 64 * RA) * S)), dim3(WA * WB * 64), 0, st,
+                         A, B, wp, wm, score, index, (int*)ws, (int)nA, (int)nB, S, (int)cdiv(nB, (int64_t)S * WB),
+                         prl_bits_gate(ws, nA, pl.S));
+      if ((r = launch_status()) != MDH_OK) return r;
+      return launch_prl_bits_finish(pl.S, nA, ws, score, index, st);
+    }
+  }
   const int64_t nWGa = cdiv(nA, (int64_t)WA * 64 * RA);
   const int64_t nblocks = nWGa * pl.S;
   if (nblocks > 0x7fffffff) return MDH_ERR_SIZE;
   const int64_t bchunk = cdiv(nB, (int64_t)pl.S * WB);
   clear_stale_error();
   hipLaunchKernelGGL((prl_fast_kernel<NF, RA, WB, WA>), dim3((unsigned)nblocks), dim3(WA * WB * 64), 0, st, A, B,
-                     wp, wm, score, index, (int*)ws, (int)nA, (int)nB, pl.S, (int)bchunk);
+                     wp, wm, score, index, (int*)ws, (int)nA, (int)nB, pl.S, (int)bchunk, (const int*)nullptr);
   mdh_status r = launch_status();
   if (r != MDH_OK || pl.S <= 1) return r;
   clear_stale_error();

@@ -242,6 +242,13 @@ mdh_status launch_prl(const PrlPlan& pl, int64_t nA, int64_t nB, int nF, const i
                       const int32_t* B, const int32_t* wp, const int32_t* wm, int32_t* score,
                       int32_t* index, void* ws, hipStream_t st);
 
+// custom reduce on bit maps (mdh_custom_reduce_bits.hip): keys into `ws`, the loop over fields behind it if the word at
+// `gate` is not 0 then, and the output of whichever ran
+mdh_status launch_prl_bits(int S, int64_t nA, int64_t nB, int nF, const int32_t* A, const int32_t* B, const int32_t* wp,
+                           const int32_t* wm, void* ws, hipStream_t st);
+const int* prl_bits_gate(void* ws, int64_t nA, int S);
+mdh_status launch_prl_bits_finish(int S, int64_t nA, void* ws, int32_t* score, int32_t* index, hipStream_t st);
+
 // The runtime's "last error" is sticky per thread and other users of the runtime in the same
 // process leave harmless codes there (an event query that is not ready yet, for instance):
 // clear it before a launch so that the status read after the launch is that launch's own.

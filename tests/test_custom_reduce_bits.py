@@ -1,0 +1,125 @@
+"""Custom reduce on bit maps: its grid and slots on the CPU, and its results where its parts meet, where scores tie and
+where values or weights send it back to the loop over fields, against the definition."""
+import ctypes
+import subprocess
+
+import numpy as np
+import pytest
+
+import oracle
+import paper_2405_05118_amd as mdh
+from paper_2405_05118_amd.build import CSRC
+
+torch = pytest.importorskip("torch")
+
+PLAN = r"""
+#include "mdh_prl_bits.h"
+using namespace mdh;
+// 0 if the grid covers all records once, a queued pair fits its bits and two workgroups fit 160 KB of LDS
+extern "C" int grid(long long nA, long long nB, int nF) {
+  const PrlBitsGrid g = prl_bits_grid(nA, nB, nF);
+  const long long c = (nB + kPrlChunk - 1) / kPrlChunk;
+  if (g.sets < 1 || g.sets * 1024 > 1 << (32 - kPrlPartBits)) return 1;
+  if ((long long)g.groups * g.sets * 1024 < nA || (long long)(g.groups - 1) * g.sets * 1024 >= nA) return 2;
+  if ((long long)g.parts * g.chunks < c || (long long)(g.parts - 1) * g.chunks >= c) return 3;
+  if ((long long)g.chunks * kPrlChunk > 1 << kPrlPartBits) return 4;
+  if ((long long)g.groups * g.parts > 0x7fffffff) return 5;
+  return 2 * prl_bits_lds_bytes(nF, g.sets) > 160 * 1024 ? 6 : 0;
+}
+// 0 if every field has 16 to 1024 slots, no two share one and all fit the maps
+extern "C" int slots(const unsigned* used, int nF) {
+  unsigned u[16];
+  for (int f = 0; f < 16; ++f) u[f] = used[f];
+  const PrlSlots s = prl_slots<16>(u, nF);
+  for (int f = 0; f < nF; ++f)
+    if (s.bits(f) < 4 || s.bits(f) > 10 || (f && s.first(f) != s.first(f - 1) + (1u << s.bits(f - 1)))) return 1;
+  return s.first(nF - 1) + (1u << s.bits(nF - 1)) > kPrlMaps / 16 ? 2 : 0;
+}
+extern "C" int applies(int S, long long nA, long long nB, int nF) { return prl_bits_applies(S, nA, nB, nF); }
+// bytes that keys, slots and head need, with 8 for alignment
+extern "C" long long bytes(long long nA, int nF) { return 8 * nA + 4 * ((nF + 1) / 2) * nA + (long long)sizeof(PrlBitsHead) + 16; }
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("bits")
+    (d / "plan.cpp").write_text(PLAN)
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(d / "plan.cpp"), "-o", str(d / "plan.so")])
+    L = ctypes.CDLL(str(d / "plan.so"))
+    L.grid.argtypes = [ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int]
+    L.bytes.argtypes, L.bytes.restype = [ctypes.c_longlong, ctypes.c_int], ctypes.c_longlong
+    L.applies.argtypes = [ctypes.c_int, ctypes.c_longlong, ctypes.c_longlong, ctypes.c_int]
+    return L
+
+
+def test_grid_slots_and_memory(plan):
+    rng = np.random.default_rng(0)
+    sizes = [(1024, 2**31 // 16, 16), (1024, 1, 1), (2**31 - 1, 1, 1), (1025, 129, 8), (1024, 2**31 - 1, 1), (65536, 2**18, 8)]
+    sizes += [(int(2 ** rng.uniform(10, 20)), int(2 ** rng.uniform(0, 27)), int(rng.integers(1, 17))) for _ in range(3000)]
+    for nA, nB, nF in sizes:
+        assert plan.grid(nA, nB, nF) == 0, (nA, nB, nF)
+        S = mdh.mdh_default_params(mdh.MDH_CUSTOM_REDUCE, (nA, nB)).prt[3][1]
+        if plan.applies(S, nA, nB, nF):  # the head stays out of the first S - 1 parts' results
+            assert plan.bytes(nA, nF) <= 8 * S * nA and 8 * nA >= 1200
+    for _ in range(2000):
+        used = (rng.integers(0, 2**32, 16, dtype=np.uint64) >> rng.integers(0, 33, 16).astype(np.uint64)).astype(np.uint32)
+        assert plan.slots(used.ctypes.data_as(ctypes.c_void_p), int(rng.integers(1, 17))) == 0
+
+
+def check(A, B, wp, wm):
+    want_s, want_i = oracle.custom_reduce(A, B, wp, wm)
+    dev = [torch.from_numpy(np.ascontiguousarray(x)).cuda() for x in (A, B, wp, wm)]
+    n = mdh.mdh_workspace_size(mdh.MDH_CUSTOM_REDUCE, (len(A), len(B), A.shape[1]))
+    ws = torch.empty(n // 4 + 1, dtype=torch.int32, device="cuda")
+    for at in (0, 1):  # a workspace that is not aligned to more than its type, too
+        s = torch.full((len(A),), -7, dtype=torch.int32, device="cuda")
+        i = torch.full((len(A),), -7, dtype=torch.int32, device="cuda")
+        mdh.mdh_custom_reduce(*dev, s, i, None, ws[at : at + n // 4])
+        assert np.array_equal(s.cpu().numpy(), want_s) and np.array_equal(i.cpu().numpy(), want_i)
+
+
+def inputs(nF, nA, top, seed):
+    rng = np.random.default_rng(seed)
+    nB = (1 << (29 if nF <= 10 else 31)) // (nF * nA) + 77
+    A = rng.integers(0, top, (nA, nF)).astype(np.int32)
+    B = rng.integers(0, top, (nB, nF)).astype(np.int32)
+    return A, B, rng.integers(1, 1 << 16, nF).astype(np.int32), rng.integers(-(1 << 16), 1, nF).astype(np.int32)
+
+
+# odd and even numbers of fields, one set of records of A and several, the last one nearly empty; 2 values: ties everywhere,
+# in the same chunk, in other chunks and in other parts; 2^30: slots shared by different values
+@pytest.mark.gpu
+@pytest.mark.parametrize("nF,nA", [(1, 3137), (2, 40000), (3, 1024), (4, 5000), (7, 1025), (8, 4161), (9, 1100), (10, 2049),
+                                   (11, 1500), (12, 3000), (13, 2100), (16, 4097)])
+@pytest.mark.parametrize("top", [2, 60, 1 << 30])
+def test_against_the_definition(nF, nA, top):
+    check(*inputs(nF, nA, top, nF))
+
+
+# agreeing never raises a score; it does in some fields; not at all; by steps no set of small weights follows; sums that
+# wrap around
+@pytest.mark.gpu
+@pytest.mark.parametrize("weights", ["lower", "mixed", "none", "steps", "wrap"])
+def test_weights(weights):
+    A, B, wp, wm = inputs(8, 2300, 9, 5)
+    if weights == "lower":
+        wp, wm = wm, wp
+    elif weights == "mixed":
+        wp[::2], wm[::2] = wm[::2].copy(), wp[::2].copy()
+    elif weights == "none":
+        wp[:], wm[:] = 3, 3
+    elif weights == "steps":
+        wp[:], wm[:] = [10**k for k in (7, 6, 5, 4, 3, 2, 1, 0)], 0
+    else:
+        wp[:], wm[:] = 2**31 - 1, -(2**31)
+    check(A, B, wp, wm)
+
+
+# every record of B is better than the one before, for all records of A: the most records that can be scored
+@pytest.mark.gpu
+def test_ever_better_records():
+    A, B, wp, wm = inputs(8, 1024, 60, 6)
+    A[:] = 0
+    B = B[np.argsort(np.where(B == 0, wp, wm).sum(axis=1), kind="stable")]
+    check(A, B, wp, wm)
