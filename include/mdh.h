@@ -274,7 +274,11 @@ mdh_status mdh_stencil(int64_t nx, int64_t ny, int64_t nz, const float* in, floa
  * (1 x 32, 2 x 16 or 4 x 8), blk[k] = 32; blk[c] = 2 selects a channel-chunked
  * kernel -- with prt[MDH_L_VGPR][c] = 8 the one that carries a value as three bf16 values
  * (see mdh_matmul; C >= 16), else the one with fp32 instructions --, blk[c] = 1 the
- * few-channel kernel that walks s and c as one dimension.
+ * few-channel kernel that walks s and c as one dimension.  With in_region[0] =
+ * MDH_MR_HBM that kernel carries every fp32 value as three bf16 values, as the
+ * larger layers' tables with eight register parts of c do; a call without a table
+ * takes it where that is faster and no less precise, mdh_default_params answers
+ * the table of the fp32 instructions.
  * prt[MDH_L_WG][c] = S > 1 splits the reduction dimension c over workgroups: the S
  * partial outputs go to `workspace` (S * N*P*Q*K floats, see mdh_workspace_size) and
  * a second kernel adds them in ascending part order.  The library default does

@@ -26,6 +26,7 @@ SOURCES = [
     "mdh_mcc.hip",
     "mdh_mcc_split.hip",
     "mdh_mcc_flat.hip",
+    "mdh_mcc_flat_split.hip",
     "mdh_calib.hip",
     "mdh_scan.hip",
     "mdh_capsule.hip",

@@ -48,7 +48,8 @@ struct MccPlan {
   // few-channel kernel: 1 = the workgroup-layer parts of (n, p, q) are dealt out to resident workgroups in
   // arrival order (QT = 1), 0 = a workgroup owns QT consecutive column tiles
   int dealt = 0;
-  // 1: the channel-chunked kernel that carries every value as three bf16 values (16 channels per MFMA: prt[VGPR][c] = 8)
+  // 1: the kernel that carries every value as three bf16 values, channel-chunked (16 channels per MFMA: prt[VGPR][c] = 8) or
+  // few-channel (the input goes from device memory to registers: in_region[0])
   int split = 0;
 };
 
@@ -211,6 +212,7 @@ mdh_status plan_matmul(const int64_t* sizes, const mdh_tile_params* p, GemmPlan*
 // for a caller without the workspace the plan asks for: the default, given as none or as its table, does with less
 void plan_matmul_lean(const int64_t* sizes, GemmPlan* pl);
 mdh_status plan_mcc(const int64_t* sizes, const mdh_tile_params* p, MccPlan* out);
+MccPlan mcc_default_table(const int64_t* sizes);  // what mdh_default_params answers
 mdh_status plan_prl(const int64_t* sizes, const mdh_tile_params* p, PrlPlan* out);
 
 // Fill a full parameter table (prt/blk/order/regions) from a launch descriptor.
@@ -238,6 +240,9 @@ mdh_status launch_mcc_split(const MccPlan& pl, int64_t N, int64_t H, int64_t W, 
 mdh_status launch_mcc_flat(const MccPlan& pl, int64_t N, int64_t H, int64_t W, int64_t C, int64_t K,
                            int64_t R, int64_t S, int64_t sh, int64_t sw, const float* in,
                            const float* filt, float* out, hipStream_t st);
+int64_t mcc_flat_split_lds_bytes(int BN, int64_t C, int64_t R, int64_t S);
+mdh_status launch_mcc_flat_split(const MccPlan& pl, int64_t N, int64_t H, int64_t W, int64_t C, int64_t K, int64_t R, int64_t S,
+                                 int64_t sh, int64_t sw, const float* in, const float* filt, float* out, hipStream_t st);
 mdh_status launch_prl(const PrlPlan& pl, int64_t nA, int64_t nB, int nF, const int32_t* A,
                       const int32_t* B, const int32_t* wp, const int32_t* wm, int32_t* score,
                       int32_t* index, void* ws, hipStream_t st);

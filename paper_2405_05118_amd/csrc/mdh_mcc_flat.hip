@@ -570,6 +570,7 @@ int64_t mcc_flat_lds_bytes(int QB, int TP, int BN, int64_t C, int64_t R, int64_t
 mdh_status launch_mcc_flat(const MccPlan& pl, int64_t N, int64_t H, int64_t W, int64_t C, int64_t K,
                            int64_t R, int64_t S, int64_t sh, int64_t sw, const float* in,
                            const float* filt, float* out, hipStream_t st) {
+  if (pl.split) return launch_mcc_flat_split(pl, N, H, W, C, K, R, S, sh, sw, in, filt, out, st);
   // pl.TQ is the block width QB, pl.TP the rows per workgroup, pl.BN the channels per workgroup
   if (!pl.dealt && pl.QT < 1) return MDH_ERR_UNSUPPORTED;
 #define MDH_FL(qb, mi, ni, wm, wn)                                                              \

@@ -598,10 +598,13 @@ static const MccInst kMccSplitMenu[] = {
     {8, 8, 128, 16, 32, 64},  {8, 8, 64, 16, 32, 32},   {8, 32, 128, 32, 64, 64}, {4, 32, 128, 32, 64, 64}, {4, 32, 64, 32, 64, 32},
     {8, 16, 128, 32, 64, 64}, {8, 16, 64, 32, 64, 32},  {16, 8, 64, 32, 64, 32}, {8, 8, 128, 32, 32, 64}, {8, 8, 64, 32, 32, 32},
 };
+// few-channel kernel that splits: a wavefront's block of 32 pixels x 32 or 64 channels
+static const MccInst kMccFlatSplitMenu[] = {{2, 16, 64, 0, 32, 64}, {1, 32, 64, 0, 32, 64}, {4, 8, 64, 0, 32, 64},
+                                            {2, 16, 32, 0, 32, 32}, {1, 32, 32, 0, 32, 32}, {4, 8, 32, 0, 32, 32}};
 
 static bool mcc_inst(const MccPlan& pl) {
-  const MccInst* menu = pl.flat ? kMccFlatMenu : pl.split ? kMccSplitMenu : kMccMenu;
-  const int n = (int)(pl.flat ? sizeof(kMccFlatMenu) : pl.split ? sizeof(kMccSplitMenu) : sizeof(kMccMenu)) / (int)sizeof(MccInst);
+  const MccInst* menu = pl.flat ? pl.split ? kMccFlatSplitMenu : kMccFlatMenu : pl.split ? kMccSplitMenu : kMccMenu;
+  const int n = (int)(pl.flat ? pl.split ? sizeof(kMccFlatSplitMenu) : sizeof(kMccFlatMenu) : pl.split ? sizeof(kMccSplitMenu) : sizeof(kMccMenu)) / (int)sizeof(MccInst);
   for (int i = 0; i < n; ++i) {
     const MccInst& m = menu[i];
     if (m.TP == pl.TP && m.TQ == pl.TQ && m.BN == pl.BN && m.CK == pl.CK && m.WM == pl.WM && m.WN == pl.WN)
@@ -612,6 +615,7 @@ static bool mcc_inst(const MccPlan& pl) {
 
 // sizes: N, P, Q, K, C, R, S, stride_h, stride_w
 int64_t mcc_lds_bytes(const MccPlan& pl, const int64_t* s) {
+  if (pl.flat && pl.split) return mcc_flat_split_lds_bytes(pl.BN, s[4], s[5], s[6]);
   if (pl.flat) return mcc_flat_lds_bytes(pl.TQ, pl.TP, pl.BN, s[4], s[5], s[6], s[7], s[8]);
   const int64_t ph = (pl.TP - 1) * s[7] + s[5], pw = (pl.TQ - 1) * s[8] + s[6];
   if (pl.split) return 6ll * pl.CK * (cdiv(ph * pw, 8) * 8 + (pl.CK == 16 ? 4 : 2)) + 12ll * pl.BN * pl.CK + 16;
@@ -660,7 +664,7 @@ void params_from_plan(const int64_t* s, const MccPlan& pl, mdh_tile_params* p) {
   // out one at a time to the workgroups resident on the chip
   p->strided = (pl.flat && pl.dealt) ? 1 : 0;
   p->lane_fast_dim = 3;
-  p->in_region[0] = MDH_MR_LDS;
+  p->in_region[0] = pl.flat && pl.split ? MDH_MR_HBM : MDH_MR_LDS;
   p->in_region[1] = MDH_MR_LDS;
   p->out_region = MDH_MR_VGPR;
   p->ragged = (uint8_t)pl.ragged;
@@ -847,11 +851,45 @@ static bool mcc_split_default(const int64_t* s, int TQ, int S, MccPlan* out) {
   return best >= 0;
 }
 
+// the few-channel kernel that splits addresses an image with 32 bits
+static bool mcc_flat_split_sizes(const int64_t* s) {
+  return flat_input_ok(s) && ((s[1] > 0 ? s[1] : 1) * s[7] + s[5]) * ((s[2] > 0 ? s[2] : 1) * s[8] + s[6]) * s[4] < (1 << 28);
+}
+
+// Does a call without a table go to the few-channel kernel that splits, and in which block?  (The default's table stays
+// that of the fp32 instructions: bit for bit the results it always had.)
+// us, against those: 16 x 230 x 230 x 3 -> 64, 7 x 7, stride 2: 32.9 / 45.6, one image 7.6 / 9.0; 16 x 200 x 170 x 3 ->
+// 64, 5 x 5: 43 / 74; 14 x 178 x 203 x 2 -> 56, 7 x 7: 51 / 97; 16 x 224 x 224 x 3 -> 64, 3 x 3: 52.3 / 57.1.  The line:
+// its matrix instructions have to take less than three quarters of the time (7 x 7 on one channel 0.43, 3 x 3 on one or
+// two 1.0 / 0.75: equal times), and from 18 terms on its error against 64 bits is the smaller one (18 terms 6.0e-8 /
+// 8.0e-8, 27 8.7e-8 / 9.4e-8, 147 1.9e-7 / 2.2e-7).  64 channels a wavefront share the split of the input, 32 leave more
+// wavefronts: one image of the first layer 7.6 with 32, 10.4 with 64.
+static void mcc_flat_split_rule(const int64_t* s, MccPlan* out) {
+  if (!mcc_flat_split_sizes(s)) return;
+  const int64_t P = s[1] > 0 ? s[1] : 1, Q = s[2] > 0 ? s[2] : 1, SC = s[6] * s[4];
+  // cycles of the matrix instructions of 32 pixels x 32 channels
+  const int64_t split = cdiv(s[5] * cdiv(SC, 8), 2) * 6 * 32, fp32 = s[5] * (SC / 8 * 4 + cdiv(SC % 8, 2)) * 64;
+  if (s[5] * SC < 18 || split * 4 > fp32 * 3) return;
+  int64_t area = -1;
+  int tq = 0;
+  for (int t : {16, 32, 8}) {  // the block that pads the image least
+    const int64_t a = cdiv(P, 32 / t) * (32 / t) * cdiv(Q, t) * t;
+    if (area < 0 || a < area) area = a, tq = t;
+  }
+  const int bn = s[3] > 32 && s[0] * area / 32 >= 2048 ? 64 : 32;
+  MccPlan pl{32 / tq, tq, bn, 0, 32, bn, 0, 1};
+  pl.split = 1;
+  pl.ragged = mcc_ragged(s, pl);
+  if (mcc_lds_bytes(pl, s) <= kLdsBytesPerWG) *out = pl;
+}
+
 static MccPlan mcc_default(const int64_t* s) {
   MccPlan pl = mcc_default_fp32(s);
   if (!pl.flat && mcc_split_default(s, pl.TQ, pl.S, &pl)) pl.ragged = mcc_ragged(s, pl);
   return pl;
 }
+
+MccPlan mcc_default_table(const int64_t* s) { return mcc_default(s); }
 
 int mcc_candidates(const int64_t* s, MccPlan* out, int cap) {
   int n = 0;
@@ -901,6 +939,12 @@ int mcc_candidates(const int64_t* s, MccPlan* out, int cap) {
           push(pl);
         }
       }
+  if (s[4] <= 16 && mcc_flat_split_sizes(s))
+    for (auto& m : kMccFlatSplitMenu) {
+      MccPlan pl{m.TP, m.TQ, m.BN, m.CK, m.WM, m.WN, 0, 1};
+      pl.split = 1;
+      push(pl);
+    }
   return n;
 }
 
@@ -908,6 +952,7 @@ mdh_status plan_mcc(const int64_t* s, const mdh_tile_params* p, MccPlan* out) {
   if (!p) {
     *out = mcc_default(s);
     if (mcc_lds_bytes(*out, s) > kLdsBytesPerWG) return MDH_ERR_TILE_RESOURCES;
+    if (out->flat) mcc_flat_split_rule(s, out);
     return MDH_OK;
   }
   if (p->D != 7) return MDH_ERR_UNSUPPORTED;
@@ -921,7 +966,9 @@ mdh_status plan_mcc(const int64_t* s, const mdh_tile_params* p, MccPlan* out) {
   pl.BN = p->prt[MDH_L_WAVE][3] * pl.WN;
   if (pl.flat) {
     pl.TQ = p->blk[2];
-    if ((pl.TQ != 16 && pl.TQ != 32) || !flat_input_ok(s)) return MDH_ERR_UNSUPPORTED;
+    pl.split = p->in_region[0] == MDH_MR_HBM;
+    if ((pl.TQ != 16 && pl.TQ != 32 && !(pl.split && pl.TQ == 8)) || !flat_input_ok(s)) return MDH_ERR_UNSUPPORTED;
+    if (pl.split && (!mcc_flat_split_sizes(s) || p->strided || p->prt[MDH_L_HBM][2] != 1)) return MDH_ERR_UNSUPPORTED;
     pl.WM = p->prt[MDH_L_VGPR][1] * 32;
     pl.TP = p->prt[MDH_L_WAVE][1] * p->prt[MDH_L_VGPR][1] * (32 / pl.TQ);
     pl.CK = 0;
@@ -1149,7 +1196,7 @@ mdh_status mdh_default_params(mdh_instance inst, const int64_t* sizes, mdh_tile_
     }
     case MDH_MCC: {
       MccPlan pl;
-      if ((st = plan_mcc(sizes, nullptr, &pl)) == MDH_OK) params_from_plan(sizes, pl, out);
+      if ((st = plan_mcc(sizes, nullptr, &pl)) == MDH_OK) params_from_plan(sizes, mcc_default_table(sizes), out);
       return st;
     }
     case MDH_CUSTOM_REDUCE: {
