@@ -80,10 +80,15 @@ class MdhError(RuntimeError):
 
 _lib = None
 
+# What every call needs of torch, set when the library is loaded.  A call of a few microseconds is as fast as the host is:
+# importing torch in every function, wrapping every pointer in an object that ctypes unwraps again and asking for the
+# stream through torch.cuda took a microsecond of the 6.4 of a 256 x 256 x 256 product (5.4 now).
+_Tensor = _F32 = _I32 = _raw_stream = _device = None
+
 
 def lib() -> ctypes.CDLL:
     """Load libmdh.so (built in-tree by ``build.py``).  No fallback: raises if absent."""
-    global _lib
+    global _lib, _Tensor, _F32, _I32, _raw_stream, _device
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError(
@@ -93,8 +98,14 @@ def lib() -> ctypes.CDLL:
         # torch ships its own copy of the HIP runtime; it has to be the first one the process
         # loads so that libmdh.so binds to the runtime that owns torch's device memory and streams
         # (loaded the other way round, launches fail with "no ROCm-capable device")
-        import torch  # noqa: F401
+        import torch
 
+        _Tensor, _F32, _I32 = torch.Tensor, torch.float32, torch.int32
+        # torch's C entry points for the stream and the device, where it has them: several times cheaper
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        _device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
+        if _raw_stream is None:
+            _raw_stream = lambda device: int(torch.cuda.current_stream(device).cuda_stream)  # noqa: E731
         L = ctypes.CDLL(LIB_PATH)
         i64, i32, vp, sz, f32 = ctypes.c_int64, ctypes.c_int32, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_float
         pp = ctypes.POINTER(TileParams)
@@ -165,36 +176,21 @@ def _check(st: int, where: str):
         raise MdhError(st, where)
 
 
-_raw_stream = None
-
-
 def _stream() -> int:
-    """Handle of torch's current stream on the current device.  torch's C entry point for it is several
-    times cheaper than building a torch.cuda.Stream object per call, which matters for kernels of a few
-    microseconds; the portable form is the fallback."""
-    global _raw_stream
-    import torch
-
-    if _raw_stream is None:
-        f = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        _raw_stream = f if f is not None else False
-    if _raw_stream:
-        return int(_raw_stream(torch.cuda.current_device()))
-    return int(torch.cuda.current_stream().cuda_stream)
+    """Handle of torch's current stream on the current device (after the checks of the operands: the device is in use)."""
+    return _raw_stream(_device())
 
 
 def _dev(t, dtype, name):
-    import torch
-
-    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous()):
-        raise TypeError("%s must be a contiguous %s tensor on the GPU" % (name, dtype))
-    return ctypes.c_void_p(t.data_ptr())
+    if isinstance(t, _Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous():
+        return t.data_ptr()
+    raise TypeError("%s must be a contiguous %s tensor on the GPU" % (name, dtype))
 
 
 def _ws(ws):
     if ws is None:
         return None, 0
-    return ctypes.c_void_p(ws.data_ptr()), ws.numel() * ws.element_size()
+    return ws.data_ptr(), ws.numel() * ws.element_size()
 
 
 # ------------------------------------------------------------------ host-only helpers
@@ -244,74 +240,62 @@ def mdh_candidate(inst: int, sizes: Sequence[int], idx: int) -> TileParams:
 
 
 def mdh_matmul(A, B, C, params: Optional[TileParams] = None, workspace=None):
-    import torch
-
     M, K = A.shape
     K2, N = B.shape
-    assert K == K2 and tuple(C.shape) == (M, N)
+    assert K == K2 and C.shape == (M, N)
     wp, wb = _ws(workspace)
-    st = lib().mdh_matmul(M, N, K, _dev(A, torch.float32, "A"), _dev(B, torch.float32, "B"), _dev(C, torch.float32, "C"),
-                          _pref(params), wp, wb, ctypes.c_void_p(_stream()))
+    st = lib().mdh_matmul(M, N, K, _dev(A, _F32, "A"), _dev(B, _F32, "B"), _dev(C, _F32, "C"),
+                          _pref(params), wp, wb, _stream())
     _check(st, "mdh_matmul")
     return C
 
 
 def mdh_stencil(x, out, c0: float, c1: float, params: Optional[TileParams] = None):
-    import torch
-
     nx, ny, nz = (s - 2 for s in x.shape)
-    assert tuple(out.shape) == (nx, ny, nz)
-    st = lib().mdh_stencil(nx, ny, nz, _dev(x, torch.float32, "in"), _dev(out, torch.float32, "out"), float(c0), float(c1),
-                           _pref(params), ctypes.c_void_p(_stream()))
+    assert out.shape == (nx, ny, nz)
+    st = lib().mdh_stencil(nx, ny, nz, _dev(x, _F32, "in"), _dev(out, _F32, "out"), float(c0), float(c1),
+                           _pref(params), _stream())
     _check(st, "mdh_stencil")
     return out
 
 
 def mdh_mcc(x, filt, out, stride=(1, 1), params: Optional[TileParams] = None, workspace=None):
-    import torch
-
     N, H, W, C = x.shape
     K, R, S, C2 = filt.shape
     assert C == C2
     sh, sw = stride
     P, Q = (H - R) // sh + 1, (W - S) // sw + 1
-    assert tuple(out.shape) == (N, P, Q, K)
+    assert out.shape == (N, P, Q, K)
     wp, wb = _ws(workspace)
-    st = lib().mdh_mcc(N, H, W, C, K, R, S, sh, sw, _dev(x, torch.float32, "in"), _dev(filt, torch.float32, "filt"),
-                       _dev(out, torch.float32, "out"), _pref(params), wp, wb, ctypes.c_void_p(_stream()))
+    st = lib().mdh_mcc(N, H, W, C, K, R, S, sh, sw, _dev(x, _F32, "in"), _dev(filt, _F32, "filt"),
+                       _dev(out, _F32, "out"), _pref(params), wp, wb, _stream())
     _check(st, "mdh_mcc")
     return out
 
 
 def mdh_custom_reduce(A, B, w_agree, w_disagree, out_score, out_index, params: Optional[TileParams] = None,
                       workspace=None):
-    import torch
-
     nA, nF = A.shape
     nB, nF2 = B.shape
     assert nF == nF2 == w_agree.numel() == w_disagree.numel()
     assert out_score.numel() == nA and out_index.numel() == nA
-    i32 = torch.int32
     wp, wb = _ws(workspace)
-    st = lib().mdh_custom_reduce(nA, nB, nF, _dev(A, i32, "A"), _dev(B, i32, "B"), _dev(w_agree, i32, "w_agree"),
-                                 _dev(w_disagree, i32, "w_disagree"), _dev(out_score, i32, "out_score"),
-                                 _dev(out_index, i32, "out_index"), _pref(params), wp, wb, ctypes.c_void_p(_stream()))
+    st = lib().mdh_custom_reduce(nA, nB, nF, _dev(A, _I32, "A"), _dev(B, _I32, "B"), _dev(w_agree, _I32, "w_agree"),
+                                 _dev(w_disagree, _I32, "w_disagree"), _dev(out_score, _I32, "out_score"),
+                                 _dev(out_index, _I32, "out_index"), _pref(params), wp, wb, _stream())
     _check(st, "mdh_custom_reduce")
     return out_score, out_index
 
 
 def mdh_custom_reduce_static(A, B, w_agree, w_disagree, out_score, out_index, params: Optional[TileParams] = None):
     """mdh_custom_reduce without a workspace: split-reduction partial results go to the library's static array."""
-    import torch
-
     nA, nF = A.shape
     nB, nF2 = B.shape
     assert nF == nF2 == w_agree.numel() == w_disagree.numel()
     assert out_score.numel() == nA and out_index.numel() == nA
-    i32 = torch.int32
-    st = lib().mdh_custom_reduce_static(nA, nB, nF, _dev(A, i32, "A"), _dev(B, i32, "B"), _dev(w_agree, i32, "w_agree"),
-                                        _dev(w_disagree, i32, "w_disagree"), _dev(out_score, i32, "out_score"),
-                                        _dev(out_index, i32, "out_index"), _pref(params), ctypes.c_void_p(_stream()))
+    st = lib().mdh_custom_reduce_static(nA, nB, nF, _dev(A, _I32, "A"), _dev(B, _I32, "B"), _dev(w_agree, _I32, "w_agree"),
+                                        _dev(w_disagree, _I32, "w_disagree"), _dev(out_score, _I32, "out_score"),
+                                        _dev(out_index, _I32, "out_index"), _pref(params), _stream())
     _check(st, "mdh_custom_reduce_static")
     return out_score, out_index
 
@@ -324,59 +308,51 @@ def mdh_matmul_ex(A, B, C, trans_a=False, trans_b=False, trans_c=False, params: 
                   workspace=None):
     """A: (batch, M, K) or (batch, K, M) if trans_a; B: (batch, K, N) or (batch, N, K) if trans_b;
     C: (batch, M, N) or (batch, N, M) if trans_c."""
-    import torch
-
     batch = A.shape[0]
     M, K = (A.shape[2], A.shape[1]) if trans_a else (A.shape[1], A.shape[2])
     N = B.shape[1] if trans_b else B.shape[2]
     assert B.shape[0] == batch and C.shape[0] == batch
-    assert tuple(B.shape[1:]) == ((N, K) if trans_b else (K, N))
-    assert tuple(C.shape[1:]) == ((N, M) if trans_c else (M, N))
+    assert B.shape[1:] == ((N, K) if trans_b else (K, N))
+    assert C.shape[1:] == ((N, M) if trans_c else (M, N))
     wp, wb = _ws(workspace)
-    st = lib().mdh_matmul_ex(batch, M, N, K, _dev(A, torch.float32, "A"), int(trans_a), _dev(B, torch.float32, "B"),
-                             int(trans_b), _dev(C, torch.float32, "C"), int(trans_c), _pref(params), wp, wb,
-                             ctypes.c_void_p(_stream()))
+    st = lib().mdh_matmul_ex(batch, M, N, K, _dev(A, _F32, "A"), int(trans_a), _dev(B, _F32, "B"),
+                             int(trans_b), _dev(C, _F32, "C"), int(trans_c), _pref(params), wp, wb,
+                             _stream())
     _check(st, "mdh_matmul_ex")
     return C
 
 
 def mdh_dot(x, y, out, params: Optional[TileParams] = None, workspace=None):
-    import torch
-
     K = x.numel()
     assert y.numel() == K and out.numel() == 1
     wp, wb = _ws(workspace)
-    st = lib().mdh_dot(K, _dev(x, torch.float32, "x"), _dev(y, torch.float32, "y"), _dev(out, torch.float32, "out"),
-                       _pref(params), wp, wb, ctypes.c_void_p(_stream()))
+    st = lib().mdh_dot(K, _dev(x, _F32, "x"), _dev(y, _F32, "y"), _dev(out, _F32, "out"),
+                       _pref(params), wp, wb, _stream())
     _check(st, "mdh_dot")
     return out
 
 
 def mdh_mcc_capsule(x, filt, out, stride=(1, 1), params: Optional[TileParams] = None):
     """x: (N,H,W,C,4,4), filt: (K,R,S,C,4,4), out: (N,P,Q,K,4,4)."""
-    import torch
-
     N, H, W, C, MI, MK = x.shape
     K, R, S, C2, MK2, MJ = filt.shape
     assert (MI, MK, MJ, MK2) == (4, 4, 4, 4) and C == C2
     sh, sw = stride
     P, Q = (H - R) // sh + 1, (W - S) // sw + 1
-    assert tuple(out.shape) == (N, P, Q, K, 4, 4)
-    st = lib().mdh_mcc_capsule(N, H, W, C, K, R, S, sh, sw, _dev(x, torch.float32, "x"), _dev(filt, torch.float32, "filt"),
-                               _dev(out, torch.float32, "out"), _pref(params), ctypes.c_void_p(_stream()))
+    assert out.shape == (N, P, Q, K, 4, 4)
+    st = lib().mdh_mcc_capsule(N, H, W, C, K, R, S, sh, sw, _dev(x, _F32, "x"), _dev(filt, _F32, "filt"),
+                               _dev(out, _F32, "out"), _pref(params), _stream())
     _check(st, "mdh_mcc_capsule")
     return out
 
 
 def mdh_scan(x, out, params: Optional[TileParams] = None, workspace=None):
     """Row-wise inclusive prefix sums of the (R, n) matrix x (a vector counts as one row)."""
-    import torch
-
     R, n = (1, x.numel()) if x.dim() == 1 else x.shape
     assert out.numel() == x.numel()
     wp, wb = _ws(workspace)
-    st = lib().mdh_scan(R, n, _dev(x, torch.float32, "x"), _dev(out, torch.float32, "out"), _pref(params), wp, wb,
-                        ctypes.c_void_p(_stream()))
+    st = lib().mdh_scan(R, n, _dev(x, _F32, "x"), _dev(out, _F32, "out"), _pref(params), wp, wb,
+                        _stream())
     _check(st, "mdh_scan")
     return out
 
@@ -387,19 +363,17 @@ def mdh_scan_timed_out(x, params: Optional[TileParams] = None, workspace=None) -
     R, n = (1, x.numel()) if x.dim() == 1 else x.shape
     wp, _ = _ws(workspace)
     flag = ctypes.c_int32(0)
-    _check(lib().mdh_scan_timed_out(R, n, _pref(params), wp, ctypes.c_void_p(_stream()), ctypes.byref(flag)),
+    _check(lib().mdh_scan_timed_out(R, n, _pref(params), wp, _stream(), ctypes.byref(flag)),
            "mdh_scan_timed_out")
     return bool(flag.value)
 
 
 def mdh_matvec(A, x, y, params: Optional[TileParams] = None, workspace=None):
-    import torch
-
     M, K = A.shape
     assert x.numel() == K and y.numel() == M
     wp, wb = _ws(workspace)
-    st = lib().mdh_matvec(M, K, _dev(A, torch.float32, "A"), _dev(x, torch.float32, "x"), _dev(y, torch.float32, "y"),
-                          _pref(params), wp, wb, ctypes.c_void_p(_stream()))
+    st = lib().mdh_matvec(M, K, _dev(A, _F32, "A"), _dev(x, _F32, "x"), _dev(y, _F32, "y"),
+                          _pref(params), wp, wb, _stream())
     _check(st, "mdh_matvec")
     return y
 
