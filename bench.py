@@ -260,13 +260,14 @@ def bench_mcc(torch, mdh, W, name, steps, warmup, cpu):
     o = torch.empty((cfg.N, P, Q, cfg.K), dtype=torch.float32, device="cuda")
     sizes = (cfg.N, P, Q, cfg.K, cfg.C, cfg.R, cfg.S, cfg.stride[0], cfg.stride[1])
     ws = _ws(torch, mdh, mdh.MDH_MCC, sizes)
-    sliced = mdh.mdh_default_params(mdh.MDH_MCC, sizes).prt[2][4] == 8  # values carried as three bf16 values
+    few = cfg.C <= 8  # s and c walked as one dimension; a call without a table carries the values as three bf16 values there
+    sliced = few or mdh.mdh_default_params(mdh.MDH_MCC, sizes).prt[2][4] == 8
     ms, wall = _events_ms(torch, lambda: mdh.mdh_mcc(x, f, o, cfg.stride, None, ws), steps, warmup)
     flop = 2.0 * cfg.N * P * Q * cfg.K * cfg.C * cfg.R * cfg.S
     tf = flop / ms / 1e9
     res = {
         "value": flop / wall / 1e6, "unit": "GFLOP/s", "ms_per_step": wall, "kernel_ms": ms, "dtype": "f32",
-        "kernel": "mcc_flat_kernel" if cfg.C <= 8 else "mcc_split_kernel" if sliced else "mcc_kernel",
+        "kernel": "mcc_flat_split_kernel" if few else "mcc_split_kernel" if sliced else "mcc_kernel",
         "roofline": _mfma_roofline(tf, sliced, TRAFFIC_BYTES.get(name)),
         "algorithmic_flop": flop,
         "algorithmic_bytes": 4 * (x.numel() + f.numel() + o.numel()),
@@ -299,17 +300,17 @@ def bench_prl(torch, mdh, W, name, steps, warmup, cpu):
     s = torch.empty(cfg.nA, dtype=torch.int32, device="cuda")
     i = torch.empty(cfg.nA, dtype=torch.int32, device="cuda")
     ws = _ws(torch, mdh, mdh.MDH_CUSTOM_REDUCE, sizes)
-    before = valu_calibration(torch, mdh, kinds=("prl_fast_mix",))
+    before = valu_calibration(torch, mdh, kinds=("add_u32_vgpr",))
     ms, wall = _events_ms(torch, lambda: mdh.mdh_custom_reduce(A, B, wp, wm, s, i, None, ws), steps, warmup)
-    after = valu_calibration(torch, mdh, kinds=("prl_fast_mix",))
+    after = valu_calibration(torch, mdh, kinds=("add_u32_vgpr",))
     pairs = float(cfg.nA) * cfg.nB
-    per_pair = VALU_PER_PAIR[name]  # SQ_INSTS_VALU of this kernel x 64 lanes / pairs
+    per_pair = VALU_PER_PAIR[name]  # SQ_INSTS_VALU of these kernels x 64 lanes / pairs
     tops = pairs * per_pair / ms / 1e9
     nbytes = 4 * (A.numel() + B.numel() + 2 * cfg.nF + 2 * cfg.nA)
     res = {
         "value": pairs / wall / 1e6, "unit": "Gpairs/s", "ms_per_step": wall, "kernel_ms": ms, "dtype": "i32",
-        "kernel": "prl_fast_kernel + combine_maxidx_kernel",
-        "roofline": _alu_roofline(tops, before, after, TRAFFIC_BYTES.get(name), "prl_fast_mix"),
+        "kernel": "prl_bits_prep_kernel + prl_bits_kernel + prl_bits_finish_kernel",
+        "roofline": _alu_roofline(tops, before, after, TRAFFIC_BYTES.get(name), "add_u32_vgpr"),
         "lane_ops_per_pair": per_pair,
         "algorithmic_bytes": nbytes,
         "hbm_GBs_algorithmic": nbytes / ms / 1e6,

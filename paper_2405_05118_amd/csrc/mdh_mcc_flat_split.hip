@@ -13,9 +13,11 @@
 // overlap between taps and pixels comes from L1 -- and is split there: 40 vector instructions a step beside 6 NI matrix
 // instructions of 32 cycles.  Splitting it once into LDS would need eight consecutive 16-bit values from any 2-byte
 // boundary.
-// us per call, the kernel on fp32 instructions / this one: 16 x 230 x 230 x 3 -> 64, 7 x 7, stride 2: 45.6 / 32.9 (matrix
-// instructions alone 25 / 10.8); 14 x 178 x 203 x 2 -> 56, 7 x 7: 97 / 51.  Bound by the vector instructions of the split:
-// a step has 54 of them, and about four are free beside each matrix instruction.
+// us per call, the kernel on fp32 instructions / this one: 16 x 230 x 230 x 3 -> 64, 7 x 7, stride 2: 45.6 / 33 (matrix
+// instructions alone 25 / 11, stores 10); 14 x 178 x 203 x 2 -> 56, 7 x 7: 97 / 51.  Of the first one's time the matrix
+// pipe is busy for 0.30, vector instructions issue for 0.35, the address unit is busy for 0.39: latency between them.  The
+// patch split once into LDS, each wavefront its own, took 33.9 (one workgroup a compute unit instead of two), the next
+// block's loads ahead of this block's stores 35.3.
 #include "mdh_split.h"
 
 namespace mdh {
