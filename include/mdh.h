@@ -309,7 +309,9 @@ mdh_status mdh_mcc(int64_t N, int64_t H, int64_t W, int64_t C, int64_t K, int64_
  *   int32.  Integer arithmetic: the result is unique and reproduced bit-exactly.
  *   If B is split over workgroups (prt[MDH_L_WG][b] = S > 1) the S partial
  *   (score,index) pairs go to `workspace` (2*S*nA int32) and a second kernel
- *   combines them.
+ *   combines them.  Large products with the default's parts evaluate bounds on
+ *   bit maps of the records first and score few pairs; they keep what they need
+ *   in the same workspace.
  */
 mdh_status mdh_custom_reduce(int64_t nA, int64_t nB, int32_t nF, const int32_t* A,
                              const int32_t* B, const int32_t* w_agree, const int32_t* w_disagree,

@@ -123,3 +123,39 @@ def test_ever_better_records():
     A[:] = 0
     B = B[np.argsort(np.where(B == 0, wp, wm).sum(axis=1), kind="stable")]
     check(A, B, wp, wm)
+
+
+# captured, replayed on new records and weights with eager calls in between; the static scratch array's entry point too
+@pytest.mark.gpu
+def test_replays_and_static_scratch():
+    nF, nA = 8, 2000
+    sets = [inputs(nF, nA, top, 20 + top) for top in (3, 60, 7, 1 << 28)]
+    nB = len(sets[0][1])
+    dev = [torch.empty(n, dtype=torch.int32, device="cuda") for n in ((nA, nF), (nB, nF), (nF,), (nF,))]
+    n = mdh.mdh_workspace_size(mdh.MDH_CUSTOM_REDUCE, (nA, nB, nF))
+    ws = torch.empty(n // 4, dtype=torch.int32, device="cuda")
+    out = [torch.empty(nA, dtype=torch.int32, device="cuda") for _ in range(4)]
+
+    def fill(k):
+        for d, x in zip(dev, sets[k]):
+            d.copy_(torch.from_numpy(x))
+
+    fill(0)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        mdh.mdh_custom_reduce(*dev, out[0], out[1], None, ws)
+    side.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        mdh.mdh_custom_reduce(*dev, out[0], out[1], None, ws)
+    torch.cuda.synchronize()
+    for k in (1, 2, 3, 0):
+        fill(k)
+        mdh.mdh_custom_reduce_static(*dev, out[2], out[3])
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        want = oracle.custom_reduce(*sets[k])
+        for o, w in zip(out, want * 2):
+            assert np.array_equal(o.cpu().numpy(), w), k
