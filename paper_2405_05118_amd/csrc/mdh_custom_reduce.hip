@@ -12,6 +12,7 @@
 //   VGPR layer      : RA records of A per lane, held in registers for the whole kernel
 //   HBM layer       : nB/(S*WB) records of B, sequential; a record of B is the same for all
 //                     lanes of a wavefront, so it is fetched with scalar loads into SGPRs
+// (large products with the default's workgroup score few of the pairs: mdh_custom_reduce_bits.hip)
 // Re-composition of b with max_idx: in registers over a lane's sequential parts; across the
 // WB wavefronts in LDS; across the S workgroups through a device-memory workspace and a
 // second kernel (workgroup results combine in device memory only).

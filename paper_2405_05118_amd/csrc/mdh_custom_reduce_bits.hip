@@ -6,12 +6,12 @@
 // of the chunk that agree with it in that field -- or collide with it, so a map may hold too many records, never too few.
 //
 // Upper bound of a score, for 32 records at a time: every field has a whole weight q_f in [0, 15], q_f = 0 unless agreeing
-// raises the score, sum_f q_f <= 62.  The maps are added up as bits, plane i of the sum holding bit i of 32 records' sums
+// raises the score, sum_f q_f <= 30.  The maps are added up as bits, plane i of the sum holding bit i of 32 records' sums
 // u = sum_f q_f [slots agree]: a full adder is two three-input bit operations, and the constant q_f, the same for every
 // lane, selects code without the operations its zero bits do not need.
 // What u has to reach follows from the 2^nF ways to agree: most[u] = the largest score among those with a sum of at most
 // u, so no record with u < t(s) = min { u : most[u] > s } scores more than s.  t comes from the best record so far, the
-// comparison u >= t is six more bit operations, and the few records that pass are scored exactly, from the values
+// comparison u >= t is five more bit operations, and the few records that pass are scored exactly, from the values
 // themselves and in the arithmetic of the definition.  The result is that of the definition for any values and weights;
 // only the time depends on them.
 //
