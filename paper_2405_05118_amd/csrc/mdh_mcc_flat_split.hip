@@ -4,20 +4,27 @@
 // As there, the dimensions s and c of a filter row r are one dimension sc of S*C consecutive values, in the input and in
 // the filter.  An operand of v_mfma_f32_32x32x16_bf16 holds eight consecutive k of a row per lane, so sc is walked in
 // chunks of eight, ceil(S*C/8) of them a filter row, filled up with zeros in the filter: a 7 x 7 filter on three channels
-// takes 11 steps of two chunks (66 instructions of 32 cycles) where the fp32 instructions take 77 of 64.
+// takes 11 steps of two chunks (88 instructions of 32 cycles) where the fp32 instructions take 77 of 64.
+//
+// Precision.  Sums of a filter with many zeros have few terms, and few roundings on the fp32 instructions: one per term
+// that is not zero.  Six products a step in one accumulator round six times a step, whatever the terms are.  So the sums
+// of h h', which is exact in 16 bits, are kept apart -- a step rounds them at most once, and not if its terms are zeros --
+// and the seven other products, below 2^-8 of those, go to sums of their own, which are added at the end (l l', below 2^-34,
+// is left out): no more roundings than terms.  Error against 64 bits, relative 2-norm in units of 2^-24, 7 x 7 x 3, n taps of
+// 147 not zero, fp32 instructions / these / six products in one accumulator: n = 1 0.42 / 0.42 / 0.60 (largest 1.0 / 1.0 /
+// 2.5), 2 0.53 / 0.43 / 0.83, 8 0.90 / 0.48 / 1.65, 24 1.5 / 0.64 / 2.5, 64 2.4 / 0.89 / 3.0.
 //
 // De-composition, dims (n,p,q,k,c,r,s): a wavefront owns a block of 32 pixels (32/QB rows x QB columns) and NI x 32
 // channels at a time; a workgroup of eight wavefronts keeps the filter slice of its NI x 32 channels in LDS, split once,
 // and walks its share of the blocks of all images, its wavefronts taking them in turn.  There is no barrier after the
 // staging of the filter.  The input goes from memory to registers, two steps ahead -- 32 bytes at any 4-byte boundary, the
-// overlap between taps and pixels comes from L1 -- and is split there: 40 vector instructions a step beside 6 NI matrix
+// overlap between taps and pixels comes from L1 -- and is split there: 40 vector instructions a step beside 8 NI matrix
 // instructions of 32 cycles.  Splitting it once into LDS would need eight consecutive 16-bit values from any 2-byte
 // boundary.
-// us per call, the kernel on fp32 instructions / this one: 16 x 230 x 230 x 3 -> 64, 7 x 7, stride 2: 45.6 / 33 (matrix
-// instructions alone 25 / 11, stores 10); 14 x 178 x 203 x 2 -> 56, 7 x 7: 97 / 51.  Of the first one's time the matrix
-// pipe is busy for 0.30, vector instructions issue for 0.35, the address unit is busy for 0.39: latency between them.  The
-// patch split once into LDS, each wavefront its own, took 33.9 (one workgroup a compute unit instead of two), the next
-// block's loads ahead of this block's stores 35.3.
+// us per call, the kernel on fp32 instructions / this one: 16 x 230 x 230 x 3 -> 64, 7 x 7, stride 2: 45.7 / 41.5 (36 with
+// six products); 14 x 178 x 203 x 2 -> 56, 7 x 7: 94 / 60 (51).  Tried with six products: the patch split once into LDS, each
+// wavefront its own, one workgroup a compute unit instead of two, 33.9 (then 33.0), the next block's loads ahead of this
+// block's stores 35.3; with eight: the split at the start of its own step instead of in the shadow of the one before 43.
 #include "mdh_split.h"
 
 namespace mdh {
@@ -120,11 +127,11 @@ __global__ __launch_bounds__(kNT, 4) void mcc_flat_split_kernel(FlatConv g) {
     const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(img), 0, (int)(unsigned)min(room, (int64_t)0xfffffffc), 0x00027000);
     const int pix = min(p, g.P - 1) * g.sh * WC + min(q, g.Q - 1) * g.sw * g.C;
 
-    f16 acc[NI];
+    f16 acc[NI], low[NI];  // sums of h h'; of the other products
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[ni][e] = 0.f;
+      for (int e = 0; e < 16; ++e) acc[ni][e] = low[ni][e] = 0.f;
     float top = 0.f;  // largest magnitude of the lane's share of the window
 
     // the two chunks of the step that `load` takes, one per half of the wavefront
@@ -140,24 +147,21 @@ __global__ __launch_bounds__(kNT, 4) void mcc_flat_split_kernel(FlatConv g) {
       if (c == g.CH) c = 0, at += WC - g.CH * 8;
     };
     auto step = [&](float (&next)[8], const u4 (&y)[3], u4 (&yn)[3], int t, bool more) {
-      u4 x[3][NI];
       const int ch = 2 * t + lh;
       const char* const f = lds + (ch * BN + (l32 ^ (ch & 15))) * 16;
 #pragma unroll
-      for (int s = 0; s < 3; ++s)
+      for (int s = L; s >= H; --s) {
+        u4 x[NI];
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni) x[s][ni] = *(const u4*)(f + s * slice + ni * 512);
-      auto mma = [&](int sx, int sy) {
+        for (int ni = 0; ni < NI; ++ni) x[ni] = *(const u4*)(f + s * slice + ni * 512);
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni) acc[ni] = mfma(x[sx][ni], y[sy], acc[ni]);
-      };
-      // the smaller products first
-      mma(Mid, Mid);
-      mma(L, H);
-      mma(H, L);
-      mma(Mid, H);
-      mma(H, Mid);
-      mma(H, H);
+        for (int sy = L - (s == L); sy >= H + (s == H); --sy)
+#pragma unroll
+          for (int ni = 0; ni < NI; ++ni) low[ni] = mfma(x[ni], y[sy], low[ni]);
+        if (s == H)
+#pragma unroll
+          for (int ni = 0; ni < NI; ++ni) acc[ni] = mfma(x[ni], y[H], acc[ni]);
+      }
       split(next, yn, top);
       if (more) load(next);
       // (otherwise the next step's magnitudes are taken at the top of this one, and wait for loads just issued)
@@ -176,6 +180,11 @@ __global__ __launch_bounds__(kNT, 4) void mcc_flat_split_kernel(FlatConv g) {
     }
     step(r1, ya, yb, t, false);
     if (t + 1 < g.T) step(r0, yb, ya, t + 1, false);
+
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[ni][e] += low[ni][e];
 
     // values the split does not carry (mdh_split.h)
     const int kw = k0;

@@ -858,18 +858,21 @@ static bool mcc_flat_split_sizes(const int64_t* s) {
 
 // Does a call without a table go to the few-channel kernel that splits, and in which block?  (The default's table stays
 // that of the fp32 instructions: bit for bit the results it always had.)
-// us, against those: 16 x 230 x 230 x 3 -> 64, 7 x 7, stride 2: 32.9 / 45.6, one image 7.6 / 9.0; 16 x 200 x 170 x 3 ->
-// 64, 5 x 5: 43 / 74; 14 x 178 x 203 x 2 -> 56, 7 x 7: 51 / 97; 16 x 224 x 224 x 3 -> 64, 3 x 3: 52.3 / 57.1.  The line:
-// its matrix instructions have to take less than three quarters of the time (7 x 7 on one channel 0.43, 3 x 3 on one or
-// two 1.0 / 0.75: equal times), and from 18 terms on its error against 64 bits is the smaller one (18 terms 6.0e-8 /
-// 8.0e-8, 27 8.7e-8 / 9.4e-8, 147 1.9e-7 / 2.2e-7).  64 channels a wavefront share the split of the input, 32 leave more
-// wavefronts: one image of the first layer 7.6 with 32, 10.4 with 64.
+// The line: its matrix instructions have to take at most two thirds of the time of the fp32 ones, four fifths where there
+// are fewer than 2^24 outputs.  us, against those, at 16 x 224 x 224 -> 64 / the same with stride 2 / 8 x 70 x 90 -> 24:
+//   7 x 7 x 3 (0.57) 127 : 143 / 39 : 45 / 11.2 : 12.1     3 x 3 x 4 (0.67) 57 : 58 / 19.9 : 23.3 / 7.0 : 9.0
+//   5 x 5 x 4 (0.64) 101 : 106 / 31 : 37 / 9.5 : 13.0      3 x 3 x 3 (0.80) 59 : 54 / 19.9 : 21.5 / 7.0 : 8.8
+//   5 x 5 x 2 (0.80) 74 : 68 / 23 : 26 / 8.1 : 10.2        3 x 3 x 2 (0.89) 50 : 45 / 18.0 : 17.4 / 6.6 : 7.5
+// one image of 230 x 230 x 3 -> 64, 7 x 7, stride 2: 8.8 : 9.0.  Below 18 terms the outputs' stores are most of a call (3 x
+// 3 x 1: 51 : 43).  64 channels a wavefront share the split of the input, 32 leave more wavefronts: one image of the first
+// layer 7.6 with 32, 10.4 with 64 (with six products).
 static void mcc_flat_split_rule(const int64_t* s, MccPlan* out) {
   if (!mcc_flat_split_sizes(s)) return;
   const int64_t P = s[1] > 0 ? s[1] : 1, Q = s[2] > 0 ? s[2] : 1, SC = s[6] * s[4];
   // cycles of the matrix instructions of 32 pixels x 32 channels
-  const int64_t split = cdiv(s[5] * cdiv(SC, 8), 2) * 6 * 32, fp32 = s[5] * (SC / 8 * 4 + cdiv(SC % 8, 2)) * 64;
-  if (s[5] * SC < 18 || split * 4 > fp32 * 3) return;
+  const int64_t split = cdiv(s[5] * cdiv(SC, 8), 2) * 8 * 32, fp32 = s[5] * (SC / 8 * 4 + cdiv(SC % 8, 2)) * 64;
+  const bool few = (double)s[0] * P * Q * s[3] < (double)(1 << 24);
+  if (s[5] * SC < 18 || split * 15 > fp32 * (few ? 12 : 10)) return;
   int64_t area = -1;
   int tq = 0;
   for (int t : {16, 32, 8}) {  // the block that pads the image least

@@ -123,3 +123,55 @@ def test_tables():
     for g in got:
         close(g, want, f[0].size)
     assert any(np.array_equal(g, run(x, f, 1)) for g in got)
+
+
+def rel(got, want):
+    return np.linalg.norm(got - want) / np.linalg.norm(want)
+
+
+def both_tables(x, f):
+    """The tables with fp32 instructions and with slices that a call is given first."""
+    (N, H, W, C), (K, R, S, _) = x.shape, f.shape
+    s = (N, H - R + 1, W - S + 1, K, C, R, S, 1, 1)
+    few = [p for p in (mdh.mdh_candidate(mdh.MDH_MCC, s, i) for i in range(mdh.mdh_num_candidates(mdh.MDH_MCC, s))) if p.blk[4] == 1]
+    return [p for p in few if p.in_region[0] != B.MR_HBM][0], [p for p in few if p.in_region[0] == B.MR_HBM]
+
+
+# Sums of few terms: filters with n taps that are not zero, anywhere, one step after the other (16 values) or side by side,
+# and inputs with few values that are not zero.  A step rounds a sum at most once, and the sum of all smaller products once
+# more, so n terms are rounded no more often than by n multiply-adds; 4 % is what 10^5 outputs leave open (one term: the same
+# error, but for a sum that lies within 2^-8 of a tie).
+@pytest.mark.parametrize("where", ["anywhere", "steps", "together", "input"])
+@pytest.mark.parametrize("terms", [1, 2, 3, 6, 17, 40])
+def test_sums_of_few_terms(where, terms):
+    rng = np.random.default_rng(terms)
+    x, f = data(2, 38, 41, 3, 64, 7, 7)
+    if where == "input":
+        x = np.where(rng.random(x.shape) < terms / f[0].size, x, np.float32(0))
+    else:
+        n = f[0].size
+        for k in range(len(f)):
+            at = {"anywhere": rng.permutation(n)[:terms], "steps": (np.arange(terms) * 16 + rng.integers(n)) % n,
+                  "together": (np.arange(terms) + rng.integers(n)) % n}[where]
+            keep = np.zeros(n, bool)
+            keep[at] = True
+            f[k] = np.where(keep.reshape(f[k].shape), f[k], np.float32(0))
+    want = reference(x, f, 1)
+    fp32, split = both_tables(x, f)
+    limit = 1.04 * rel(run(x, f, 1, fp32), want)
+    for p in split + [None]:
+        assert rel(run(x, f, 1, p), want) <= limit
+
+
+# a filter of one tap: the product, rounded once, after a sum of the smaller products that is rounded 2^-8 as finely
+def test_one_tap():
+    x, f = data(2, 40, 41, 3, 40, 7, 7)
+    f[:] = 0
+    rng = np.random.default_rng(3)
+    taps = [(int(rng.integers(7)), int(rng.integers(7)), int(rng.integers(3))) for _ in f]
+    for k, t in enumerate(taps):
+        f[(k,) + t] = np.float32(0.3) if k == 0 else np.float32(rng.standard_normal())
+    got = run(x, f, 1)
+    for k, (r, s, c) in enumerate(taps):
+        want = x[:, r : r + 34, s : s + 35, c].astype(np.float64) * np.float64(f[k, r, s, c])
+        assert (np.abs(got[..., k] - want) <= 2.0**-24 * (1 + 2.0**-7) * np.abs(want)).all(), k
