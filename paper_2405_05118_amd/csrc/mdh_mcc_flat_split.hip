@@ -146,7 +146,7 @@ __global__ __launch_bounds__(kNT, 4) void mcc_flat_split_kernel(FlatConv g) {
       c = c1 + 1, at = at1 + 8;
       if (c == g.CH) c = 0, at += WC - g.CH * 8;
     };
-    auto step = [&](float (&next)[8], const u4 (&y)[3], u4 (&yn)[3], int t, bool more) {
+    auto step = [&](float (&next)[8], const u4 (&y)[3], u4 (&yn)[3], int t, float& top, bool more) {
       const int ch = 2 * t + lh;
       const char* const f = lds + (ch * BN + (l32 ^ (ch & 15))) * 16;
 #pragma unroll
@@ -175,11 +175,15 @@ __global__ __launch_bounds__(kNT, 4) void mcc_flat_split_kernel(FlatConv g) {
     load(r0);
     int t = 0;
     for (; t + 2 < g.T; t += 2) {
-      step(r1, ya, yb, t, true);
-      step(r0, yb, ya, t + 1, true);
+      step(r1, ya, yb, t, top, true);
+      step(r0, yb, ya, t + 1, top, true);
     }
-    step(r1, ya, yb, t, false);
-    if (t + 1 < g.T) step(r0, yb, ya, t + 1, false);
+    float next = top;  // (what the last step splits is not in the windows)
+    step(r1, ya, yb, t, next, false);
+    if (t + 1 < g.T) {
+      top = next;
+      step(r0, yb, ya, t + 1, next, false);
+    }
 
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni)

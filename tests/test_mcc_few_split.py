@@ -100,6 +100,16 @@ def test_small_magnitudes(where):
         close(got[:, 10:14, 10:14], want[:, 10:14, 10:14], f[0].size)
 
 
+# The row below the last windows is in none of them, whatever it holds: with an even number of chunks it is what a next step
+# would take.  The filter's middle slices would be lost to subnormal numbers.
+@pytest.mark.parametrize("value", [np.inf, np.nan, 3e38])
+def test_what_lies_below_the_windows(value):
+    x, f = data(1, 8, 40, 2, 33, 7, 7)
+    f *= np.float32(2.0**-118)
+    x[0, 7] = value
+    close(run(x, f, 2), reference(x, f, 2), f[0].size)
+
+
 # zeros are exact, and cost no second evaluation's rounding: a dead filter, a blank patch, a delta filter
 def test_zeros_and_single_products():
     x, f = data(2, 40, 41, 3, 40, 7, 7)
