@@ -652,11 +652,10 @@ struct Layout {
   PrlBitsHead* head;
 };
 
-// The head lies at the end of the workspace, in the last of the S parts' results, which the loop over fields (S - 1 parts)
-// leaves alone; keys and slots lie before it.
+// (keys and slots lie before the head)
 Layout layout(void* ws, int64_t nA, int S) {
   Layout l;
-  l.head = (PrlBitsHead*)((uintptr_t)((int32_t*)ws + 2 * (int64_t)S * nA) - sizeof(PrlBitsHead) & ~(uintptr_t)7);
+  l.head = prl_bits_head(ws, nA, S);
   l.keys = (unsigned long long*)(((uintptr_t)ws + 7) & ~(uintptr_t)7);
   l.slots = (unsigned*)(l.keys + nA);
   return l;

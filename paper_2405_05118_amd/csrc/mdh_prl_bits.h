@@ -57,6 +57,12 @@ struct PrlBitsHead {
   } found[kSearch];
 };
 
+// The head lies at the end of the workspace, in the last of the S parts' results, which the loop over fields (S - 1 parts)
+// leaves alone.  After a call its first word tells which of the two the result is from.
+inline PrlBitsHead* prl_bits_head(void* ws, int64_t nA, int S) {
+  return (PrlBitsHead*)(((uintptr_t)((int32_t*)ws + 2 * (int64_t)S * nA) - sizeof(PrlBitsHead)) & ~(uintptr_t)7);
+}
+
 // maps, records of the chunk, the largest scores of 32 sums, the flag, 16 queues, t of the records of A
 constexpr int64_t prl_bits_lds_bytes(int nF, int sets) {
   return kPrlMaps + 4ll * kPrlChunk * nF + 4 * 32 + 16 + 16 * 4 * kPrlQueue + 1024ll * sets;
