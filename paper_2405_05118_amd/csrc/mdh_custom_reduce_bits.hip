@@ -19,9 +19,12 @@
 // raised with atomicMax: the workgroups that walk other parts of B profit from one another's records.  What the result is
 // does not depend on when they see them: a record of an earlier part with an equal score has to pass (t(s - 1)).
 //
-// Slots that collide throughout or weights that q cannot tell apart would have too many records scored: a workgroup that
-// scores more than a few per step raises a flag and the others stop; the loop over fields, launched behind, starts only
-// if the flag is up (2^14 x 2^17 records of 8 fields, weights that wrap around: 1362 / 1320 us).
+// Slots that collide throughout or weights that q cannot tell apart would have too many records scored: a wavefront that
+// does (`limit`) raises a flag and the others stop; the loop over fields, launched behind, starts only if the flag is up.
+// us, that loop alone / a call that takes both: weights that wrap around, known before the walk, 2^14 x 2^17 records of 8
+// fields 1300 / 1350, 4096 x 2^16 202 / 233; B of eight different records 2^14 x 2^17 950 / 1180, 2^16 x 2^18 6850 / 7600;
+// slots that all collide 2^14 x 2^17 950 / 1160, 4096 x 2^16 158 / 380, 2^16 x 2^18 6860 / 7610; in the last quarter of
+// every part only, 2^14 x 2^17, 950 / 1500.  (32-bit hashes, none equal: 1300 / 480, 2^16 x 2^18 9990 / 3000.)
 //
 // Bound by the issue of vector instructions, 320 per 128 x 64 pairs of 8 fields (the loop over fields: 25.6 a pair and
 // lane).  us, the loop over fields / this: 2^16 x 2^18 records of 8 fields 6870 / 1030; 2^15 x 2^17 of 12 3010 / 550; 2^15 x
@@ -390,17 +393,23 @@ __global__ __launch_bounds__(kNT, 8) void prl_bits_kernel(const int* __restrict_
   }
   const unsigned long long q_all = (unsigned long long)__builtin_amdgcn_readfirstlane(q_high) << 32 |
                                    (unsigned)__builtin_amdgcn_readfirstlane(q_low);
-  // a field's share of the score; the weights are read again for every use, registers for them would be missing elsewhere
-  const int *agree = wp, *differ = wm;
-  auto again = [&] {
+  // Scores: what disagreeing everywhere makes, and what agreeing in a field adds (wraps around as the definition does).  The
+  // weights are read again for every use, registers for them would be missing elsewhere.  An odd number of fields is
+  // followed by one that adds nothing, with the last one's values.  (No branch on the number of fields: with one per field
+  // every load was waited for by itself, 4096 x 2^16 records whose slots all collide 710 -> 520 us.)
+  auto field = [&](int f) { return f < NF - 1 ? f : nF - 1; };
+  unsigned none, adds[NF];
+  auto weights = [&] {
     int zero;
     asm volatile("s_mov_b32 %0, 0" : "=s"(zero));
     zero = __builtin_amdgcn_readfirstlane(zero);
-    agree = wp + zero, differ = wm + zero;
-  };
-  auto share = [&](int f, bool same) {
-    const unsigned p = (unsigned)agree[min(f, nF - 1)], m = (unsigned)differ[min(f, nF - 1)];
-    return f < nF ? same ? p : m : 0u;
+    none = 0;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+      const unsigned m = (unsigned)wm[zero + field(f)], keep = f < NF - 1 || nF == NF ? ~0u : 0u;
+      adds[f] = ((unsigned)wp[zero + field(f)] - m) & keep;
+      none += m & keep;
+    }
   };
   // items of a chunk this thread puts into the maps: field and record stay the same from chunk to chunk
   // where the adder's code for each field is, a byte a field
@@ -455,10 +464,10 @@ __global__ __launch_bounds__(kNT, 8) void prl_bits_kernel(const int* __restrict_
       const int ai = (int)(e >> kPrlPartBits), b = c0 * kPrlChunk + (int)(e & ((1u << kPrlPartBits) - 1));
       const int* const ra = A + (int64_t)(a0 + ai) * nF;
       const int* const rb = B + (int64_t)b * nF;
-      again();
-      unsigned sc = 0;
+      weights();
+      unsigned sc = none;
 #pragma unroll
-      for (int f = 0; f < NF; ++f) sc += share(f, ra[min(f, nF - 1)] == rb[min(f, nF - 1)]);
+      for (int f = 0; f < NF; ++f) sc += ra[field(f)] == rb[field(f)] ? adds[f] : 0u;
       const unsigned long long k = key_of((int)sc, b);
       const int t = reach(k, behind), before = tl[ai];
       // (two lanes with one record of A: either t holds)
@@ -471,12 +480,13 @@ __global__ __launch_bounds__(kNT, 8) void prl_bits_kernel(const int* __restrict_
   fetch(c0);
   __syncthreads();
   if (*stop) return;
+  weights();
   for (int p = tid; p < 1 << nF; p += kNT) {
-    unsigned s = 0;
+    unsigned s = none;
     int u = 0;
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
-      s += share(f, p >> f & 1);
+      s += p >> f & 1 ? adds[f] : 0u;
       u += p >> f & 1 ? (int)(q_all >> (4 * f)) & 15 : 0;
     }
     atomicMax(&most[u], (int)s);
@@ -494,6 +504,10 @@ __global__ __launch_bounds__(kNT, 8) void prl_bits_kernel(const int* __restrict_
 
   // sets in which this wavefront has records of A
   const int mine = min(sets, max(0, (int)(((int64_t)nA - a0 - wave * 64 + kNT - 1) / kNT)));
+  // An iteration that scores takes about 280 cycles of a wavefront's issue, the loop over fields 27 times as much for the
+  // records of a step: so many a step that the rest still pays, a sixth of the loop's time for the whole walk on top (the
+  // start, at which little is known), and at least one step whose records all have to be scored.
+  const int limit = max(160, 4 * mine * (c1 - c0));
   for (int c = c0; c < c1; ++c) {
     // a bit of a map belongs to one thread: taking the last chunk's out and putting this one's in needs no barrier between
 #pragma unroll
@@ -575,10 +589,10 @@ __global__ __launch_bounds__(kNT, 8) void prl_bits_kernel(const int* __restrict_
         } while (lanes);
       } else {
         // many, as at the start of a part: each lane scores its next one, and leaves out those that no longer reach t
-        again();
+        weights();
         int ar[NF];
 #pragma unroll
-        for (int f = 0; f < NF; ++f) ar[f] = A[(int64_t)a * nF + min(f, nF - 1)];
+        for (int f = 0; f < NF; ++f) ar[f] = A[(int64_t)a * nF + field(f)];
         unsigned long long key = __hip_atomic_load(keys + a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         t = max(t, reach(key, behind - kPrlChunk));
 #pragma unroll 1
@@ -588,11 +602,11 @@ __global__ __launch_bounds__(kNT, 8) void prl_bits_kernel(const int* __restrict_
             if (todo) {
               const int r = w * 32 + __builtin_ctz(todo);
               todo &= todo - 1;
-              unsigned sc = 0;
+              unsigned sc = none;
 #pragma unroll
-              for (int f = 0; f < NF; ++f) sc += share(f, ar[f] == rec[r * nF + min(f, nF - 1)]);
+              for (int f = 0; f < NF; ++f) sc += ar[f] == rec[r * nF + field(f)] ? adds[f] : 0u;
               const unsigned long long k = key_of((int)sc, c * kPrlChunk + r);
-              if (k > key) {
+              if (k >= key) {  // (the best record itself: those behind it have to score more)
                 key = k;
                 t = max(t, reach(key, behind));
                 todo &= at_least(s, 0, t);
@@ -611,11 +625,9 @@ __global__ __launch_bounds__(kNT, 8) void prl_bits_kernel(const int* __restrict_
         }
       }
       scored += here;
-      if (scored > 24 * steps + 256) {
-        if (lane == 0) {
-          *stop = 1;
-          __hip_atomic_store(&head->stop, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+      if (scored > limit + 24 * steps) {
+        // one store a workgroup: 8192 wavefronts that store to one address take 250 us
+        if (lane == 0 && !atomicExch(stop, 1)) __hip_atomic_store(&head->stop, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         break;
       }
     }

@@ -152,6 +152,16 @@ def test_given_up_on_the_way(plan, nF, nA, where):
     check(plan, A, B, wp, wm, loop=1)
 
 
+# The first record of B is the best but for few, so a bound that lets what is as good as it pass lets all of B pass: four sets
+# of records of A, each with a first chunk to be scored, are no reason to give up.
+@pytest.mark.gpu
+def test_first_record_among_the_best(plan):
+    rng = np.random.default_rng(8)
+    A, B = (np.stack([rng.integers(0, a, n) for a in (4, 16, 64, 128)], 1).astype(np.int32) for n in (1 << 16, 1 << 17))
+    wp, wm = rng.integers(-(1 << 16), 1, 4).astype(np.int32), rng.integers(1, 1 << 16, 4).astype(np.int32)
+    check(plan, A, B, wp, wm, loop=0)
+
+
 # captured, replayed on new records and weights with eager calls in between; the static scratch array's entry point too
 @pytest.mark.gpu
 def test_replays_and_static_scratch():
