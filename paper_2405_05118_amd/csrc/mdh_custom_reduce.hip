@@ -169,12 +169,13 @@ __global__ __launch_bounds__(WA* WB * 64) void prl_kernel(
 // sum_f max(|w_agree_f|, |w_disagree_f|) < 2^24 and every |w_disagree_f - w_agree_f| <= 2^24 (all partial sums, and
 // what a field that differs adds, are then integers fp32 holds exactly).
 // The result is the unique (score, index) of the definition, bit for bit, on either path.
-template <int NF, int RA, int WB, int WA>
+// GATED: behind the bit maps (mdh_custom_reduce_bits.hip), for records that they gave up on.
+template <int NF, int RA, int WB, int WA, bool GATED>
 __global__ __launch_bounds__(WA* WB * 64) void prl_fast_kernel(
     const int* __restrict__ A, const int* __restrict__ B, const int* __restrict__ wp,
     const int* __restrict__ wm, int* __restrict__ out_s, int* __restrict__ out_i,
     int* __restrict__ ws, int nA, int nB, int S, int bchunk, const int* __restrict__ gate) {
-  if (gate && !*gate) return;  // the bit maps did it
+  if (GATED && !*gate) return;
   constexpr int BI = (NF > 10 ? 4 : 8) / RA;  // records of B interleaved per step: RA * BI independent chains
   static_assert(RA == 2 || RA == 4, "eight or four chains per lane");
   __shared__ int red_s[WB > 1 ? (WB - 1) * WA * RA * 64 : 1];
@@ -439,7 +440,7 @@ mdh_status launch_fast(const PrlPlan& pl, int64_t nA, int64_t nB, const int32_t*
       mdh_status r = launch_prl_bits(pl.S, nA, nB, NF, A, B, wp, wm, ws, st);
       if (r != MDH_OK) return r;
       const int S = pl.S - 1;
-      hipLaunchKernelGGL((prl_fast_kernel<NF, RA, WB, WA>), dim3((unsigned)(cdiv(nA, 64 * RA) * S)), dim3(WA * WB * 64), 0, st,
+      hipLaunchKernelGGL((prl_fast_kernel<NF, RA, WB, WA, true>), dim3((unsigned)(cdiv(nA, 64 * RA) * S)), dim3(WA * WB * 64), 0, st,
                          A, B, wp, wm, score, index, (int*)ws, (int)nA, (int)nB, S, (int)cdiv(nB, (int64_t)S * WB),
                          prl_bits_gate(ws, nA, pl.S));
       if ((r = launch_status()) != MDH_OK) return r;
@@ -451,7 +452,7 @@ mdh_status launch_fast(const PrlPlan& pl, int64_t nA, int64_t nB, const int32_t*
   if (nblocks > 0x7fffffff) return MDH_ERR_SIZE;
   const int64_t bchunk = cdiv(nB, (int64_t)pl.S * WB);
   clear_stale_error();
-  hipLaunchKernelGGL((prl_fast_kernel<NF, RA, WB, WA>), dim3((unsigned)nblocks), dim3(WA * WB * 64), 0, st, A, B,
+  hipLaunchKernelGGL((prl_fast_kernel<NF, RA, WB, WA, false>), dim3((unsigned)nblocks), dim3(WA * WB * 64), 0, st, A, B,
                      wp, wm, score, index, (int*)ws, (int)nA, (int)nB, pl.S, (int)bchunk, (const int*)nullptr);
   mdh_status r = launch_status();
   if (r != MDH_OK || pl.S <= 1) return r;
