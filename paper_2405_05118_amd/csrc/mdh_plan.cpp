@@ -972,6 +972,9 @@ mdh_status plan_mcc(const int64_t* s, const mdh_tile_params* p, MccPlan* out) {
     pl.split = p->in_region[0] == MDH_MR_HBM;
     if ((pl.TQ != 16 && pl.TQ != 32 && !(pl.split && pl.TQ == 8)) || !flat_input_ok(s)) return MDH_ERR_UNSUPPORTED;
     if (pl.split && (!mcc_flat_split_sizes(s) || p->strided || p->prt[MDH_L_HBM][2] != 1)) return MDH_ERR_UNSUPPORTED;
+    // tiles beyond any LDS, and beyond 32 bits further on
+    if (p->prt[MDH_L_VGPR][3] > 4096 || p->prt[MDH_L_WAVE][3] > 4096) return MDH_ERR_TILE_RESOURCES;
+    if (p->prt[MDH_L_VGPR][1] > 4096 || p->prt[MDH_L_WAVE][1] > 4096) return pl.split ? MDH_ERR_UNSUPPORTED : MDH_ERR_TILE_RESOURCES;
     pl.WM = p->prt[MDH_L_VGPR][1] * 32;
     pl.TP = p->prt[MDH_L_WAVE][1] * p->prt[MDH_L_VGPR][1] * (32 / pl.TQ);
     pl.CK = 0;

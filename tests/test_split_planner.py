@@ -35,6 +35,30 @@ def test_tables_whose_products_wrap_are_refused():
     assert r.returncode == 0 and r.stdout.endswith("all refused\n"), (r.returncode, r.stdout[-200:], r.stderr[-500:])
 
 
+# the tables of the few-channel kernels, with fp32 instructions and with slices
+FEW = """
+import paper_2405_05118_amd as mdh
+sizes = (2, 40, 43, 64, 3, 7, 7, 1, 1)
+cands = [mdh.mdh_candidate(mdh.MDH_MCC, sizes, i) for i in range(mdh.mdh_num_candidates(mdh.MDH_MCC, sizes))]
+for region in (0, 1):
+    p = next(p for p in cands if p.blk[4] == 1 and p.in_region[0] == region)
+    for layer in range(6):
+        for d in range(p.D):
+            for v in [1 << b for b in range(12, 31)] + [(1 << b) + 1 for b in range(25, 31)] + [(1 << 31) - 1]:
+                q = p.copy()
+                q.ragged = 1
+                q.prt[layer][d] = v
+                print(region, layer, d, v, flush=True)
+                assert mdh.mdh_validate_params(mdh.MDH_MCC, sizes, q) != 0
+print("all refused")
+"""
+
+
+def test_few_channel_tables_whose_products_wrap_are_refused():
+    r = subprocess.run([sys.executable, "-c", FEW], cwd=ROOT, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0 and r.stdout.endswith("all refused\n"), (r.returncode, r.stdout[-200:], r.stderr[-500:])
+
+
 # the default's tile in column bands, and what the small-M kernel stands in front of, where the split kernels or parts
 # of k have become the default: WG, WAVE and VGPR parts of (i, j, k), and the loop order's first entry
 @pytest.mark.parametrize("sizes, wg, wave, vgpr, first", [
