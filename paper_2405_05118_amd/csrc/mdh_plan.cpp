@@ -851,9 +851,11 @@ static bool mcc_split_default(const int64_t* s, int TQ, int S, MccPlan* out) {
   return best >= 0;
 }
 
-// the few-channel kernel that splits addresses an image with 32 bits
+// the few-channel kernel that splits addresses an image with 32 bits (a stride that is not used may have any value: the
+// product of what the sizes allow is no whole number of 64 bits)
 static bool mcc_flat_split_sizes(const int64_t* s) {
-  return flat_input_ok(s) && ((s[1] > 0 ? s[1] : 1) * s[7] + s[5]) * ((s[2] > 0 ? s[2] : 1) * s[8] + s[6]) * s[4] < (1 << 28);
+  const double rows = (double)(s[1] > 0 ? s[1] : 1) * s[7] + s[5], columns = (double)(s[2] > 0 ? s[2] : 1) * s[8] + s[6];
+  return flat_input_ok(s) && rows * columns * s[4] < (double)(1 << 28);
 }
 
 // Does a call without a table go to the few-channel kernel that splits, and in which block?  (The default's table stays

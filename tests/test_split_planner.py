@@ -59,6 +59,17 @@ def test_few_channel_tables_whose_products_wrap_are_refused():
     assert r.returncode == 0 and r.stdout.endswith("all refused\n"), (r.returncode, r.stdout[-200:], r.stderr[-500:])
 
 
+# the few-channel kernel on slices is for images of less than 2^28 values: the largest that the sizes allow counts, also where
+# one output a row or column leaves the stride open, up to products beyond 64 bits
+@pytest.mark.parametrize("P, Q, C, stride, offered", [(112, 112, 3, 2, True), (1, 1, 3, 9000, True), (1, 1, 3, 10000, False),
+                                                      (9000, 9000, 4, 1, False), (1, 1, 1, 2**31 - 1, False), (1, 1, 3, 2**31 - 1, False),
+                                                      (2, 2, 1, 2**31 - 1, False), (1, 1, 2, 2**30 + 2**29, False)])
+def test_few_channel_images_beyond_32_bits(P, Q, C, stride, offered):
+    sizes = (1, P, Q, 64, C, 7, 7, stride, stride)
+    tables = [mdh.mdh_candidate(mdh.MDH_MCC, sizes, i) for i in range(mdh.mdh_num_candidates(mdh.MDH_MCC, sizes))]
+    assert any(p.blk[4] == 1 and p.in_region[0] == 0 for p in tables) == offered
+
+
 # the default's tile in column bands, and what the small-M kernel stands in front of, where the split kernels or parts
 # of k have become the default: WG, WAVE and VGPR parts of (i, j, k), and the loop order's first entry
 @pytest.mark.parametrize("sizes, wg, wave, vgpr, first", [
