@@ -196,9 +196,19 @@ mdh_status mdh_part_offset(int64_t N, int32_t L, const int32_t* P, const int32_t
  * `sizes` holds the D index-space extents in the dimension order listed at
  * mdh_instance; for MDH_MCC two more entries follow: stride_h, stride_w; for
  * MDH_CUSTOM_REDUCE one more entry follows: nF (read by mdh_tune only).
- * Host only; writes *out.
+ * Host only; writes *out.  For few-channel MCC (blk[c] = 1) that is the table with
+ * fp32 instructions, the same for stored tables as ever; a call without a table may
+ * run another one there: see mdh_call_params.
  */
 mdh_status mdh_default_params(mdh_instance inst, const int64_t* sizes, mdh_tile_params* out);
+
+/*
+ * The configuration that a call with params == NULL runs, given the workspace that
+ * mdh_workspace_size asks for: mdh_default_params but for few-channel MCC, where it
+ * may be the table of the kernel on bf16 slices (mdh_mcc).  A call with this table
+ * has the results of a call without one, bit for bit.  Host only; writes *out.
+ */
+mdh_status mdh_call_params(mdh_instance inst, const int64_t* sizes, mdh_tile_params* out);
 
 /*
  * Check a configuration against the algorithmic constraint of parameter 0 and
@@ -276,18 +286,21 @@ mdh_status mdh_stencil(int64_t nx, int64_t ny, int64_t nz, const float* in, floa
  * (see mdh_matmul; C >= 16), else the one with fp32 instructions --, blk[c] = 1 the
  * few-channel kernel that walks s and c as one dimension.  With in_region[0] =
  * MDH_MR_HBM that kernel carries every fp32 value as three bf16 values, as the
- * larger layers' tables with eight register parts of c do; a call without a table
- * takes it where that is faster and no less precise, mdh_default_params answers
- * the table of the fp32 instructions.
+ * larger layers' tables with eight register parts of c do, but sums the products of
+ * the first of them apart: no more roundings than terms that are not zero.  A call
+ * without a table takes it where it is faster; mdh_call_params tells,
+ * mdh_default_params answers the table of the fp32 instructions.
  * prt[MDH_L_WG][c] = S > 1 splits the reduction dimension c over workgroups: the S
  * partial outputs go to `workspace` (S * N*P*Q*K floats, see mdh_workspace_size) and
  * a second kernel adds them in ascending part order.  The library default does
  * that for small images with many channels, so pass the workspace
  * mdh_workspace_size asks for; it may be NULL when that size is 0.
- * Precondition of the few-channel kernel (blk[c] = 1, the default for C <= 8): the
+ * Precondition of the few-channel kernel with fp32 instructions (blk[c] = 1,
+ * in_region[0] = MDH_MR_LDS; a call without a table may take it for C <= 8): the
  * input holds finite values.  Its fused (s,c) walk is padded to a multiple of 8 with
  * zero filter entries whose partners are real neighbouring input cells, and 0 * Inf
- * or 0 * NaN would put a NaN into an output whose own terms are all finite.
+ * or 0 * NaN would put a NaN into an output whose own terms are all finite.  The one
+ * on slices evaluates such blocks again, without the padding: any values.
  */
 mdh_status mdh_mcc(int64_t N, int64_t H, int64_t W, int64_t C, int64_t K, int64_t R, int64_t S,
                    int64_t stride_h, int64_t stride_w, const float* in, const float* filt,

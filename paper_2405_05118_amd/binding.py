@@ -19,7 +19,7 @@ L_HBM, L_LDS, L_VGPR, L_WG, L_WAVE, L_LANE = range(6)
 MR_HBM, MR_LDS, MR_VGPR = range(3)  # memory regions of in_region / out_region
 
 EXPORTS = (
-    "mdh_strerror", "mdh_version", "mdh_part_offset", "mdh_default_params", "mdh_validate_params",
+    "mdh_strerror", "mdh_version", "mdh_part_offset", "mdh_default_params", "mdh_call_params", "mdh_validate_params",
     "mdh_workspace_size", "mdh_matmul", "mdh_stencil", "mdh_mcc", "mdh_custom_reduce", "mdh_tune",
     "mdh_num_candidates", "mdh_candidate", "mdh_last_launch_error", "mdh_dot", "mdh_matvec",
     "mdh_matmul_ex", "mdh_scan", "mdh_mcc_capsule", "mdh_calib_copy", "mdh_calib_read", "mdh_calib_mfma", "mdh_calib_valu",
@@ -116,6 +116,7 @@ def lib() -> ctypes.CDLL:
         L.mdh_last_launch_error.restype = ctypes.c_char_p
         L.mdh_part_offset.argtypes = [i64, i32, ctypes.POINTER(i32), ctypes.POINTER(i32), p64, p64]
         L.mdh_default_params.argtypes = [ctypes.c_int, p64, pp]
+        L.mdh_call_params.argtypes = [ctypes.c_int, p64, pp]
         L.mdh_validate_params.argtypes = [ctypes.c_int, p64, pp]
         L.mdh_workspace_size.restype = sz
         L.mdh_workspace_size.argtypes = [ctypes.c_int, p64, pp]
@@ -215,6 +216,12 @@ def mdh_part_offset(N: int, P: Sequence[int], p: Sequence[int]):
 def mdh_default_params(inst: int, sizes: Sequence[int]) -> TileParams:
     p = TileParams()
     _check(lib().mdh_default_params(inst, _sizes(sizes), ctypes.byref(p)), "mdh_default_params")
+    return p
+
+
+def mdh_call_params(inst: int, sizes: Sequence[int]) -> TileParams:
+    p = TileParams()
+    _check(lib().mdh_call_params(inst, _sizes(sizes), ctypes.byref(p)), "mdh_call_params")
     return p
 
 

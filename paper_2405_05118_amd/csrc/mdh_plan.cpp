@@ -1241,6 +1241,13 @@ mdh_status mdh_default_params(mdh_instance inst, const int64_t* sizes, mdh_tile_
   return MDH_ERR_UNSUPPORTED;
 }
 
+mdh_status mdh_call_params(mdh_instance inst, const int64_t* sizes, mdh_tile_params* out) {
+  mdh_status st = mdh_default_params(inst, sizes, out);
+  MccPlan pl;
+  if (st == MDH_OK && inst == MDH_MCC && (st = plan_mcc(sizes, nullptr, &pl)) == MDH_OK) params_from_plan(sizes, pl, out);
+  return st;
+}
+
 mdh_status mdh_validate_params(mdh_instance inst, const int64_t* sizes, const mdh_tile_params* p) {
   if (!p) return MDH_ERR_NULL;
   mdh_status st = check_sizes(inst, sizes);

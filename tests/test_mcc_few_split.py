@@ -28,6 +28,9 @@ def run(x, f, st, params=None):
     N, H, W, C = x.shape
     K, R, S, _ = f.shape
     P, Q = (H - R) // st + 1, (W - S) // st + 1
+    if params is None:  # a call without a table is the kernel that this file is about
+        p = mdh.mdh_call_params(mdh.MDH_MCC, (N, P, Q, K, C, R, S, st, st))
+        assert p.blk[4] == 1 and p.in_region[0] == B.MR_HBM
     out = torch.full((N * P * Q * K + 64,), -7.0, device="cuda")  # guard words behind the output
     mdh.mdh_mcc(torch.from_numpy(x).cuda(), torch.from_numpy(f).cuda(), out[: N * P * Q * K].view(N, P, Q, K), (st, st), params, None)
     assert (out[N * P * Q * K :] == -7.0).all()
@@ -133,6 +136,7 @@ def test_tables():
     for g in got:
         close(g, want, f[0].size)
     assert any(np.array_equal(g, run(x, f, 1)) for g in got)
+    assert np.array_equal(run(x, f, 1, mdh.mdh_call_params(mdh.MDH_MCC, s)), run(x, f, 1))
 
 
 def rel(got, want):

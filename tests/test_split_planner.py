@@ -70,6 +70,30 @@ def test_few_channel_images_beyond_32_bits(P, Q, C, stride, offered):
     assert any(p.blk[4] == 1 and p.in_region[0] == 0 for p in tables) == offered
 
 
+# What a call without a table runs: the default's table, but for few channels the kernel on slices where its matrix
+# instructions take at most two thirds of the time (four fifths below 2^24 outputs) and a sum has 18 terms or more.
+@pytest.mark.parametrize("sizes, sliced", [
+    ((16, 112, 112, 64, 3, 7, 7, 2, 2), True), ((1, 112, 112, 64, 3, 7, 7, 2, 2), True), ((16, 224, 224, 64, 3, 5, 5, 1, 1), True),
+    ((16, 222, 222, 64, 4, 3, 3, 1, 1), True), ((16, 222, 222, 64, 3, 3, 3, 1, 1), False), ((8, 222, 222, 32, 3, 3, 3, 1, 1), True),
+    ((16, 220, 220, 64, 2, 5, 5, 1, 1), False), ((4, 60, 60, 32, 2, 5, 5, 1, 1), True), ((4, 60, 60, 32, 2, 3, 3, 1, 1), False),
+    ((4, 60, 60, 32, 1, 3, 3, 1, 1), False), ((4, 60, 60, 32, 2, 1, 7, 1, 1), False),
+])
+def test_what_a_call_without_a_table_runs(sizes, sliced):
+    p, d = mdh.mdh_call_params(mdh.MDH_MCC, sizes), mdh.mdh_default_params(mdh.MDH_MCC, sizes)
+    assert p.blk[4] == d.blk[4] == 1 and d.in_region[0] == 1 and (p.in_region[0] == 0) == sliced
+    assert sliced or bytes(p) == bytes(d)
+    assert mdh.mdh_validate_params(mdh.MDH_MCC, sizes, p) == 0 and mdh.mdh_workspace_size(mdh.MDH_MCC, sizes) == 0
+
+
+@pytest.mark.parametrize("inst, sizes", [
+    (mdh.MDH_MATMUL, (300, 200, 100)), (mdh.MDH_MATMUL, (4096, 4096, 4096)), (mdh.MDH_MATMUL, (3, 500, 4000)),
+    (mdh.MDH_MCC, (16, 56, 56, 64, 64, 3, 3, 1, 1)), (mdh.MDH_STENCIL, (30, 40, 50)), (mdh.MDH_CUSTOM_REDUCE, (5000, 9000, 8)),
+    (mdh.MDH_BMATMUL, (4, 60, 70, 80, 0, 1, 0)), (mdh.MDH_DOT, (1 << 20,)), (mdh.MDH_MATVEC, (100, 200)), (mdh.MDH_SCAN, (4, 10000)),
+    (mdh.MDH_MCC_CAPSULE, (1, 8, 8, 16, 4, 3, 3, 1, 1))])
+def test_elsewhere_that_is_the_default(inst, sizes):
+    assert bytes(mdh.mdh_call_params(inst, sizes)) == bytes(mdh.mdh_default_params(inst, sizes))
+
+
 # the default's tile in column bands, and what the small-M kernel stands in front of, where the split kernels or parts
 # of k have become the default: WG, WAVE and VGPR parts of (i, j, k), and the loop order's first entry
 @pytest.mark.parametrize("sizes, wg, wave, vgpr, first", [
