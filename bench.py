@@ -26,9 +26,9 @@ METRIC = "per-instance GFLOP/s or GB/s and % of roofline on 1 MI355X"
 # MI355X published peaks
 PEAK_HBM_GBS = 8000.0
 PEAK_FP32_MFMA_TFLOPS = 157.3
-# the contractions that carry an fp32 value as three bf16 values spend six bf16 matrix products on a multiply-add:
-# 256 CU x 4096 FLOP/clk x 2.4 GHz / 6
-PEAK_SPLIT_MFMA_TFLOPS = 2516.6 / 6
+# 256 CU x 4096 FLOP/clk x 2.4 GHz; the contractions that carry an fp32 value as three bf16 values spend six bf16 matrix
+# products on a multiply-add, few-channel MCC eight
+PEAK_BF16_MFMA_TFLOPS = 2516.6
 # Vector ALU: 256 CUs x 4 SIMDs x 32 lanes x 2.4 GHz = 78.6 T lane-op/s.  This is the width behind the
 # published FP32 vector peak (157.3 TFLOP/s = 78.6 T fused multiply-adds a second), and no instruction
 # kind issues faster: moves, 32-bit add / subtract, bitwise logic and fp32 add / multiply / FMA on
@@ -194,9 +194,9 @@ def _split_variant(mdh, sizes, S):
     return None
 
 
-def _mfma_roofline(tf, sliced, traffic):
-    """Roofline object of a contraction; sliced: six bf16 matrix products per multiply-add instead of fp32 ones."""
-    peak = PEAK_SPLIT_MFMA_TFLOPS if sliced else PEAK_FP32_MFMA_TFLOPS
+def _mfma_roofline(tf, sliced, traffic, products=6):
+    """Roofline object of a contraction; sliced: so many bf16 matrix products per multiply-add instead of fp32 ones."""
+    peak = PEAK_BF16_MFMA_TFLOPS / products if sliced else PEAK_FP32_MFMA_TFLOPS
     return {"bound": "mfma", "achieved": tf, "peak": peak, "unit": "TFLOP/s", "frac": tf / peak, "traffic": traffic}
 
 
@@ -260,15 +260,16 @@ def bench_mcc(torch, mdh, W, name, steps, warmup, cpu):
     o = torch.empty((cfg.N, P, Q, cfg.K), dtype=torch.float32, device="cuda")
     sizes = (cfg.N, P, Q, cfg.K, cfg.C, cfg.R, cfg.S, cfg.stride[0], cfg.stride[1])
     ws = _ws(torch, mdh, mdh.MDH_MCC, sizes)
-    few = cfg.C <= 8  # s and c walked as one dimension; a call without a table carries the values as three bf16 values there
-    sliced = few or mdh.mdh_default_params(mdh.MDH_MCC, sizes).prt[2][4] == 8
+    p = mdh.mdh_call_params(mdh.MDH_MCC, sizes)
+    few = p.blk[4] == 1  # s and c walked as one dimension
+    sliced = p.in_region[0] == 0 if few else p.prt[2][4] == 8  # values carried as three bf16 values
     ms, wall = _events_ms(torch, lambda: mdh.mdh_mcc(x, f, o, cfg.stride, None, ws), steps, warmup)
     flop = 2.0 * cfg.N * P * Q * cfg.K * cfg.C * cfg.R * cfg.S
     tf = flop / ms / 1e9
     res = {
         "value": flop / wall / 1e6, "unit": "GFLOP/s", "ms_per_step": wall, "kernel_ms": ms, "dtype": "f32",
-        "kernel": "mcc_flat_split_kernel" if few else "mcc_split_kernel" if sliced else "mcc_kernel",
-        "roofline": _mfma_roofline(tf, sliced, TRAFFIC_BYTES.get(name)),
+        "kernel": "mcc_%s%s%skernel" % ("flat_" if few else "", "split_" if sliced else "", "dealt_" if p.strided else ""),
+        "roofline": _mfma_roofline(tf, sliced, TRAFFIC_BYTES.get(name), 8 if few else 6),
         "algorithmic_flop": flop,
         "algorithmic_bytes": 4 * (x.numel() + f.numel() + o.numel()),
         "cache_resident": 4 * (x.numel() + f.numel() + o.numel()) < LLC_BYTES,
