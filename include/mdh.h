@@ -322,9 +322,10 @@ mdh_status mdh_mcc(int64_t N, int64_t H, int64_t W, int64_t C, int64_t K, int64_
  *   int32.  Integer arithmetic: the result is unique and reproduced bit-exactly.
  *   If B is split over workgroups (prt[MDH_L_WG][b] = S > 1) the S partial
  *   (score,index) pairs go to `workspace` (2*S*nA int32) and a second kernel
- *   combines them.  Large products with the default's parts evaluate bounds on
- *   bit maps of the records first and score few pairs; they keep what they need
- *   in the same workspace.
+ *   combines them.  Large products with the default's workgroup evaluate bounds on
+ *   bit maps of the records first and score few pairs; they keep what they need in
+ *   the same workspace, where its S parts hold it: 8 + 4 * ceil(nF/2) <= 8 * (S-1),
+ *   with the default's S fewer than 2^20 records of A (2^19 above 8 fields).
  */
 mdh_status mdh_custom_reduce(int64_t nA, int64_t nB, int32_t nF, const int32_t* A,
                              const int32_t* B, const int32_t* w_agree, const int32_t* w_disagree,

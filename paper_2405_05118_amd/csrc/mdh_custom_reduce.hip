@@ -548,8 +548,11 @@ extern "C" mdh_status mdh_custom_reduce_static(int64_t nA, int64_t nB, int32_t n
   if (pl.S > 1 && (int64_t)pl.S * nA * 2 > (int64_t)MDH_STATIC_SCRATCH_INTS) return MDH_ERR_STATIC_LIMIT;
   int32_t* ws = nullptr;
   if (pl.S > 1 && (st = scratch_of_current_device(&ws)) != MDH_OK) return st;
-  // every (part, record) slot the second pass reads is written by the first kernel of this call:
-  // nothing left by an earlier call is read, so nothing has to be cleared
+  // Nothing left by an earlier call is read, so nothing has to be cleared.  The loop over fields writes every (part, record)
+  // slot before the second pass reads it.  On bit maps the preparation writes every key, every slot word of A and the whole
+  // head (flag, widths, all candidates for the weights) before the walk reads them, the walk only raises keys and the flag;
+  // if that is up the loop writes all of its S - 1 parts, which may lie over keys and slots, and the finishing pass reads
+  // those, else the keys.
   return launch_prl(pl, nA, nB, nF, A, B, w_agree, w_disagree, out_score, out_index, ws, (hipStream_t)stream);
 }
 

@@ -20,15 +20,15 @@
 // does not depend on when they see them: a record of an earlier part with an equal score has to pass (t(s - 1)).
 //
 // Slots that collide throughout or weights that q cannot tell apart would have too many records scored: a wavefront that
-// does (`limit`) raises a flag and the others stop; the loop over fields, launched behind, starts only if the flag is up.
+// does (`left`) raises a flag and the others stop; the loop over fields, launched behind, starts only if the flag is up.
 // us, that loop alone / a call that takes both: weights that wrap around, known before the walk, 2^14 x 2^17 records of 8
-// fields 1300 / 1350, 4096 x 2^16 202 / 233; B of eight different records 2^14 x 2^17 950 / 1180, 2^16 x 2^18 6850 / 7600;
-// slots that all collide 2^14 x 2^17 950 / 1160, 4096 x 2^16 158 / 380, 2^16 x 2^18 6860 / 7610; in the last quarter of
-// every part only, 2^14 x 2^17, 950 / 1500.  (32-bit hashes, none equal: 1300 / 480, 2^16 x 2^18 9990 / 3000.)
+// fields 1300 / 1350, 4096 x 2^16 203 / 234; B of eight different records 2^14 x 2^17 953 / 1180, 2^16 x 2^18 6870 / 7810;
+// slots that all collide 2^14 x 2^17 957 / 1170, 4096 x 2^16 160 / 377, 2^16 x 2^18 6890 / 7660; in every other eight chunks
+// 2^14 x 2^17 954 / 1530.  (32-bit hashes, none equal, stay with the maps: 1290 / 450, 2^16 x 2^18 10030 / 2930.)
 //
 // Bound by the issue of vector instructions, 320 per 128 x 64 pairs of 8 fields (the loop over fields: 25.6 a pair and
-// lane).  us, the loop over fields / this: 2^16 x 2^18 records of 8 fields 6870 / 1030; 2^15 x 2^17 of 12 3010 / 550; 2^15 x
-// 2^18 of 4 2080 / 365; 2^10 x 2^18 of 8 227 / 95; 2^12 x 2^14 of 8 63 / 54.  Two workgroups of 16 wavefronts a compute unit
+// lane).  us, the loop over fields / this: 2^16 x 2^18 records of 8 fields 6850 / 985; 2^15 x 2^17 of 12 3000 / 520; 2^15 x
+// 2^18 of 4 2080 / 346; 2^10 x 2^18 of 8 224 / 83; 2^12 x 2^14 of 8 63 / 51.  Two workgroups of 16 wavefronts a compute unit
 // (64 KB of maps) are ahead of one (128 KB, 1024 slots for every field): a wavefront issues every five cycles, a SIMD twice
 // as often.
 #include <limits.h>
@@ -250,7 +250,7 @@ __global__ __launch_bounds__(kPrepNT) void prl_bits_prep_kernel(const int* __res
 // Adds a constant, the same for every lane, to the sums of the records of the maps e: u += e ? q : 0, in planes of four
 // words.  There is code for every q, 256 bytes apart, and it is jumped into; sums that are still small have code that
 // leaves out the upper planes.  (A switch has the compiler compare its way to the code, and give every case registers of
-// its own, with 20 moves to bring them together: 1310 us at 2^16 x 2^18 records of 8 fields, against 1030.)
+// its own, with 20 moves to bring them together: 1310 us at 2^16 x 2^18 records of 8 fields, against 1030 then.)
 #define MDH_FOUR(op, ...) op(__VA_ARGS__, 0) op(__VA_ARGS__, 1) op(__VA_ARGS__, 2) op(__VA_ARGS__, 3)
 #define MDH_V(x, w) "%[" #x #w "]"
 // lowest set bit of q, plane i: carry c
@@ -411,7 +411,6 @@ __global__ __launch_bounds__(kNT, 8) void prl_bits_kernel(const int* __restrict_
       none += m & keep;
     }
   };
-  // items of a chunk this thread puts into the maps: field and record stay the same from chunk to chunk
   // where the adder's code for each field is, a byte a field
   unsigned long long code[2] = {0, 0};
   for (int f = 0, before = 0; f < nF; ++f) {
@@ -421,6 +420,7 @@ __global__ __launch_bounds__(kNT, 8) void prl_bits_kernel(const int* __restrict_
   }
 
   const PrlSlots sl{head->bits};
+  // items of a chunk this thread puts into the maps: field and record stay the same from chunk to chunk
   unsigned at[ITEMS], bit[ITEMS], old[ITEMS];
   int width[ITEMS], next[ITEMS];
 #pragma unroll
@@ -453,12 +453,12 @@ __global__ __launch_bounds__(kNT, 8) void prl_bits_kernel(const int* __restrict_
     for (int d = kLevels / 2; d; d /= 2) t += most[t + d - 1] <= s ? d : 0;
     return t;
   };
-  int queued = 0, scored = 0, steps = 0;
+  int queued = 0, left;
   // scores the last `n` records of the queue, one a lane
   auto flush = [&](int n, unsigned behind) {
     __builtin_amdgcn_wave_barrier();
     queued -= n;
-    scored += 4;
+    left -= 4;
     if (lane < n) {
       const unsigned e = queue[queued + lane];
       const int ai = (int)(e >> kPrlPartBits), b = c0 * kPrlChunk + (int)(e & ((1u << kPrlPartBits) - 1));
@@ -507,7 +507,7 @@ __global__ __launch_bounds__(kNT, 8) void prl_bits_kernel(const int* __restrict_
   // An iteration that scores takes about 280 cycles of a wavefront's issue, the loop over fields 27 times as much for the
   // records of a step: so many a step that the rest still pays, a sixth of the loop's time for the whole walk on top (the
   // start, at which little is known), and at least one step whose records all have to be scored.
-  const int limit = max(160, 4 * mine * (c1 - c0));
+  left = max(160, 4 * mine * (c1 - c0));
   for (int c = c0; c < c1; ++c) {
     // a bit of a map belongs to one thread: taking the last chunk's out and putting this one's in needs no barrier between
 #pragma unroll
@@ -556,7 +556,7 @@ __global__ __launch_bounds__(kNT, 8) void prl_bits_kernel(const int* __restrict_
         q >>= 16;
         if (KP > 4) q |= q_next << 48, q_next >>= 16;
       }
-      ++steps;
+      left += 24;
       int t = tl[ai];
       unsigned g[4];
 #pragma unroll
@@ -582,7 +582,7 @@ __global__ __launch_bounds__(kNT, 8) void prl_bits_kernel(const int* __restrict_
 #pragma unroll
             for (int i = 0; i < 4; ++i) g[i] = i == w ? x & (x - 1) : g[i];
           }
-          queued += __builtin_popcountll(lanes);
+          queued = __builtin_amdgcn_readfirstlane(queued + __builtin_popcountll(lanes));
           if (queued >= 64) flush(64, behind);
           ++here;
           lanes = __builtin_amdgcn_ballot_w64((g[0] | g[1] | g[2] | g[3]) != 0);
@@ -624,8 +624,8 @@ __global__ __launch_bounds__(kNT, 8) void prl_bits_kernel(const int* __restrict_
           tl[ai] = (unsigned char)t;
         }
       }
-      scored += here;
-      if (scored > limit + 24 * steps) {
+      left = __builtin_amdgcn_readfirstlane(left - here);
+      if (left < 0) {
         // one store a workgroup: 8192 wavefronts that store to one address take 250 us
         if (lane == 0 && !atomicExch(stop, 1)) __hip_atomic_store(&head->stop, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         break;

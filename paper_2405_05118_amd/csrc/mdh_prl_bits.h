@@ -95,9 +95,13 @@ inline PrlBitsGrid prl_bits_grid(int64_t nA, int64_t nB, int nF) {
   return best;
 }
 
-// Keys and slots fit the workspace of S parts less one; the rest is what the launches and the search for weights take (us,
-// the loop over fields / the maps: 2^12 x 2^14 records of 8 fields 63 / 54, 2^13 x 2^14 91 / 62; 2^11 x 2^15 of 12, with a
-// search over 4096 patterns, 89 / 100, 2^11 x 2^18 528 / 182).  Below 1024 records of A most lanes would have none.
+// Keys and slots have to fit the workspace of S parts less one.  S is the loop's split, which a caller's workspace has been
+// sized for: it falls with more records of A and with fewer of B, and so the maps are not taken from 2^20 records of A on (two
+// parts: 2^20 x 2^15 of 8 fields 13.5 ms with the loop, 2^19 x 2^16, four parts, 13.4 / 2.05), for more than 8 fields from 2^19
+// (of 10 17.5 ms); nor below 4096 records of B, 8192 for more than 8 fields, where there are 2^15 records of A or more.
+// The rest is what the launches and the search for weights take (us, the loop over fields / the maps: 2^12 x 2^14 records of
+// 8 fields 63 / 51, 2^13 x 2^14 91 / 60; 2^11 x 2^18 of 12, with a search over 4096 patterns, 525 / 168; 2^11 x 2^15 89 / 100
+// when the line was drawn).  Below 1024 records of A most lanes would have none.
 inline bool prl_bits_applies(int S, int64_t nA, int64_t nB, int nF) {
   return nF <= 16 && 8 + 4 * ((nF + 1) / 2) <= 8 * (S - 1) && nA >= 1024 &&
          (double)nA * (double)nB * nF >= (nF <= 10 ? 536870912.0 : 2147483648.0);
