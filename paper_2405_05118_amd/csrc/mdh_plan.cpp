@@ -860,7 +860,7 @@ static bool mcc_flat_split_sizes(const int64_t* s) {
 
 // Does a call without a table go to the few-channel kernel that splits, and in which block?  (The default's table stays
 // that of the fp32 instructions: bit for bit the results it always had.)
-// The line: its matrix instructions have to take at most two thirds of the time of the fp32 ones, four fifths where there
+// The line: its matrix instructions have to take at most two thirds of the time of the fp32 ones, nine tenths where there
 // are fewer than 2^24 outputs.  us, against those, at 16 x 224 x 224 -> 64 / the same with stride 2 / 8 x 70 x 90 -> 24:
 //   7 x 7 x 3 (0.57) 127 : 143 / 39 : 45 / 11.2 : 12.1     3 x 3 x 4 (0.67) 57 : 58 / 19.9 : 23.3 / 7.0 : 9.0
 //   5 x 5 x 4 (0.64) 101 : 106 / 31 : 37 / 9.5 : 13.0      3 x 3 x 3 (0.80) 59 : 54 / 19.9 : 21.5 / 7.0 : 8.8
@@ -874,7 +874,7 @@ static void mcc_flat_split_rule(const int64_t* s, MccPlan* out) {
   // cycles of the matrix instructions of 32 pixels x 32 channels
   const int64_t split = cdiv(s[5] * cdiv(SC, 8), 2) * 8 * 32, fp32 = s[5] * (SC / 8 * 4 + cdiv(SC % 8, 2)) * 64;
   const bool few = (double)s[0] * P * Q * s[3] < (double)(1 << 24);
-  if (s[5] * SC < 18 || split * 15 > fp32 * (few ? 12 : 10)) return;
+  if (s[5] * SC < 18 || split * 30 > fp32 * (few ? 27 : 20)) return;
   int64_t area = -1;
   int tq = 0;
   for (int t : {16, 32, 8}) {  // the block that pads the image least
