@@ -25,6 +25,8 @@
 // six products); 14 x 178 x 203 x 2 -> 56, 7 x 7: 94 / 60 (51).  Tried with six products: the patch split once into LDS, each
 // wavefront its own, one workgroup a compute unit instead of two, 33.9 (then 33.0), the next block's loads ahead of this
 // block's stores 35.3; with eight: the split at the start of its own step instead of in the shadow of the one before 43.
+#include <type_traits>
+
 #include "mdh_split.h"
 
 namespace mdh {
@@ -48,6 +50,18 @@ struct FlatConv {
 
 __device__ __forceinline__ f4 buf4(__amdgpu_buffer_rsrc_t r, int off) {
   return __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0));
+}
+
+// the largest of a wavefront's 64 values (not negative), in a scalar register; no address register for a shuffle
+__device__ __forceinline__ float wave_max(float v) {
+  auto other = [&](auto x) { return __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), x.value << 10 | 0x1f)); };
+  v = fmaxf(v, other(std::integral_constant<int, 1>()));
+  v = fmaxf(v, other(std::integral_constant<int, 2>()));
+  v = fmaxf(v, other(std::integral_constant<int, 4>()));
+  v = fmaxf(v, other(std::integral_constant<int, 8>()));
+  v = fmaxf(v, other(std::integral_constant<int, 16>()));
+  return fmaxf(__builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 0)),
+               __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 32)));
 }
 
 // fp32 evaluation of a wavefront's block, for values the split does not carry
@@ -76,8 +90,7 @@ template <int NI>
 __global__ __launch_bounds__(kNT, 4) void mcc_flat_split_kernel(FlatConv g) {
   constexpr int BN = NI * 32;
   extern __shared__ __attribute__((aligned(16))) char lds[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, lh = lane >> 5;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int chunks = 2 * g.T, slice = chunks * BN * 16;
   unsigned* const ftop = (unsigned*)(lds + 3 * slice);  // largest magnitude of every channel (bits of a float)
   unsigned* const ftiny = ftop + BN;
@@ -111,14 +124,17 @@ __global__ __launch_bounds__(kNT, 4) void mcc_flat_split_kernel(FlatConv g) {
     for (int s = 0; s < 3; ++s) *(u4*)(p + s * slice) = v[s];
   }
   __syncthreads();
-  float fmost = __uint_as_float(ftop[lane % BN]);
-#pragma unroll
-  for (int d = 32; d > 0; d >>= 1) fmost = fmaxf(fmost, __shfl_xor(fmost, d));
+  const float fmost = wave_max(__uint_as_float(ftop[tid % BN]));
 
   // contiguous shares, and contiguous runs of them per XCD
   const int ws = (g.G & 7) == 0 ? (w & 7) * (g.G >> 3) + (w >> 3) : w;
   const int u0 = (int)((int64_t)g.units * ws / g.G), u1 = (int)((int64_t)g.units * (ws + 1) / g.G);
   for (int u = u0 + wave; u < u1; u += kWaves) {
+    // (the lane's numbers anew for every block: what follows from them would wait in registers through the steps, which have
+    // none to spare -- 24 bytes a lane went to memory)
+    int lane = tid & 63;
+    asm volatile("" : "+v"(lane));
+    const int l32 = lane & 31, lh = lane >> 5;
     const int tq = u % g.tq_n, band = u / g.tq_n, tp = band % g.tp_n, n = band / g.tp_n;
     const int p = (tp << (5 - g.qb)) + (l32 >> g.qb), q = (tq << g.qb) + (l32 & ((1 << g.qb) - 1));
     const int64_t first = (int64_t)n * g.H * WC;
@@ -200,10 +216,7 @@ __global__ __launch_bounds__(kNT, 4) void mcc_flat_split_kernel(FlatConv g) {
         z = __builtin_fmaf(acc[ni][e], 0.f, z);
         least = fminf(least, fabsf(acc[ni][e]));
       }
-    float most = finite(top);
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) most = fmaxf(most, __shfl_xor(most, d));
-    const float bound = (float)(g.R * SC) * kTiny * fmaxf(most, fmost);
+    const float bound = (float)(g.R * SC) * kTiny * fmaxf(wave_max(finite(top)), fmost);
     bool fp32 = __any(!(z == 0.f));
     if (!fp32 && __any(least < bound)) {
       // an output too small, of a channel and a window that are not all zeros?
