@@ -246,7 +246,8 @@ size_t mdh_workspace_size(mdh_instance inst, const int64_t* sizes, const mdh_til
  *   kernel that carries a value as three bf16 values and multiplies with six bf16 matrix
  *   products (K >= 32; the default for large products; Inf, NaN, overflow and values below
  *   2^-100 take the fp32 instructions; a product with a permutation is exact, a sum of one
- *   term within 3 * 2^-24).  Two kernels with fp32 instructions, told apart by
+ *   term within 3 * 2^-24; sums with many zero terms are up to twice as far off as with
+ *   fp32 instructions, which a table selects).  Two kernels with fp32 instructions, told apart by
  *   prt[MDH_L_WAVE][k]: 1 = the wavefronts of a workgroup tile its output tile,
  *   operands staged in LDS (in_region = MDH_MR_LDS); WK > 1 = every wavefront owns
  *   the whole (small) output tile and 1/WK of the k-range, operands go straight to

@@ -13,7 +13,10 @@
 // 2-norm, one v_mfma_f32_32x32x2_f32 per two k against six bf16 instructions per 32 k:
 //     U[-1,1]  K = 64: 1.4e-7 / 1.1e-7   256: 2.9e-7 / 2.4e-7   4096: 1.15e-6 / 1.0e-6   25088: 2.8e-6 / 2.7e-6
 //     U[0,1]   K = 64: 1.2e-7 / 0.8e-7   256: 2.2e-7 / 1.8e-7   4096: 0.85e-6 / 0.5e-6   25088: 2.4e-6 / 1.6e-6
-// (all nine products: the same digits).  Rate of the bare instruction loops on random operands: 154 TFLOP/s in
+// (all nine products: the same digits).  Sums with many zeros in one operand have fewer terms than that chain has k, and
+// up to six roundings for the steps they spread over: 64 of 147 terms 3.0 x 2^-24 against 2.4 with fp32 instructions, 8 of
+// them 1.65 / 0.90 (dense 3.2 / 3.6).  Few-channel MCC, whose filters are like that, keeps h h' in a sum of its own.
+//  Rate of the bare instruction loops on random operands: 154 TFLOP/s in
 // fp32, 1850 / 6 = 308 TFLOP/s in six bf16 products (the 16x16x32 form: 2220 / 6).
 //
 // Two kinds of values need more than that, and get the fp32 instructions (recompute_* in the kernels):
