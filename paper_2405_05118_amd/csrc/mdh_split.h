@@ -16,7 +16,7 @@
 // (all nine products: the same digits).  Sums with many zeros in one operand have fewer terms than that chain has k, and
 // up to six roundings for the steps they spread over: 64 of 147 terms 3.0 x 2^-24 against 2.4 with fp32 instructions, 8 of
 // them 1.65 / 0.90 (dense 3.2 / 3.6).  Few-channel MCC, whose filters are like that, keeps h h' in a sum of its own.
-//  Rate of the bare instruction loops on random operands: 154 TFLOP/s in
+// Rate of the bare instruction loops on random operands: 154 TFLOP/s in
 // fp32, 1850 / 6 = 308 TFLOP/s in six bf16 products (the 16x16x32 form: 2220 / 6).
 //
 // Two kinds of values need more than that, and get the fp32 instructions (recompute_* in the kernels):
