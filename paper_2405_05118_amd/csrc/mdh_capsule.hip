@@ -48,9 +48,7 @@ __global__ __launch_bounds__(256 * RW) void capsule_kernel(const float* __restri
   const int wave = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);  // output row of the workgroup
   const int rw = __builtin_amdgcn_readfirstlane(tid >> 8);          // part of the reduction walk
   const int l32 = lane & 31, h = lane >> 5;
-  int b = blockIdx.x;
-  const int nb = gridDim.x;
-  if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);  // contiguous run of tiles per XCD
+  int b = xcd_order(blockIdx.x, gridDim.x);  // contiguous run of tiles per XCD
   const int tk = b % tk_n;
   const int tq = (b / tk_n) % tq_n;
   const int tp = (b / (tk_n * tq_n)) % tp_n;

@@ -147,6 +147,17 @@ struct GemmExPlan {
   // (row-contiguous loads), 0 = read straight into the MFMA layout
   int lds = 0;
 };
+// Workgroup ids are dealt round-robin to the 8 XCDs, each with an L2 of its own: the place of workgroup b of n in an order
+// in which every XCD has one contiguous run, whatever n.  Without a run for the counts that 8 does not divide, the panels
+// of every tile go through all eight L2s: B transposed 53 x 397 x 164 x 536 49.2 us, 42.4 with; 20 x 316 x 676 x 286 33.4 /
+// 28.1; 61 x 122 x 81 x 465 14.9 / 13.2; 3000^3 the same.
+#if defined(__HIPCC__)
+__device__ __forceinline__ int xcd_order(int b, int n) {
+  const int x = b & 7, r = n & 7;
+  return x * (n >> 3) + (x < r ? x : r) + (b >> 3);
+}
+#endif
+
 // Device-coherent accesses for results that pass between workgroups of ONE launch (the parts of a split
 // reduction folded by the last part to arrive).  The L2 caches of the chip's eight XCDs are not kept
 // coherent for ordinary loads and stores inside a kernel; a device-scope fence would write back and

@@ -232,9 +232,7 @@ __global__ __launch_bounds__((GemmCfg<BM, BN, BK, WM, WN>::NT)) void matmul_kern
   // contiguous run of tiles, walked in bands of 8 tile-rows so that the tiles resident on one
   // XCD at a time share few panels of A and B in that XCD's L2.  jmajor: the other loop order of the
   // workgroup layer -- bands of 8 tile-columns, j fastest inside a band.
-  int b = blockIdx.x;
-  const int nb = gridDim.x;
-  if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);
+  int b = xcd_order(blockIdx.x, gridDim.x);
   const int tiles = tiles_m * tiles_n;
   const int s = b / tiles;
   int t = b % tiles;

@@ -242,9 +242,7 @@ __global__ __launch_bounds__(((BM / WM) * (BN / WN) * 64)) void matmul_ex_kernel
   // XCD-aware order: workgroup ids are dealt round-robin to the 8 XCDs; each XCD gets a contiguous
   // run (whole batches when there are at least 8), walked in bands of 8 tile-rows so that the tiles
   // resident on one XCD at a time share few panels of A and B in that XCD's L2.
-  int b = blockIdx.x;
-  const int nb = gridDim.x;
-  if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);
+  int b = xcd_order(blockIdx.x, gridDim.x);
   const int tiles = tiles_m * tiles_n;
   const int batch = b / (tiles * S);
   b -= batch * tiles * S;

@@ -471,9 +471,7 @@ __global__ __launch_bounds__(((BM / WM) * (BN / WN) * 64), (BM + BN > 128 ? 2 : 
   // XCD-aware order: workgroup ids are dealt round-robin to the 8 XCDs; each XCD gets a contiguous run (whole
   // batches when there are at least 8), walked in bands of 8 tile rows (jmajor: tile columns) so that the tiles
   // resident on one XCD at a time share few panels of the operands in that XCD's L2.
-  int b = blockIdx.x;
-  const int nb = gridDim.x;
-  if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);
+  int b = xcd_order(blockIdx.x, gridDim.x);
   const int tiles = tiles_m * tiles_n;
   const int batch = b / (tiles * S);
   b -= batch * tiles * S;

@@ -213,9 +213,7 @@ __global__ __launch_bounds__((MccCfg<TP, TQ, BN, CK, WM, WN>::NT),
   extern __shared__ __attribute__((aligned(16))) float lds[];
   // XCD-aware order: each of the 8 XCDs gets a contiguous run of tiles; inside a run the
   // channel tiles of one pixel patch come first (they share the patch), then q, p, n.
-  int b = blockIdx.x;
-  const int nb = gridDim.x;
-  if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);
+  int b = xcd_order(blockIdx.x, gridDim.x);
   const int tk = b % tk_n;
   const int tq = (b / tk_n) % tq_n;
   const int tp = (b / (tk_n * tq_n)) % tp_n;

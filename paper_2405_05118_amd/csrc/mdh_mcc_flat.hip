@@ -324,9 +324,7 @@ __global__ __launch_bounds__((WAVES_M * WAVES_N * 64)) void mcc_flat_kernel(
   const int lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
   const int l32 = lane & 31, lh = lane >> 5;
-  int b = blockIdx.x;
-  const int nb = gridDim.x;
-  if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);  // contiguous run of tiles per XCD
+  int b = xcd_order(blockIdx.x, gridDim.x);  // contiguous run of tiles per XCD
   const int tk = b % tk_n;
   const int tq = (b / tk_n) % tq_n;
   const int tp = (b / (tk_n * tq_n)) % tp_n;

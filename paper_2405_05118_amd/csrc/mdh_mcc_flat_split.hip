@@ -127,7 +127,7 @@ __global__ __launch_bounds__(kNT, 4) void mcc_flat_split_kernel(FlatConv g) {
   const float fmost = wave_max(__uint_as_float(ftop[tid % BN]));
 
   // contiguous shares, and contiguous runs of them per XCD
-  const int ws = (g.G & 7) == 0 ? (w & 7) * (g.G >> 3) + (w >> 3) : w;
+  const int ws = xcd_order(w, g.G);
   const int u0 = (int)((int64_t)g.units * ws / g.G), u1 = (int)((int64_t)g.units * (ws + 1) / g.G);
   for (int u = u0 + wave; u < u1; u += kWaves) {
     // (the lane's numbers anew for every block: what follows from them would wait in registers through the steps, which have

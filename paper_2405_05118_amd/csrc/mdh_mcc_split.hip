@@ -176,9 +176,7 @@ __global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT), (Cfg<TP, TQ, BN,
   extern __shared__ __attribute__((aligned(16))) char lds[];
   // XCD-aware order: each of the 8 XCDs gets a contiguous run of tiles; inside a run the channel tiles of one
   // pixel patch come first (they share the patch), then q, p, n.
-  int b = blockIdx.x;
-  const int nb = gridDim.x;
-  if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);
+  int b = xcd_order(blockIdx.x, gridDim.x);
   const int tk = b % tk_n, tq = (b / tk_n) % tq_n, tp = (b / (tk_n * tq_n)) % tp_n;
   const int n = (b / (tk_n * tq_n * tp_n)) % n_img;
   const int sc = b / (tk_n * tq_n * tp_n * n_img);  // part of the reduction dimension c

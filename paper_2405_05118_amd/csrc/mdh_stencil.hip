@@ -190,9 +190,7 @@ __global__ __launch_bounds__(TY* LK) void stencil_kernel(const float* __restrict
   // XCD-aware order: consecutive workgroup ids go to different XCDs (8 of them, each with
   // its own L2); give every XCD one contiguous chunk of tiles so that tiles sharing halo
   // rows/planes hit the same L2.
-  int b = blockIdx.x;
-  const int nb = gridDim.x;
-  if ((nb & 7) == 0) b = (b & 7) * (nb >> 3) + (b >> 3);
+  int b = xcd_order(blockIdx.x, gridDim.x);
   const int kt = b % nkt;
   const int jt = (b / nkt) % njt;
   const int is = b / (nkt * njt);
