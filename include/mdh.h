@@ -243,11 +243,13 @@ size_t mdh_workspace_size(mdh_instance inst, const int64_t* sizes, const mdh_til
  *   workspace mdh_workspace_size asks for (for some sizes it is asked for but not needed:
  *   a call with the default, as NULL or as its table, that brings less then runs with
  *   fewer parts).  blk = (32,32,16) selects the
- *   kernel that carries a value as three bf16 values and multiplies with six bf16 matrix
- *   products (K >= 32; the default for large products; Inf, NaN, overflow and values below
+ *   kernels that carry a value as three bf16 values and multiply with six bf16 matrix
+ *   products (K >= 32; the default for large products; prt[MDH_L_WAVE][k] = 1: tiles staged in
+ *   LDS, 4 or 8: k over the wavefronts of a workgroup, tiles of 32 to 96 rows and columns inside C; Inf, NaN, overflow and values below
  *   2^-100 take the fp32 instructions; a product with a permutation is exact, a sum of one
  *   term within 3 * 2^-24; sums with many zero terms are up to twice as far off as with
- *   fp32 instructions, which a table selects).  Two kernels with fp32 instructions, told apart by
+ *   fp32 instructions, which a table selects -- not so those of the tiles of one or two
+ *   blocks with k over the wavefronts).  Two kernels with fp32 instructions, told apart by
  *   prt[MDH_L_WAVE][k]: 1 = the wavefronts of a workgroup tile its output tile,
  *   operands staged in LDS (in_region = MDH_MR_LDS); WK > 1 = every wavefront owns
  *   the whole (small) output tile and 1/WK of the k-range, operands go straight to
@@ -459,7 +461,8 @@ mdh_status mdh_matvec(int64_t M, int64_t K, const float* A, const float* x, floa
  * For mdh_default_params etc. the `sizes` of MDH_BMATMUL are
  * (batch, M, N, K, trans_a, trans_b, trans_c); a configuration's in_transposed[0..1]
  * and out_transposed must equal the call's flags.
- * Two kernels: blk = (1,32,32,2), LDS-tiled, any views; blk = (1,16,16,4) for M <= 16
+ * Besides MatMul's kernels on slices, blk = (1,32,32,16), any views, two kernels with fp32
+ * instructions: blk = (1,32,32,2), LDS-tiled, any views; blk = (1,16,16,4) for M <= 16
  * with A and C plain (B plain or transposed), which streams both operands from
  * device memory straight into MFMA operand registers and parallelises k over
  * wavefronts and workgroups (the library default for those shapes).  That kernel

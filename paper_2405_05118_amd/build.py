@@ -23,6 +23,7 @@ SOURCES = [
     "mdh_matmul.hip",
     "mdh_matmul_ksplit.hip",
     "mdh_matmul_split.hip",
+    "mdh_matmul_split_k.hip",
     "mdh_mcc.hip",
     "mdh_mcc_split.hip",
     "mdh_mcc_flat.hip",

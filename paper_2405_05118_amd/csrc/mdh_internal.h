@@ -34,7 +34,8 @@ struct GemmPlan {
   // rows, i fastest inside a band (order (WG,i),(WG,j),(WG,k)); 1 = bands of 8 tile columns, j fastest
   // (order (WG,j),(WG,i),(WG,k)).  Decides which panels of A and B the tiles resident together share.
   int jmajor = 0;
-  // 1: the kernel that carries every value as three bf16 values (blk = 32 x 32 x 16; BK = 16 or 32 by tile)
+  // 1: the kernels that carry every value as three bf16 values (blk = 32 x 32 x 16): WK = 1, LDS-tiled (BK = 16 or 32 by
+  // tile); WK > 1, k over the wavefronts (BK = 32, a wavefront's chunk)
   int split = 0;
 };
 
@@ -69,12 +70,15 @@ mdh_status check_products(const mdh_tile_params* p, const int64_t* sizes, bool* 
 mdh_status check_lanes(const mdh_tile_params* p);
 bool same_table(const mdh_tile_params& a, const mdh_tile_params& b);
 // the kernel that splits fp32 values into bf16 slices (mdh_plan_split.cpp); tc: C is stored transposed
-constexpr int kSplitTiles = 5;
+constexpr int kSplitTiles = 13;
 bool split_inst(const GemmPlan& g, bool tc);
 bool split_sizes(int64_t M, int64_t N, int64_t K);
+bool split_fits(int64_t M, int64_t N, int64_t K, const GemmPlan& g);
 int64_t split_lds_bytes(const GemmPlan& g);
 inline int64_t split_part(int64_t K, const GemmPlan& g) { return cdiv(cdiv(K, g.S), g.BK) * g.BK; }  // k of a workgroup part
 int split_tiles(bool tc, GemmPlan* out);
+int split_offered(int64_t batch, int64_t M, int64_t N, int64_t K, bool tc, GemmPlan* out);
+bool split_k_default(int64_t M, int64_t N, int64_t K, const GemmPlan& f, GemmPlan* g);
 bool split_default(int64_t batch, int64_t M, int64_t N, int64_t K, bool tc, int S, GemmPlan* g);
 }  // namespace detail
 
@@ -194,6 +198,8 @@ mdh_status launch_matmul_ksplit(const GemmPlan& pl, int64_t M, int64_t N, int64_
                                 const float* B, float* C, void* ws, hipStream_t st);
 mdh_status launch_matmul_split(const GemmPlan& pl, bool ta, bool tb, bool tc, int64_t batch, int64_t M, int64_t N, int64_t K,
                                const float* A, const float* B, float* C, void* ws, hipStream_t st);
+mdh_status launch_matmul_split_k(const GemmPlan& pl, bool ta, bool tb, bool tc, int64_t batch, int64_t M, int64_t N, int64_t K,
+                                 const float* A, const float* B, float* C, void* ws, hipStream_t st);
 // dst[i] = part_0[i] + ... + part_{S-1}[i], i < n (defined in mdh_matmul.hip)
 mdh_status launch_combine_sum(const float* ws, float* dst, int64_t n, int S, hipStream_t st);
 

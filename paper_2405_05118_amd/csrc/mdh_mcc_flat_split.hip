@@ -96,7 +96,7 @@ __global__ __launch_bounds__(kNT, 4) void mcc_flat_split_kernel(FlatConv g) {
   unsigned* const ftiny = ftop + BN;
   const int SC = g.S * g.C, WC = g.W * g.C;
   const int tk = blockIdx.x % g.tk_n, w = blockIdx.x / g.tk_n, k0 = tk * BN;
-  const Split split;
+  const Split<true> split;
 
   if (tid <= BN) ftop[tid] = 0;
   __syncthreads();

@@ -201,7 +201,7 @@ __global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT), (Cfg<TP, TQ, BN,
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
 
-  const Split split;
+  const Split<true> split;
   const int taps = g.R * g.S;
   // filter chunks of this thread: eight channels of one output channel; channels beyond K repeat the last one
   float fx[F::F_CH][8];

@@ -238,6 +238,26 @@ void params_from_plan(const int64_t* s, const GemmPlan& pl, mdh_tile_params* p) 
   p->blk[1] = 32;
   const int bk = pl.split ? 16 : 2;
   p->blk[2] = bk;  // one v_mfma_f32_32x32x2_f32, or six v_mfma_f32_32x32x16_bf16
+  if (pl.WK > 1 && pl.split) {
+    // k on the wavefront layer, chunks of 32 as two register parts: combined in LDS
+    p->prt[MDH_L_VGPR][2] = 2;
+    p->prt[MDH_L_WG][0] = (int32_t)cdiv(s[0], pl.BM);
+    p->prt[MDH_L_WG][1] = (int32_t)cdiv(s[1], pl.BN);
+    p->prt[MDH_L_WG][2] = pl.S;
+    p->prt[MDH_L_WAVE][2] = pl.WK;
+    p->prt[MDH_L_HBM][2] = (int32_t)cdiv(cdiv(s[2], (int64_t)pl.S * pl.WK), 32);
+    p->prt[MDH_L_VGPR][0] = pl.BM / 32;
+    p->prt[MDH_L_VGPR][1] = pl.BN / 32;
+    static const int kdims[3] = {0, 1, 2};
+    set_order(p, kdims);
+    p->strided = 0;
+    p->lane_fast_dim = 1;
+    p->in_region[0] = MDH_MR_VGPR;
+    p->in_region[1] = MDH_MR_VGPR;
+    p->out_region = MDH_MR_LDS;
+    p->ragged = (uint8_t)pl.ragged;
+    return;
+  }
   if (pl.WK > 1) {
     // k on the wavefront layer: every wavefront owns the whole tile and walks groups of 8 k (4 MFMA
     // steps of 2; with the 16 x 16 x 4 block: groups of 16 k, 4 steps of 4) read straight into
@@ -287,7 +307,8 @@ void params_from_plan(const int64_t* s, const GemmPlan& pl, mdh_tile_params* p) 
 }
 
 static int gemm_ragged(const int64_t* s, const GemmPlan& pl) {
-  if (pl.WK > 1) return (s[0] % pl.BM) || (s[1] % pl.BN) || (s[2] % ((int64_t)pl.S * pl.WK * (pl.BM == 16 ? 16 : 8)));
+  if (pl.WK > 1)
+    return (s[0] % pl.BM) || (s[1] % pl.BN) || (s[2] % ((int64_t)pl.S * pl.WK * (pl.split ? 32 : pl.BM == 16 ? 16 : 8)));
   return (s[0] % pl.BM) || (s[1] % pl.BN) || (s[2] % ((int64_t)pl.S * pl.BK));
 }
 
@@ -355,15 +376,15 @@ static GemmPlan gemm_default_fp32(const int64_t* s) {
 // The default without more workspace than the fp32 rule asks for.
 static GemmPlan gemm_default_lean(const int64_t* s) {
   GemmPlan pl = gemm_default_fp32(s);
-  // outputs of few tiles stay with k over the wavefronts (512^3: 8.9 us against 13.2; 400 x 600 x 1000: 13.3 / 23)
-  if (pl.WK > 1 || !split_default(1, s[0], s[1], s[2], false, pl.S, &pl)) return pl;
+  // outputs of few tiles stay with k over the wavefronts, on either kernel
+  if (!(pl.WK > 1 ? split_k_default(s[0], s[1], s[2], pl, &pl) : split_default(1, s[0], s[1], s[2], false, pl.S, &pl))) return pl;
   pl.ragged = gemm_ragged(s, pl);
   return pl;
 }
 
 static GemmPlan gemm_default(const int64_t* s) {
-  GemmPlan pl = gemm_default_lean(s);
-  if (pl.WK <= 1) return pl;
+  GemmPlan pl = gemm_default_fp32(s);
+  if (pl.WK <= 1) return gemm_default_lean(s);
   // Few tiles and many k: parts of k over workgroups too, as many as leave a compute unit one workgroup and a part
   // its worth of k, against the second pass (us, replayed from a graph; WK wavefronts, S parts)
   const int64_t K = s[2];
@@ -384,13 +405,14 @@ static GemmPlan gemm_default(const int64_t* s) {
     // 2500: 26 against 53; 40 x 2000 x 2000: 17 against 26; 512 x 512 x 4096: 28.8 against 28.7)
     const GemmPlan sp{64, 64, 32, 32, 32, 1, 0};
     const int S = parts(cdiv(s[0], 64) * cdiv(s[1], 64), 256);
-    if (S >= 4) {
+    if (S >= 4 && !split_default(1, s[0], s[1], K, false, S, &pl)) {
       pl = sp;
       pl.split = 1;
       pl.S = S;
     }
   }
-  while (pl.split && (pl.S - 1) * split_part(K, pl) >= K) pl.S /= 2;
+  if (!pl.split) split_k_default(s[0], s[1], K, pl, &pl);
+  while (pl.split && pl.WK == 1 && (pl.S - 1) * split_part(K, pl) >= K) pl.S /= 2;
   pl.ragged = gemm_ragged(s, pl);
   return pl;
 }
@@ -427,12 +449,12 @@ int matmul_candidates(const int64_t* s, GemmPlan* out, int cap) {
   }
   if (split_sizes(s[0], s[1], s[2])) {
     GemmPlan sp[kSplitTiles];
-    const int ns = split_tiles(false, sp);
+    const int ns = split_offered(1, s[0], s[1], s[2], false, sp);
     for (int i = 0; i < ns; ++i)
       for (int S : {1, 2, 4}) {
         if (S > 1 && (cdiv(s[0], sp[i].BM) * cdiv(s[1], sp[i].BN) * (S / 2) >= 2048 || s[2] / S < 128)) continue;
         sp[i].S = S;
-        push(sp[i]);
+        if (split_fits(s[0], s[1], s[2], sp[i])) push(sp[i]);
       }
   }
   // k over the wavefronts of a workgroup, for outputs of few tiles (every wavefront keeps 8 k or more)
@@ -470,14 +492,18 @@ mdh_status plan_matmul(const int64_t* s, const mdh_tile_params* p, GemmPlan* out
     // wavefront-layer parts of k: the register-streaming kernel
     GemmPlan pl;
     const bool b16 = p->blk[0] == 16;
-    if (!((p->blk[0] == 32 && p->blk[1] == 32 && p->blk[2] == 2) || (b16 && p->blk[1] == 16 && p->blk[2] == 4)))
+    pl.split = p->blk[2] == 16;
+    if (!((p->blk[0] == 32 && p->blk[1] == 32 && (p->blk[2] == 2 || pl.split)) || (b16 && p->blk[1] == 16 && p->blk[2] == 4)))
       return MDH_ERR_UNSUPPORTED;
     pl.BM = pl.WM = p->prt[MDH_L_VGPR][0] * p->blk[0];
     pl.BN = pl.WN = p->prt[MDH_L_VGPR][1] * p->blk[1];
-    pl.BK = b16 ? 16 : 8;
+    pl.BK = pl.split ? 32 : b16 ? 16 : 8;
     pl.S = p->prt[MDH_L_WG][2];
     pl.WK = p->prt[MDH_L_WAVE][2];
     pl.ragged = ragged;
+    if (pl.split && !split_inst(pl, false)) return MDH_ERR_UNSUPPORTED;
+    if (pl.split && (pl.S - 1) * split_part(s[2], pl) >= s[2]) return MDH_ERR_TILE_NOT_DIVIDING;  // a part without k
+    if (pl.split && !split_fits(s[0], s[1], s[2], pl)) return MDH_ERR_UNSUPPORTED;
     // model constraints: lanes per workgroup, and the LDS that holds the WK partial tiles
     if ((int64_t)pl.WK * 64 > kMaxLanesPerWG) return MDH_ERR_TILE_RESOURCES;
     if ((int64_t)pl.WK * pl.BM * pl.BN * 4 > kLdsBytesPerWG) return MDH_ERR_TILE_RESOURCES;

@@ -98,25 +98,27 @@ void params_from_plan(const int64_t* s, const GemmExPlan& pl, mdh_tile_params* p
   clear_params(p, 4);
   p->blk[1] = 32;
   p->blk[2] = 32;
+  const bool wk = g.WK > 1;  // k over the wavefronts, as in MatMul's table
   const int bk = g.split ? 16 : 2;
   p->blk[3] = bk;
   p->prt[MDH_L_WG][0] = (int32_t)s[0];
   p->prt[MDH_L_WG][1] = (int32_t)cdiv(s[1], g.BM);
   p->prt[MDH_L_WG][2] = (int32_t)cdiv(s[2], g.BN);
   p->prt[MDH_L_WG][3] = g.S;
-  p->prt[MDH_L_HBM][3] = (int32_t)cdiv(cdiv(s[3], g.S), g.BK);
+  p->prt[MDH_L_WAVE][3] = g.WK;
+  p->prt[MDH_L_HBM][3] = (int32_t)cdiv(cdiv(s[3], (int64_t)g.S * g.WK), g.BK);
   p->prt[MDH_L_WAVE][1] = g.BM / g.WM;
   p->prt[MDH_L_WAVE][2] = g.BN / g.WN;
-  p->prt[MDH_L_LDS][3] = g.BK / bk;
+  p->prt[wk ? MDH_L_VGPR : MDH_L_LDS][3] = g.BK / bk;
   p->prt[MDH_L_VGPR][1] = g.WM / 32;
   p->prt[MDH_L_VGPR][2] = g.WN / 32;
   static const int dims[4] = {0, 1, 2, 3};
   set_order(p, dims);
   p->strided = 0;
   p->lane_fast_dim = pl.tc ? 1 : 2;
-  p->in_region[0] = MDH_MR_LDS;
-  p->in_region[1] = MDH_MR_LDS;
-  p->out_region = MDH_MR_VGPR;
+  p->in_region[0] = wk ? MDH_MR_VGPR : MDH_MR_LDS;
+  p->in_region[1] = wk ? MDH_MR_VGPR : MDH_MR_LDS;
+  p->out_region = wk ? MDH_MR_LDS : MDH_MR_VGPR;
   p->in_transposed[0] = (uint8_t)pl.ta;
   p->in_transposed[1] = (uint8_t)pl.tb;
   p->out_transposed = (uint8_t)pl.tc;
@@ -124,7 +126,7 @@ void params_from_plan(const int64_t* s, const GemmExPlan& pl, mdh_tile_params* p
 }
 
 static int ex_ragged(const int64_t* s, const GemmPlan& g) {
-  return (s[1] % g.BM) || (s[2] % g.BN) || (s[3] % ((int64_t)g.S * g.BK));
+  return (s[1] % g.BM) || (s[2] % g.BN) || (s[3] % ((int64_t)g.S * g.WK * g.BK));
 }
 
 static GemmExPlan ex_default_tiled(const int64_t* s);
@@ -215,7 +217,7 @@ int matmul_ex_candidates(const int64_t* s, GemmExPlan* out, int cap) {
     g.ragged = ex_ragged(s, g);
     for (int i = 0; i < n; ++i)
       if (!out[i].skinny && out[i].g.BM == g.BM && out[i].g.BN == g.BN && out[i].g.BK == g.BK && out[i].g.S == g.S &&
-          out[i].g.split == g.split)
+          out[i].g.split == g.split && out[i].g.WK == g.WK)
         return;
     out[n++] = GemmExPlan{g, (int)s[4], (int)s[5], (int)s[6]};
   };
@@ -242,12 +244,12 @@ int matmul_ex_candidates(const int64_t* s, GemmExPlan* out, int cap) {
   push(ex_default_tiled(s).g);
   if (split_sizes(s[1], s[2], s[3])) {
     GemmPlan sp[kSplitTiles];
-    const int ns = split_tiles(s[6] != 0, sp);
+    const int ns = split_offered(s[0], s[1], s[2], s[3], s[6] != 0, sp);
     for (int i = 0; i < ns; ++i)
       for (int S : {1, 2, 4}) {
         if (S > 1 && (s[0] * cdiv(s[1], sp[i].BM) * cdiv(s[2], sp[i].BN) * (S / 2) >= 2048 || s[3] / S < 128)) continue;
         sp[i].S = S;
-        push(sp[i]);
+        if (split_fits(s[1], s[2], s[3], sp[i])) push(sp[i]);
       }
   }
   static const int splits[] = {1, 2, 4, 8, 16, 32};
@@ -295,11 +297,13 @@ mdh_status plan_matmul_ex(const int64_t* s, const mdh_tile_params* p, GemmExPlan
   g.BN = p->prt[MDH_L_WAVE][2] * g.WN;
   if (p->blk[1] != 32 || p->blk[2] != 32 || (p->blk[3] != 2 && p->blk[3] != 16)) return MDH_ERR_UNSUPPORTED;
   g.split = p->blk[3] == 16;
-  g.BK = p->prt[MDH_L_LDS][3] * p->blk[3];
+  if (g.split) g.WK = p->prt[MDH_L_WAVE][3];
+  g.BK = g.WK > 1 ? 32 : p->prt[MDH_L_LDS][3] * p->blk[3];
   if (g.split && (!split_inst(g, s[6] != 0) || !split_sizes(s[1], s[2], s[3]))) return MDH_ERR_UNSUPPORTED;
   g.S = p->prt[MDH_L_WG][3];
   g.ragged = ragged;
   if (g.split && (g.S - 1) * split_part(s[3], g) >= s[3]) return MDH_ERR_TILE_NOT_DIVIDING;  // a part without k
+  if (g.split && !split_fits(s[1], s[2], s[3], g)) return MDH_ERR_UNSUPPORTED;
   GemmExPlan pl{g, (int)s[4], (int)s[5], (int)s[6]};
   mdh_tile_params chk;
   params_from_plan(s, pl, &chk);

@@ -47,40 +47,55 @@ struct No { static constexpr bool value = false; };
 
 constexpr float kTiny = 7.88860905e-31f;  // 2^-100
 
-// Two values per register, and v_dot2c_f32_bf16 (x += p.lo q.lo + p.hi q.hi) to take a rounded value off again: with
-// q = (-1, 0) or (0, -1) that is the difference, in one instruction instead of an unpacking and a subtraction.
-// The vector pipe gets four instructions per 32x32x16 MFMA for free, so they count: eight values take 32.
-// The constants are hidden from the compiler, which would encode 0x0000bf80 as the inline constant -1.0 -- in a
-// packed operand that is (0, -1).
+// Two values per register (v_cvt_pk_bf16_f32), unpacked again by a shift and a mask for the subtractions: eight values
+// take 48 instructions.  v_dot2c_f32_bf16 (DOT) unpacks and subtracts in one (x += p.lo q.lo + p.hi q.hi with q = (-1, 0)
+// or (0, -1): 32 for eight values) but runs in the matrix pipe: beside a 32x32x16 MFMA (32 clocks) two of them take 45,
+// four 56 and eight 78, six instructions of the other kinds 35 and eight 41-44 (clocks a slot and wavefront, one and two
+// wavefronts a SIMD).
+// The constants of the former are hidden from the compiler, which would encode 0x0000bf80 as the inline constant -1.0 --
+// in a packed operand that is (0, -1).
+template <bool DOT = false>
 struct Split {
   unsigned neg_lo = 0x0000bf80u, neg_hi = 0xbf800000u;
 
-  __device__ __forceinline__ Split() { asm("" : "+s"(neg_lo), "+s"(neg_hi)); }
+  __device__ __forceinline__ Split() {
+    if (DOT) asm("" : "+s"(neg_lo), "+s"(neg_hi));
+  }
 
   static __device__ __forceinline__ unsigned pack(float a, float b) {
     const f2 v = {a, b};
     return __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf2));
   }
-  static __device__ __forceinline__ float minus(float x, unsigned p, unsigned q) {
-    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf2, p), __builtin_bit_cast(bf2, q), x, false);
-  }
-  // eight consecutive k of one row: the three slices, 16 bytes each, and the largest magnitude met so far.  Level by
-  // level, because a result of v_dot2c can be read only a few instructions later.
-  __device__ __forceinline__ void operator()(float (&x)[8], u4 (&out)[3], float& largest) const {
+  // slice s of eight consecutive k of one row; what is left of them takes their place.  H also raises the largest
+  // magnitude met so far.  (Level by level: a result of v_dot2c can be read only a few instructions later.)
+  template <int s>
+  __device__ __forceinline__ u4 slice(float (&x)[8], float& largest) const {
+    u4 out;
 #pragma unroll
-    for (int s = 0; s < 3; ++s) {
+    for (int e = 0; e < 4; ++e) {
+      if (s == H) largest = fmaxf(fmaxf(largest, fabsf(x[2 * e])), fabsf(x[2 * e + 1]));
+      out[e] = pack(x[2 * e], x[2 * e + 1]);
+    }
+    if (s < L)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        if (s == 0) largest = fmaxf(fmaxf(largest, fabsf(x[2 * e])), fabsf(x[2 * e + 1]));
-        out[s][e] = pack(x[2 * e], x[2 * e + 1]);
-      }
-      if (s < 2)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          x[2 * e] = minus(x[2 * e], out[s][e], neg_lo);
-          x[2 * e + 1] = minus(x[2 * e + 1], out[s][e], neg_hi);
+        if (DOT) {
+          const unsigned word = out[e];  // (a cast of the element itself takes the first one's)
+          const bf2 p = __builtin_bit_cast(bf2, word);
+          x[2 * e] = __builtin_amdgcn_fdot2_f32_bf16(p, __builtin_bit_cast(bf2, neg_lo), x[2 * e], false);
+          x[2 * e + 1] = __builtin_amdgcn_fdot2_f32_bf16(p, __builtin_bit_cast(bf2, neg_hi), x[2 * e + 1], false);
+        } else {
+          x[2 * e] -= __uint_as_float(out[e] << 16);
+          x[2 * e + 1] -= __uint_as_float(out[e] & 0xffff0000u);
         }
-    }
+      }
+    return out;
+  }
+  // all three, 16 bytes each
+  __device__ __forceinline__ void operator()(float (&x)[8], u4 (&out)[3], float& largest) const {
+    out[H] = slice<H>(x, largest);
+    out[Mid] = slice<Mid>(x, largest);
+    out[L] = slice<L>(x, largest);
   }
 };
 
