@@ -17,7 +17,9 @@
 // 55, and MFMAs alone were 417 us: the parts add up instead of overlapping.  So what counts is bytes and instructions per
 // product, and the largest tile wins: 4096^3 256 x 256 588 us, 256 x 128 646, 128 x 128 710, 128 x 64 794, 64 x 64 879
 // (fp32 instructions: 1010-1070); where that leaves compute units idle, smaller ones: 2048^3 237, 140, 94, 110, 126
-// (145).  The 256 x 256 tile has k-tiles of 16, because two of 32 (192 KB) exceed LDS.  Measured when they were chosen:
+// (145).  The split keeps out of the matrix pipe (mdh_split.h) and is spread evenly over the phases: 4096^3 590 -> 569 us,
+// 16 x 1024^3 163 -> 155.  64 x 64 tiles, whose walk is more split than products, lose by it (1021 x 1531 x 777 25.6 ->
+// 26.7 us), but k over the wavefronts (mdh_matmul_split_k.hip) is faster there.  The 256 x 256 tile has k-tiles of 16, because two of 32 (192 KB) exceed LDS.  Measured when they were chosen:
 // 16x16x32 MFMAs equal at 4096^3 (717 / 726), slower at 1024^3 in 128 x 128 tiles (55.2 / 48.8) -- the smaller one
 // leaves room for one vector instruction beside it, the larger for four; 128 x 128 tiles on eight wavefronts of 32 x 64
 // rather than four of 64 x 64 (2048^3 99.6 / 107, 4096^3 776 / 819): with one wavefront per SIMD nothing covers its
@@ -81,14 +83,17 @@ struct Operand {
 #pragma unroll
     for (int e = 0; e < 8; ++e) x[c][e] = k + e < skip ? 0.f : x[c][e];
   }
-  __device__ __forceinline__ void store(char* st, const Split<true>& split, int c) {
+  // the first half of the work on chunk c is its high slice, the second the other two: 24 vector instructions each
+  __device__ __forceinline__ void store(char* st, const Split<>& split, int c, bool second) {
     const int f = threadIdx.x + c * NT;
     const int row = KC ? f / KP : f % ROWS, kc = KC ? f % KP : f / ROWS;
-    u4 v[3];
-    split(x[c], v, top[c]);
     char* p = st + kc * PLANE + (row ^ (SWZ * kc)) * 16;
-#pragma unroll
-    for (int s = 0; s < 3; ++s) *(u4*)(p + s * SLICE) = v[s];
+    if (!second) {
+      *(u4*)p = split.template slice<H>(x[c], top[c]);
+    } else {
+      *(u4*)(p + Mid * SLICE) = split.template slice<Mid>(x[c], top[c]);
+      *(u4*)(p + L * SLICE) = split.template slice<L>(x[c], top[c]);
+    }
   }
   __device__ __forceinline__ float largest() const {
     float t = 0.f;
@@ -141,7 +146,7 @@ __device__ __forceinline__ void split_tile(const float* __restrict__ Y, const fl
 
   OY oy;
   OX ox;
-  Split<true> split;
+  const Split<> split;
   oy.init(ldy, m0, M);
   ox.init(ldx, n0, N);
   if (threadIdx.x == 0) *largest = 0;
@@ -168,11 +173,11 @@ __device__ __forceinline__ void split_tile(const float* __restrict__ Y, const fl
     else
       ox.load(Xt, ldx, k0, c - OY::CH);
   };
-  auto store = [&](char* st, int c) {
+  auto store = [&](char* st, int c, bool second) {
     if (c < OY::CH)
-      oy.store(st, split, c);
+      oy.store(st, split, c, second);
     else
-      ox.store(st + OY::BYTES, split, c - OY::CH);
+      ox.store(st + OY::BYTES, split, c - OY::CH, second);
   };
   auto mask_last = [&](int t) {
     if (t == nk - 1 && skip) {
@@ -208,11 +213,11 @@ __device__ __forceinline__ void split_tile(const float* __restrict__ Y, const fl
     constexpr int NM = KH * MI * NI;
     if (more && p < 4) {
 #pragma unroll
-      for (int c = p * CH / 4; c < (p + 1) * CH / 4; ++c) {
-        store(lds + ((t + 1) & 1) * STAGE, c);
-        load(t + 2, c);
+      for (int h = p * CH / 2; h < (p + 1) * CH / 2; ++h) {
+        store(lds + ((t + 1) & 1) * STAGE, h / 2, h % 2);
+        if (h % 2) load(t + 2, h / 2);
       }
-      constexpr int V = (32 * ((CH + 3) / 4) + NM - 1) / NM;
+      constexpr int V = (24 * ((CH + 1) / 2) + NM - 1) / NM;
 #pragma unroll
       for (int i = 0; i < NM; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -250,7 +255,8 @@ __device__ __forceinline__ void split_tile(const float* __restrict__ Y, const fl
   mask_last(0);
 #pragma unroll
   for (int c = 0; c < CH; ++c) {
-    store(lds, c);
+    store(lds, c, false);
+    store(lds, c, true);
     load(1, c);
   }
   __syncthreads();
@@ -367,7 +373,7 @@ __device__ __forceinline__ void split_tile(const float* __restrict__ Y, const fl
 // (second launch bound: the wavefronts of a SIMD that LDS has room for, so that the fp32 evaluation, whose registers
 // would allow fewer, does not come into it)
 template <int BM, int BN, int BK, int WM, int WN, bool YK, bool XK>
-__global__ __launch_bounds__(((BM / WM) * (BN / WN) * 64), (BM + BN > 128 ? 2 : 3)) void matmul_split_kernel(
+__global__ __launch_bounds__(((BM / WM) * (BN / WN) * 64), 2) void matmul_split_kernel(
     const float* __restrict__ Y, const float* __restrict__ X, float* __restrict__ C, float* __restrict__ ws, int M, int N,
     int K, int tiles_m, int tiles_n, int S, int kchunk, int nbatch, int jmajor) {
   extern __shared__ __attribute__((aligned(16))) char lds[];

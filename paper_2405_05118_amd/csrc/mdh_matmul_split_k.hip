@@ -17,7 +17,8 @@
 // every 4.6 clocks, so six fit under an MFMA of 32 clocks; the split takes 8 (MI + NI) / (MI NI) of them (2 x 2: 8.0, 2 x
 // 3: 6.7, 3 x 3: 5.3).  The kernel that shares the split through LDS (mdh_matmul_split.hip) has fewer with its large tiles
 // but needs M N for 256 of them, and on small ones a barrier and two trips through LDS per 32 k: 64 x 64 tiles take
-// 0.57 us for that, 0.3 here: 1021 x 1531 x 777 25.6 -> 21.0 us, 1024^3 22.7 -> 17.4, 1500^3 62 -> 45.  Loads are not what bounds it (hits in the first level cost the same).
+// 0.57 us for that, 0.3 here: 1021 x 1531 x 777 25.6 -> 21.0 us, 1024^3 22.7 -> 17.4, 1500^3 62 -> 45.  Loads are not what
+// bounds it (hits in the first level cost the same).
 // Measured without gain: the split of the next 16 k between the matrix instructions of these (by the compiler's
 // scheduling groups); loads a chunk earlier; 16-byte loads of row-contiguous operands, exchanged between lanes.
 #include "mdh_matmul_split.h"
@@ -190,6 +191,8 @@ __global__ __launch_bounds__(W * 64, (MI * NI > 6 ? 1 : 2)) void matmul_split_k_
       }
   OY oy;
   OX ox;
+  // (six blocks on one wavefront a SIMD: 1024^3 in 64 x 96 tiles 21.5 us with v_dot2c, 24.1 without; the others: 96 x 96
+  // at 1500^3 45.7 / 44.8, 64 x 64 at 2048^3 105 / 100)
   const Split<MI * NI == 6> split;
   oy.init(Y, (int64_t)M * K, ldy, m0);
   ox.init(X, (int64_t)N * K, ldx, n0);

@@ -201,7 +201,7 @@ __global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT), (Cfg<TP, TQ, BN,
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[mi][ni][r] = 0.f;
 
-  const Split<true> split;
+  const Split<> split;
   const int taps = g.R * g.S;
   // filter chunks of this thread: eight channels of one output channel; channels beyond K repeat the last one
   float fx[F::F_CH][8];
@@ -285,7 +285,8 @@ __global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT), (Cfg<TP, TQ, BN,
 #pragma unroll
         for (int ni = 0; ni < F::NI; ++ni) acc[mi][ni] = mfma(x[sx][ni][h], y[sy][mi][h], acc[mi][ni]);
   };
-  // phases 0 to 3 are one scheduling region: an MFMA, an LDS read for a later phase, a share of the next tap's split
+  // phases 0 to 3 are one scheduling region: an MFMA, an LDS read for a later phase, a share of the next tap's split (out of
+  // the matrix pipe: 16 x 224 x 224 x 64 -> 128, 7 x 7, 2790 -> 2650 us; 16 x 56 x 56 x 64 -> 64, 3 x 3, 28.9 -> 28.3)
   auto body = [&](int tap, int at, int at_next, int c0, auto more_) {
     constexpr bool more = decltype(more_)::value;
     const char* cur = lds + (tap & 1) * F::F_STAGE;
@@ -304,7 +305,7 @@ __global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT), (Cfg<TP, TQ, BN,
         load_filter(min(tap + 2, taps - 1), c0, c);
       }
     }
-    constexpr int NM = 4 * F::KH * F::MI * F::NI, V = (36 * F::F_CH + NM - 1) / NM;
+    constexpr int NM = 4 * F::KH * F::MI * F::NI, V = (48 * F::F_CH + NM - 1) / NM;
 #pragma unroll
     for (int i = 0; i < NM; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
