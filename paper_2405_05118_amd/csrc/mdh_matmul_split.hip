@@ -266,8 +266,31 @@ __device__ __forceinline__ void split_tile(const float* __restrict__ Y, const fl
   for (; t + 1 < nk; ++t) body(t, Yes{});
   body(t, No{});
 
-  // values the split does not carry (mdh_split.h): bit mi * NI + ni of `redo` is a block of this wavefront that holds an
-  // output they may have entered
+  const bool whole = m0 + BM <= M && n0 + BN <= N;
+#pragma unroll
+  for (int mi = 0; mi < MI; ++mi) {
+    const int row = m0 + wm + mi * 32 + l32;
+    float* const p = Cout + (int64_t)row * N + n0 + wn + 4 * lh;
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int j = ni * 32 + 8 * g;
+        const f4 v = {acc[mi][ni][4 * g], acc[mi][ni][4 * g + 1], acc[mi][ni][4 * g + 2], acc[mi][ni][4 * g + 3]};
+        if (whole) {
+          *(f4u*)(p + j) = v;
+        } else if (row < M) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (n0 + wn + 4 * lh + j + r < N) p[j + r] = v[r];
+        }
+      }
+    }
+  }
+
+  // Values the split does not carry (mdh_split.h): bit mi * NI + ni of `redo` is a block of this wavefront that holds an
+  // output they may have entered.  The outputs are on their way by now: the search takes its time beside the stores, and
+  // what is evaluated again is written over them.
   unsigned redo = 0;
   float least = __builtin_huge_valf();
 #pragma unroll
@@ -289,6 +312,7 @@ __device__ __forceinline__ void split_tile(const float* __restrict__ Y, const fl
     unsigned* const blocks = rows + BM + BN;
     const Marks ym(blocks + 2, BM), xm(blocks + 2 + Marks::words(BM), BN);
     static_assert((BM + BN + 2 + Marks::words(BM) + Marks::words(BN)) * 4 <= 2 * STAGE, "");
+    wait_stores_done();  // (other wavefronts may write some of them again)
     for (int i = threadIdx.x; i < BM + BN + 2 + Marks::words(BM) + Marks::words(BN); i += NT) rows[i] = 0;
     __syncthreads();
     oy.merge(rows);
@@ -325,29 +349,6 @@ __device__ __forceinline__ void split_tile(const float* __restrict__ Y, const fl
     __syncthreads();
     const unsigned lo = __builtin_amdgcn_readfirstlane(blocks[0]), hi = __builtin_amdgcn_readfirstlane(blocks[1]);
     todo = lo | (unsigned long long)hi << 32;
-  }
-
-  const bool whole = m0 + BM <= M && n0 + BN <= N;
-#pragma unroll
-  for (int mi = 0; mi < MI; ++mi) {
-    const int row = m0 + wm + mi * 32 + l32;
-    float* const p = Cout + (int64_t)row * N + n0 + wn + 4 * lh;
-#pragma unroll
-    for (int ni = 0; ni < NI; ++ni) {
-      if (redo >> (mi * NI + ni) & 1) continue;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int j = ni * 32 + 8 * g;
-        const f4 v = {acc[mi][ni][4 * g], acc[mi][ni][4 * g + 1], acc[mi][ni][4 * g + 2], acc[mi][ni][4 * g + 3]};
-        if (whole) {
-          *(f4u*)(p + j) = v;
-        } else if (row < M) {
-#pragma unroll
-          for (int r = 0; r < 4; ++r)
-            if (n0 + wn + 4 * lh + j + r < N) p[j + r] = v[r];
-        }
-      }
-    }
   }
 
   if (!todo) return;

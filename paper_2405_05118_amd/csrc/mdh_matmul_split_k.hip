@@ -311,8 +311,24 @@ __global__ __launch_bounds__(W * 64, (MI * NI > 6 ? 1 : 2)) void matmul_split_k_
     for (int e = 0; e < 4; ++e) odd |= !(fabsf(c[i][e]) < __builtin_huge_valf()) || fabsf(c[i][e]) < bound;
   }
 
-  // values the split does not carry (mdh_split.h): bit of a 32 x 32 block of the tile that holds an output they may have
-  // entered
+#pragma unroll
+  for (int i = 0; i < NQ; ++i) {
+    const int u = threadIdx.x + i * NT, row = u / (BN / 4), col = u % (BN / 4) * 4;
+    if (QUADS % NT && u >= QUADS) break;
+    if (row < mskip) continue;
+    float* const p = out + (int64_t)(m0 + row) * N + n0 + col;
+    if (col >= nskip) {
+      *(f4u*)p = c[i];
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (col + e >= nskip) p[e] = c[i][e];
+    }
+  }
+
+  // Values the split does not carry (mdh_split.h): bit of a 32 x 32 block of the tile that holds an output they may have
+  // entered.  The outputs are on their way by now: the search takes its time beside the stores, and what is evaluated
+  // again is written over them.
   unsigned todo = 0;
   if (__syncthreads_or(odd)) {
     unsigned* const rows = (unsigned*)lds;  // the partial tiles are done with
@@ -320,6 +336,7 @@ __global__ __launch_bounds__(W * 64, (MI * NI > 6 ? 1 : 2)) void matmul_split_k_
     const Marks ym(blocks + 2, BM), xm(blocks + 2 + Marks::words(BM), BN);
     constexpr int WORDS = BM + BN + 2 + Marks::words(BM) + Marks::words(BN);
     static_assert(WORDS * 4 <= LD::TOP, "");
+    wait_stores_done();  // (other wavefronts may write some of them again)
     for (int i = threadIdx.x; i < WORDS; i += NT) rows[i] = 0;
     __syncthreads();
     oy.merge(rows);
@@ -348,21 +365,6 @@ __global__ __launch_bounds__(W * 64, (MI * NI > 6 ? 1 : 2)) void matmul_split_k_
       if (__syncthreads_or(found)) todo = blocks[1];
     }
     todo = __builtin_amdgcn_readfirstlane(todo | blocks[0]);
-  }
-
-#pragma unroll
-  for (int i = 0; i < NQ; ++i) {
-    const int u = threadIdx.x + i * NT, row = u / (BN / 4), col = u % (BN / 4) * 4;
-    if (QUADS % NT && u >= QUADS) break;
-    if (row < mskip || (todo >> (row / 32 * NI + col / 32) & 1)) continue;
-    float* const p = out + (int64_t)(m0 + row) * N + n0 + col;
-    if (col >= nskip) {
-      *(f4u*)p = c[i];
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (col + e >= nskip) p[e] = c[i][e];
-    }
   }
   for (int i = 0; todo; ++i, todo &= todo - 1)
     if (i % W == wave) {

@@ -169,8 +169,8 @@ __device__ __forceinline__ bool holds_tiny(const Conv& g, int n, int p0, int q0,
 // the filter of tap t+1 is split while tap t is multiplied, that of tap t+2 is on its way from memory, and the one
 // barrier of a tap stands where all its operands are in registers.  The smaller products come first, for the reason
 // given there.
-template <int TP, int TQ, int BN, int CK, int WM, int WN>
-__global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT), (Cfg<TP, TQ, BN, CK, WM, WN>::HELD)) void mcc_split_kernel(
+template <int TP, int TQ, int BN, int CK, int WM, int WN, bool AHEAD>
+__global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT), (AHEAD && CK == 32 && Cfg<TP, TQ, BN, CK, WM, WN>::MI * Cfg<TP, TQ, BN, CK, WM, WN>::NI == 2 ? 2 : Cfg<TP, TQ, BN, CK, WM, WN>::HELD)) void mcc_split_kernel(
     Conv g, float* __restrict__ ws, int tp_n, int tq_n, int tk_n, int n_img, int SC, int cchunk) {
   using F = Cfg<TP, TQ, BN, CK, WM, WN>;
   extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -258,46 +258,56 @@ __global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT), (Cfg<TP, TQ, BN,
     }
   };
 
-  u4 y[3][F::MI][F::KH], x[3][F::NI][F::KH];
+  // Operands of the tap that is multiplied; the high slices of the one before are still in use when those of the next are
+  // read, so they have two places.
+  struct Regs {
+    u4 y[F::MI][F::KH], x[F::NI][F::KH];
+  } mid, low, high[2];
   const int pix0 = (wm * F::MI * F::RB + l32 / TQ) * g.sh * PW + l32 % TQ * g.sw;
   const int block_rows = F::RB * g.sh * PW * 16;  // LDS distance between consecutive blocks of a wavefront
-  auto read_y = [&](int at, int s) {  // at: the tap's pixel offset
+  auto read_y = [&](Regs& to, int at, int s) {  // at: the tap's pixel offset
 #pragma unroll
     for (int h = 0; h < F::KH; ++h)
 #pragma unroll
       for (int mi = 0; mi < F::MI; ++mi)
-        y[s][mi][h] = *(const u4*)(patch + s * pslice + (2 * h + lh) * pplane + (pix0 + at) * 16 + mi * block_rows);
+        to.y[mi][h] = *(const u4*)(patch + s * pslice + (2 * h + lh) * pplane + (pix0 + at) * 16 + mi * block_rows);
   };
-  auto read_x = [&](const char* st, int s) {
+  auto read_x = [&](Regs& to, const char* st, int s) {
 #pragma unroll
     for (int h = 0; h < F::KH; ++h) {
       const int kc = 2 * h + lh;
       const char* p = st + s * F::F_SLICE + kc * F::F_PLANE + (wn * WN + (l32 ^ (64 / CK * kc))) * 16;
 #pragma unroll
-      for (int ni = 0; ni < F::NI; ++ni) x[s][ni][h] = *(const u4*)(p + ni * 512);
+      for (int ni = 0; ni < F::NI; ++ni) to.x[ni][h] = *(const u4*)(p + ni * 512);
     }
   };
-  auto mma = [&](int sy, int sx) {
+  auto mma = [&](const Regs& a, const Regs& b) {  // pixels of a, filter of b
 #pragma unroll
     for (int h = 0; h < F::KH; ++h)
 #pragma unroll
       for (int mi = 0; mi < F::MI; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < F::NI; ++ni) acc[mi][ni] = mfma(x[sx][ni][h], y[sy][mi][h], acc[mi][ni]);
+        for (int ni = 0; ni < F::NI; ++ni) acc[mi][ni] = mfma(b.x[ni][h], a.y[mi][h], acc[mi][ni]);
   };
-  // phases 0 to 3 are one scheduling region: an MFMA, an LDS read for a later phase, a share of the next tap's split (out of
-  // the matrix pipe: 16 x 224 x 224 x 64 -> 128, 7 x 7, 2790 -> 2650 us; 16 x 56 x 56 x 64 -> 64, 3 x 3, 28.9 -> 28.3)
-  auto body = [&](int tap, int at, int at_next, int c0, auto more_) {
+  // Phases 0 to 3 are one scheduling region: an MFMA, an LDS read, a share of the next tap's split (out of the matrix pipe:
+  // 16 x 224 x 224 x 64 -> 128, 7 x 7, 2790 -> 2650 us; 16 x 56 x 56 x 64 -> 64, 3 x 3, 28.9 -> 28.3).
+  // AHEAD: the patch is there for all taps, so the pixels of the next one are read from phase 2 on, its filter behind the
+  // barrier, and every operand is requested two phases or more before it is multiplied; else one phase.
+  constexpr int PM = F::KH * F::MI * F::NI;  // MFMAs of a phase
+  auto body = [&](int tap, int at, int at_next, int c0, auto par_, auto more_) {
     constexpr bool more = decltype(more_)::value;
-    const char* cur = lds + (tap & 1) * F::F_STAGE;
-    read_x(cur, H);
-    mma(Mid, Mid);
-    read_y(at, H);
-    mma(Mid, H);
-    read_x(cur, L);
-    mma(H, Mid);
-    read_y(at, L);
-    mma(H, L);
+    constexpr int par = decltype(par_)::value ? 1 : 0;
+    const char *const cur = lds + (tap & 1) * F::F_STAGE, *const nxt = lds + ((tap + 1) & 1) * F::F_STAGE;
+    if (!AHEAD) read_x(high[par], cur, H);
+    mma(mid, mid);
+    if (!AHEAD) read_y(high[par], at, H);
+    mma(mid, high[par]);
+    if (!AHEAD) read_x(low, cur, L);
+    if (AHEAD && more) read_y(mid, at_next, Mid);
+    mma(high[par], mid);
+    if (!AHEAD) read_y(low, at, L);
+    if (AHEAD && more) read_y(high[par ^ 1], at_next, H);
+    mma(high[par], low);
     if (more) {
 #pragma unroll
       for (int c = 0; c < F::F_CH; ++c) {
@@ -305,21 +315,24 @@ __global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT), (Cfg<TP, TQ, BN,
         load_filter(min(tap + 2, taps - 1), c0, c);
       }
     }
-    constexpr int NM = 4 * F::KH * F::MI * F::NI, V = (48 * F::F_CH + NM - 1) / NM;
+    constexpr int V = (48 * F::F_CH + 4 * PM - 1) / (4 * PM);
 #pragma unroll
-    for (int i = 0; i < NM; ++i) {
+    for (int i = 0; i < 4 * PM; ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      if (!AHEAD || (more && i >= 2 * PM)) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       if (more) __builtin_amdgcn_sched_group_barrier(0x002, V, 0);
     }
     __builtin_amdgcn_sched_barrier(0);
     if (more) {
       __syncthreads();
-      read_y(at_next, Mid);
-      read_x(lds + ((tap + 1) & 1) * F::F_STAGE, Mid);
+      if (!AHEAD) read_y(mid, at_next, Mid);
+      read_x(mid, nxt, Mid);
+      if (AHEAD) read_x(high[par ^ 1], nxt, H);
+      if (AHEAD) read_x(low, nxt, L);
     }
-    mma(L, H);
-    mma(H, H);
+    mma(low, high[par]);
+    if (AHEAD && more) read_y(low, at_next, L);
+    mma(high[par], high[par]);
     __builtin_amdgcn_sched_barrier(0);
   };
 
@@ -337,18 +350,62 @@ __global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT), (Cfg<TP, TQ, BN,
       load_filter(min(1, taps - 1), c0, c);
     }
     __syncthreads();
-    read_y(0, Mid);
-    read_x(lds, Mid);
-    int r = 0, s = 0;
-    for (int tap = 0; tap + 1 < taps; ++tap) {
-      const int at = r * PW + s;
-      if (++s == g.S) s = 0, ++r;
-      body(tap, at, r * PW + s, c0, Yes{});
+    read_y(mid, 0, Mid);
+    read_x(mid, lds, Mid);
+    if (AHEAD) {
+      read_x(high[0], lds, H);
+      read_y(high[0], 0, H);
+      read_x(low, lds, L);
+      read_y(low, 0, L);
     }
-    body(taps - 1, r * PW + s, 0, c0, No{});
+    int r = 0, s = 0, at = 0, tap = 0;
+    auto step = [&](auto par) {
+      if (++s == g.S) s = 0, ++r;
+      const int to = r * PW + s;
+      body(tap++, at, to, c0, par, Yes{});
+      at = to;
+    };
+    if constexpr (AHEAD) {
+      while (tap + 2 < taps) {
+        step(No{});
+        step(Yes{});
+      }
+      if (tap + 1 < taps) {
+        step(No{});
+        body(tap, at, 0, c0, Yes{}, No{});
+      } else {
+        body(tap, at, 0, c0, No{}, No{});
+      }
+    } else {
+      while (tap + 1 < taps) step(No{});
+      body(tap, at, 0, c0, No{}, No{});
+    }
   }
 
-  // values the split does not carry (mdh_split.h)
+  // output view (n,p,q,k,0,0,0) -> out[n,p,q,k]: a lane holds four consecutive k of one pixel
+  const bool whole = p0 + TP <= g.P && q0 + TQ <= g.Q && k0 + BN <= g.K;
+#pragma unroll
+  for (int mi = 0; mi < F::MI; ++mi) {
+    const int p = p0 + (wm * F::MI + mi) * F::RB + l32 / TQ, q = q0 + l32 % TQ, kb = k0 + wn * WN + 4 * lh;
+    float* const o = dst + (((int64_t)n * g.P + p) * g.Q + q) * g.K + kb;
+#pragma unroll
+    for (int ni = 0; ni < F::NI; ++ni)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const int j = ni * 32 + 8 * q4;
+        const f4 v = {acc[mi][ni][4 * q4], acc[mi][ni][4 * q4 + 1], acc[mi][ni][4 * q4 + 2], acc[mi][ni][4 * q4 + 3]};
+        if (whole) {
+          *(f4u*)(o + j) = v;
+        } else if (p < g.P && q < g.Q) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            if (kb + j + e < g.K) o[j + e] = v[e];
+        }
+      }
+  }
+
+  // Values the split does not carry (mdh_split.h).  The outputs are on their way by now: the search takes its time beside
+  // the stores (before them it was 1.4 us of the 28 of 16 x 56 x 56 x 64 -> 64, 3 x 3).
   float z = 0.f, least = __builtin_huge_valf();
 #pragma unroll
   for (int mi = 0; mi < F::MI; ++mi)
@@ -421,32 +478,8 @@ __global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT), (Cfg<TP, TQ, BN,
       }
     }
   }
-  if (fp32) {
-    recompute_fp32<TP, TQ, BN, CK, WM, WN>(g, dst, n, p0, q0, k0, cbeg, cend);
-    return;
-  }
-
-  // output view (n,p,q,k,0,0,0) -> out[n,p,q,k]: a lane holds four consecutive k of one pixel
-  const bool whole = p0 + TP <= g.P && q0 + TQ <= g.Q && k0 + BN <= g.K;
-#pragma unroll
-  for (int mi = 0; mi < F::MI; ++mi) {
-    const int p = p0 + (wm * F::MI + mi) * F::RB + l32 / TQ, q = q0 + l32 % TQ, kb = k0 + wn * WN + 4 * lh;
-    float* const o = dst + (((int64_t)n * g.P + p) * g.Q + q) * g.K + kb;
-#pragma unroll
-    for (int ni = 0; ni < F::NI; ++ni)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const int j = ni * 32 + 8 * q4;
-        const f4 v = {acc[mi][ni][4 * q4], acc[mi][ni][4 * q4 + 1], acc[mi][ni][4 * q4 + 2], acc[mi][ni][4 * q4 + 3]};
-        if (whole) {
-          *(f4u*)(o + j) = v;
-        } else if (p < g.P && q < g.Q) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (kb + j + e < g.K) o[j + e] = v[e];
-        }
-      }
-  }
+  // (written over what was stored above, by the same lanes; a wavefront's stores to an address stay in order)
+  if (fp32) recompute_fp32<TP, TQ, BN, CK, WM, WN>(g, dst, n, p0, q0, k0, cbeg, cend);
 }
 
 template <int TP, int TQ, int BN, int CK, int WM, int WN>
@@ -455,9 +488,14 @@ mdh_status launch_t(int SC, int64_t N, const Conv& g, void* ws, hipStream_t st) 
   const int npix = ((TP - 1) * g.sh + g.R) * ((TQ - 1) * g.sw + g.S);
   const int64_t lds_bytes = 2ll * F::F_STAGE + 3ll * F::KP * F::plane(npix) + 16;
   if (lds_bytes > 160 * 1024) return MDH_ERR_TILE_RESOURCES;
-  auto kern = mcc_split_kernel<TP, TQ, BN, CK, WM, WN>;
-  static int64_t lds_allowed[kMaxDevices] = {};
-  if (allow_dynamic_lds((const void*)kern, lds_bytes, lds_allowed) != MDH_OK) return MDH_ERR_LAUNCH;
+  // One tap has nothing to read ahead, tiles of 64 x 64 a wavefront have no registers for it, and 64 pixels x 32 channels in
+  // chunks of 32 are slower with it (16 x 56 x 56 x 64 -> 64, 3 x 3, 30.6 -> 32.2 us).  The others: 8 x 16 x 16 x 33 -> 90,
+  // 5 x 5, 18.3 -> 15.7; 20 x 12 x 12 x 160 -> 100, 7 x 7, 111 -> 95; 32 x 7 x 7 x 200 -> 64, 3 x 3, 17.0 -> 15.0.
+  constexpr bool ROOM = F::MI * F::NI == 1 || (F::MI * F::NI == 2 && (CK == 16 || F::NI == 2));
+  const bool ahead = ROOM && g.R * g.S > 1;
+  auto kern = ahead ? mcc_split_kernel<TP, TQ, BN, CK, WM, WN, ROOM> : mcc_split_kernel<TP, TQ, BN, CK, WM, WN, false>;
+  static int64_t lds_allowed[2][kMaxDevices] = {};
+  if (allow_dynamic_lds((const void*)kern, lds_bytes, lds_allowed[ahead]) != MDH_OK) return MDH_ERR_LAUNCH;
   const int64_t tp_n = cdiv(g.P, TP), tq_n = cdiv(g.Q, TQ), tk_n = cdiv(g.K, BN);
   if (SC < 1) return MDH_ERR_UNSUPPORTED;
   const int64_t cchunk = cdiv(cdiv(g.C, SC), CK) * CK;
