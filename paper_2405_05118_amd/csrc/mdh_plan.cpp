@@ -823,37 +823,47 @@ static MccPlan mcc_default_fp32(const int64_t* s) {
   return pl;
 }
 
-// Microseconds one filter tap of 32 channels takes the workgroups a compute unit holds (index: how many, less one),
-// per tile of kMccSplitMenu's shapes.  Measured on 3 x 3 and 7 x 7 layers of 16 to 512 channels.
+// Microseconds that a filter tap of one channel chunk takes the workgroups a compute unit holds at once (index: how many,
+// less one), per number of pixels, channels and CK of kMccSplitMenu; `full` is the share by which the clock gives way with
+// all compute units at work.  A chunk's patch takes `patch` and `pixel` per hundred of its pixels, a call `once`.  Fitted to
+// 160 random layers (16 to 512 channels, 1 x 1 to 7 x 7, stride 1 and 2, up to 4e10 operations), every tile in every number
+// of parts on each: off by 6 to 8 % rms; the tile it picks takes 0.7 % longer on average than the fastest.
 struct TapTime {
-  int px, BN, held;
-  double us[4];
+  int px, BN, CK, held;
+  double once, patch, pixel, full, us[4];
 };
-static const TapTime kTap[] = {{64, 64, 4, {0.58, 0.80, 1.10, 1.40}}, {64, 128, 2, {0.80, 1.40}}, {128, 64, 3, {0.70, 1.30, 1.90}},
-                               {128, 128, 2, {1.40, 2.40}},          {256, 128, 1, {2.17}}};
+static const TapTime kTap[] = {{64, 64, 16, 4, 4.7, 0.25, 0.313, 0.04, {0.292, 0.389, 0.565, 0.730}},
+                               {64, 64, 32, 4, 4.6, 0.0, 0.779, 0.17, {0.310, 0.525, 0.725, 1.005}},
+                               {64, 128, 16, 2, 4.9, 0.24, 0.315, 0.12, {0.326, 0.469}},
+                               {64, 128, 32, 2, 5.1, 0.21, 0.656, 0.10, {0.582, 0.978}},
+                               {128, 64, 16, 3, 5.1, 0.17, 0.308, 0.11, {0.339, 0.490, 0.739}},
+                               {128, 64, 32, 3, 5.2, 0.12, 0.592, 0.16, {0.459, 0.761, 1.477}},
+                               {128, 128, 16, 2, 6.1, 0.18, 0.319, 0.13, {0.469, 0.807}},
+                               {128, 128, 32, 2, 6.2, 0.28, 0.591, 0.18, {0.837, 1.705}},
+                               {256, 128, 16, 1, 7.6, 0.52, 0.148, 0.26, {0.753}},
+                               {256, 128, 32, 1, 7.8, 0.0, 0.506, 0.25, {1.340}}};
 
 static double mcc_split_estimate(const int64_t* s, const MccPlan& pl) {
-  const int64_t P = s[1] > 0 ? s[1] : 1, Q = s[2] > 0 ? s[2] : 1;
+  const int64_t P = s[1] > 0 ? s[1] : 1, Q = s[2] > 0 ? s[2] : 1, N = s[0] > 0 ? s[0] : 1, K = s[3] > 0 ? s[3] : 1;
   const TapTime* t = kTap;
-  while (t->px != pl.TP * pl.TQ || t->BN != pl.BN) ++t;
+  while (t->px != pl.TP * pl.TQ || t->BN != pl.BN || t->CK != pl.CK) ++t;
   const int64_t lds = kLdsBytesPerWG / mcc_lds_bytes(pl, s);
   const int held = (int)(lds < t->held ? lds : t->held);
-  const int64_t work = (s[0] > 0 ? s[0] : 1) * cdiv(P, pl.TP) * cdiv(Q, pl.TQ) * cdiv(s[3] > 0 ? s[3] : 1, pl.BN) * pl.S;
+  const int64_t work = N * cdiv(P, pl.TP) * cdiv(Q, pl.TQ) * cdiv(K, pl.BN) * pl.S;
   const int64_t npix = ((pl.TP - 1) * s[7] + s[5]) * ((pl.TQ - 1) * s[8] + s[6]);
-  // per chunk of channels: the patch, then the taps; a chunk of 16 channels takes a little more than half of 32
-  const double half = pl.CK == 16 ? 0.55 : 1.0;
   const int64_t chunks = cdiv(cdiv(s[4], pl.S), pl.CK);
   auto round = [&](int r) {
-    return chunks * (s[5] * s[6] * t->us[r - 1] * half + (0.5 + 0.002 * npix * half) * (1 + 0.3 * (r - 1)));
+    return chunks * (s[5] * s[6] * t->us[r - 1] + (t->patch + t->pixel * npix / 100) * (1 + 0.3 * (r - 1)));
   };
-  double us = (double)(work / (256 * held)) * round(held);
+  double us = t->once + (double)(work / (256 * held)) * round(held) * (1 + t->full);
   const int64_t rest = work % (256 * held);
-  if (rest) us += round((int)cdiv(rest, 256));
-  if (pl.S > 1) us += 3.0 + 0.5 * pl.S + (double)(pl.S + 1) * s[0] * P * Q * s[3] * 1e-6;  // second pass: 4 bytes at 4 TB/s
+  if (rest) us += round((int)cdiv(rest, 256)) * (1 + t->full * (rest < 256 ? rest : 256) / 256);
+  if (pl.S > 1) us += 0.4 + 0.3 * pl.S + (double)(pl.S + 1) * N * P * Q * K * 2.3e-6;  // second pass
   return us;
 }
 
-// Which tile of the split kernel the default is.  The pixel block is the fp32 rule's (TQ).  `S` is the number of parts
+// Which tile of the split kernel the default is.  The fp32 rule's pixel block (TQ) is kept unless another is 3 % faster by
+// the estimate (16 x 56 x 56 x 64 -> 64, 3 x 3: 30.6 with blocks of 4 x 8, 30.1 with 2 x 16).  `S` is the number of parts
 // the fp32 rule splits c into: not more parts here, so that no call needs more workspace than it does there.  It is ahead of the fp32 kernels on every
 // layer measured from 16 channels on (us, against theirs): 16 x 224 x 224 x 64 -> 128, 7 x 7: 2766 / 4829; 16 x 56 x
 // 56 x 64 -> 64, 3 x 3: 28.8 / 51.1; 1 x 1, 256 -> 64: 21.5 / 29.6; 32 x 7 x 7 x 512 -> 512, 3 x 3: 67.5 / 109;
@@ -870,8 +880,8 @@ static bool mcc_split_default(const int64_t* s, int TQ, int S, MccPlan* out) {
       MccPlan pl{m.TP, m.TQ, m.BN, m.CK, m.WM, m.WN, 0, 0};
       pl.S = parts;
       pl.split = 1;
-      if (pl.TQ != TQ || !mcc_split_sizes(s, pl) || mcc_lds_bytes(pl, s) > kLdsBytesPerWG) continue;
-      const double us = mcc_split_estimate(s, pl);
+      if (!mcc_split_sizes(s, pl) || mcc_lds_bytes(pl, s) > kLdsBytesPerWG) continue;
+      const double us = mcc_split_estimate(s, pl) * (pl.TQ == TQ ? 1.0 : 1.03);
       if (best < 0 || us < best) best = us, *out = pl;
     }
   return best >= 0;
@@ -1018,6 +1028,8 @@ mdh_status plan_mcc(const int64_t* s, const mdh_tile_params* p, MccPlan* out) {
     pl.WM = p->prt[MDH_L_VGPR][1] * 32;
     pl.TP = p->prt[MDH_L_WAVE][1] * p->prt[MDH_L_VGPR][1] * (32 / pl.TQ);
     pl.split = p->prt[MDH_L_VGPR][4] == 8;
+    // chunks beyond any LDS, and beyond 32 bits here
+    if (p->prt[MDH_L_LDS][4] > 4096 || p->prt[MDH_L_VGPR][4] > 4096) return MDH_ERR_TILE_RESOURCES;
     pl.CK = p->prt[MDH_L_LDS][4] * 2 * p->prt[MDH_L_VGPR][4];
     pl.S = p->prt[MDH_L_WG][4];
     // a workgroup part of c that owns no channel would leave its partial output unset
