@@ -78,6 +78,7 @@ int64_t split_lds_bytes(const GemmPlan& g);
 inline int64_t split_part(int64_t K, const GemmPlan& g) { return cdiv(cdiv(K, g.S), g.BK) * g.BK; }  // k of a workgroup part
 int split_tiles(bool tc, GemmPlan* out);
 int split_offered(int64_t batch, int64_t M, int64_t N, int64_t K, bool tc, GemmPlan* out);
+bool split_small_default(int64_t batch, int64_t M, int64_t N, int64_t K, bool tc, const GemmPlan& f, GemmPlan* g);
 bool split_k_default(int64_t M, int64_t N, int64_t K, const GemmPlan& f, GemmPlan* g);
 bool split_default(int64_t batch, int64_t M, int64_t N, int64_t K, bool tc, int S, GemmPlan* g);
 }  // namespace detail

@@ -133,7 +133,8 @@ static GemmExPlan ex_default_tiled(const int64_t* s);
 
 static GemmExPlan ex_default_large(const int64_t* s) {
   GemmExPlan pl = ex_default_tiled(s);
-  if (split_default(s[0], s[1], s[2], s[3], s[6] != 0, pl.g.S, &pl.g)) pl.g.ragged = ex_ragged(s, pl.g);
+  if (split_default(s[0], s[1], s[2], s[3], s[6] != 0, pl.g.S, &pl.g) || split_small_default(s[0], s[1], s[2], s[3], s[6] != 0, pl.g, &pl.g))
+    pl.g.ragged = ex_ragged(s, pl.g);
   return pl;
 }
 

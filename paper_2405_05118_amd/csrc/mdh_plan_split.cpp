@@ -151,6 +151,23 @@ bool split_default(int64_t batch, int64_t M, int64_t N, int64_t K, bool tc, int 
   return best_tile(0, batch, M, N, K, tc, S, g) >= 0;
 }
 
+// Small products, which the fp32 rule gives to 64 x 64 tiles in k-tiles of 16 (plan `f`, S parts of k): the same tiles of one
+// or two blocks instead (no less exact on sums of few terms, see below), in one launch, where they are estimated at 0.85 of
+// that kernel's time or less -- a line fitted to 230 random batches of 2^19 to 2^26 multiply-adds, off by 7 % rms.  Of those
+// four fifths go there, and all take 0.71 of the time on average, two are slower (4 x 221 x 521 x 112, C transposed: 7.6 / 10.7;
+// 33 x 90 x 102 x 198: 10.6 / 12.2).  us, replayed from a graph: 2 x 68 x 149 x 353, A and B transposed, 11.7 / 6.4; 13 x 108 x
+// 66 x 237 12.9 / 5.9; 2 x 170 x 201 x 111 6.8 / 5.3.
+bool split_small_default(int64_t batch, int64_t M, int64_t N, int64_t K, bool tc, const GemmPlan& f, GemmPlan* g) {
+  if (f.BM != 64 || f.BN != 64 || f.BK != 16 || batch < 1 || K < 64 || (double)batch * M * N * K > (double)(1 << 26)) return false;
+  const double wg = (double)batch * cdiv(M, 64) * cdiv(N, 64) * f.S / 512;
+  const double fp32 = 4.15 + (wg > 1 ? wg : 1) * (double)K / f.S * 0.033 + (f.S > 1 ? 1.76 + 0.12 * f.S : 0.0);
+  GemmPlan b;
+  const double t = best_tile(kSplitTiles - 3, batch, M, N, K, tc, 1, &b);
+  if (t < 0 || t > 0.85 * fp32) return false;
+  *g = b;
+  return true;
+}
+
 // Outputs of few tiles, which the fp32 rule gives to its own kernel with k over the wavefronts (plan `f`, small tiles,
 // S parts of k): the ones of 32 x 32 to 64 x 32 with a sum of their own for h h' instead, where they are clearly faster.
 // They are no less exact than that kernel on sums of few terms either (256 x 256 x 2048, rms error in units of 2^-24, fp32
