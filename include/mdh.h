@@ -271,6 +271,9 @@ mdh_status mdh_matmul(int64_t M, int64_t N, int64_t K, const float* A, const flo
  *   in : (nx+2) x (ny+2) x (nz+2) fp32 (size rule N_buf = 1 + max index),
  *   out: nx x ny x nz fp32, compact (output view (i,j,k)->(i,j,k)).
  *   Any of nx, ny, nz == 0 is a valid empty call.
+ *   Two kernels, bit for bit the same results: in_region[0] = MDH_MR_LDS, a workgroup marches over
+ *   prt[MDH_L_HBM][i] planes; MDH_MR_VGPR, a lane holds prt[MDH_L_VGPR][i] planes at once (the
+ *   default but for large grids of whole tiles of 512 columns).
  */
 mdh_status mdh_stencil(int64_t nx, int64_t ny, int64_t nz, const float* in, float* out, float c0,
                        float c1, const mdh_tile_params* params, void* stream);

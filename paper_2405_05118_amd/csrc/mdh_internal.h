@@ -18,6 +18,7 @@ struct StencilPlan {
   int RJ, TY, LK;  // kernel instantiation
   int SI;          // planes per workgroup (sequential HBM-layer parts of dimension i)
   int ragged;
+  int PI = 0;  // > 0: the kernel without LDS, whose lanes hold PI planes at once (register-layer parts of i; SI = PI)
 };
 
 // MatMul / MCC contraction core: workgroup tile BM x BN, K-step BK through LDS,

@@ -89,6 +89,16 @@ static bool stencil_inst(int RJ, int TY, int LK) {
   return false;
 }
 
+// the kernel without LDS: rows and planes a lane holds, workgroups of 256 lanes
+static const int kStencilDirect[][2] = {{2, 2}, {2, 4}, {4, 2}, {4, 4}, {1, 2}, {2, 1}};
+
+static bool stencil_direct_inst(const StencilPlan& pl) {
+  if ((pl.LK != 16 && pl.LK != 32 && pl.LK != 64) || pl.TY != 256 / pl.LK) return false;
+  for (auto& m : kStencilDirect)
+    if (m[0] == pl.RJ && m[1] == pl.PI) return true;
+  return false;
+}
+
 int64_t stencil_lds_bytes(int RJ, int TY, int LK) {
   return 2ll * (TY * RJ + 2) * (LK * 4 + 8) * 4;
 }
@@ -99,7 +109,7 @@ void params_from_plan(const int64_t* sizes, const StencilPlan& pl, mdh_tile_para
   p->prt[MDH_L_WG][0] = (int32_t)cdiv(sizes[0], pl.SI);
   p->prt[MDH_L_WG][1] = (int32_t)cdiv(sizes[1], TJ);
   p->prt[MDH_L_WG][2] = (int32_t)cdiv(sizes[2], KT);
-  p->prt[MDH_L_HBM][0] = pl.SI;
+  p->prt[pl.PI ? MDH_L_VGPR : MDH_L_HBM][0] = pl.SI;
   if (pl.LK >= 64) {
     p->prt[MDH_L_WAVE][1] = pl.TY;
     p->prt[MDH_L_WAVE][2] = pl.LK / 64;
@@ -115,12 +125,19 @@ void params_from_plan(const int64_t* sizes, const StencilPlan& pl, mdh_tile_para
   set_order(p, dims);
   p->strided = 0;
   p->lane_fast_dim = 2;            // k is contiguous in both buffers
-  p->in_region[0] = MDH_MR_LDS;    // current plane staged in LDS
+  p->in_region[0] = pl.PI ? MDH_MR_VGPR : MDH_MR_LDS;  // a lane's planes and rows at once; current plane staged in LDS
   p->out_region = MDH_MR_VGPR;     // results leave from registers
   p->ragged = (uint8_t)pl.ragged;
 }
 
-static StencilPlan stencil_default(const int64_t* s) {
+static StencilPlan stencil_direct(const int64_t* s, int RJ, int PI) {
+  StencilPlan pl{RJ, 0, s[2] <= 64 ? 16 : s[2] <= 128 ? 32 : 64, PI, 0, PI};
+  pl.TY = 256 / pl.LK;
+  pl.ragged = (s[0] % PI) || (s[1] % (pl.TY * RJ)) || (s[2] % (pl.LK * 4));
+  return pl;
+}
+
+static StencilPlan stencil_march(const int64_t* s) {
   StencilPlan pl;
   pl.RJ = 4;
   pl.TY = 4;
@@ -151,6 +168,21 @@ static StencilPlan stencil_default(const int64_t* s) {
   return pl;
 }
 
+// Which kernel, and how much a lane of the one without LDS holds.  us, that one / the marching one: 86 x 72 x 69 5.0 / 15.1
+// (of which 5 is the host's launch), 154 x 191 x 65 5.8 / 15.7, 226 x 214 x 89 9.3 / 20.1, 143 x 70 x 501 9.8 / 24.7, 256^3
+// 21.0 / 28.1, 300^3 41 / 81, 400^3 78 / 158, 640^3 411 / 507; over 80 random grids of 64 to 512 a side 2.4 times as fast.
+// Rows x planes a lane: 2 x 2 has the most wavefronts (143 x 70 x 501 9.8; 2 x 4 9.7, 4 x 4 12.1), 4 x 4 reads the least twice
+// (500^3 211; 2 x 4 234, 2 x 2 272), 2 x 4 is between (168 x 307 x 146 14.4, 13.8 and 16.6; 300^3 43.0, 47.4 and 42.3).
+// The marching kernel stays for large grids that its tiles of 512 columns fit, where every input cell comes from memory
+// once: 512^3 183 (4 x 4 202), 200 x 512 x 512 81.8 (84.6); 384^3, in tiles of 256 columns, 109.7 (109.2).
+static StencilPlan stencil_default(const int64_t* s) {
+  const double points = (double)s[0] * s[1] * s[2];
+  const StencilPlan march = stencil_march(s);
+  if (points >= (double)(1 << 25) && march.LK == 128 && s[2] % 512 == 0 && s[1] % (march.TY * march.RJ) == 0) return march;
+  if (points < (double)(1 << 23)) return stencil_direct(s, 2, 2);
+  return points < (double)(1 << 24) ? stencil_direct(s, 2, 4) : stencil_direct(s, 4, 4);
+}
+
 int stencil_candidates(const int64_t* s, StencilPlan* out, int cap) {
   int n = 0;
   auto push = [&](int RJ, int TY, int LK, int SI) {
@@ -162,14 +194,20 @@ int stencil_candidates(const int64_t* s, StencilPlan* out, int cap) {
       if (out[i].RJ == RJ && out[i].TY == TY && out[i].LK == LK && out[i].SI == SI) return;
     out[n++] = pl;
   };
-  StencilPlan d = stencil_default(s);
-  push(d.RJ, d.TY, d.LK, d.SI);
+  const StencilPlan d = stencil_default(s);
+  if (d.PI) out[n++] = d;
+  const StencilPlan march = stencil_march(s);
+  push(march.RJ, march.TY, march.LK, march.SI);
   static const int menu[][3] = {{4, 2, 128}, {2, 2, 128}, {8, 2, 128}, {4, 4, 128}, {2, 4, 128},
                                 {4, 1, 128}, {8, 1, 128}, {4, 4, 64},  {2, 4, 64},  {4, 2, 64},
                                 {4, 8, 32},  {4, 16, 16}};
   static const int sis[] = {16, 32, 64, 128};
   for (auto& m : menu)
     for (int si : sis) push(m[0], m[1], m[2], si);
+  for (auto& m : kStencilDirect) {
+    const StencilPlan pl = stencil_direct(s, m[0], m[1]);
+    if (n < cap && !(d.PI == pl.PI && d.RJ == pl.RJ)) out[n++] = pl;
+  }
   return n;
 }
 
@@ -187,12 +225,14 @@ mdh_status plan_stencil(const int64_t* s, const mdh_tile_params* p, StencilPlan*
   pl.RJ = p->prt[MDH_L_VGPR][1];
   pl.TY = p->prt[MDH_L_WAVE][1] * p->prt[MDH_L_LANE][1];
   pl.LK = p->prt[MDH_L_WAVE][2] * p->prt[MDH_L_LANE][2];
-  pl.SI = p->prt[MDH_L_HBM][0];
+  pl.PI = p->in_region[0] == MDH_MR_VGPR ? p->prt[MDH_L_VGPR][0] : 0;
+  pl.SI = pl.PI ? pl.PI : p->prt[MDH_L_HBM][0];
   pl.ragged = ragged;
-  if (stencil_lds_bytes(pl.RJ, pl.TY, pl.LK) > kLdsBytesPerWG) return MDH_ERR_TILE_RESOURCES;
+  if (pl.PI && !stencil_direct_inst(pl)) return MDH_ERR_UNSUPPORTED;
+  if (!pl.PI && stencil_lds_bytes(pl.RJ, pl.TY, pl.LK) > kLdsBytesPerWG) return MDH_ERR_TILE_RESOURCES;
   mdh_tile_params chk;
   params_from_plan(s, pl, &chk);
-  if (!same_table(chk, *p) || !stencil_inst(pl.RJ, pl.TY, pl.LK)) return MDH_ERR_UNSUPPORTED;
+  if (!same_table(chk, *p) || !(pl.PI || stencil_inst(pl.RJ, pl.TY, pl.LK))) return MDH_ERR_UNSUPPORTED;
   *out = pl;
   return MDH_OK;
 }

@@ -218,10 +218,105 @@ mdh_status launch_t(const StencilPlan& pl, int64_t nx, int64_t ny, int64_t nz, c
   return launch_status();
 }
 
+// The same sum without LDS, for grids that do not keep the chip busy for long: a lane owns PI planes x RJ rows x 4 columns
+// and requests all they need at once -- its centres, the planes and rows around them, the two columns beside them -- so a
+// workgroup takes one trip to memory, where the kernel above takes one per plane (1.7 to 3 us each: with 16 planes a
+// workgroup, 67 x 66 x 87 was 15 us for 3 MB).  What is read more than once comes from the first and second level.  Bound by
+// those and by launch: us, before / now, 86 x 72 x 69 15.1 / 5.0 (the host's launch), 226 x 214 x 89 20.1 / 9.3, 300^3 81 / 41,
+// 500^3 352 / 211.  The output of 4 x 4 tiles, whose grids are larger than the second level, passes it by (non-temporal), so
+// that the input has it and the memory-side cache to itself: 333 x 222 x 511 79 -> 50, 500^3 220 -> 211; their centres
+// non-temporal too: no difference.
+// The columns beyond a row's end that a last lane reads belong to the next row (of the grid's last plane no row below the
+// last is read), and reach no output that is stored.
+template <int RJ, int PI, int LK>
+__global__ __launch_bounds__(256) void stencil_direct_kernel(const float* __restrict__ in, float* __restrict__ out, int nx, int ny,
+                                                             int nz, int njt, int nkt, float c0, float c1) {
+  constexpr int TY = 256 / LK;
+  const int b = xcd_order(blockIdx.x, gridDim.x);
+  const int kt = b % nkt, jt = (b / nkt) % njt, it = b / (nkt * njt);
+  const int k0 = (kt * LK + threadIdx.x % LK) * 4, j0 = (jt * TY + threadIdx.x / LK) * RJ, i0 = it * PI;
+  if (k0 >= nz || j0 >= ny) return;
+  const int sy = nz + 2;
+  const int64_t sx = (int64_t)(ny + 2) * sy;
+  f4 c[PI + 2][RJ], jm[PI], jp[PI];
+  float kl[PI][RJ], kr[PI][RJ];
+#pragma unroll
+  for (int p = 0; p < PI + 2; ++p) {
+    const int plane = min(i0 + p, nx + 1), last = plane > nx ? ny : ny + 1;
+    const float* const q = in + plane * sx + k0;
+#pragma unroll
+    for (int r = 0; r < RJ; ++r) {
+      const float* const row = q + (int64_t)min(j0 + r + 1, last) * sy;
+      c[p][r] = *(const f4u*)(row + 1);
+      if (p > 0 && p <= PI) {
+        const float* const mid = in + min(i0 + p, nx) * sx + (int64_t)min(j0 + r + 1, ny) * sy + k0;
+        kl[p - 1][r] = mid[0];
+        kr[p - 1][r] = mid[5];
+      }
+    }
+    if (p > 0 && p <= PI) {
+      const float* const h = in + min(i0 + p, nx) * sx + k0 + 1;
+      jm[p - 1] = *(const f4u*)(h + (int64_t)j0 * sy);
+      jp[p - 1] = *(const f4u*)(h + (int64_t)min(j0 + RJ + 1, ny + 1) * sy);
+    }
+  }
+  const bool four = k0 + 4 <= nz;
+#pragma unroll
+  for (int p = 0; p < PI; ++p) {
+    if (i0 + p >= nx) break;
+    float* const o = out + ((int64_t)(i0 + p) * ny + j0) * nz + k0;
+#pragma unroll
+    for (int r = 0; r < RJ; ++r) {
+      if (j0 + r >= ny) break;
+      const f4 m = c[p + 1][r], up = r == 0 ? jm[p] : c[p + 1][r - 1], dn = r == RJ - 1 ? jp[p] : c[p + 1][r + 1];
+      const f4 km = {kl[p][r], m[0], m[1], m[2]}, kp = {m[1], m[2], m[3], kr[p][r]};
+      const f4 nb = (((up + dn) + (km + kp)) + c[p][r]) + c[p + 2][r];
+      f4 v;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = __builtin_fmaf(c0, m[e], c1 * nb[e]);
+      if (four) {
+        if (RJ * PI == 16)
+          st_stream(o + (int64_t)r * nz, v);
+        else
+          *(f4u*)(o + (int64_t)r * nz) = v;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (k0 + e < nz) o[(int64_t)r * nz + e] = v[e];
+      }
+    }
+  }
+}
+
+template <int RJ, int PI, int LK>
+mdh_status launch_direct(int64_t nx, int64_t ny, int64_t nz, const float* in, float* out, float c0, float c1, hipStream_t st) {
+  const int64_t njt = cdiv(ny, 256 / LK * RJ), nkt = cdiv(nz, LK * 4);
+  const int64_t nblocks = njt * nkt * cdiv(nx, PI);
+  if (nblocks <= 0 || nblocks > 0x7fffffff) return MDH_ERR_SIZE;
+  clear_stale_error();
+  hipLaunchKernelGGL((stencil_direct_kernel<RJ, PI, LK>), dim3((unsigned)nblocks), dim3(256), 0, st, in, out, (int)nx, (int)ny,
+                     (int)nz, (int)njt, (int)nkt, c0, c1);
+  return launch_status();
+}
+
 }  // namespace
 
 mdh_status launch_stencil(const StencilPlan& pl, int64_t nx, int64_t ny, int64_t nz,
                           const float* in, float* out, float c0, float c1, hipStream_t st) {
+#define MDH_SD(rj, pi)                                                                                  \
+  if (pl.RJ == rj && pl.PI == pi) {                                                                     \
+    if (pl.LK == 64) return launch_direct<rj, pi, 64>(nx, ny, nz, in, out, c0, c1, st);                 \
+    if (pl.LK == 32) return launch_direct<rj, pi, 32>(nx, ny, nz, in, out, c0, c1, st);                 \
+    if (pl.LK == 16) return launch_direct<rj, pi, 16>(nx, ny, nz, in, out, c0, c1, st);                 \
+  }
+  MDH_SD(2, 2)
+  MDH_SD(2, 4)
+  MDH_SD(4, 2)
+  MDH_SD(4, 4)
+  MDH_SD(1, 2)
+  MDH_SD(2, 1)
+#undef MDH_SD
+  if (pl.PI) return MDH_ERR_UNSUPPORTED;
 #define MDH_ST(rj, ty, lk) \
   if (pl.RJ == rj && pl.TY == ty && pl.LK == lk) return launch_t<rj, ty, lk>(pl, nx, ny, nz, in, out, c0, c1, st);
   MDH_ST(4, 2, 128)

@@ -1,0 +1,46 @@
+"""The stencil without LDS: every tile at the edges of its lanes, rows and planes against the marching kernel, whose results
+it repeats bit for bit, and the tables that the planner takes."""
+import pytest
+
+import paper_2405_05118_amd as mdh
+
+torch = pytest.importorskip("torch")
+
+
+def tables(shape):
+    all_ = [mdh.mdh_candidate(mdh.MDH_STENCIL, shape, i) for i in range(mdh.mdh_num_candidates(mdh.MDH_STENCIL, shape))]
+    return [p for p in all_ if p.in_region[0] == 2], [p for p in all_ if p.in_region[0] == 1]
+
+
+def test_planner():
+    direct, march = tables((100, 90, 200))
+    assert {(p.prt[2][1], p.prt[2][0]) for p in direct} == {(2, 2), (2, 4), (4, 2), (4, 4), (1, 2), (2, 1)} and march
+    assert mdh.mdh_default_params(mdh.MDH_STENCIL, (100, 90, 200)).in_region[0] == 2
+    assert mdh.mdh_default_params(mdh.MDH_STENCIL, (512, 512, 512)).in_region[0] == 1
+    for layer, d, v in ((0, 0, 2), (2, 0, 3), (2, 1, 3), (4, 1, 8), (5, 2, 32), (2, 0, (1 << 30) + 2)):
+        q = direct[0].copy()
+        q.ragged = 1
+        q.prt[layer][d] = v
+        assert mdh.mdh_validate_params(mdh.MDH_STENCIL, (100, 90, 200), q) != 0, (layer, d, v)
+
+
+# one cell, one more and one less than the lanes' columns of each width, than their rows and planes; a last row and plane
+# that end the buffer
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(1, 1, 1), (2, 3, 5), (5, 17, 63), (4, 33, 64), (3, 32, 65), (6, 31, 127), (7, 9, 129), (9, 16, 255), (8, 8, 257), (3, 65, 514)])
+def test_same_as_the_marching_kernel(shape):
+    g = torch.Generator(device="cuda").manual_seed(sum(shape))
+    x = torch.rand([n + 2 for n in shape], generator=g, device="cuda")
+    direct, march = tables(shape)
+    n = shape[0] * shape[1] * shape[2]
+    ref = torch.empty(shape, device="cuda")
+    mdh.mdh_stencil(x, ref, 0.5, 1.0 / 12.0, march[0])
+    v = x.double()
+    c1 = float(torch.tensor(1.0 / 12.0))
+    want = 0.5 * v[1:-1, 1:-1, 1:-1] + c1 * (v[:-2, 1:-1, 1:-1] + v[2:, 1:-1, 1:-1] + v[1:-1, :-2, 1:-1] + v[1:-1, 2:, 1:-1] + v[1:-1, 1:-1, :-2] + v[1:-1, 1:-1, 2:])
+    assert bool(((ref.double() - want).abs() <= 7 * 2.0**-24 * want).all())  # seven roundings of positive terms
+    for p in direct:
+        guard = torch.full((n + 64,), 7.0, device="cuda")
+        mdh.mdh_stencil(x, guard[:n].view(shape), 0.5, 1.0 / 12.0, p)
+        assert torch.equal(guard[:n].view(shape), ref), p.table()
+        assert bool((guard[n:] == 7.0).all())
