@@ -184,14 +184,14 @@ def bench_stencil(torch, mdh, W, name, steps, warmup, cpu):
 
 
 def _split_variant(mdh, sizes, S):
-    """The default tile configuration with the reduction dimension split S ways over workgroups."""
+    """The default tile configuration with the reduction dimension split S ways over workgroups; where that tile is not
+    offered with S parts, the first of the same kind of value that is, and as many columns a workgroup."""
     d = mdh.mdh_default_params(mdh.MDH_MATMUL, sizes)
-    for i in range(mdh.mdh_num_candidates(mdh.MDH_MATMUL, sizes)):
-        p = mdh.mdh_candidate(mdh.MDH_MATMUL, sizes, i)
-        same_tile = all(list(p.prt[l][:3]) == list(d.prt[l][:3]) for l in (1, 2, 4, 5))
-        if same_tile and p.prt[3][2] == S:
-            return p
-    return None
+    cand = [mdh.mdh_candidate(mdh.MDH_MATMUL, sizes, i) for i in range(mdh.mdh_num_candidates(mdh.MDH_MATMUL, sizes))]
+    cand = [p for p in cand if p.prt[3][2] == S and p.blk[2] == d.blk[2]]
+    same_tile = [p for p in cand if all(list(p.prt[l][:3]) == list(d.prt[l][:3]) for l in (1, 2, 4, 5))]
+    same_cols = [p for p in cand if p.prt[3][1] == d.prt[3][1] and p.prt[4][1] * p.prt[2][1] == d.prt[4][1] * d.prt[2][1]]
+    return (same_tile + same_cols)[0]
 
 
 def _mfma_roofline(tf, sliced, traffic, products=6):
@@ -215,7 +215,7 @@ def bench_matmul(torch, mdh, W, name, steps, warmup, cpu, split=None):
     tf = flop / ms / 1e9
     res = {
         "value": flop / wall / 1e6, "unit": "GFLOP/s", "ms_per_step": wall, "kernel_ms": ms, "dtype": "f32",
-        "kernel": ("matmul_split_kernel" if sliced else "matmul_ksplit16_kernel" if p.blk[0] == 16 else "matmul_ksplit_kernel" if p.prt[4][2] > 1 else "matmul_kernel")
+        "kernel": ("matmul_split_k_kernel" if sliced and p.prt[4][2] > 1 else "matmul_split_kernel" if sliced else "matmul_ksplit16_kernel" if p.blk[0] == 16 else "matmul_ksplit_kernel" if p.prt[4][2] > 1 else "matmul_kernel")
         + (" + combine_sum_kernel" if p.prt[3][2] > 1 else ""),
         "wavefront_parts_of_k": int(p.prt[4][2]),
         "split_k": int(p.prt[3][2]),
