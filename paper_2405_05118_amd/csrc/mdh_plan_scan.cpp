@@ -99,10 +99,15 @@ static ScanPlan scan_default(const int64_t* s) {
     // eight wavefronts and half of them idle; 65536 x 1536: 126 against 146 us)
     return scan_plan(s, s[1] <= 1536 ? 4 : 8, 1);
   }
-  // few long rows: chunks of j over workgroups, a chunk resident in registers (one pass over the
-  // input); as many tiles per chunk as still give a workgroup per compute unit
-  int tpc = 8;
-  while (tpc > 2 && rows * cdiv(s[1], (int64_t)4096 * tpc) < 256) tpc /= 2;
+  // a row that fits a workgroup's registers: nothing to exchange and one launch, however few the rows (against chunks of
+  // 2 or 4 tiles: 1 x 32768 8.4 -> 5.7 us, 48 x 24576 9.4 -> 7.1, 128 x 16384 10.7 -> 5.2, 255 x 32768 20.0 -> 10.5)
+  if (s[1] <= 4096 * 8) return scan_onepass_plan(s, 16, 8);
+  // few long rows: chunks of j over workgroups, a chunk resident in registers (one pass over the input).  A chunk costs
+  // its ticket and its place in the chain of totals, and more chunks than compute units a second round, so as many tiles
+  // a chunk as keep them to one round; half of one for two tiles, where four take as long with half the chunks (us with
+  // 2 / 4 / 8 tiles: 800000 9.7 / 9.4 / 11.1, 1250000 11.3 / 10.4 / 11.6, 3000000 16.1 / 12.7 / 13.2, 4000000 18.7 / 13.8 /
+  // 13.9, 4400000 19.6 / 15.5 / 14.7, 8000000 29.4 / 21.7 / 17.5; the same with the elements in 2 to 14 rows)
+  const int tpc = rows * cdiv(s[1], 4096 * 2) <= 128 ? 2 : rows * cdiv(s[1], 4096 * 4) <= 256 ? 4 : 8;
   return scan_onepass_plan(s, 16, tpc);  // 16 wavefronts measured fastest (8: +8 %)
 }
 
