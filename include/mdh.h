@@ -242,7 +242,8 @@ size_t mdh_workspace_size(mdh_instance inst, const int64_t* sizes, const mdh_til
  *   them in ascending part order.  The library default may split k, so pass the
  *   workspace mdh_workspace_size asks for (for some sizes it is asked for but not needed:
  *   a call with the default, as NULL or as its table, that brings less then runs with
- *   fewer parts).  blk = (32,32,16) selects the
+ *   fewer parts; where the default is the kernel that tiles in LDS with fp32 instructions it
+ *   is needed).  blk = (32,32,16) selects the
  *   kernels that carry a value as three bf16 values and multiply with six bf16 matrix
  *   products (K >= 32; the default for large products; prt[MDH_L_WAVE][k] = 1: tiles staged in
  *   LDS, 4 or 8: k over the wavefronts of a workgroup, tiles of 32 to 96 rows and columns inside C; Inf, NaN, overflow and values below
@@ -300,7 +301,9 @@ mdh_status mdh_stencil(int64_t nx, int64_t ny, int64_t nz, const float* in, floa
  * partial outputs go to `workspace` (S * N*P*Q*K floats, see mdh_workspace_size) and
  * a second kernel adds them in ascending part order.  The library default does
  * that for small images with many channels, so pass the workspace
- * mdh_workspace_size asks for; it may be NULL when that size is 0.
+ * mdh_workspace_size asks for; it may be NULL when that size is 0.  Where the default
+ * is a table on slices, a call with it, as NULL or as the table, that brings less runs
+ * with fewer parts.
  * Precondition of the few-channel kernel with fp32 instructions (blk[c] = 1,
  * in_region[0] = MDH_MR_LDS; a call without a table may take it for C <= 8): the
  * input holds finite values.  Its fused (s,c) walk is padded to a multiple of 8 with

@@ -51,7 +51,7 @@ mdh_status mdh_matmul(int64_t M, int64_t N, int64_t K, const float* A, const flo
   if (!A || !B || !C) return MDH_ERR_NULL;
   auto fits = [&] { return pl.S <= 1 || (workspace && workspace_bytes >= (size_t)pl.S * (size_t)M * (size_t)N * sizeof(float)); };
   // the default splits k further where there is room for it
-  if (!fits()) plan_matmul_lean(sizes, &pl);
+  if (!fits()) plan_matmul_lean(sizes, workspace ? workspace_bytes : 0, &pl);
   if (pl.S > 1 && too_big((int64_t)pl.S * M * N)) return MDH_ERR_SIZE;
   if (!fits()) return MDH_ERR_WORKSPACE;
   return launch_matmul(pl, M, N, K, A, B, C, workspace, (hipStream_t)stream);
@@ -91,11 +91,11 @@ mdh_status mdh_mcc(int64_t N, int64_t H, int64_t W, int64_t C, int64_t K, int64_
   if (!in || !filt || !out) return MDH_ERR_NULL;
   if (pl.flat)
     return launch_mcc_flat(pl, N, H, W, C, K, R, S, stride_h, stride_w, in, filt, out, (hipStream_t)stream);
-  if (pl.S > 1) {
-    if (too_big((int64_t)pl.S * N * P * Q * K)) return MDH_ERR_SIZE;
-    const size_t need = (size_t)pl.S * (size_t)(N * P * Q * K) * sizeof(float);
-    if (!workspace || workspace_bytes < need) return MDH_ERR_WORKSPACE;
-  }
+  auto fits = [&] { return pl.S <= 1 || (workspace && workspace_bytes >= (size_t)pl.S * (size_t)(N * P * Q * K) * sizeof(float)); };
+  // the default splits c further where there is room for it
+  if (!fits()) plan_mcc_lean(sizes, workspace ? workspace_bytes : 0, &pl);
+  if (pl.S > 1 && too_big((int64_t)pl.S * N * P * Q * K)) return MDH_ERR_SIZE;
+  if (!fits()) return MDH_ERR_WORKSPACE;
   return launch_mcc(pl, N, H, W, C, K, R, S, stride_h, stride_w, in, filt, out, workspace, (hipStream_t)stream);
 }
 

@@ -228,9 +228,11 @@ mdh_status launch_matvec(const MatVecPlan& pl, int64_t M, int64_t K, const float
 
 mdh_status plan_stencil(const int64_t* sizes, const mdh_tile_params* p, StencilPlan* out);
 mdh_status plan_matmul(const int64_t* sizes, const mdh_tile_params* p, GemmPlan* out);
-// for a caller without the workspace the plan asks for: the default, given as none or as its table, does with less
-void plan_matmul_lean(const int64_t* sizes, GemmPlan* pl);
+// for a caller whose `workspace` bytes do not hold what the plan asks for: the default, given as none or as its table, does
+// with less
+void plan_matmul_lean(const int64_t* sizes, size_t workspace, GemmPlan* pl);
 mdh_status plan_mcc(const int64_t* sizes, const mdh_tile_params* p, MccPlan* out);
+void plan_mcc_lean(const int64_t* sizes, size_t workspace, MccPlan* pl);
 MccPlan mcc_default_table(const int64_t* sizes);  // what mdh_default_params answers
 mdh_status plan_prl(const int64_t* sizes, const mdh_tile_params* p, PrlPlan* out);
 

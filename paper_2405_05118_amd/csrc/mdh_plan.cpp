@@ -413,11 +413,12 @@ static GemmPlan gemm_default_fp32(const int64_t* s) {
   return pl;
 }
 
-// The default without more workspace than the fp32 rule asks for.
-static GemmPlan gemm_default_lean(const int64_t* s) {
+// The default without more workspace than the fp32 rule asks for; on slices in at most `most` parts of k.
+static GemmPlan gemm_default_lean(const int64_t* s, int64_t most = 1 << 20) {
   GemmPlan pl = gemm_default_fp32(s);
+  const int S = pl.S < most ? pl.S : (int)most;
   // outputs of few tiles stay with k over the wavefronts, on either kernel
-  if (!(pl.WK > 1 ? split_k_default(s[0], s[1], s[2], pl, &pl) : split_default(1, s[0], s[1], s[2], false, pl.S, &pl))) return pl;
+  if (!(pl.WK > 1 ? split_k_default(s[0], s[1], s[2], pl, &pl) : split_default(1, s[0], s[1], s[2], false, S, &pl))) return pl;
   pl.ragged = gemm_ragged(s, pl);
   return pl;
 }
@@ -457,12 +458,18 @@ static GemmPlan gemm_default(const int64_t* s) {
   return pl;
 }
 
-void plan_matmul_lean(const int64_t* s, GemmPlan* pl) {
+// parts of `bytes` each that a workspace holds, 1 at the least: what is left of a default that asked for more
+static int64_t parts_held(size_t workspace, int64_t bytes) {
+  const int64_t n = (int64_t)(workspace / (size_t)(bytes > 0 ? bytes : 1));
+  return n > 1 ? n : 1;
+}
+
+void plan_matmul_lean(const int64_t* s, size_t workspace, GemmPlan* pl) {
   const GemmPlan d = gemm_default(s);
   mdh_tile_params a, b;
   params_from_plan(s, d, &a);
   params_from_plan(s, *pl, &b);
-  if (same_table(a, b)) *pl = gemm_default_lean(s);
+  if (same_table(a, b)) *pl = gemm_default_lean(s, parts_held(workspace, s[0] * s[1] * 4));
 }
 
 int matmul_candidates(const int64_t* s, GemmPlan* out, int cap) {
@@ -964,13 +971,21 @@ static void mcc_flat_split_rule(const int64_t* s, MccPlan* out) {
   if (mcc_lds_bytes(pl, s) <= kLdsBytesPerWG) *out = pl;
 }
 
-static MccPlan mcc_default(const int64_t* s) {
+// on slices in at most `most` parts of c
+static MccPlan mcc_default(const int64_t* s, int64_t most = 1 << 20) {
   MccPlan pl = mcc_default_fp32(s);
-  if (!pl.flat && mcc_split_default(s, pl.TQ, pl.S, &pl)) pl.ragged = mcc_ragged(s, pl);
+  if (!pl.flat && mcc_split_default(s, pl.TQ, pl.S < most ? pl.S : (int)most, &pl)) pl.ragged = mcc_ragged(s, pl);
   return pl;
 }
 
 MccPlan mcc_default_table(const int64_t* s) { return mcc_default(s); }
+
+void plan_mcc_lean(const int64_t* s, size_t workspace, MccPlan* pl) {
+  mdh_tile_params a, b;
+  params_from_plan(s, mcc_default(s), &a);
+  params_from_plan(s, *pl, &b);
+  if (same_table(a, b)) *pl = mcc_default(s, parts_held(workspace, s[0] * s[1] * s[2] * s[3] * 4));
+}
 
 int mcc_candidates(const int64_t* s, MccPlan* out, int cap) {
   int n = 0;

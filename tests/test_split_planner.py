@@ -125,3 +125,43 @@ def test_table_of_the_default_without_workspace(shape):
     with pytest.raises(mdh.MdhError) as e:
         mdh.mdh_matmul(A, B, C, next(q for q in cands if q.prt[3][2] == 2), None)
     assert e.value.status == 5
+
+
+# Products and layers whose default asks for a workspace and did not always: they run with fewer parts where it is missing or
+# holds only some, also for the default's table, and are close to 64 bits all the same (as in test_split_k).
+LESS = [(mdh.MDH_MATMUL, (15890, 62, 1233)), (mdh.MDH_MATMUL, (12627, 59, 976)), (mdh.MDH_MCC, (9, 28, 28, 248, 464, 7, 7, 1, 1)),
+        (mdh.MDH_MCC, (3, 13, 16, 487, 47, 3, 3, 2, 2)), (mdh.MDH_MCC, (4, 20, 20, 77, 174, 1, 1, 1, 1)), (mdh.MDH_MCC, (8, 10, 15, 332, 405, 3, 3, 1, 1))]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("inst,sizes", LESS)
+@pytest.mark.parametrize("parts", [0, 1, 2, 3])
+def test_default_with_less_workspace(inst, sizes, parts):
+    import torch
+
+    g = torch.Generator(device="cuda").manual_seed(parts + sizes[0])
+    rand = lambda *shape: torch.rand(shape, generator=g, device="cuda") * 2 - 1
+    if inst == mdh.MDH_MATMUL:
+        M, N, K = sizes
+        a, b = rand(M, K), rand(K, N)
+        ref, mag, terms = a.double() @ b.double(), a.double().abs() @ b.double().abs(), K
+        call = mdh.mdh_matmul
+    else:
+        n, P, Q, K, C, R, S, st, _ = sizes
+        a, b = rand(n, (P - 1) * st + R, (Q - 1) * st + S, C), rand(K, R, S, C)
+        ref, mag, terms = torch.zeros((n * P * Q, K), dtype=torch.float64, device="cuda"), 0.0, C * R * S
+        for r in range(R):
+            for s in range(S):
+                tap = a[:, r : r + (P - 1) * st + 1 : st, s : s + (Q - 1) * st + 1 : st].reshape(-1, C).double()
+                w = b[:, r, s].double().t().contiguous()
+                ref += tap @ w
+                mag = mag + tap.abs() @ w.abs()
+        call = lambda a, b, out, p, ws: mdh.mdh_mcc(a, b, out.view(n, P, Q, K), (st, st), p, ws)
+    need = mdh.mdh_workspace_size(inst, sizes)
+    assert need > 0 and need % (ref.numel() * 4) == 0
+    for p in (None, mdh.mdh_default_params(inst, sizes)):
+        out = torch.full(ref.shape, float("nan"), device="cuda")
+        room = torch.full((parts * ref.numel() + 64,), 7.0, device="cuda")  # 64 guard words
+        call(a, b, out, p, room[: parts * ref.numel()] if parts else None)
+        assert bool(((out.double() - ref).abs() <= terms * 2.0**-24 * mag).all())
+        assert bool((room[parts * ref.numel() :] == 7.0).all())
