@@ -890,9 +890,25 @@ static const TapTime kTap[] = {{64, 64, 16, 4, 4.7, 0.25, 0.313, 0.04, {0.292, 0
                                {256, 128, 16, 1, 7.6, 0.52, 0.148, 0.26, {0.753}},
                                {256, 128, 32, 1, 7.8, 0.0, 0.506, 0.25, {1.340}}};
 
-static double mcc_split_estimate(const int64_t* s, const MccPlan& pl) {
+// A coarser estimate, of 3 x 3 and 7 x 7 layers alone, which leans towards more parts of c: it has the least number of them.
+static const TapTime kTapParts[] = {{64, 64, 16, 4, 0.0, 0.5, 0.11, 0.0, {0.319, 0.44, 0.605, 0.77}},
+                                    {64, 64, 32, 4, 0.0, 0.5, 0.2, 0.0, {0.58, 0.80, 1.10, 1.40}},
+                                    {64, 128, 16, 2, 0.0, 0.5, 0.11, 0.0, {0.44, 0.77}},
+                                    {64, 128, 32, 2, 0.0, 0.5, 0.2, 0.0, {0.80, 1.40}},
+                                    {128, 64, 16, 3, 0.0, 0.5, 0.11, 0.0, {0.385, 0.715, 1.045}},
+                                    {128, 64, 32, 3, 0.0, 0.5, 0.2, 0.0, {0.70, 1.30, 1.90}},
+                                    {128, 128, 16, 2, 0.0, 0.5, 0.11, 0.0, {0.77, 1.32}},
+                                    {128, 128, 32, 2, 0.0, 0.5, 0.2, 0.0, {1.40, 2.40}},
+                                    {256, 128, 16, 1, 0.0, 0.5, 0.11, 0.0, {1.1935}},
+                                    {256, 128, 32, 1, 0.0, 0.5, 0.2, 0.0, {2.17}}};
+
+// second pass: microseconds, per part, per 10^6 of the outputs' partial results and outputs
+struct SecondPass {
+  double once, part, output;
+};
+
+static double mcc_split_estimate(const int64_t* s, const MccPlan& pl, const TapTime* t, const SecondPass& pass) {
   const int64_t P = s[1] > 0 ? s[1] : 1, Q = s[2] > 0 ? s[2] : 1, N = s[0] > 0 ? s[0] : 1, K = s[3] > 0 ? s[3] : 1;
-  const TapTime* t = kTap;
   while (t->px != pl.TP * pl.TQ || t->BN != pl.BN || t->CK != pl.CK) ++t;
   const int64_t lds = kLdsBytesPerWG / mcc_lds_bytes(pl, s);
   const int held = (int)(lds < t->held ? lds : t->held);
@@ -905,7 +921,7 @@ static double mcc_split_estimate(const int64_t* s, const MccPlan& pl) {
   double us = t->once + (double)(work / (256 * held)) * round(held) * (1 + t->full);
   const int64_t rest = work % (256 * held);
   if (rest) us += round((int)cdiv(rest, 256)) * (1 + t->full * (rest < 256 ? rest : 256) / 256);
-  if (pl.S > 1) us += 0.4 + 0.3 * pl.S + (double)(pl.S + 1) * N * P * Q * K * 2.3e-6;  // second pass
+  if (pl.S > 1) us += pass.once + pass.part * pl.S + (double)(pl.S + 1) * N * P * Q * K * pass.output * 1e-6;
   return us;
 }
 
@@ -919,19 +935,28 @@ static double mcc_split_estimate(const int64_t* s, const MccPlan& pl) {
 // / 12.2).  Of 400 random layers of stride 2 to 5, where much of a patch is split and not used, 1.5 % are slower by more
 // than 4 % (26 x 3 x 1 x 665 -> 9, 2 x 1, stride 4: 32 / 37), the mean is 0.73.
 static bool mcc_split_default(const int64_t* s, int TQ, int S, MccPlan* out) {
-  double best = -1;
   if (s[4] * s[5] * s[6] < 128) return false;
   if (s[5] * s[6] == 1 && (double)s[0] * s[1] * s[2] * s[3] * s[4] < (double)(1 << 24)) return false;
-  for (auto& m : kMccSplitMenu)
-    for (int parts = 1; parts <= S; parts *= 2) {
-      MccPlan pl{m.TP, m.TQ, m.BN, m.CK, m.WM, m.WN, 0, 0};
-      pl.S = parts;
-      pl.split = 1;
-      if (!mcc_split_sizes(s, pl) || mcc_lds_bytes(pl, s) > kLdsBytesPerWG) continue;
-      const double us = mcc_split_estimate(s, pl) * (pl.TQ == TQ ? 1.0 : 1.03);
-      if (best < 0 || us < best) best = us, *out = pl;
-    }
-  return best >= 0;
+  // the fastest tile in `least` parts of c or more; `other`: what another pixel block counts for
+  auto fastest = [&](const TapTime* t, const SecondPass& pass, int least, double other) {
+    double best = -1;
+    for (auto& m : kMccSplitMenu)
+      for (int parts = least; parts <= S; parts *= 2) {
+        MccPlan pl{m.TP, m.TQ, m.BN, m.CK, m.WM, m.WN, 0, 0};
+        pl.S = parts;
+        pl.split = 1;
+        if (pl.TQ != TQ && other < 1) continue;
+        if (!mcc_split_sizes(s, pl) || mcc_lds_bytes(pl, s) > kLdsBytesPerWG) continue;
+        const double us = mcc_split_estimate(s, pl, t, pass) * (pl.TQ == TQ ? 1.0 : other);
+        if (best < 0 || us < best) best = us, *out = pl;
+      }
+    return best >= 0;
+  };
+  // A part twice as long is 1.4 times as far from 64 bits, so not fewer parts than the coarser estimate has, though the
+  // other one would take fewer on 7 % of random layers and be 3 % faster there (35 of them: 0.71 of the error; 5 x 19 x 24,
+  // 121 -> 235, 3 x 3: four parts; 3 x 55 x 56, 180 -> 51, 5 x 5: 55.2 us and 9.0 x 2^-24 in four, 48.6 and 12.7 in two).
+  const int least = S > 1 && fastest(kTapParts, {3.0, 0.5, 1.0}, 1, 0.0) ? out->S : 1;
+  return fastest(kTap, {0.4, 0.3, 2.3}, least, 1.03);
 }
 
 // the few-channel kernel that splits addresses an image with 32 bits (a stride that is not used may have any value: the

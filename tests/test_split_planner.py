@@ -165,3 +165,13 @@ def test_default_with_less_workspace(inst, sizes, parts):
         call(a, b, out, p, room[: parts * ref.numel()] if parts else None)
         assert bool(((out.double() - ref).abs() <= terms * 2.0**-24 * mag).all())
         assert bool((room[parts * ref.numel() :] == 7.0).all())
+
+
+# a part of c is a chain in one accumulator, and a longer one is further from 64 bits: the number of parts that the estimate
+# of the tiles alone would take is half of these or less
+@pytest.mark.parametrize("sizes,parts", [
+    ((5, 19, 24, 235, 121, 3, 3, 1, 1), 4), ((3, 55, 56, 51, 180, 5, 5, 1, 1), 4), ((9, 10, 15, 489, 127, 3, 3, 1, 1), 4), ((5, 8, 9, 229, 339, 3, 3, 1, 1), 8),
+    ((2, 19, 20, 497, 67, 7, 7, 1, 1), 2), ((14, 7, 12, 57, 279, 1, 1, 1, 1), 4), ((7, 26, 26, 397, 110, 5, 5, 2, 2), 2)])
+def test_parts_of_c_stay_short(sizes, parts):
+    p = mdh.mdh_default_params(mdh.MDH_MCC, sizes)
+    assert p.prt[2][4] == 8 and p.prt[3][4] >= parts
