@@ -302,8 +302,7 @@ mdh_status mdh_stencil(int64_t nx, int64_t ny, int64_t nz, const float* in, floa
  * a second kernel adds them in ascending part order.  The library default does
  * that for small images with many channels, so pass the workspace
  * mdh_workspace_size asks for; it may be NULL when that size is 0.  Where the default
- * is a table on slices, a call with it, as NULL or as the table, that brings less runs
- * with fewer parts.
+ * is a table on slices, a call without a table that brings less runs with fewer parts.
  * Precondition of the few-channel kernel with fp32 instructions (blk[c] = 1,
  * in_region[0] = MDH_MR_LDS; a call without a table may take it for C <= 8): the
  * input holds finite values.  Its fused (s,c) walk is padded to a multiple of 8 with
@@ -463,7 +462,9 @@ mdh_status mdh_matvec(int64_t M, int64_t K, const float* A, const float* x, floa
  *   trans_b: B_b is stored N x K and read through (b,i,j,k)->B[b,j,k]
  *   trans_c: C_b is stored N x M, written through (b,i,j,0)->C[b,j,i]
  * All buffers dense, batch-major, fp32, device.  K >= 1; batch, M or N == 0 is an
- * empty call; batch <= 65535.  Split reductions need batch*S*M*N floats of workspace.
+ * empty call; batch <= 65535.  Split reductions need batch*S*M*N floats of workspace;
+ * where the default is a table on slices, a call without a table that brings less runs
+ * with fewer parts.
  * For mdh_default_params etc. the `sizes` of MDH_BMATMUL are
  * (batch, M, N, K, trans_a, trans_b, trans_c); a configuration's in_transposed[0..1]
  * and out_transposed must equal the call's flags.

@@ -93,7 +93,7 @@ mdh_status mdh_mcc(int64_t N, int64_t H, int64_t W, int64_t C, int64_t K, int64_
     return launch_mcc_flat(pl, N, H, W, C, K, R, S, stride_h, stride_w, in, filt, out, (hipStream_t)stream);
   auto fits = [&] { return pl.S <= 1 || (workspace && workspace_bytes >= (size_t)pl.S * (size_t)(N * P * Q * K) * sizeof(float)); };
   // the default splits c further where there is room for it
-  if (!fits()) plan_mcc_lean(sizes, workspace ? workspace_bytes : 0, &pl);
+  if (!params && !fits()) pl = mcc_default_lean(sizes, workspace ? workspace_bytes : 0);
   if (pl.S > 1 && too_big((int64_t)pl.S * N * P * Q * K)) return MDH_ERR_SIZE;
   if (!fits()) return MDH_ERR_WORKSPACE;
   return launch_mcc(pl, N, H, W, C, K, R, S, stride_h, stride_w, in, filt, out, workspace, (hipStream_t)stream);
@@ -155,11 +155,11 @@ mdh_status mdh_matmul_ex(int64_t batch, int64_t M, int64_t N, int64_t K, const f
   if (st != MDH_OK) return st;
   if (batch == 0 || M == 0 || N == 0) return MDH_OK;
   if (!A || !B || !C) return MDH_ERR_NULL;
-  if (pl.g.S > 1) {
-    if (too_big((int64_t)pl.g.S * batch * M * N)) return MDH_ERR_SIZE;
-    const size_t need = (size_t)pl.g.S * (size_t)batch * (size_t)M * (size_t)N * sizeof(float);
-    if (!workspace || workspace_bytes < need) return MDH_ERR_WORKSPACE;
-  }
+  auto fits = [&] { return pl.g.S <= 1 || (workspace && workspace_bytes >= (size_t)pl.g.S * (size_t)(batch * M * N) * sizeof(float)); };
+  // the default splits k further where there is room for it
+  if (!params && !fits()) pl = matmul_ex_default_lean(sizes, workspace ? workspace_bytes : 0);
+  if (pl.g.S > 1 && too_big((int64_t)pl.g.S * batch * M * N)) return MDH_ERR_SIZE;
+  if (!fits()) return MDH_ERR_WORKSPACE;
   return launch_matmul_ex(pl, batch, M, N, K, A, B, C, workspace, (hipStream_t)stream);
 }
 

@@ -72,6 +72,11 @@ mdh_status check_lanes(const mdh_tile_params* p);
 bool same_table(const mdh_tile_params& a, const mdh_tile_params& b);
 // the kernel that splits fp32 values into bf16 slices (mdh_plan_split.cpp); tc: C is stored transposed
 constexpr int kSplitTiles = 13;
+// parts of the reduction, a result of n floats each, that a workspace of these bytes holds; 1 at the least
+inline int64_t parts_held(size_t workspace, int64_t n) {
+  const int64_t parts = (int64_t)(workspace / sizeof(float)) / (n > 0 ? n : 1);
+  return parts > 1 ? parts : 1;
+}
 bool split_inst(const GemmPlan& g, bool tc);
 bool split_sizes(int64_t M, int64_t N, int64_t K);
 bool split_fits(int64_t M, int64_t N, int64_t K, const GemmPlan& g);
@@ -232,7 +237,8 @@ mdh_status plan_matmul(const int64_t* sizes, const mdh_tile_params* p, GemmPlan*
 // with less
 void plan_matmul_lean(const int64_t* sizes, size_t workspace, GemmPlan* pl);
 mdh_status plan_mcc(const int64_t* sizes, const mdh_tile_params* p, MccPlan* out);
-void plan_mcc_lean(const int64_t* sizes, size_t workspace, MccPlan* pl);
+MccPlan mcc_default_lean(const int64_t* sizes, size_t workspace);  // the same for a call without a table
+GemmExPlan matmul_ex_default_lean(const int64_t* sizes, size_t workspace);
 MccPlan mcc_default_table(const int64_t* sizes);  // what mdh_default_params answers
 mdh_status plan_prl(const int64_t* sizes, const mdh_tile_params* p, PrlPlan* out);
 

@@ -458,18 +458,12 @@ static GemmPlan gemm_default(const int64_t* s) {
   return pl;
 }
 
-// parts of `bytes` each that a workspace holds, 1 at the least: what is left of a default that asked for more
-static int64_t parts_held(size_t workspace, int64_t bytes) {
-  const int64_t n = (int64_t)(workspace / (size_t)(bytes > 0 ? bytes : 1));
-  return n > 1 ? n : 1;
-}
-
 void plan_matmul_lean(const int64_t* s, size_t workspace, GemmPlan* pl) {
   const GemmPlan d = gemm_default(s);
   mdh_tile_params a, b;
   params_from_plan(s, d, &a);
   params_from_plan(s, *pl, &b);
-  if (same_table(a, b)) *pl = gemm_default_lean(s, parts_held(workspace, s[0] * s[1] * 4));
+  if (same_table(a, b)) *pl = gemm_default_lean(s, parts_held(workspace, s[0] * s[1]));
 }
 
 int matmul_candidates(const int64_t* s, GemmPlan* out, int cap) {
@@ -1005,12 +999,7 @@ static MccPlan mcc_default(const int64_t* s, int64_t most = 1 << 20) {
 
 MccPlan mcc_default_table(const int64_t* s) { return mcc_default(s); }
 
-void plan_mcc_lean(const int64_t* s, size_t workspace, MccPlan* pl) {
-  mdh_tile_params a, b;
-  params_from_plan(s, mcc_default(s), &a);
-  params_from_plan(s, *pl, &b);
-  if (same_table(a, b)) *pl = mcc_default(s, parts_held(workspace, s[0] * s[1] * s[2] * s[3] * 4));
-}
+MccPlan mcc_default_lean(const int64_t* s, size_t workspace) { return mcc_default(s, parts_held(workspace, s[0] * s[1] * s[2] * s[3])); }
 
 int mcc_candidates(const int64_t* s, MccPlan* out, int cap) {
   int n = 0;

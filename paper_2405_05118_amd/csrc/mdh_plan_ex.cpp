@@ -131,9 +131,10 @@ static int ex_ragged(const int64_t* s, const GemmPlan& g) {
 
 static GemmExPlan ex_default_tiled(const int64_t* s);
 
-static GemmExPlan ex_default_large(const int64_t* s) {
+// on slices in at most `most` parts of k
+static GemmExPlan ex_default_large(const int64_t* s, int64_t most = 1 << 20) {
   GemmExPlan pl = ex_default_tiled(s);
-  if (split_default(s[0], s[1], s[2], s[3], s[6] != 0, pl.g.S, &pl.g) || split_small_default(s[0], s[1], s[2], s[3], s[6] != 0, pl.g, &pl.g))
+  if (split_default(s[0], s[1], s[2], s[3], s[6] != 0, pl.g.S < most ? pl.g.S : (int)most, &pl.g) || split_small_default(s[0], s[1], s[2], s[3], s[6] != 0, pl.g, &pl.g))
     pl.g.ragged = ex_ragged(s, pl.g);
   return pl;
 }
@@ -169,6 +170,10 @@ static GemmExPlan ex_default(const int64_t* s) {
     return skinny_plan(s, 1, 8, S);
   }
   return ex_default_large(s);
+}
+
+GemmExPlan matmul_ex_default_lean(const int64_t* s, size_t workspace) {
+  return skinny_applies(s) ? ex_default(s) : ex_default_large(s, parts_held(workspace, s[0] * s[1] * s[2]));
 }
 
 static GemmExPlan ex_default_tiled(const int64_t* s) {

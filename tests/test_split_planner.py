@@ -127,10 +127,11 @@ def test_table_of_the_default_without_workspace(shape):
     assert e.value.status == 5
 
 
-# Products and layers whose default asks for a workspace and did not always: they run with fewer parts where it is missing or
-# holds only some, also for the default's table, and are close to 64 bits all the same (as in test_split_k).
+# Products and layers whose default asks for a workspace and did not always: a call without a table runs with fewer parts where
+# it is missing or holds only some, and is close to 64 bits all the same (as in test_split_k).
 LESS = [(mdh.MDH_MATMUL, (15890, 62, 1233)), (mdh.MDH_MATMUL, (12627, 59, 976)), (mdh.MDH_MCC, (9, 28, 28, 248, 464, 7, 7, 1, 1)),
-        (mdh.MDH_MCC, (3, 13, 16, 487, 47, 3, 3, 2, 2)), (mdh.MDH_MCC, (4, 20, 20, 77, 174, 1, 1, 1, 1)), (mdh.MDH_MCC, (8, 10, 15, 332, 405, 3, 3, 1, 1))]
+        (mdh.MDH_MCC, (3, 13, 16, 487, 47, 3, 3, 2, 2)), (mdh.MDH_MCC, (4, 20, 20, 77, 174, 1, 1, 1, 1)), (mdh.MDH_MCC, (8, 10, 15, 332, 405, 3, 3, 1, 1)),
+        (mdh.MDH_BMATMUL, (1, 12677, 62, 1283, 1, 0, 0)), (mdh.MDH_BMATMUL, (5, 2934, 52, 1067, 0, 1, 1))]
 
 
 @pytest.mark.gpu
@@ -141,12 +142,7 @@ def test_default_with_less_workspace(inst, sizes, parts):
 
     g = torch.Generator(device="cuda").manual_seed(parts + sizes[0])
     rand = lambda *shape: torch.rand(shape, generator=g, device="cuda") * 2 - 1
-    if inst == mdh.MDH_MATMUL:
-        M, N, K = sizes
-        a, b = rand(M, K), rand(K, N)
-        ref, mag, terms = a.double() @ b.double(), a.double().abs() @ b.double().abs(), K
-        call = mdh.mdh_matmul
-    else:
+    if inst == mdh.MDH_MCC:
         n, P, Q, K, C, R, S, st, _ = sizes
         a, b = rand(n, (P - 1) * st + R, (Q - 1) * st + S, C), rand(K, R, S, C)
         ref, mag, terms = torch.zeros((n * P * Q, K), dtype=torch.float64, device="cuda"), 0.0, C * R * S
@@ -156,15 +152,33 @@ def test_default_with_less_workspace(inst, sizes, parts):
                 w = b[:, r, s].double().t().contiguous()
                 ref += tap @ w
                 mag = mag + tap.abs() @ w.abs()
-        call = lambda a, b, out, p, ws: mdh.mdh_mcc(a, b, out.view(n, P, Q, K), (st, st), p, ws)
-    need = mdh.mdh_workspace_size(inst, sizes)
-    assert need > 0 and need % (ref.numel() * 4) == 0
-    for p in (None, mdh.mdh_default_params(inst, sizes)):
+        ref, mag = ref.view(n, P, Q, K), mag.view(n, P, Q, K)
+        call = lambda out, p, ws: mdh.mdh_mcc(a, b, out, (st, st), p, ws)
+    else:
+        batch, M, N, terms, ta, tb, tc = sizes if inst == mdh.MDH_BMATMUL else (1, *sizes, 0, 0, 0)
+        a, b = rand(batch, M, terms), rand(batch, terms, N)
+        ref = torch.stack([a[i].double() @ b[i].double() for i in range(batch)])
+        mag = torch.stack([a[i].double().abs() @ b[i].double().abs() for i in range(batch)])
+        ref, mag = (ref.transpose(1, 2), mag.transpose(1, 2)) if tc else (ref, mag)
+        A, B = (a.transpose(1, 2).contiguous() if ta else a), (b.transpose(1, 2).contiguous() if tb else b)
+        if inst == mdh.MDH_BMATMUL:
+            call = lambda out, p, ws: mdh.mdh_matmul_ex(A, B, out, bool(ta), bool(tb), bool(tc), p, ws)
+        else:
+            call = lambda out, p, ws: mdh.mdh_matmul(A[0], B[0], out[0], p, ws)
+    need, n = mdh.mdh_workspace_size(inst, sizes), ref.numel()
+    assert need > 0 and need % (n * 4) == 0
+    table = mdh.mdh_default_params(inst, sizes)
+    for p in (None, table):
         out = torch.full(ref.shape, float("nan"), device="cuda")
-        room = torch.full((parts * ref.numel() + 64,), 7.0, device="cuda")  # 64 guard words
-        call(a, b, out, p, room[: parts * ref.numel()] if parts else None)
+        room = torch.full((parts * n + 64,), 7.0, device="cuda")  # 64 guard words
+        if p and inst != mdh.MDH_MATMUL and parts * n * 4 < need:  # a table is taken as it stands, but MatMul's default
+            with pytest.raises(mdh.MdhError) as e:
+                call(out, p, room[: parts * n] if parts else None)
+            assert e.value.status == 5
+            continue
+        call(out, p, room[: parts * n] if parts else None)
         assert bool(((out.double() - ref).abs() <= terms * 2.0**-24 * mag).all())
-        assert bool((room[parts * ref.numel() :] == 7.0).all())
+        assert bool((room[parts * n :] == 7.0).all())
 
 
 # a part of c is a chain in one accumulator, and a longer one is further from 64 bits: the number of parts that the estimate
