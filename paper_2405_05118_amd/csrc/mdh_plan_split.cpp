@@ -8,6 +8,7 @@ namespace detail {
 
 static const int kSplitMenu[][5] = {  // BM, BN, BK, WM, WN
     {256, 256, 16, 64, 128}, {256, 128, 32, 64, 64}, {128, 128, 32, 32, 64}, {128, 64, 32, 64, 32}, {64, 64, 32, 32, 32}};
+constexpr int kSplitLds = 5;
 // k over the wavefronts (mdh_matmul_split_k.hip): BM, BN, wavefronts
 static const int kSplitKMenu[][3] = {{64, 64, 8}, {64, 64, 4}, {64, 96, 4}, {96, 64, 4}, {96, 96, 4}, {32, 64, 8}, {64, 32, 8}, {32, 32, 8}};
 
@@ -91,8 +92,11 @@ static const StepTime kStep[kSplitTiles] = {
     {{0.212}, 0.040, 1, 15.0, 2.0},
     {{0.125, 0.243}, 0.048, 2, 9.3, 3.1}};
 
-static double estimate(int i, int64_t tiles, int64_t M, int64_t N, int64_t batch, int64_t K, int S) {
-  const StepTime& t = kStep[i];
+// A coarser estimate of the tiles in LDS, which leans towards more parts of k: it has the least number of them.
+static const StepTime kStepParts[] = {
+    {{3.5}, 0.9, 1, 3, 0}, {{1.95}, 0.45, 1, 3, 0}, {{1.1}, 0.2, 1, 3, 0}, {{0.98, 1.56}, 0, 2, 2, 0}, {{0.57, 0.95, 1.30}, 0, 3, 1, 0}};
+
+static double estimate(const StepTime& t, int64_t tiles, int64_t M, int64_t N, int64_t batch, int64_t K, int S) {
   const int64_t slots = 256 * t.held, work = tiles * S, rest = work % slots;
   const double fill = t.full * (work < 256 ? (double)work / 256 : 1.0);
   double round = (double)(work / slots) * (t.us[t.held - 1] + fill);
@@ -108,7 +112,7 @@ int split_offered(int64_t batch, int64_t M, int64_t N, int64_t K, bool tc, GemmP
   double us[kSplitTiles], best = 1e30;
   const int n = split_tiles(tc, sp);
   for (int i = 0; i < n; ++i) {
-    us[i] = split_fits(M, N, K, sp[i]) ? estimate(i, batch * cdiv(M, sp[i].BM) * cdiv(N, sp[i].BN), M, N, batch, K, 1) : 1e30;
+    us[i] = split_fits(M, N, K, sp[i]) ? estimate(kStep[i], batch * cdiv(M, sp[i].BM) * cdiv(N, sp[i].BN), M, N, batch, K, 1) : 1e30;
     if (us[i] < best) best = us[i];
   }
   int m = 0;
@@ -117,17 +121,20 @@ int split_offered(int64_t batch, int64_t M, int64_t N, int64_t K, bool tc, GemmP
   return m;
 }
 
-// the fastest of the tiles from `first` on, at most S parts of k; < 0: none takes these sizes
-static double best_tile(int first, int64_t batch, int64_t M, int64_t N, int64_t K, bool tc, int S, GemmPlan* g) {
+// the fastest of the tiles from `first` to before `last` by the estimate `step`, in `least` to S parts of k; < 0: none takes
+// these sizes
+static double best_tile(const StepTime* step, int first, int last, int64_t batch, int64_t M, int64_t N, int64_t K, bool tc, int least,
+                        int S, GemmPlan* g) {
   GemmPlan sp[kSplitTiles];
-  const int n = split_tiles(tc, sp);
+  split_tiles(tc, sp);
   double best = -1;
-  for (int i = first; i < n; ++i)
-    for (int s = 1; s <= S; s *= 2) {
+  for (int i = first; i < last; ++i)
+    for (int s = least; s <= S; s *= 2) {
       sp[i].S = s;
       if ((s - 1) * split_part(K, sp[i]) >= K) break;  // a part without k
       if (!split_fits(M, N, K, sp[i])) continue;
-      const double t = estimate(i, batch * cdiv(M, sp[i].BM) * cdiv(N, sp[i].BN), M, N, batch, K, s);
+      const int64_t k = step == kStepParts ? cdiv(K, 32 * s) * 32 * s : K;  // (the coarser one counts whole steps)
+      const double t = estimate(step[i], batch * cdiv(M, sp[i].BM) * cdiv(N, sp[i].BN), M, N, batch, k, s);
       if (best < 0 || t < best) {
         best = t;
         *g = sp[i];
@@ -148,7 +155,16 @@ static double best_tile(int first, int64_t batch, int64_t M, int64_t N, int64_t 
 bool split_default(int64_t batch, int64_t M, int64_t N, int64_t K, bool tc, int S, GemmPlan* g) {
   if (!split_sizes(M, N, K) || K < 128 || M < 48 || N < 48 || batch < 1) return false;
   if ((double)batch * M * N * K < (double)(1 << 26)) return false;
-  return best_tile(0, batch, M, N, K, tc, S, g) >= 0;
+  if (best_tile(kStep, 0, kSplitTiles, batch, M, N, K, tc, 1, S, g) < 0) return false;
+  // A part is one chain in an accumulator, and twice as long a chain is 1.4 times as far from 64 bits: not fewer parts than
+  // the coarser estimate has, though the other one would take fewer for 1 % of tall and narrow outputs and be up to a fifth
+  // faster there (us and error in 2^-24, those / these: 25978 x 49 x 1755 56 and 10.7 / 56 and 7.5, 23917 x 54 x 692 24.4 and
+  // 6.6 / 28.4 and 4.6, 1844 x 53 x 10969 32.4 and 7.0 / 39.6 and 5.1).  With k over the wavefronts a chain is a quarter or
+  // an eighth as long anyway.
+  GemmPlan p;
+  if (g->WK == 1 && S > 1 && best_tile(kStepParts, 0, kSplitLds, batch, M, N, K, tc, 1, S, &p) >= 0 && p.S > g->S)
+    best_tile(kStep, 0, kSplitTiles, batch, M, N, K, tc, p.S, S, g);
+  return true;
 }
 
 // Small products, which the fp32 rule gives to 64 x 64 tiles in k-tiles of 16 (plan `f`, S parts of k): the same tiles of one
@@ -162,7 +178,7 @@ bool split_small_default(int64_t batch, int64_t M, int64_t N, int64_t K, bool tc
   const double wg = (double)batch * cdiv(M, 64) * cdiv(N, 64) * f.S / 512;
   const double fp32 = 4.15 + (wg > 1 ? wg : 1) * (double)K / f.S * 0.033 + (f.S > 1 ? 1.76 + 0.12 * f.S : 0.0);
   GemmPlan b;
-  const double t = best_tile(kSplitTiles - 3, batch, M, N, K, tc, 1, &b);
+  const double t = best_tile(kStep, kSplitTiles - 3, kSplitTiles, batch, M, N, K, tc, 1, 1, &b);
   if (t < 0 || t > 0.85 * fp32) return false;
   *g = b;
   return true;
@@ -183,7 +199,7 @@ bool split_k_default(int64_t M, int64_t N, int64_t K, const GemmPlan& f, GemmPla
   const double *c = per[b16][whole], wg = (double)cdiv(M, f.BM) * cdiv(N, f.BN) * f.S;
   const double fp32 = c[0] + (double)K / (f.WK * f.S) * (c[1] + c[2] * wg * f.WK / 1024) + (f.S > 1 ? 3.0 : 0.0);
   GemmPlan b;
-  const double t = best_tile(kSplitTiles - 3, 1, M, N, K, false, f.S, &b);
+  const double t = best_tile(kStep, kSplitTiles - 3, kSplitTiles, 1, M, N, K, false, 1, f.S, &b);
   if (t < 0 || t > 0.76 * fp32) return false;
   *g = b;
   return true;

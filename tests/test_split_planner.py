@@ -189,3 +189,10 @@ def test_default_with_less_workspace(inst, sizes, parts):
 def test_parts_of_c_stay_short(sizes, parts):
     p = mdh.mdh_default_params(mdh.MDH_MCC, sizes)
     assert p.prt[2][4] == 8 and p.prt[3][4] >= parts
+
+
+@pytest.mark.parametrize("sizes,parts", [((25978, 49, 1755), 2), ((14058, 51, 1529), 4), ((19632, 55, 887), 2), ((54, 21694, 783), 2), ((1844, 53, 10969), 32)])
+def test_parts_of_k_stay_short(sizes, parts):
+    for inst, s, k in ((mdh.MDH_MATMUL, sizes, 2), (mdh.MDH_BMATMUL, (1, *sizes, 0, 0, 0), 3)):
+        p = mdh.mdh_default_params(inst, s)
+        assert p.blk[k] == 16 and p.prt[3][k] * p.prt[4][k] >= parts, inst
