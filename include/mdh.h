@@ -245,12 +245,15 @@ size_t mdh_workspace_size(mdh_instance inst, const int64_t* sizes, const mdh_til
  *   fewer parts; where the default is the kernel that tiles in LDS with fp32 instructions it
  *   is needed).  blk = (32,32,16) selects the
  *   kernels that carry a value as three bf16 values and multiply with six bf16 matrix
- *   products (K >= 32; the default for large products; prt[MDH_L_WAVE][k] = 1: tiles staged in
+ *   products (K >= 32; the default for large products, and, in tiles of one or two blocks, for
+ *   smaller ones of few tiles and mdh_matmul_ex's batches of them; prt[MDH_L_WAVE][k] = 1: tiles staged in
  *   LDS, 4 or 8: k over the wavefronts of a workgroup, tiles of 32 to 96 rows and columns inside C; Inf, NaN, overflow and values below
  *   2^-100 take the fp32 instructions; a product with a permutation is exact, a sum of one
  *   term within 3 * 2^-24; sums with many zero terms are up to twice as far off as with
- *   fp32 instructions, which a table selects -- not so those of the tiles of one or two
- *   blocks with k over the wavefronts).  Two kernels with fp32 instructions, told apart by
+ *   fp32 instructions, which a table with blk[k] = 2 selects).  The tiles of one or two blocks
+ *   with k over the wavefronts multiply with eight products and sum the first of them apart: a
+ *   sum of one term is within 1.11 * 2^-24 (fp32 instructions: 1.0), one of few terms as close
+ *   as from the fp32 kernels that add up parts of k.  Two kernels with fp32 instructions, told apart by
  *   prt[MDH_L_WAVE][k]: 1 = the wavefronts of a workgroup tile its output tile,
  *   operands staged in LDS (in_region = MDH_MR_LDS); WK > 1 = every wavefront owns
  *   the whole (small) output tile and 1/WK of the k-range, operands go straight to
@@ -468,8 +471,9 @@ mdh_status mdh_matvec(int64_t M, int64_t K, const float* A, const float* x, floa
  * For mdh_default_params etc. the `sizes` of MDH_BMATMUL are
  * (batch, M, N, K, trans_a, trans_b, trans_c); a configuration's in_transposed[0..1]
  * and out_transposed must equal the call's flags.
- * Besides MatMul's kernels on slices, blk = (1,32,32,16), any views, two kernels with fp32
- * instructions: blk = (1,32,32,2), LDS-tiled, any views; blk = (1,16,16,4) for M <= 16
+ * Besides MatMul's kernels on slices, blk = (1,32,32,16), any views (the default from K = 128
+ * and 2^26 products on, and for most smaller batches from K = 64 on: a table with blk[k] = 2
+ * selects fp32 instructions), two kernels with fp32 instructions: blk = (1,32,32,2), LDS-tiled, any views; blk = (1,16,16,4) for M <= 16
  * with A and C plain (B plain or transposed), which streams both operands from
  * device memory straight into MFMA operand registers and parallelises k over
  * wavefronts and workgroups (the library default for those shapes).  That kernel

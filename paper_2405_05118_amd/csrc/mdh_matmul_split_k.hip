@@ -132,8 +132,16 @@ struct Lds {
   static constexpr int BYTES = TOP + 16;
 };
 
-// Tiles of one or two blocks have registers to spare for a sum of their own for h h', which rounds once per 16 k where
-// six products in one accumulator round up to six times: for sums of few terms, whose rounding that is (mdh_split.h).
+// Tiles of one or two blocks stand in for kernels on fp32 instructions, whose sums of few terms are rounded once per term.
+// They have registers to spare for a sum of their own for h h', which is exact in 16 bits and rounds once per 16 k where
+// products in one accumulator round up to six times, and take eight of the nine products (mdh_split.h; all but l l', below
+// 2^-34): with six a single product is off by up to 1.7 x 2^-24 instead of 1.0, and 4 % of them are not the correctly
+// rounded ones.  Error against 64 bits, 256 x 256 x 512, n terms of a sum not zero, relative 2-norm in units of 2^-24, fp32
+// instructions in LDS tiles / with k over eight wavefronts / these / with six products: n = 1 0.42 / 0.42 / 0.42 / 0.44, 2
+// 0.52 / 0.61 / 0.60 / 0.61, 4 0.67 / 0.76 / 0.74 / 0.75, 8 0.90 / 0.92 / 0.88 / 0.88, 32 1.7 / 1.2 / 1.0 / 1.0, dense 6.8 /
+// 2.6 / 1.3 / 1.3.  (A pair of sums a wavefront up to the end, h h' and the rest, has 0.43, 0.44, 0.48 for 2, 4, 8 terms but
+// takes 6 % more of a call of 5 us.)  The two products more cost 2.4 % over 45 products of 4.6 to 34 us: a step of one block
+// 0.128 -> 0.140 us for 32 k, 4 x 203 x 171 x 183 5.2 / 5.2, 288 x 320 x 2880 16.2 / 17.9, 340 x 2912 x 1786 34 / 38.
 template <int MI, int NI, int W, bool YK, bool XK>
 __global__ __launch_bounds__(W * 64, (MI * NI > 6 ? 1 : 2)) void matmul_split_k_kernel(
     const float* __restrict__ Y, const float* __restrict__ X, float* __restrict__ C, float* __restrict__ ws, int M, int N, int K,
@@ -232,6 +240,8 @@ __global__ __launch_bounds__(W * 64, (MI * NI > 6 ? 1 : 2)) void matmul_split_k_
       for (int i = 0; i < MI; ++i)
 #pragma unroll
         for (int j = 0; j < NI; ++j) sum[i][j] = mfma(x[j][H], y[i][H], sum[i][j]);
+      mma(Mid, L);
+      mma(L, Mid);
     }
     // the smaller products first, as in mdh_matmul_split.hip
     mma(Mid, Mid);

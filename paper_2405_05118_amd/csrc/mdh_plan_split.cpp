@@ -88,8 +88,8 @@ static const StepTime kStep[kSplitTiles] = {
     {{0.489}, 0.073, 1, 10.1, 2.1},
     {{0.507}, 0.054, 1, 9.6, 2.0},
     {{0.675}, 0.081, 1, 10.1, 2.0},
-    {{0.205}, 0.044, 1, 14.8, 2.0},
-    {{0.212}, 0.040, 1, 15.0, 2.0},
+    {{0.205}, 0.044, 1, 14.8, 2.0},  // (4 % below their times since they take eight products, and left so: the tiles they
+    {{0.212}, 0.040, 1, 15.0, 2.0},  // would give way to are further from 64 bits)
     {{0.125, 0.243}, 0.048, 2, 9.3, 3.1}};
 
 // A coarser estimate of the tiles in LDS, which leans towards more parts of k: it has the least number of them.
@@ -168,11 +168,10 @@ bool split_default(int64_t batch, int64_t M, int64_t N, int64_t K, bool tc, int 
 }
 
 // Small products, which the fp32 rule gives to 64 x 64 tiles in k-tiles of 16 (plan `f`, S parts of k): the same tiles of one
-// or two blocks instead (no less exact on sums of few terms, see below), in one launch, where they are estimated at 0.85 of
-// that kernel's time or less -- a line fitted to 230 random batches of 2^19 to 2^26 multiply-adds, off by 7 % rms.  Of those
-// four fifths go there, and all take 0.71 of the time on average, two are slower (4 x 221 x 521 x 112, C transposed: 7.6 / 10.7;
-// 33 x 90 x 102 x 198: 10.6 / 12.2).  us, replayed from a graph: 2 x 68 x 149 x 353, A and B transposed, 11.7 / 6.4; 13 x 108 x
-// 66 x 237 12.9 / 5.9; 2 x 170 x 201 x 111 6.8 / 5.3.
+// or two blocks instead (with eight products: see mdh_matmul_split_k.hip for their errors), in one launch, where they are
+// estimated at 0.85 of that kernel's time or less -- a line fitted to 230 random batches of 2^19 to 2^26 multiply-adds, off by
+// 7 % rms.  Four fifths go there; 170 of them take 0.62 of the time on average, none is slower.  us, replayed from a graph: 2 x
+// 68 x 149 x 353, A and B transposed, 11.7 / 5.8; 13 x 108 x 66 x 237 12.9 / 5.2; 4 x 203 x 171 x 183 11.1 / 5.2.
 bool split_small_default(int64_t batch, int64_t M, int64_t N, int64_t K, bool tc, const GemmPlan& f, GemmPlan* g) {
   if (f.BM != 64 || f.BN != 64 || f.BK != 16 || batch < 1 || K < 64 || (double)batch * M * N * K > (double)(1 << 26)) return false;
   const double wg = (double)batch * cdiv(M, 64) * cdiv(N, 64) * f.S / 512;
@@ -186,12 +185,11 @@ bool split_small_default(int64_t batch, int64_t M, int64_t N, int64_t K, bool tc
 
 // Outputs of few tiles, which the fp32 rule gives to its own kernel with k over the wavefronts (plan `f`, small tiles,
 // S parts of k): the ones of 32 x 32 to 64 x 32 with a sum of their own for h h' instead, where they are clearly faster.
-// They are no less exact than that kernel on sums of few terms either (256 x 256 x 2048, rms error in units of 2^-24, fp32
-// / slices: 1 term 0.41 / 0.42, 4 0.74 / 0.75, 16 0.98 / 0.98, 64 1.3 / 1.06, 2048 4.9 / 1.6).
+// They are no further from 64 bits than that kernel, on sums of few terms either (256 x 256 x 2048, relative 2-norm in units
+// of 2^-24, fp32 / slices: 1 term 0.42 / 0.42, 2 0.61 / 0.60, 4 0.76 / 0.74, 16 1.06 / 0.98, 64 1.3 / 1.06, 2048 4.9 / 1.8).
 // The fp32 kernel's time is a fit that is off by up to 40 %, so theirs has to be below three quarters of it: of 97 random
-// sizes 36 go there, 1.7 times as fast on average, none slower (four fifths: 195 x 292 x 7618 34.1 -> 40.0; nine tenths: 128
-// x 512 x 4032 16.1 -> 20.6).  us, replayed from a graph: 288 x 320 x 2880 36.4 / 16.7; 164 x 409 x 2447 21.7 / 14.6;
-// stays: 512^3 6.0 / 7.0.
+// sizes 36 go there, and 110 that do take 0.61 of the time on average, none more (four fifths: 195 x 292 x 7618 34.1 -> 40.0;
+// nine tenths: 128 x 512 x 4032 16.1 -> 20.6).  us, replayed from a graph: 288 x 320 x 2880 36.4 / 17.9; stays: 512^3 6.0 / 7.0.
 bool split_k_default(int64_t M, int64_t N, int64_t K, const GemmPlan& f, GemmPlan* g) {
   if (!split_sizes(M, N, K) || K < 128 || (double)M * N * K < (double)(1 << 26)) return false;
   const bool b16 = f.BM == 16, whole = M % f.BM == 0 && N % f.BN == 0 && K % 16 == 0;

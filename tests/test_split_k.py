@@ -140,4 +140,77 @@ def test_a_permutation_is_exact_and_single_terms_round_once():
         assert torch.equal(out, perm @ x), p.table()
         mdh.mdh_matmul(perm * scale, x, out, p, workspace(mdh.MDH_MATMUL, sizes, p))
         ref, mag = sums(perm * scale, x)
-        assert bool(((out.double() - ref).abs() <= 3 * 2.0**-24 * mag).all()), p.table()
+        assert bool(((out.double() - ref).abs() <= (ONE_TERM if apart(p) else 3.0) * 2.0**-24 * mag).all()), p.table()
+
+
+# Tiles of one or two blocks sum h h', which 16 bits hold exactly, apart: the seven smaller products, below 2^-7 of it
+# together, are cut off at 2^-30 each, the sum of both is rounded once, and l l' (2^-34) is left out.
+ONE_TERM = 1 + 7 * 2.0**-6 + 2.0**-10
+
+
+def apart(p):
+    return tile(p)[0] * tile(p)[1] <= 2
+
+
+# Sums of few terms, as close to 64 bits as on the fp32 instructions with k over as many wavefronts.  Limit: over 12 times 65536
+# outputs the ratio of the two errors was 1.000 for one term, 0.88 to 0.99 for 2 to 32 and less beyond; six products are at 1.026
+# for one term, and one accumulator for all of them (MCC of few channels) at 1.4 for one and 1.8 for eight.
+@pytest.mark.gpu
+@pytest.mark.parametrize("terms", [1, 2, 3, 8, 32, 512])
+def test_sums_of_few_terms(terms):
+    sizes = M, N, K = 256, 256, 512
+    g = torch.Generator(device="cuda").manual_seed(terms)
+    at = torch.stack([torch.randperm(K, generator=g, device="cuda")[:terms] for _ in range(M)])
+    a = torch.zeros((M, K), device="cuda").scatter_(1, at, torch.randn((M, terms), generator=g, device="cuda"))
+    b = torch.randn((K, N), generator=g, device="cuda")
+    ref = a.double() @ b.double()
+
+    def error(p):
+        out = torch.full((M, N), float("nan"), device="cuda")
+        mdh.mdh_matmul(a, b, out, p, workspace(mdh.MDH_MATMUL, sizes, p))
+        return float((out.double() - ref).norm())
+
+    cands = [mdh.mdh_candidate(mdh.MDH_MATMUL, sizes, i) for i in range(mdh.mdh_num_candidates(mdh.MDH_MATMUL, sizes))]
+    fp32 = next(p for p in cands if p.blk[2] != 16 and p.prt[4][2] == 8 and p.prt[3][2] == 1)
+    tiles = [p for p in tables(mdh.MDH_MATMUL, sizes) if apart(p) and p.prt[3][2] == 1]
+    assert len(tiles) == 3
+    for p in tiles:
+        assert error(p) <= 1.01 * error(fp32), p.table()
+
+
+# Small batches and outputs of few tiles whose default is these tiles (K from 64 on), and the line: close to 64 bits through the
+# default, and tables with fp32 instructions to choose instead.
+SMALL = [(2, 64, 64, 64, 0, 0, 0), (1, 33, 33, 64, 0, 0, 0), (3, 70, 90, 65, 0, 1, 0), (5, 97, 61, 100, 1, 0, 1), (4, 203, 171, 127, 1, 1, 0), (4, 203, 171, 183, 0, 1, 0)]
+
+
+@pytest.mark.parametrize("sizes", SMALL)
+def test_default_of_small_batches(sizes):
+    p = mdh.mdh_default_params(mdh.MDH_BMATMUL, sizes)
+    assert p.blk[3] == 16 and apart(p) and tile(p)[2] == 8 and mdh.mdh_workspace_size(mdh.MDH_BMATMUL, sizes) == 0
+    cands = [mdh.mdh_candidate(mdh.MDH_BMATMUL, sizes, i) for i in range(mdh.mdh_num_candidates(mdh.MDH_BMATMUL, sizes))]
+    assert any(p.blk[3] == 2 for p in cands)
+
+
+def test_line_of_small_batches():
+    for sizes, split in (((2, 64, 64, 63, 0, 0, 0), False), ((2, 64, 64, 64, 0, 0, 0), True), ((2, 31, 64, 64, 0, 0, 0), False),
+                         ((64, 512, 512, 100, 0, 0, 0), False)):
+        assert (mdh.mdh_default_params(mdh.MDH_BMATMUL, sizes).blk[3] == 16) == split, sizes
+    p = mdh.mdh_default_params(mdh.MDH_MATMUL, (288, 320, 2880))
+    assert p.blk[2] == 16 and apart(p)
+    assert mdh.mdh_default_params(mdh.MDH_MATMUL, (512, 512, 512)).blk[2] == 2
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("sizes", SMALL)
+def test_small_batches_are_close(sizes):
+    batch, M, N, K, ta, tb, tc = sizes
+    g = torch.Generator(device="cuda").manual_seed(K)
+    a = torch.rand((batch, M, K), generator=g, device="cuda") * 2 - 1
+    b = torch.rand((batch, K, N), generator=g, device="cuda") * 2 - 1
+    A, B = (a.transpose(1, 2).contiguous() if ta else a), (b.transpose(1, 2).contiguous() if tb else b)
+    C = torch.full((batch, N, M) if tc else (batch, M, N), float("nan"), device="cuda")
+    mdh.mdh_matmul_ex(A, B, C, bool(ta), bool(tb), bool(tc))
+    # 1.8e-8 sqrt(K) is what fp32 sums of random products show, 1.2e-7 at the least
+    for i in range(batch):
+        ref = a[i].double() @ b[i].double()
+        assert float(((C[i].t() if tc else C[i]).double() - ref).norm() / ref.norm()) <= max(1.2e-7, 1.8e-8 * K**0.5)
