@@ -372,9 +372,11 @@ __device__ __forceinline__ void split_tile(const float* __restrict__ Y, const fl
 }
 
 // (second launch bound: the wavefronts of a SIMD that LDS has room for, so that the fp32 evaluation, whose registers
-// would allow fewer, does not come into it)
+// would allow fewer, does not come into it: three workgroups of 64 x 64 tiles.  With A transposed and B plain those take 176
+// registers if they may, which leaves two: 64 x 803 x 431 x 216 109 us, 100 with three and four registers spilled in the fp32
+// evaluation; 16 x 400 x 700 x 260 30.1 / 28.0)
 template <int BM, int BN, int BK, int WM, int WN, bool YK, bool XK>
-__global__ __launch_bounds__(((BM / WM) * (BN / WN) * 64), 2) void matmul_split_kernel(
+__global__ __launch_bounds__(((BM / WM) * (BN / WN) * 64), (BM + BN > 128 ? 2 : 3)) void matmul_split_kernel(
     const float* __restrict__ Y, const float* __restrict__ X, float* __restrict__ C, float* __restrict__ ws, int M, int N,
     int K, int tiles_m, int tiles_n, int S, int kchunk, int nbatch, int jmajor) {
   extern __shared__ __attribute__((aligned(16))) char lds[];
