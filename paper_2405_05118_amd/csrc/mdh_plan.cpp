@@ -137,6 +137,12 @@ static StencilPlan stencil_direct(const int64_t* s, int RJ, int PI) {
   return pl;
 }
 
+// A launch has less than 2^32 lanes, which grids of few points a plane reach first (nx = 2^26, ny = nz = 1: 2^24 workgroups of
+// 256); the marching kernel's workgroups take up to 64 planes.
+static bool stencil_direct_fits(const int64_t* s, const StencilPlan& pl) {
+  return cdiv(s[0], pl.PI) * cdiv(s[1], (int64_t)pl.TY * pl.RJ) * cdiv(s[2], (int64_t)pl.LK * 4) < (1 << 24);
+}
+
 static StencilPlan stencil_march(const int64_t* s) {
   StencilPlan pl;
   pl.RJ = 4;
@@ -179,8 +185,8 @@ static StencilPlan stencil_default(const int64_t* s) {
   const double points = (double)s[0] * s[1] * s[2];
   const StencilPlan march = stencil_march(s);
   if (points >= (double)(1 << 25) && march.LK == 128 && s[2] % 512 == 0 && s[1] % (march.TY * march.RJ) == 0) return march;
-  if (points < (double)(1 << 23)) return stencil_direct(s, 2, 2);
-  return points < (double)(1 << 24) ? stencil_direct(s, 2, 4) : stencil_direct(s, 4, 4);
+  const StencilPlan direct = points < (double)(1 << 23) ? stencil_direct(s, 2, 2) : points < (double)(1 << 24) ? stencil_direct(s, 2, 4) : stencil_direct(s, 4, 4);
+  return stencil_direct_fits(s, direct) ? direct : march;
 }
 
 int stencil_candidates(const int64_t* s, StencilPlan* out, int cap) {
@@ -206,7 +212,7 @@ int stencil_candidates(const int64_t* s, StencilPlan* out, int cap) {
     for (int si : sis) push(m[0], m[1], m[2], si);
   for (auto& m : kStencilDirect) {
     const StencilPlan pl = stencil_direct(s, m[0], m[1]);
-    if (n < cap && !(d.PI == pl.PI && d.RJ == pl.RJ)) out[n++] = pl;
+    if (n < cap && !(d.PI == pl.PI && d.RJ == pl.RJ) && stencil_direct_fits(s, pl)) out[n++] = pl;
   }
   return n;
 }
@@ -229,6 +235,7 @@ mdh_status plan_stencil(const int64_t* s, const mdh_tile_params* p, StencilPlan*
   pl.SI = pl.PI ? pl.PI : p->prt[MDH_L_HBM][0];
   pl.ragged = ragged;
   if (pl.PI && !stencil_direct_inst(pl)) return MDH_ERR_UNSUPPORTED;
+  if (pl.PI && !stencil_direct_fits(s, pl)) return MDH_ERR_SIZE;
   if (!pl.PI && stencil_lds_bytes(pl.RJ, pl.TY, pl.LK) > kLdsBytesPerWG) return MDH_ERR_TILE_RESOURCES;
   mdh_tile_params chk;
   params_from_plan(s, pl, &chk);

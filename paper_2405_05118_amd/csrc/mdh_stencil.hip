@@ -292,7 +292,7 @@ template <int RJ, int PI, int LK>
 mdh_status launch_direct(int64_t nx, int64_t ny, int64_t nz, const float* in, float* out, float c0, float c1, hipStream_t st) {
   const int64_t njt = cdiv(ny, 256 / LK * RJ), nkt = cdiv(nz, LK * 4);
   const int64_t nblocks = njt * nkt * cdiv(nx, PI);
-  if (nblocks <= 0 || nblocks > 0x7fffffff) return MDH_ERR_SIZE;
+  if (nblocks <= 0 || nblocks >= 1 << 24) return MDH_ERR_SIZE;  // 2^32 lanes
   clear_stale_error();
   hipLaunchKernelGGL((stencil_direct_kernel<RJ, PI, LK>), dim3((unsigned)nblocks), dim3(256), 0, st, in, out, (int)nx, (int)ny,
                      (int)nz, (int)njt, (int)nkt, c0, c1);

@@ -24,6 +24,35 @@ def test_planner():
         assert mdh.mdh_validate_params(mdh.MDH_STENCIL, (100, 90, 200), q) != 0, (layer, d, v)
 
 
+# a launch has less than 2^32 lanes: the longest grids stay with the kernel whose workgroups march over planes
+@pytest.mark.parametrize("shape,marches", [((1 << 25, 1, 1), False), ((1 << 26, 1, 1), True), ((200000000, 1, 1), True), ((80000000, 2, 3), True), ((60000000, 3, 4), False)])
+def test_grids_of_many_planes(shape, marches):
+    p = mdh.mdh_default_params(mdh.MDH_STENCIL, shape)
+    assert (p.in_region[0] == 1) == marches
+    for q in [p] + sum(tables(shape), []):
+        workgroups = q.prt[3][0] * q.prt[3][1] * q.prt[3][2]
+        assert mdh.mdh_validate_params(mdh.MDH_STENCIL, shape, q) == 0 and (q.in_region[0] == 1 or workgroups * 256 < 1 << 32)
+    if marches:
+        q = tables((100, 1, 1))[0][0].copy()
+        q.prt[3][0] = -(-shape[0] // q.prt[2][0])
+        q.ragged = 1
+        assert mdh.mdh_validate_params(mdh.MDH_STENCIL, shape, q) == 2  # MDH_ERR_SIZE
+
+
+@pytest.mark.gpu
+def test_a_grid_of_2_to_the_26_planes():
+    n = 1 << 26
+    x = torch.rand((n + 2, 3, 3), generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    out = torch.full((n, 1, 1), float("nan"), device="cuda")
+    mdh.mdh_stencil(x, out, 0.5, 1.0 / 12.0)
+    c1 = float(torch.tensor(1.0 / 12.0))
+    for a in range(0, n, 1 << 24):
+        v = x[a : a + (1 << 24) + 2].double()
+        m = v[1:-1]
+        want = 0.5 * m[:, 1, 1] + c1 * (v[:-2, 1, 1] + v[2:, 1, 1] + m[:, 0, 1] + m[:, 2, 1] + m[:, 1, 0] + m[:, 1, 2])
+        assert bool(((out[a : a + (1 << 24)].flatten().double() - want).abs() <= 7 * 2.0**-24 * want).all())  # as below
+
+
 # one cell, one more and one less than the lanes' columns of each width, than their rows and planes; a last row and plane
 # that end the buffer
 @pytest.mark.gpu
