@@ -197,7 +197,7 @@ int stencil_candidates(const int64_t* s, StencilPlan* out, int cap) {
     StencilPlan pl{RJ, TY, LK, SI, 0};
     pl.ragged = (s[0] % SI) || (s[1] % (TY * RJ)) || (s[2] % (LK * 4));
     for (int i = 0; i < n; ++i)
-      if (out[i].RJ == RJ && out[i].TY == TY && out[i].LK == LK && out[i].SI == SI) return;
+      if (!out[i].PI && out[i].RJ == RJ && out[i].TY == TY && out[i].LK == LK && out[i].SI == SI) return;
     out[n++] = pl;
   };
   const StencilPlan d = stencil_default(s);

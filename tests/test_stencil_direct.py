@@ -24,6 +24,15 @@ def test_planner():
         assert mdh.mdh_validate_params(mdh.MDH_STENCIL, (100, 90, 200), q) != 0, (layer, d, v)
 
 
+# grids of two or four planes, where both kernels have tiles of the same numbers: the marching one's is a candidate all the same
+@pytest.mark.parametrize("shape,rows", [((2, 100, 200), 2), ((4, 40000, 128), 4)])
+def test_marching_tables_are_offered(shape, rows):
+    direct, march = tables(shape)
+    same = [p for p in march if p.prt[0][0] == shape[0] and p.prt[2][1] == rows]
+    assert any((p.prt[4][1] * p.prt[5][1], p.prt[4][2] * p.prt[5][2]) == (q.prt[4][1] * q.prt[5][1], q.prt[4][2] * q.prt[5][2]) and q.prt[2][:2] == [shape[0], rows]
+               for p in same for q in [direct[0]]), [p.table() for p in same]
+
+
 # a launch has less than 2^32 lanes: the longest grids stay with the kernel whose workgroups march over planes
 @pytest.mark.parametrize("shape,marches", [((1 << 25, 1, 1), False), ((1 << 26, 1, 1), True), ((200000000, 1, 1), True), ((80000000, 2, 3), True), ((60000000, 3, 4), False)])
 def test_grids_of_many_planes(shape, marches):
