@@ -277,7 +277,8 @@ mdh_status mdh_matmul(int64_t M, int64_t N, int64_t K, const float* A, const flo
  *   Any of nx, ny, nz == 0 is a valid empty call.
  *   Two kernels, bit for bit the same results: in_region[0] = MDH_MR_LDS, a workgroup marches over
  *   prt[MDH_L_HBM][i] planes; MDH_MR_VGPR, a lane holds prt[MDH_L_VGPR][i] planes at once (the
- *   default but for large grids of whole tiles of 512 columns).
+ *   default but for large grids of whole tiles of 512 columns that fill whole rounds of
+ *   workgroups, and for 2^26 planes and more of few points).
  */
 mdh_status mdh_stencil(int64_t nx, int64_t ny, int64_t nz, const float* in, float* out, float c0,
                        float c1, const mdh_tile_params* params, void* stream);

@@ -179,12 +179,18 @@ static StencilPlan stencil_march(const int64_t* s) {
 // 21.0 / 28.1, 300^3 41 / 81, 400^3 78 / 158, 640^3 411 / 507; over 80 random grids of 64 to 512 a side 2.4 times as fast.
 // Rows x planes a lane: 2 x 2 has the most wavefronts (143 x 70 x 501 9.8; 2 x 4 9.7, 4 x 4 12.1), 4 x 4 reads the least twice
 // (500^3 211; 2 x 4 234, 2 x 2 272), 2 x 4 is between (168 x 307 x 146 14.4, 13.8 and 16.6; 300^3 43.0, 47.4 and 42.3).
-// The marching kernel stays for large grids that its tiles of 512 columns fit, where every input cell comes from memory
-// once: 512^3 183 (4 x 4 202), 200 x 512 x 512 81.8 (84.6); 384^3, in tiles of 256 columns, 109.7 (109.2).
+// The marching kernel stays for large grids that its tiles of 512 columns and 16 rows fit, where every input cell comes from
+// memory once, if its workgroups are whole rounds of one a compute unit.  us, it / 4 x 4, buffers in turn: 512^3 181 / 203,
+// 256 x 512 x 512 93 / 105, 1024 x 512 x 512 387 / 419, 512 x 512 x 1024 383 / 394, 1024 x 1024 x 512 838 / 833; with a last
+// round that is not full 512 x 544 x 512 267 / 219, 400 x 400 x 1024 282 / 249, 512 x 320 x 512 147 / 126, 640 x 640 x 512 314 /
+// 311, 512 x 480 x 512 191 / 194; with a last row of tiles that is not full 512 x 520 x 512 371 / 202, 512 x 508 x 512 281 /
+// 205, 1000 x 1000 x 1024 1675 / 1525; in tiles of 256 columns 384^3 109.7 / 109.2.
 static StencilPlan stencil_default(const int64_t* s) {
   const double points = (double)s[0] * s[1] * s[2];
   const StencilPlan march = stencil_march(s);
-  if (points >= (double)(1 << 25) && march.LK == 128 && s[2] % 512 == 0 && s[1] % (march.TY * march.RJ) == 0) return march;
+  if (points >= (double)(1 << 25) && march.LK == 128 && s[2] % 512 == 0 && s[1] % (march.TY * march.RJ) == 0 &&
+      cdiv(s[0], march.SI) * (s[1] / (march.TY * march.RJ)) * (s[2] / 512) % 256 == 0)
+    return march;
   const StencilPlan direct = points < (double)(1 << 23) ? stencil_direct(s, 2, 2) : points < (double)(1 << 24) ? stencil_direct(s, 2, 4) : stencil_direct(s, 4, 4);
   return stencil_direct_fits(s, direct) ? direct : march;
 }

@@ -24,6 +24,13 @@ def test_planner():
         assert mdh.mdh_validate_params(mdh.MDH_STENCIL, (100, 90, 200), q) != 0, (layer, d, v)
 
 
+# the marching kernel where its workgroups are whole tiles and whole rounds of compute units
+@pytest.mark.parametrize("shape,marches", [((512, 512, 512), True), ((256, 512, 512), True), ((512, 256, 512), True), ((256, 256, 1024), True), ((512, 544, 512), False),
+                                           ((400, 400, 1024), False), ((512, 508, 512), False), ((512, 512, 500), False), ((200, 256, 512), False)])
+def test_line_between_the_kernels(shape, marches):
+    assert (mdh.mdh_default_params(mdh.MDH_STENCIL, shape).in_region[0] == 1) == marches
+
+
 # grids of two or four planes, where both kernels have tiles of the same numbers: the marching one's is a candidate all the same
 @pytest.mark.parametrize("shape,rows", [((2, 100, 200), 2), ((4, 40000, 128), 4)])
 def test_marching_tables_are_offered(shape, rows):
