@@ -184,14 +184,15 @@ def bench_stencil(torch, mdh, W, name, steps, warmup, cpu):
 
 
 def _split_variant(mdh, sizes, S):
-    """The default tile configuration with the reduction dimension split S ways over workgroups; where that tile is not
-    offered with S parts, the first of the same kind of value that is, and as many columns a workgroup."""
-    d = mdh.mdh_default_params(mdh.MDH_MATMUL, sizes)
-    cand = [mdh.mdh_candidate(mdh.MDH_MATMUL, sizes, i) for i in range(mdh.mdh_num_candidates(mdh.MDH_MATMUL, sizes))]
-    cand = [p for p in cand if p.prt[3][2] == S and p.blk[2] == d.blk[2]]
-    same_tile = [p for p in cand if all(list(p.prt[l][:3]) == list(d.prt[l][:3]) for l in (1, 2, 4, 5))]
-    same_cols = [p for p in cand if p.prt[3][1] == d.prt[3][1] and p.prt[4][1] * p.prt[2][1] == d.prt[4][1] * d.prt[2][1]]
-    return (same_tile + same_cols)[0]
+    """The default table with the reduction dimension in S parts over workgroups, the same tile; None if that is no table."""
+    p = mdh.mdh_default_params(mdh.MDH_MATMUL, sizes).copy()
+    p.prt[3][2] = S
+    step = p.prt[1][2] * p.prt[2][2] * p.blk[2]  # k of a step, of the LDS and register layers
+    p.prt[0][2] = -(-(-(-sizes[2] // (S * p.prt[4][2]))) // step)
+    for p.ragged in (0, 1):
+        if mdh.mdh_validate_params(mdh.MDH_MATMUL, sizes, p) == 0:
+            return p
+    return None
 
 
 def _mfma_roofline(tf, sliced, traffic, products=6):
@@ -207,6 +208,9 @@ def bench_matmul(torch, mdh, W, name, steps, warmup, cpu, split=None):
     b = W.device_uniform(cfg.seed, 2, (cfg.K, cfg.N), -1.0, 1.0)
     c = torch.empty((cfg.M, cfg.N), dtype=torch.float32, device="cuda")
     p = mdh.mdh_default_params(mdh.MDH_MATMUL, sizes) if split is None else _split_variant(mdh, sizes, split)
+    if p is None:
+        return {"missing": "the default's tile does not take k in %d parts" % split, "value": None, "unit": "GFLOP/s", "ms_per_step": None,
+                "dtype": "f32", "roofline": {"bound": "mfma", "frac": None}}
     sliced = p.blk[2] == 16  # values carried as three bf16 values
     nws = mdh.mdh_workspace_size(mdh.MDH_MATMUL, sizes, p)
     ws = torch.empty(max(nws, 4) // 4, dtype=torch.int32, device="cuda") if nws else None
