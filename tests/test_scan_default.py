@@ -27,7 +27,9 @@ def test_plan(R, n, tiles, chunks):
 @pytest.mark.gpu
 @pytest.mark.parametrize("R,n,tiles,chunks", EDGES)
 def test_rows(R, n, tiles, chunks):
-    """fp32 trees inside a tile, fp64 carries: 1e-5 of the prefix sum of |x|."""
+    """A lane adds up its four elements, a wavefront its lanes in six steps, and takes its own off again; the carries are fp64; one
+    rounding when they become fp32, one in the last addition: 3 + 6 + 1 + 2 roundings, of sums of no more than the |x| up to
+    the lane's last element."""
     import torch
 
     x = W.uniform(W.SEED_BASE + 97, 1, (R, n), -1, 1)
@@ -36,4 +38,5 @@ def test_rows(R, n, tiles, chunks):
     ws = torch.empty(nb // 4, device="cuda") if nb else None
     out = torch.full((R, n), float("nan"), device="cuda")
     mdh.mdh_scan(torch.from_numpy(x).cuda(), out, None, ws)
-    assert float(np.max(np.abs(out.cpu().numpy() - ref) / refabs)) <= 1e-5
+    bound = refabs[:, np.minimum(np.arange(n) | 3, n - 1)]
+    assert float(np.max(np.abs(out.cpu().numpy() - ref) / bound)) <= 12 * 2.0**-24
