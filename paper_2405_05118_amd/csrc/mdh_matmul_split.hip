@@ -17,8 +17,8 @@
 // 55, and MFMAs alone were 417 us: the parts add up instead of overlapping.  So what counts is bytes and instructions per
 // product, and the largest tile wins: 4096^3 256 x 256 588 us, 256 x 128 646, 128 x 128 710, 128 x 64 794, 64 x 64 879
 // (fp32 instructions: 1010-1070); where that leaves compute units idle, smaller ones: 2048^3 237, 140, 94, 110, 126
-// (145).  The split keeps out of the matrix pipe (mdh_split.h) and is spread evenly over the phases: 4096^3 590 -> 569 us,
-// 16 x 1024^3 163 -> 155.  64 x 64 tiles, whose walk is more split than products, lose by it (1021 x 1531 x 777 25.6 ->
+// (145).  The split keeps out of the matrix pipe (mdh_split.h) and is spread evenly over the phases: 4096^3 600 -> 571 us,
+// 16 x 1024^3 165 -> 156.  64 x 64 tiles, whose walk is more split than products, lose by it (1021 x 1531 x 777 25.6 ->
 // 26.7 us), but k over the wavefronts (mdh_matmul_split_k.hip) is faster there.  The 256 x 256 tile has k-tiles of 16, because two of 32 (192 KB) exceed LDS.  Measured when they were chosen:
 // 16x16x32 MFMAs equal at 4096^3 (717 / 726), slower at 1024^3 in 128 x 128 tiles (55.2 / 48.8) -- the smaller one
 // leaves room for one vector instruction beside it, the larger for four; 128 x 128 tiles on eight wavefronts of 32 x 64

@@ -6,21 +6,25 @@
 //   wavefront layer : W parts of k; every wavefront owns the whole tile of its workgroup
 //   HBM layer       : chunks of 32 k
 //   VGPR layer      : MI x NI x 2 blocks
-//   block           : 32 x 32 x 16, six v_mfma_f32_32x32x16_bf16
+//   block           : 32 x 32 x 16, six v_mfma_f32_32x32x16_bf16 (eight in tiles of one or two blocks)
 // A wavefront loads, splits and multiplies its own k: nothing is shared before the end, where the W partial tiles are
 // added up in LDS, so there is no barrier in the walk, and every value of the tile's panels is split once per workgroup,
 // in the registers the matrix instructions read.  A k-contiguous operand is turned around in a private piece of LDS
-// (rows of 128 bytes, 16-byte pieces swizzled by the row: no bank conflicts); one with contiguous rows is loaded as it is
-// multiplied, a lane holding MI or NI neighbouring rows, which the output's index undoes.
+// (rows of 128 bytes, 16-byte pieces swizzled by the row's last three bits: 65536 x 64 x 4096 counts 4.5e6 conflict cycles for
+// its 2.3e6 LDS instructions, 4 % of the time); one with contiguous rows is
+// loaded as it is multiplied, a lane holding MI or NI neighbouring rows, which the output's index undoes.
 //
 // What bounds it: instructions issued beside the matrix instructions.  With one in flight a SIMD issues something else
 // every 4.6 clocks, so six fit under an MFMA of 32 clocks; the split takes 8 (MI + NI) / (MI NI) of them (2 x 2: 8.0, 2 x
 // 3: 6.7, 3 x 3: 5.3).  The kernel that shares the split through LDS (mdh_matmul_split.hip) has fewer with its large tiles
 // but needs M N for 256 of them, and on small ones a barrier and two trips through LDS per 32 k: 64 x 64 tiles take
-// 0.57 us for that, 0.3 here: 1021 x 1531 x 777 25.6 -> 21.0 us, 1024^3 22.7 -> 17.4, 1500^3 62 -> 45.  Loads are not what
+// 0.57 us for that, 0.3 here: 1021 x 1531 x 777 26.0 -> 21.4 us, 1024^3 22.7 -> 17.4, 1500^3 62 -> 45.  Loads are not what
 // bounds it (hits in the first level cost the same).
 // Measured without gain: the split of the next 16 k between the matrix instructions of these (by the compiler's
-// scheduling groups); loads a chunk earlier; 16-byte loads of row-contiguous operands, exchanged between lanes.
+// scheduling groups); loads a chunk earlier; 16-byte loads of row-contiguous operands, exchanged between lanes -- with six
+// blocks all within the 256 registers that the launch bound leaves them, though LDS (102 KB of partial tiles) holds one
+// workgroup of four wavefronts a compute unit, one a SIMD, which could have 512.  Nine blocks have them, and with A transposed
+// and B plain still move 30 registers to accumulation registers and back.
 #include "mdh_matmul_split.h"
 
 namespace mdh {

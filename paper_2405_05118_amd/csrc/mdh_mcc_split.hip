@@ -290,7 +290,8 @@ __global__ __launch_bounds__((Cfg<TP, TQ, BN, CK, WM, WN>::NT), (AHEAD && CK == 
         for (int ni = 0; ni < F::NI; ++ni) acc[mi][ni] = mfma(b.x[ni][h], a.y[mi][h], acc[mi][ni]);
   };
   // Phases 0 to 3 are one scheduling region: an MFMA, an LDS read, a share of the next tap's split (out of the matrix pipe:
-  // 16 x 224 x 224 x 64 -> 128, 7 x 7, 2790 -> 2650 us; 16 x 56 x 56 x 64 -> 64, 3 x 3, 28.9 -> 28.3).
+  // with the reads ahead and the search behind the stores, side by side, 16 x 224 x 224 x 64 -> 128, 7 x 7, 2740 -> 2655 us;
+  // 16 x 56 x 56 x 64 -> 64, 3 x 3, 29.3 -> 28.2).
   // AHEAD: the patch is there for all taps, so the pixels of the next one are read from phase 2 on, its filter behind the
   // barrier, and every operand is requested two phases or more before it is multiplied; else one phase.
   constexpr int PM = F::KH * F::MI * F::NI;  // MFMAs of a phase

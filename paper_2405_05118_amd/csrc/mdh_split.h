@@ -15,7 +15,8 @@
 //     U[0,1]   K = 64: 1.2e-7 / 0.8e-7   256: 2.2e-7 / 1.8e-7   4096: 0.85e-6 / 0.5e-6   25088: 2.4e-6 / 1.6e-6
 // (all nine products: the same digits).  Sums with many zeros in one operand have fewer terms than that chain has k, and
 // up to six roundings for the steps they spread over: 64 of 147 terms 3.0 x 2^-24 against 2.4 with fp32 instructions, 8 of
-// them 1.65 / 0.90 (dense 3.2 / 3.6).  Few-channel MCC, whose filters are like that, keeps h h' in a sum of its own.
+// them 1.65 / 0.90 (dense 3.2 / 3.6).  Few-channel MCC, whose filters are like that, keeps h h' in a sum of its own
+// and takes eight of the products, as do the tiles of MatMul that stand in for small ones on fp32 instructions.
 // Rate of the bare instruction loops on random operands: 154 TFLOP/s in
 // fp32, 1850 / 6 = 308 TFLOP/s in six bf16 products (the 16x16x32 form: 2220 / 6).
 //
