@@ -499,7 +499,9 @@ mdh_status launch_t(int SC, int64_t N, const Conv& g, void* ws, hipStream_t st) 
   if (allow_dynamic_lds((const void*)kern, lds_bytes, lds_allowed[ahead]) != MDH_OK) return MDH_ERR_LAUNCH;
   const int64_t tp_n = cdiv(g.P, TP), tq_n = cdiv(g.Q, TQ), tk_n = cdiv(g.K, BN);
   if (SC < 1) return MDH_ERR_UNSUPPORTED;
-  const int64_t cchunk = cdiv(cdiv(g.C, SC), CK) * CK;
+  // Parts of whole steps of 16 channels, also in chunks of 32 (a part's last chunk starts inside the one before; the first needs
+  // 32 channels): with whole chunks 66 channels in two parts were 64 and 2, and 1.25 times as far from 64 bits as 48 and 18.
+  const int64_t even = cdiv(cdiv(g.C, SC), 16) * 16, cchunk = even > CK ? even : CK;
   if ((SC - 1) * cchunk >= g.C) return MDH_ERR_TILE_NOT_DIVIDING;  // a part without channels
   const int64_t nblocks = N * tp_n * tq_n * tk_n * SC;
   if (nblocks > 0x7fffffff) return MDH_ERR_SIZE;

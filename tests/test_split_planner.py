@@ -196,3 +196,28 @@ def test_parts_of_k_stay_short(sizes, parts):
     for inst, s, k in ((mdh.MDH_MATMUL, sizes, 2), (mdh.MDH_BMATMUL, (1, *sizes, 0, 0, 0), 3)):
         p = mdh.mdh_default_params(inst, s)
         assert p.blk[k] == 16 and p.prt[3][k] * p.prt[4][k] >= parts, inst
+
+
+# the tiles in chunks of 32 channels cut c as evenly as those in chunks of 16, so that their chains are as short
+@pytest.mark.gpu
+@pytest.mark.parametrize("sizes,parts", [((2, 20, 24, 64, 66, 5, 5, 1, 1), 2), ((1, 9, 33, 70, 134, 3, 3, 2, 2), 2), ((1, 18, 18, 32, 129, 3, 3, 1, 1), 2),
+                                         ((1, 18, 18, 32, 226, 3, 3, 1, 1), 4)])
+def test_parts_of_c_are_even(sizes, parts):
+    import torch
+
+    n, P, Q, K, C, R, S, st, _ = sizes
+    g = torch.Generator(device="cuda").manual_seed(C)
+    x = torch.randn((n, (P - 1) * st + R, (Q - 1) * st + S, C), generator=g, device="cuda")
+    f = torch.randn((K, R, S, C), generator=g, device="cuda")
+    ref = torch.zeros((n * P * Q, K), dtype=torch.float64, device="cuda")
+    for r in range(R):
+        for s in range(S):
+            ref += x[:, r : r + (P - 1) * st + 1 : st, s : s + (Q - 1) * st + 1 : st].reshape(-1, C).double() @ f[:, r, s].double().t().contiguous()
+    error = {16: [], 32: []}
+    for p in (mdh.mdh_candidate(mdh.MDH_MCC, sizes, i) for i in range(mdh.mdh_num_candidates(mdh.MDH_MCC, sizes))):
+        if p.blk[4] == 2 and p.prt[2][4] == 8 and p.prt[3][4] == parts:
+            out = torch.full((n, P, Q, K), float("nan"), device="cuda")
+            mdh.mdh_mcc(x, f, out, (st, st), p, torch.empty(parts * out.numel(), device="cuda"))
+            error[16 * p.prt[1][4]].append(float((out.view(-1, K).double() - ref).norm()))
+    assert error[16] and error[32]
+    assert max(error[32]) <= 1.03 * min(error[16])  # every tile takes the same parts, and the same steps of 16 in them
