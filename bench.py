@@ -183,9 +183,9 @@ def bench_stencil(torch, mdh, W, name, steps, warmup, cpu):
     return res
 
 
-def _split_variant(mdh, sizes, S):
-    """The default table with the reduction dimension in S parts over workgroups, the same tile; None if that is no table."""
-    p = mdh.mdh_default_params(mdh.MDH_MATMUL, sizes).copy()
+def _in_parts(mdh, sizes, p, S):
+    """The table with the reduction dimension in S parts over workgroups, the same tile; None if that is no table."""
+    p = p.copy()
     p.prt[3][2] = S
     step = p.prt[1][2] * p.prt[2][2] * p.blk[2]  # k of a step, of the LDS and register layers
     p.prt[0][2] = -(-(-(-sizes[2] // (S * p.prt[4][2]))) // step)
@@ -193,6 +193,17 @@ def _split_variant(mdh, sizes, S):
         if mdh.mdh_validate_params(mdh.MDH_MATMUL, sizes, p) == 0:
             return p
     return None
+
+
+def _split_variant(mdh, sizes, S):
+    """The default's tile with the reduction dimension split S ways over workgroups; where the candidates do not have it, the
+    first of the same kind of value that they have, and as many columns a workgroup; else None."""
+    d = mdh.mdh_default_params(mdh.MDH_MATMUL, sizes)
+    cand = [mdh.mdh_candidate(mdh.MDH_MATMUL, sizes, i) for i in range(mdh.mdh_num_candidates(mdh.MDH_MATMUL, sizes))]
+    cand = [p for p in cand if p.prt[3][2] == S and p.blk[2] == d.blk[2]]
+    same_tile = [p for p in cand if all(list(p.prt[l][:3]) == list(d.prt[l][:3]) for l in (1, 2, 4, 5))]
+    same_cols = [p for p in cand if p.prt[3][1] == d.prt[3][1] and p.prt[4][1] * p.prt[2][1] == d.prt[4][1] * d.prt[2][1]]
+    return next(iter(same_tile + same_cols), None)
 
 
 def _mfma_roofline(tf, sliced, traffic, products=6):
@@ -209,7 +220,7 @@ def bench_matmul(torch, mdh, W, name, steps, warmup, cpu, split=None):
     c = torch.empty((cfg.M, cfg.N), dtype=torch.float32, device="cuda")
     p = mdh.mdh_default_params(mdh.MDH_MATMUL, sizes) if split is None else _split_variant(mdh, sizes, split)
     if p is None:
-        return {"missing": "the default's tile does not take k in %d parts" % split, "value": None, "unit": "GFLOP/s", "ms_per_step": None,
+        return {"missing": "no candidate of the default's columns takes k in %d parts" % split, "value": None, "unit": "GFLOP/s", "ms_per_step": None,
                 "dtype": "f32", "roofline": {"bound": "mfma", "frac": None}}
     sliced = p.blk[2] == 16  # values carried as three bf16 values
     nws = mdh.mdh_workspace_size(mdh.MDH_MATMUL, sizes, p)
@@ -767,8 +778,23 @@ def _rounded(x):
 
 def bench_matmul_ts_split(torch, mdh, W, name, steps, warmup, cpu):
     """The tall-skinny MatMul with the reduction dimension split four ways over workgroups (partial
-    results in a device-memory workspace + second-pass combine)."""
-    return bench_matmul(torch, mdh, W, "matmul_ts", steps, warmup, False, split=4)
+    results in a device-memory workspace + second-pass combine); its tile need not be the default's, so the
+    same one without parts beside it (but in profiler runs, which leave out the oracle too)."""
+    res = bench_matmul(torch, mdh, W, "matmul_ts", steps, warmup, False, split=4)
+    cfg = W.CONFIGS["matmul_ts"]
+    sizes = (cfg.M, cfg.N, cfg.K)
+    p = _split_variant(mdh, sizes, 4)
+    whole = _in_parts(mdh, sizes, p, 1) if p is not None and cpu else None
+    if whole is not None:
+        spread = dict(LAST_SPREAD)
+        a = W.device_uniform(cfg.seed, 1, (cfg.M, cfg.K), -1.0, 1.0)
+        b = W.device_uniform(cfg.seed, 2, (cfg.K, cfg.N), -1.0, 1.0)
+        c = torch.empty((cfg.M, cfg.N), dtype=torch.float32, device="cuda")
+        _, wall = _events_ms(torch, lambda: mdh.mdh_matmul(a, b, c, whole), steps, warmup)
+        res["same_tile_unsplit"] = {"ms_per_step": wall}
+        LAST_SPREAD.clear()
+        LAST_SPREAD.update(spread)
+    return res
 
 
 BENCHES = {
